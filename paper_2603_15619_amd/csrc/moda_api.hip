@@ -158,6 +158,11 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   const int rows = moda::fwd_bf16_tile_rows(waves) / p.heads_per_tile;  // positions per tile
   p.n_qtiles = (s->T + rows - 1) / rows;
 
+  if (s->dtype == MODA_F32) {  // one head per tile; a head streams twice the bytes of a bf16 one
+    p.n_qtiles = (s->T + moda::fwd_f32_tile_rows() - 1) / moda::fwd_f32_tile_rows();
+    p.head_group = heads_per_die_at_a_time((long long)s->B * s->Hq, s->T, 2 * s->d);
+  }
+
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   return launch_status((s->dtype == MODA_BF16) ? moda::launch_fwd_bf16(p, s->d, waves, stream)
                                                : moda::launch_fwd_f32(p, s->d, stream));

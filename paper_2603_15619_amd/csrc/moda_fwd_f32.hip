@@ -1,123 +1,418 @@
-// MoDA attention forward, fp32 inputs, fp32 arithmetic on the vector ALUs.
+// MoDA attention forward, fp32 inputs, fp32 arithmetic throughout, gfx950 fp32 MFMA.
 //
-// Accuracy path (max abs error 1e-5 against an fp64 evaluation is the target),
-// not a throughput path: one wave per query.  Keys are walked 64 at a time, one
-// key per lane: the lane computes the full dot product with fused multiply-adds
-// in channel order, the wave agrees on the running max, and the value rows are
-// accumulated with lane = channel.  The sequence keys and then the depth slots
-// of the query's own position feed the SAME running max / normaliser / output
-// (Algorithm 1), with one division at the end.
+// The accuracy path (max abs error 1e-5 against an fp64 evaluation is the target).  Its products
+// run on v_mfma_f32_32x32x2_f32 (fp32 operands, fp32 accumulation, twice the rate of the vector
+// ALUs' fused multiply-adds), and its depth slots on the vector ALUs at the memory rate.
+//
+// A workgroup = 32 queries of one head; its 4 waves share the queries and DEAL OUT THE KEYS: key
+// tile kt (32 keys) belongs to wave kt % 4, every wave keeps a running (max, normaliser, output) of
+// its own, and the four are folded into one softmax at the end, together with the partial result
+// of the depth slots.  Dealing out keys instead of queries makes the unit of work 32 queries per
+// 4 SIMDs: a few thousand rows of causal attention then fill 256 compute units evenly (32 queries
+// per wave left the last query tiles of a T = 2000 call alone on the chip for twice the mean), and
+// a call of a few hundred rows walks its longest row in a quarter of the steps.
+//
+// What bounds it: the fp32 matrix pipe (64 FLOP per cycle and SIMD) on the sequence keys, HBM on
+// the depth slots (4 bytes per FLOP); every other workgroup takes its slots before its key tiles,
+// the others after, so that both are busy.
+//   B=1 H=16 T=2000 d=128, 15 slots: 0.209 ms, 80 TFLOP/s and 2.7 TB/s (one wave per query on the
+//                                    vector ALUs, the form before: 2.69 ms)
+//   B=1 H=16 T=8000 d=128, no slots: 1.95 ms, 134 TFLOP/s of the 154 that a library product of
+//                                    8192^3 reaches on the same card
+//   B=1 H=2 T=256 d=64, 4 slots:     10 us (36 us), most of it latency from one end to the other
+//
+// Operand layouts.  S^T = K Q^T (keys on M, queries on N): the contraction may take the channels
+// in any order that both operands share, so lane (l32, hi) holds channels 8 j + 4 hi .. + 3 of key
+// l32 and one 128-bit load feeds four matrix instructions; K comes straight from global memory
+// (four consecutive loads use up a 128-byte line), Q from LDS.  A lane then owns 16 scores of one
+// query, and register i of them is, as it stands, the B operand of O^T += V^T P^T for the keys
+// 8 (i / 4) + i % 4 (lanes < 32) and 4 more (lanes >= 32).  Channels are dealt to the output blocks
+// so that one load of a V row feeds them all: block cb, row r is channel r * (d / 32) + cb.
+#include <type_traits>
+
 #include "moda_launch.h"
 
 namespace moda {
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
+constexpr int kF32Rows = 32;   // queries per workgroup
+constexpr int kF32Keys = 32;   // keys per tile (of one wave)
+constexpr int kF32Waves = 4;
 
 template <int D>
-struct F32State {
-  float m, l;
-  float o[D / 64];
+struct F32Cfg {
+  static constexpr int kRow = D + 4;                 // floats per LDS row (16 consecutive rows hit 16 bank groups)
+  static constexpr int kBlocks = D / 32;             // output blocks of 32 channels
+  static constexpr int kFrags = D / 8;               // 128-bit K fragments per tile and lane
+  static constexpr int kRounds = D / 64;             // the waves' outputs are summed 64 channels at a time
+  static constexpr int kXRow = 64 + 4;
+  static constexpr int kXWave = kF32Rows * kXRow;    // floats of one wave's share in a round
+  static constexpr int kShared = kF32Rows * kRow > kF32Waves * kXWave ? kF32Rows * kRow : kF32Waves * kXWave;
 };
 
-// Fold `count` keys/values (rows of D floats, `stride` floats apart) into the state.
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// exp(scale * (a - b)) of raw scores a, b; the difference is formed before it is scaled, so that
+// a large common part of the scores costs no precision.  b = -inf (an empty state) counts as 0.
+__device__ __forceinline__ float weight(float a, float b, float c2) {
+  return fast_exp2((a - (b == -INFINITY ? 0.f : b)) * c2);
+}
+
 template <int D>
-__device__ __forceinline__ void fold_keys(F32State<D>& st, const float* qs, const float* Kp,
-                                          const float* Vp, int count, size_t stride, float scale,
-                                          int lane) {
-  for (int c0 = 0; c0 < count; c0 += 64) {
-    const int j = c0 + lane;
-    float s = -INFINITY;
-    if (j < count) {
-      const float4* kr = (const float4*)(Kp + (size_t)j * stride);
-      float a = 0.f;
-#pragma unroll 4
-      for (int k = 0; k < D / 4; ++k) {
-        float4 kv = kr[k];
-        a = fmaf(qs[4 * k], kv.x, a);
-        a = fmaf(qs[4 * k + 1], kv.y, a);
-        a = fmaf(qs[4 * k + 2], kv.z, a);
-        a = fmaf(qs[4 * k + 3], kv.w, a);
+__global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_kernel(FwdParams p) {
+  using C = F32Cfg<D>;
+  // the queries, later the waves' outputs; the depth slots' partial outputs; (max, normaliser) of
+  // each wave and of the depth slots; scratch for the rare path below
+  __shared__ __attribute__((aligned(16))) float shared[C::kShared];
+  __shared__ __attribute__((aligned(16))) float depth_o[kF32Rows * C::kRow];
+  __shared__ float stat_m[kF32Waves + 1][kF32Rows], stat_l[kF32Waves + 1][kF32Rows];
+  __shared__ float p_tile[kF32Keys][kF32Rows];
+
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int bh, tile;
+  head_blocked_id((int)blockIdx.x, p.B * p.Hq, p.n_qtiles, bh, tile, p.head_group);
+  const int q0 = (p.n_qtiles - 1 - tile) * kF32Rows;  // heavy (late) tiles first
+  const int b = bh / p.Hq, g = (bh - b * p.Hq) / (p.Hq / p.Hk);
+  const size_t bg = (size_t)b * p.Hk + g;
+  const int T = p.T, L = p.depth_count;
+  const float c2 = p.scale_log2;
+
+  // ---- queries -> LDS (rows past the end repeat the last one; nothing of them is stored)
+  for (int i = tid; i < kF32Rows * (D / 4); i += kF32Waves * 64) {
+    const int r = i / (D / 4), c = i % (D / 4);
+    *(f32x4*)(shared + r * C::kRow + c * 4) =
+        *(const f32x4*)((const float*)p.Q + ((size_t)bh * T + min(q0 + r, T - 1)) * D + c * 4);
+  }
+  __syncthreads();
+
+  // ---- depth slots: 16 lanes per row, 4 (d = 64) or 8 (d = 128) channels each; a wave takes 8 of
+  // the tile's rows, 4 at a time, kC slots at a time with the next kC in flight
+  auto depth_rows = [&]() {
+    constexpr int NV = D / 64, kC = D == 128 ? 3 : 6;
+    const int rg = lane >> 4, l16 = lane & 15;
+    const int nch = (L + kC - 1) / kC;
+    struct Chunk {
+      f32x4 k[kC][NV], v[kC][NV];
+    };
+    const size_t drow = (size_t)p.depth_alloc * D;
+    auto row_of = [&](int it) { return wave * 8 + it * 4 + rg; };
+    auto issue = [&](int it, int c, Chunk& x) {
+      const size_t base = (bg * T + min(q0 + row_of(it), T - 1)) * drow + l16 * 4;
+#pragma unroll
+      for (int u = 0; u < kC; ++u) {
+        // (slots of the last chunk past depth_count re-read the last attended one: a cache hit)
+        const size_t s = base + (size_t)min(c * kC + u, L - 1) * D;
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+          x.k[u][n] = __builtin_nontemporal_load((const f32x4*)((const float*)p.Kdepth + s + n * 64));
+          x.v[u][n] = __builtin_nontemporal_load((const f32x4*)((const float*)p.Vdepth + s + n * 64));
+        }
       }
-      s = a * scale;
+    };
+    f32x4 q[NV], o[NV];
+    float m = -INFINITY, l = 0.f;
+    auto fold = [&](int c, const Chunk& x) {
+      float s[kC], mn = m;
+#pragma unroll
+      for (int u = 0; u < kC; ++u) {
+        float a = 0.f;
+#pragma unroll
+        for (int n = 0; n < NV; ++n)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a = fmaf(q[n][e], x.k[u][n][e], a);
+        a = group_sum<16>(a);
+        s[u] = c * kC + u < L ? a : -INFINITY;
+        mn = fmaxf(mn, s[u]);
+      }
+      const float al = weight(m, mn, c2);
+      m = mn;
+      l *= al;
+#pragma unroll
+      for (int n = 0; n < NV; ++n) o[n] *= al;
+#pragma unroll
+      for (int u = 0; u < kC; ++u) {
+        if (c * kC + u >= L) break;  // (uniform)
+        const float w = weight(s[u], mn, c2);
+        l += w;
+#pragma unroll
+        for (int n = 0; n < NV; ++n)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[n][e] = fmaf(w, x.v[u][n][e], o[n][e]);
+      }
+    };
+    int it = 0, c = 0, iti = 0, ci = 0;
+    auto advance = [&](int& i_, int& c_) {
+      if (++c_ == nch) {
+        c_ = 0;
+        ++i_;
+      }
+    };
+    auto issue_next = [&](Chunk& x) {  // (past the end: the last chunk again, ignored)
+      issue(min(iti, 1), iti < 2 ? ci : nch - 1, x);
+      if (iti < 2) advance(iti, ci);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto one = [&](const Chunk& cur, Chunk& refill) -> bool {
+      issue_next(refill);
+      const int r = row_of(it);
+      if (c == 0) {
+        m = -INFINITY;
+        l = 0.f;
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+          o[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+          q[n] = *(const f32x4*)((const float*)p.Q + ((size_t)bh * T + min(q0 + r, T - 1)) * D + l16 * 4 + n * 64);
+        }
+      }
+      fold(c, cur);
+      if (c == nch - 1) {
+#pragma unroll
+        for (int n = 0; n < NV; ++n) *(f32x4*)(depth_o + r * C::kRow + l16 * 4 + n * 64) = o[n];
+        if (l16 == 0) {
+          stat_m[kF32Waves][r] = m;
+          stat_l[kF32Waves][r] = l;
+        }
+      }
+      advance(it, c);
+      return it < 2;
+    };
+    Chunk xa, xb;
+    issue_next(xa);
+    while (true) {
+      if (!one(xa, xb)) break;
+      if (!one(xb, xa)) break;
     }
-    const float m_new = fmaxf(st.m, wave_max(s));
-    const float alpha = expf(st.m - m_new);  // exp(-inf) = 0 on the first chunk
-    const float pj = (j < count) ? expf(s - m_new) : 0.f;
-    st.l = st.l * alpha + wave_sum(pj);
-    st.m = m_new;
+  };
+  const bool depth_first = L > 0 && ((blockIdx.x >> 3) & 1) != 0;
+  if (depth_first) depth_rows();
+
+  // ---- this wave's key tiles: wave, wave + 4, ...
+  f32x16 o[C::kBlocks];
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) st.o[i] *= alpha;
-    const int n = min(64, count - c0);
-    for (int jj = 0; jj < n; ++jj) {
-      const float pw = __shfl(pj, jj, 64);
-      const float* vr = Vp + (size_t)(c0 + jj) * stride;
+  for (int cb = 0; cb < C::kBlocks; ++cb)
 #pragma unroll
-      for (int i = 0; i < D / 64; ++i) st.o[i] = fmaf(pw, vr[lane + 64 * i], st.o[i]);
+    for (int i = 0; i < 16; ++i) o[cb][i] = 0.f;
+  float m = -INFINITY, l = 0.f;  // reference max of the raw scores; this lane's share of the normaliser
+  const int n_keys = p.causal ? min(T, q0 + kF32Rows) : T;
+  const int nt = (n_keys + kF32Keys - 1) / kF32Keys;
+  // tiles that every query sees in full; at most one more (the diagonal, or the ragged end) follows
+  const int n_full = p.causal ? q0 / kF32Keys : T / kF32Keys;
+  const int lim = p.causal ? min(q0 + l32, T - 1) : T - 1;  // last key that this lane's query sees
+  // (rows past the end of the tensor read as zeros: their scores are masked, their values weighted with 0)
+  const float* Kb = (const float*)p.Kseq + bg * T * D;
+  const float* Vb = (const float*)p.Vseq + bg * T * D;
+  const unsigned bytes = (unsigned)T * (unsigned)(D * 4);
+  const __amdgpu_buffer_rsrc_t k_buf = __builtin_amdgcn_make_buffer_rsrc((void*)Kb, 0, (int)bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t v_buf = __builtin_amdgcn_make_buffer_rsrc((void*)Vb, 0, (int)bytes, 0x00020000);
+  const int k_off = l32 * D * 4 + hi * 16;
+  const int v_off = hi * 4 * D * 4 + l32 * C::kBlocks * 4;
+  f32x4 kf[C::kFrags];
+  float vf[16][C::kBlocks];
+  auto load_k = [&](int kt, int half) {
+    const int soff = (int)((unsigned)kt * (unsigned)(kF32Keys * D * 4));
+    int off = k_off;  // (opaque here, so that the sums below stay immediates of the loads instead of
+    asm volatile("" : "+v"(off));  // being hoisted out of the key loop into a register each)
+#pragma unroll
+    for (int j = half * (C::kFrags / 2); j < (half + 1) * (C::kFrags / 2); ++j)
+      kf[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(k_buf, off + j * 32, soff, 0));
+  };
+  auto load_v = [&](int kt, int half) {
+    const unsigned soff = (unsigned)kt * (unsigned)(kF32Keys * D * 4);
+#pragma unroll
+    for (int i = half * 8; i < half * 8 + 8; ++i) {
+      const int so = (int)(soff + ((i >> 2) * 8 + (i & 3)) * D * 4);
+      if constexpr (D == 128) {
+        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(v_buf, v_off, so, 0));
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) vf[i][cb] = v[cb];
+      } else {
+        const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(v_buf, v_off, so, 0));
+        vf[i][0] = v[0];
+        vf[i][1] = v[1];
+      }
+    }
+  };
+  if (wave < nt) {
+    load_k(wave, 0);
+    load_k(wave, 1);
+  }
+  auto fold_tile = [&](int kt, auto PARTIAL) {
+    constexpr bool partial = decltype(PARTIAL)::value;
+    // loads in flight: half of the tile's V during the scores; then its other half and half of the
+    // next tile's K; the rest of that K from the middle of the output products on (all of K and V
+    // at once do not fit 256 registers)
+    const int k_next = kt + kF32Waves;  // (past the last tile: rows that exist or zeros, not used)
+    load_v(kt, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    // S^T = K Q^T: two accumulation chains (even and odd fragments)
+    // (issued strictly in turn: left to itself the scheduler runs one chain after the other)
+    f32x16 s, s1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
+    const float* q_row = shared + l32 * C::kRow + hi * 4;
+    f32x4 qa = *(const f32x4*)q_row, qb = *(const f32x4*)(q_row + 8);
+#pragma unroll
+    for (int j = 0; j < C::kFrags; j += 2) {
+      const int jn = j + 2 < C::kFrags ? j + 2 : 0;  // Q fragments are read one step ahead
+      const f32x4 na = *(const f32x4*)(q_row + jn * 8), nb = *(const f32x4*)(q_row + jn * 8 + 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        __builtin_amdgcn_sched_barrier(0);
+        s = mfma_f32(kf[j][e], qa[e], s);
+        s1 = mfma_f32(kf[j + 1][e], qb[e], s1);
+      }
+      qa = na;
+      qb = nb;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(kt, 1);
+    load_k(k_next, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] += s1[i];
+    const int k0 = kt * kF32Keys;
+    if constexpr (partial) {
+      int past = lim - k0 - hi * 4;  // (evaluated here: the loop has no registers for 16 constants)
+      asm volatile("" : "+v"(past));
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if ((i >> 2) * 8 + (i & 3) > past) s[i] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+    const float m_new = fmaxf(m, pair_max(mx));
+    if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {
+      const float al = weight(m, m_new, c2);
+      m = m_new;
+      l *= al;
+#pragma unroll
+      for (int cb = 0; cb < C::kBlocks; ++cb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[cb][i] *= al;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = weight(s[i], m, c2);
+      l += s[i];
+    }
+    // O^T += V^T P^T.  On a tile that the diagonal crosses a key's weight is zero for the queries
+    // before it, but zero times an infinite or NaN value is not: if the tile holds such values the
+    // visible (key, query) pairs are taken one by one.
+    bool plain = true;
+    if (partial && p.causal) {  // (uniform)
+      bool finite = true;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int cb = 0; cb < C::kBlocks; ++cb) finite = finite && fabsf(vf[i][cb]) < INFINITY;
+      plain = __builtin_amdgcn_ballot_w64(!finite) == 0;
+    }
+    auto fold_v = [&](int first) {
+#pragma unroll
+      for (int i = first; i < first + 8; ++i)
+#pragma unroll
+        for (int cb = 0; cb < C::kBlocks; ++cb) o[cb] = mfma_f32(vf[i][cb], s[i], o[cb]);
+    };
+    if (plain) {
+      fold_v(0);
+    } else {
+      // (one tile per workgroup at most is crossed by the diagonal: one wave uses p_tile)
+      int h = hi, q = l32;  // (addresses formed here, not kept across the loop)
+      asm volatile("" : "+v"(h), "+v"(q));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) p_tile[(i >> 2) * 8 + h * 4 + (i & 3)][q] = s[i];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (int key = k0; key < min(T, k0 + kF32Keys); ++key) {
+        const float w = p_tile[key - k0][q];
+        const float* vr = Vb + (size_t)key * D;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int cb = 0; cb < C::kBlocks; ++cb) {
+            const float x = fmaf(w, vr[((i >> 2) * 8 + h * 4 + (i & 3)) * C::kBlocks + cb], o[cb][i]);
+            o[cb][i] = key <= lim ? x : o[cb][i];
+          }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(k_next, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (plain) fold_v(8);
+  };
+  int kt = wave;
+  for (; kt < n_full; kt += kF32Waves) fold_tile(kt, std::false_type{});
+  if (kt < nt) fold_tile(kt, std::true_type{});
+  if (L > 0 && !depth_first) depth_rows();
+
+  // ---- fold the partial softmaxes: (max, normaliser) of each wave, then the outputs, each scaled
+  // to the common reference, summed 64 channels at a time
+  l = pair_sum(l);
+  if (hi == 0) {
+    stat_m[wave][l32] = m;
+    stat_l[wave][l32] = l;
+  }
+  __syncthreads();  // (also: every wave is done with the queries in LDS)
+  const int n_part = kF32Waves + (L > 0 ? 1 : 0);
+  {
+    float mt = stat_m[0][l32];
+    for (int w = 1; w < n_part; ++w) mt = fmaxf(mt, stat_m[w][l32]);
+    const float f = weight(m, mt, c2);
+#pragma unroll
+    for (int cb = 0; cb < C::kBlocks; ++cb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[cb][i] *= f;
+  }
+  // thread: row tid / 8, 8 of the round's 64 channels
+  const int row = tid >> 3, ch = (tid & 7) * 8, t = q0 + row;
+  float mt = stat_m[0][row];
+  for (int w = 1; w < n_part; ++w) mt = fmaxf(mt, stat_m[w][row]);
+  float lt = 0.f;
+  for (int w = 0; w < n_part; ++w) lt += stat_l[w][row] * weight(stat_m[w][row], mt, c2);
+  const float fd = L > 0 ? weight(stat_m[kF32Waves][row], mt, c2) : 0.f;
+  const float inv = 1.0f / lt;
+#pragma unroll
+  for (int rd = 0; rd < C::kRounds; ++rd) {
+    if (rd > 0) __syncthreads();
+    float* xw = shared + wave * C::kXWave + l32 * C::kXRow;
+    // output row r (of 32) of the blocks = channels r * kBlocks ..: 64 channels are 64 / kBlocks rows
+#pragma unroll
+    for (int i = rd * (16 / C::kRounds); i < (rd + 1) * (16 / C::kRounds); ++i) {
+      const int c0 = ((i >> 2) * 8 + hi * 4 + (i & 3)) * C::kBlocks - rd * 64;
+      if constexpr (D == 128) *(f32x4*)(xw + c0) = (f32x4){o[0][i], o[1][i], o[2][i], o[3][i]};
+      else *(f32x2*)(xw + c0) = (f32x2){o[0][i], o[1][i]};
+    }
+    __syncthreads();
+    f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+      x0 += *(const f32x4*)(shared + w * C::kXWave + row * C::kXRow + ch);
+      x1 += *(const f32x4*)(shared + w * C::kXWave + row * C::kXRow + ch + 4);
+    }
+    if (L > 0) {
+      x0 += *(const f32x4*)(depth_o + row * C::kRow + rd * 64 + ch) * fd;
+      x1 += *(const f32x4*)(depth_o + row * C::kRow + rd * 64 + ch + 4) * fd;
+    }
+    if (t < T) {
+      float* dst = (float*)p.O + ((size_t)bh * T + t) * D + rd * 64 + ch;
+      *(f32x4*)dst = x0 * inv;
+      *(f32x4*)(dst + 4) = x1 * inv;
     }
   }
+  if ((tid & 7) == 0 && t < T) p.LSE[(size_t)bh * T + t] = mt * p.scale + logf(lt);
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void moda_fwd_f32_kernel(FwdParams p) {
-  __shared__ float qsm[4][D];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const long long row = (long long)blockIdx.x * 4 + wave;  // flat (b, h, t)
-  const long long total = (long long)p.B * p.Hq * p.T;
-  if (row >= total) return;  // whole wave leaves together; no block barrier is used below
-  const int t = (int)(row % p.T);
-  const int bh = (int)(row / p.T);
-  const int b = bh / p.Hq;
-  const int h = bh - b * p.Hq;
-  const int g = h / (p.Hq / p.Hk);
-  const size_t kvh = (size_t)(b * p.Hk + g);
-
-  const float* q = (const float*)p.Q + (size_t)row * D;
-  float* qs = qsm[wave];
-#pragma unroll
-  for (int i = 0; i < D / 64; ++i) qs[lane + 64 * i] = q[lane + 64 * i];
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-  F32State<D> st;
-  st.m = -INFINITY;
-  st.l = 0.f;
-#pragma unroll
-  for (int i = 0; i < D / 64; ++i) st.o[i] = 0.f;
-
-  const float* Ks = (const float*)p.Kseq + kvh * p.T * D;
-  const float* Vs = (const float*)p.Vseq + kvh * p.T * D;
-  fold_keys<D>(st, qs, Ks, Vs, p.causal ? t + 1 : p.T, D, p.scale, lane);
-  if (p.depth_count > 0) {
-    const size_t doff = (kvh * p.T + t) * (size_t)p.depth_alloc * D;
-    fold_keys<D>(st, qs, (const float*)p.Kdepth + doff, (const float*)p.Vdepth + doff,
-                 p.depth_count, D, p.scale, lane);
-  }
-  float* o = (float*)p.O + (size_t)row * D;
-#pragma unroll
-  for (int i = 0; i < D / 64; ++i) o[lane + 64 * i] = st.o[i] / st.l;
-  if (lane == 0) p.LSE[row] = st.m + logf(st.l);
-}
-
-}  // namespace moda
-
-namespace moda {
+int fwd_f32_tile_rows() { return kF32Rows; }
 
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream) {
-  const long long rows = (long long)p.B * p.Hq * p.T;
-  const long long blocks = (rows + 3) / 4;
+  if (p.n_qtiles != (p.T + kF32Rows - 1) / kF32Rows) return hipErrorInvalidValue;
+  const long long blocks = (long long)p.B * p.Hq * p.n_qtiles;
   if (!grid_ok(blocks)) return kGridTooLarge;
-  dim3 grid((unsigned)blocks), block(256);
+  dim3 grid((unsigned)blocks), block(kF32Waves * 64);
   if (d == 128) return launch_kernel(moda_fwd_f32_kernel<128>, grid, block, stream, p);
   if (d == 64) return launch_kernel(moda_fwd_f32_kernel<64>, grid, block, stream, p);
   return hipErrorInvalidValue;
