@@ -16,6 +16,8 @@
 //            workgroup also takes the depth slots of its 128 positions (row-local: dKdepth,
 //            dVdepth and the depth share of dQ, left in the workspace in fp32), before or
 //            after its key-tile work: that part is bound by HBM, the rest by the matrix pipe.
+//            (When there are too few key tiles to fill the chip, dkdv_short: one workgroup per 32
+//            keys, whose waves deal out the queries; and dq_short likewise for dQ.)
 //   dq     : one workgroup per 128 queries; K / V tiles stream through LDS; S^T, dP^T
 //            are recomputed in the transposed orientation (a lane owns one query),
 //            dQ^T += K^T dS^T on top of the depth share found in the workspace; every
@@ -75,16 +77,16 @@ __device__ __forceinline__ void buffer_store16_nt(const u32x4& v, const i32x4& r
 }
 
 // ---------------------------------------------------------------- depth-slot gradients (G = 1)
-// The depth slots of 32 consecutive positions (row0 ...) of one head, handled by one wave in a
+// The depth slots of ROWS consecutive positions (row0 ...) of one head, handled by one wave in a
 // row-major mapping (d/8 lanes x 8 channels per row, 64 / (d/8) rows per wave step): dKdepth,
 // dVdepth (row-local, written once) and the depth share of dQ, which is left in the workspace
 // (fp32, not yet multiplied by the softmax scale) for the dQ kernel to start from.
 // Work items (row step, chunk of kChunk slots) are walked with the loads of the next two
 // items in flight (the phase is bound by memory latency).  Uses no LDS.
-template <int D>
+template <int D, int ROWS>
 __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int row0, int lane) {
   using Tl = Tile<D>;
-  constexpr int LPR = Tl::kChunks, RPS = 64 / LPR, NIT = 32 / RPS;
+  constexpr int LPR = Tl::kChunks, RPS = 64 / LPR, NIT = ROWS / RPS;
   constexpr int kChunk = 5;
   const int T = p.T, L = p.depth_count, La = p.depth_alloc;
   const int bg = bh, qw0 = row0;
@@ -95,7 +97,7 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
   const int rg = lane / LPR, l16 = lane % LPR;
   const size_t drow = (size_t)La * Tl::kRowBytes;
   // (this phase only runs when every key/value head serves one query head: bg == bh)
-  // The depth tensors are addressed from the first of the wave's 32 positions (a 64-bit base)
+  // The depth tensors are addressed from the first of the wave's positions (a 64-bit base)
   // with 32-bit offsets from there, so they may be of any size; `slab` is what is left of the
   // (batch, head) slab from that position on, clamped to what 32 bits hold.
   const int rbase = min(qw0, T - 1);
@@ -178,7 +180,7 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
     // The common case, every slot of the chunk attended and every row of the wave inside the
     // sequence, has no branch per slot: the slots' chains of dependent instructions (dot
     // products, lane sums, exponential) then overlap.
-    if ((c + 1) * kChunk <= L && qw0 + 32 <= T) {  // (uniform)
+    if ((c + 1) * kChunk <= L && qw0 + ROWS <= T) {  // (uniform)
       float pe[kChunk], e[kChunk];
 #pragma unroll
       for (int i = 0; i < kChunk; ++i) {
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   // units stream while others compute.
   const bool own_depth = G == 1 && p.depth_alloc > 0;
   const bool depth_first = ((blockIdx.x >> 3) & 1) != 0;
-  if (own_depth && depth_first) depth_grad_rows<D>(p, bg, kw0, lane);
+  if (own_depth && depth_first) depth_grad_rows<D, 32>(p, bg, kw0, lane);
   // grouped queries: the workgroup's 128 positions, 256 / (d/8) at a time
   auto group_depth = [&]() {
     if constexpr (GT > 0) {
@@ -628,8 +630,192 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if (own_depth && !depth_first) depth_grad_rows<D>(p, bg, kw0, lane);
+  if (own_depth && !depth_first) depth_grad_rows<D, 32>(p, bg, kw0, lane);
   if (GT > 0 && !depth_first) group_depth();
+}
+
+// ---------------------------------------------------------------- dK, dV, few key tiles
+// The kernel above needs B * Hk * T / 128 workgroups to fill the chip; below that most compute units
+// idle while the first key tiles walk all query tiles of the group one after the other.  Here a
+// workgroup = 32 keys and its 4 waves DEAL OUT THE QUERIES: item i, 32 queries of one head of the
+// group, belongs to wave i % 4, which copies its Q / dO rows and their (LSE, delta) into LDS of its
+// own (two stages, no workgroup barrier in the loop); the four dK^T, dV^T are summed through LDS at
+// the end, in wave order.  Four times the workgroups with a quarter of the steps each, for four
+// times the reads of Q and dO, which the L2 serves.  The depth slots of the 32 positions are taken
+// here as well.
+// Bound by the latency of a wave's serial chain copy -> products -> exponentials -> products:
+// B=2 Hq=16 Hk=8 T=1000 d=64, 12 slots: 82 -> 34 us; whole backward call at B=1 Hq=64 Hk=8 T=1024
+// d=64, 64 slots: 293 -> 160 us, d=128: 530 -> 282 us.
+template <int D>
+struct BwdShortCfg {
+  static constexpr int kTile = 32 * D * 2;               // 32 rows of Q or dO
+  static constexpr int kStage = 2 * kTile + 32 * 8;      // Q, dO, (LSE log2 e, delta)
+  static constexpr int kPieces = kTile / 1024;           // copy instructions per tile
+  static constexpr int kXRow = D + 4;                    // floats per row of the exchange buffer
+  static constexpr int kXWave = 32 * kXRow;
+  static constexpr int kRing = 4 * 2 * kStage;
+  static constexpr int kLds = kRing > 4 * kXWave * 4 ? kRing : 4 * kXWave * 4;
+};
+
+template <int D, int GT>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kernel(BwdParams p) {
+  using Tl = Tile<D>;
+  using C = BwdShortCfg<D>;
+  using Ld = TileLoader<D>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int T = p.T, G = p.Hq / p.Hk;
+  int bg, jt;  // (batch, key/value head); key tiles in natural order: the first ones see the most queries
+  head_blocked_id((int)blockIdx.x, p.B * p.Hk, (T + 31) / 32, bg, jt, p.head_group);
+  const int j0 = jt * 32;
+  const int bh0 = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G;
+  const float c2 = p.scale_log2;
+
+  // depth slots of the 32 positions, before or after the key tile (alternating, as above)
+  auto depth = [&]() {
+    if constexpr (GT > 0) {
+      constexpr int LPR = D / 8, ROWS = 256 / LPR;
+      for (int r0 = 0; r0 < 32; r0 += ROWS) {
+        const int t = j0 + r0 + tid / LPR;
+        depth_gqa_row<D, GT>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR);
+      }
+    } else if (G == 1 && p.depth_alloc > 0) {
+      depth_grad_rows<D, 8>(p, bg, j0 + wave * 8, lane);
+    }
+  };
+  const bool depth_first = ((blockIdx.x >> 3) & 1) != 0;
+  if (depth_first) depth();
+
+  bf16x8 kf[Tl::kDSteps], vf[Tl::kDSteps];
+  {
+    const size_t row = ((size_t)bg * T + min(j0 + l32, T - 1)) * Tl::kRowBytes + hi * 16;
+#pragma unroll
+    for (int st = 0; st < Tl::kDSteps; ++st) {
+      kf[st] = *(const bf16x8*)((const char*)p.Kseq + row + st * 32);
+      vf[st] = *(const bf16x8*)((const char*)p.Vseq + row + st * 32);
+    }
+  }
+  f32x16 dk[Tl::kDBlocks], dv[Tl::kDBlocks];
+#pragma unroll
+  for (int db = 0; db < Tl::kDBlocks; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dk[db][i] = dv[db][i] = 0.f;
+
+  const int qt0 = p.causal ? jt : 0;
+  const int span = (T + 31) / 32 - qt0;
+  const int n_items = G * span;
+  const unsigned ring = (unsigned)(size_t)(lds_ptr)smem + wave * 2 * C::kStage;
+  FragAddr<D> fa;
+  fa.init(lane);
+  const int goff = (lane / Tl::kChunks) * Tl::kRowBytes + (((lane % Tl::kChunks) ^ Tl::swz(lane / Tl::kChunks)) << 4);
+  auto issue = [&](int item, int stage) {
+    const int bh = bh0 + item / span, qt = qt0 + item % span;
+    const unsigned dst = ring + stage * C::kStage;
+    const i32x4 q_buf = make_tile_buffer((const char*)p.Q + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+    const i32x4 do_buf = make_tile_buffer((const char*)p.dO + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+    const i32x4 st_buf = make_tile_buffer(p.rowstat + (size_t)bh * T * 2, (unsigned)T * 8);
+#pragma unroll
+    for (int q = 0; q < C::kPieces; ++q) {
+      const int voff = xor_here(goff, Ld::piece_xor(q));
+      tile_copy16(q_buf, voff, qt * C::kTile + q * 1024, dst + q * 1024);
+      tile_copy16(do_buf, voff, qt * C::kTile + q * 1024, dst + C::kTile + q * 1024);
+    }
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane((int)(dst + 2 * C::kTile))), "v"(lane * 4), "s"(st_buf),
+                   "s"(__builtin_amdgcn_readfirstlane(qt * 256))
+                 : "memory");
+  };
+  if (wave < n_items) issue(wave, 0);
+  int stage = 0;
+  for (int item = wave; item < n_items; item += 4, stage ^= 1) {
+    // (the wave's own copies into its own LDS: its wait publishes them.  The stage that the next
+    // copies overwrite was read for matrix instructions that have been issued: those reads are done)
+    wait_copies();
+    if (item + 4 < n_items) issue(item + 4, stage ^ 1);
+    const int q0 = (qt0 + item % span) * 32;
+    const unsigned qtile = ring + stage * C::kStage;
+    const unsigned b_row = fa.row + qtile, b_tr = fa.tr + qtile, b_tr8 = fa.tr8 + qtile;
+    const float* stat_s = (const float*)(smem + (qtile - (unsigned)(size_t)(lds_ptr)smem) + 2 * C::kTile);
+    f32x16 s, dp;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+#pragma unroll
+    for (int st = 0; st < Tl::kDSteps; ++st) {
+      const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
+      s = mfma_bf16(FragAddr<D>::row_frag(x, 0, 0), kf[st], s);
+      dp = mfma_bf16(FragAddr<D>::row_frag(x, 0, C::kTile), vf[st], dp);
+    }
+    if (q0 + 32 > T || (p.causal && q0 < j0 + 31)) {  // (uniform) the diagonal, rows past the end
+      const int key = j0 + l32;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int q = q0 + (i >> 2) * 8 + hi * 4 + (i & 3);
+        s[i] = q < T && (!p.causal || key <= q) ? s[i] : -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      float pv[8], dsv[8];
+#pragma unroll
+      for (int b2 = 0; b2 < 2; ++b2) {
+        const int b4 = hf * 2 + b2;
+        const float* st4 = stat_s + (b4 * 8 + hi * 4) * 2;
+        const f32x4 ld01 = *(const f32x4*)st4, ld23 = *(const f32x4*)(st4 + 4);
+        const float l4[4] = {ld01[0], ld01[2], ld23[0], ld23[2]};
+        const float d4[4] = {ld01[1], ld01[3], ld23[1], ld23[3]};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = b4 * 4 + r;
+          const float pe = fast_exp2(s[i] * c2 - l4[r]);
+          pv[b2 * 4 + r] = pe;
+          dsv[b2 * 4 + r] = pe * (dp[i] - d4[r]);
+        }
+      }
+      const bf16x8 pb = pack8(pv), dsb = pack8(dsv);
+#pragma unroll
+      for (int db = 0; db < Tl::kDBlocks; ++db) {
+        const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
+        dv[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, C::kTile), pb, dv[db]);
+        dk[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, 0), dsb, dk[db]);
+      }
+    }
+  }
+
+  // ---- sum of the four waves, row-major, 16-byte stores
+  float* xb = (float*)smem;
+  constexpr int LPR = Tl::kChunks;
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    __syncthreads();
+#pragma unroll
+    for (int db = 0; db < Tl::kDBlocks; ++db)
+#pragma unroll
+      for (int bq = 0; bq < 4; ++bq) {
+        const f32x16& acc = which ? dv[db] : dk[db];
+        *(f32x4*)(xb + wave * C::kXWave + l32 * C::kXRow + db * 32 + bq * 8 + hi * 4) =
+            (f32x4){acc[4 * bq], acc[4 * bq + 1], acc[4 * bq + 2], acc[4 * bq + 3]};
+      }
+    __syncthreads();
+    char* outb = (char*)(which ? p.dVseq : p.dKseq) + (size_t)bg * T * Tl::kRowBytes;
+    const float f = which ? 1.0f : p.scale;
+    for (int row = tid / LPR; row < 32; row += 256 / LPR) {
+      const float* x = xb + row * C::kXRow + (tid % LPR) * 8;
+      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        a += *(const f32x4*)(x + w * C::kXWave);
+        b += *(const f32x4*)(x + w * C::kXWave + 4);
+      }
+      if (j0 + row < T)
+        *(u32x4*)(outb + (size_t)(j0 + row) * Tl::kRowBytes + (tid % LPR) * 16) =
+            (u32x4){pack_bf16(a[0] * f, a[1] * f), pack_bf16(a[2] * f, a[3] * f), pack_bf16(b[0] * f, b[1] * f),
+                    pack_bf16(b[2] * f, b[3] * f)};
+    }
+  }
+  if (!depth_first) depth();
 }
 
 // ---------------------------------------------------------------- dQ
@@ -841,6 +1027,135 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
         *(u32x4*)(dQb + (size_t)t * Tl::kRowBytes + l16 * 16) = ov;
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------- dQ, few query tiles
+// The same change of split for dQ when the kernel above would have fewer workgroups than the chip
+// takes: a workgroup = 32 queries, its 4 waves deal out the key tiles (32 keys, private LDS stages),
+// the four dQ^T and the depth share are summed at the end.
+// Whole backward call, B=1 H=8 T=2048, 4 slots: d=64 67 -> 47 us, d=128 104 -> 85 us; B=1 H=2
+// T=16384 d=64: 427 -> 328 us.
+template <int D>
+__global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
+  using Tl = Tile<D>;
+  using C = BwdShortCfg<D>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int T = p.T, G = p.Hq / p.Hk;
+  const int n_qt = (T + 31) / 32;
+  int bg, tile_idx;  // (as above: a group's heads one right after the other, late query tiles first)
+  head_blocked_id((int)blockIdx.x, p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
+  const int q0 = (n_qt - 1 - tile_idx / G) * 32;
+  const int bh = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G;
+  const float c2 = p.scale_log2;
+
+  const int nt = ((p.causal ? min(T, q0 + 32) : T) + 31) / 32;
+  const unsigned ring = (unsigned)(size_t)(lds_ptr)smem + wave * 2 * C::kStage;
+  FragAddr<D> fa;
+  fa.init(lane);
+  const i32x4 k_buf = make_tile_buffer((const char*)p.Kseq + (size_t)bg * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+  const i32x4 v_buf = make_tile_buffer((const char*)p.Vseq + (size_t)bg * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+  const int goff = (lane / Tl::kChunks) * Tl::kRowBytes + (((lane % Tl::kChunks) ^ Tl::swz(lane / Tl::kChunks)) << 4);
+  auto issue = [&](int kt, int stage) {
+    const unsigned dst = ring + stage * C::kStage;
+#pragma unroll
+    for (int q = 0; q < C::kPieces; ++q) {
+      const int voff = xor_here(goff, TileLoader<D>::piece_xor(q));
+      tile_copy16(k_buf, voff, kt * C::kTile + q * 1024, dst + q * 1024);
+      tile_copy16(v_buf, voff, kt * C::kTile + q * 1024, dst + C::kTile + q * 1024);
+    }
+  };
+  if (wave < nt) issue(wave, 0);
+
+  const int qrow = min(q0 + l32, T - 1);
+  bf16x8 qf[Tl::kDSteps], dof[Tl::kDSteps];
+  {
+    const size_t row = ((size_t)bh * T + qrow) * Tl::kRowBytes + hi * 16;
+#pragma unroll
+    for (int st = 0; st < Tl::kDSteps; ++st) {
+      qf[st] = *(const bf16x8*)((const char*)p.Q + row + st * 32);
+      dof[st] = *(const bf16x8*)((const char*)p.dO + row + st * 32);
+    }
+  }
+  const f32x2 stat = *(const f32x2*)(p.rowstat + ((size_t)bh * T + qrow) * 2);
+  const float lse2 = stat[0], delta = stat[1];
+  const int lim = p.causal ? qrow : T - 1;  // last visible key of this lane's query
+  f32x16 dq[Tl::kDBlocks];
+#pragma unroll
+  for (int db = 0; db < Tl::kDBlocks; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
+
+  int stage = 0;
+  for (int kt = wave; kt < nt; kt += 4, stage ^= 1) {
+    wait_copies();  // (the wave's own copies into its own LDS, as in the dK/dV kernel)
+    if (kt + 4 < nt) issue(kt + 4, stage ^ 1);
+    const unsigned ktile = ring + stage * C::kStage;
+    const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
+    f32x16 s, dp;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+#pragma unroll
+    for (int st = 0; st < Tl::kDSteps; ++st) {
+      const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
+      s = mfma_bf16(FragAddr<D>::row_frag(x, 0, 0), qf[st], s);
+      dp = mfma_bf16(FragAddr<D>::row_frag(x, 0, C::kTile), dof[st], dp);
+    }
+    const int k0 = kt * 32;
+    if (k0 + 32 > T || (p.causal && k0 + 31 > q0)) {  // (uniform) the diagonal, keys past the end
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        s[i] = k0 + (i >> 2) * 8 + hi * 4 + (i & 3) <= lim ? s[i] : -INFINITY;
+    }
+    float ds[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) ds[i] = fast_exp2(s[i] * c2 - lse2) * (dp[i] - delta);
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      float a[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) a[k] = ds[hf * 8 + k];
+      const bf16x8 dsb = pack8(a);
+#pragma unroll
+      for (int db = 0; db < Tl::kDBlocks; ++db)
+        dq[db] = mfma_bf16(FragAddr<D>::tr_frag((unsigned)xor_here((int)b_tr, db << 6), (unsigned)xor_here((int)b_tr8, db << 6),
+                                                hf, 0), dsb, dq[db]);
+    }
+  }
+
+  // ---- depth share + the four waves, row-major, 16-byte stores
+  __syncthreads();
+  float* xb = (float*)smem;
+#pragma unroll
+  for (int db = 0; db < Tl::kDBlocks; ++db)
+#pragma unroll
+    for (int bq = 0; bq < 4; ++bq)
+      *(f32x4*)(xb + wave * C::kXWave + l32 * C::kXRow + db * 32 + bq * 8 + hi * 4) =
+          (f32x4){dq[db][4 * bq], dq[db][4 * bq + 1], dq[db][4 * bq + 2], dq[db][4 * bq + 3]};
+  __syncthreads();
+  constexpr int LPR = Tl::kChunks;
+  for (int row = tid / LPR; row < 32; row += 256 / LPR) {
+    const int t = q0 + row, ch = (tid % LPR) * 8;
+    if (t >= T) break;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    if (p.depth_alloc > 0) {
+      const float* share = p.dq_depth + ((size_t)bh * T + t) * D + ch;
+      a = *(const f32x4*)share;
+      b = *(const f32x4*)(share + 4);
+    }
+    const float* x = xb + row * C::kXRow + ch;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      a += *(const f32x4*)(x + w * C::kXWave);
+      b += *(const f32x4*)(x + w * C::kXWave + 4);
+    }
+    const float f = p.scale;
+    *(u32x4*)((char*)p.dQ + ((size_t)bh * T + t) * Tl::kRowBytes + ch * 2) =
+        (u32x4){pack_bf16(a[0] * f, a[1] * f), pack_bf16(a[2] * f, a[3] * f), pack_bf16(b[0] * f, b[1] * f),
+                pack_bf16(b[2] * f, b[3] * f)};
   }
 }
 
@@ -1079,6 +1394,22 @@ int bwd_bf16_max_group() { return 64; }
 
 int bwd_bf16_kernels(const BwdParams& p) { return 3 + ((p.Hq / p.Hk > 4 && p.depth_alloc > 0) ? 1 : 0); }
 
+// Where the short kernels take over, in workgroups of the other kernel (the chip holds 512 of them,
+// two per compute unit).  The lines lie between the sizes at which either side was seen ahead, whole
+// call timed (other kernel / short kernel, us):
+//   dK/dV  d=64   causal, G > 1:  640 wgs 333 / 294, 768 wgs 1110 / 1079 and 3062 / 3127, 1024 wgs 2015 / 2105
+//          d=64   causal, G = 1:  384 wgs 183 / 158, 448 wgs 144 / 147, 512 wgs 264 / 283
+//          d=64   not causal:     256 wgs 346 / 312, 512 wgs 566 / 596
+//          d=128  causal:         320 wgs 927 / 775, 384 wgs 252 / 248 and 286 / 285, 512 wgs 676 / 788
+//          d=128  not causal:     128 wgs 306 / 216, 256 wgs 627 / 679
+//   dQ     d=64:                  256 wgs 427 / 328 and 60 / 60, 384 wgs 87 / 87, 512 wgs 122 / 131
+//          d=128:                 128 wgs 104 / 85, 256 wgs 243 / 247 and 117 / 128
+static long long few_key_tiles(int D, int G, bool causal) {
+  if (D == 64) return !causal ? 384 : G > 1 ? 704 : 448;
+  return causal ? 352 : 192;
+}
+static long long few_query_tiles(int D) { return D == 64 ? 257 : 192; }
+
 template <int D>
 static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   const long long rows = (long long)p.B * p.Hq * p.T;
@@ -1113,13 +1444,18 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   {
-    const dim3 gk((unsigned)g_dkdv), blk(256);
+    const bool few = g_dkdv < few_key_tiles(D, G, p.causal != 0);  // (see moda_bwd_dkdv_short_kernel)
+    const dim3 gk((unsigned)(few ? (long long)p.B * p.Hk * ((p.T + 31) / 32) : g_dkdv)), blk(256);
     const bool grouped = G > 1 && G <= 4 && p.depth_alloc > 0;  // the depth-slot gradients of the group run inside dK/dV
-    if (!grouped) e = launch_kernel(moda_bwd_dkdv_kernel<D, 0>, gk, blk, stream, p);
-    else if (G <= 2) e = launch_kernel(moda_bwd_dkdv_kernel<D, 2>, gk, blk, stream, p);
-    else e = launch_kernel(moda_bwd_dkdv_kernel<D, 4>, gk, blk, stream, p);
+    const auto kernel = !grouped ? (few ? moda_bwd_dkdv_short_kernel<D, 0> : moda_bwd_dkdv_kernel<D, 0>)
+                        : G <= 2 ? (few ? moda_bwd_dkdv_short_kernel<D, 2> : moda_bwd_dkdv_kernel<D, 2>)
+                                 : (few ? moda_bwd_dkdv_short_kernel<D, 4> : moda_bwd_dkdv_kernel<D, 4>);
+    e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;
+  if (g_dq < few_query_tiles(D))
+    return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)((long long)p.B * p.Hq * ((p.T + 31) / 32))), dim3(256),
+                         stream, p);
   return launch_kernel(moda_bwd_dq_kernel<D, kDqWaves>, dim3((unsigned)g_dq), dim3(kDqWaves * 64), stream, p);
 }
 
