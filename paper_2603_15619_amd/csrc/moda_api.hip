@@ -55,6 +55,23 @@ int fwd_waves_per_workgroup(const moda_shape* s) {
   return tiles8 < 256 ? 4 : 8;
 }
 
+// Calls that take the kernel for few tiles (moda_fwd_short.hip): n = tiles of 128 (position, head)
+// pairs, i.e. the other kernel's workgroups; the short kernel has 4 n, of which the chip holds 768
+// at d = 64 and 512 at d = 128.  As long as they fit, it is ahead (other / short kernel, us, whole
+// call):
+//   d=64   n=128 33/18 and (not causal) 61/40, n=192 25/23 and 65/43;  n=256 25/29 (T=1000, 7 slots)
+//   d=128  n=128 34/25 and 73/53 and (not causal) 68/54;               n=160 36/41, n=256 38/51
+// A second round of its workgroups only pays when the other kernel's longest tile is long: causal
+// calls with n <= 256
+//   d=64   T=4096 59/49, T=16384 200/121, several heads per tile 25/23 and 32/26; (not causal) 22/25
+//   d=128  T=16384 248/207;                                        T=4096 77/80
+bool fwd_few_tiles(const moda_shape* s, int heads_per_tile) {
+  const long long n = (long long)s->B * s->Hq * ((s->T + 127) / 128);
+  if (n <= (s->d == 64 ? 192 : 128)) return true;
+  if (n > 256 || !s->causal) return false;
+  return s->d == 64 ? heads_per_tile > 1 || s->T >= 4096 : s->T >= 8192;
+}
+
 // Heads that one die (workgroup ids equal mod 8) walks together, tile by tile: as many as have
 // their streamed tensors (2 * T * d bf16 elements each: K and V, or Q and dO) in its 4 MB L2, at
 // least one; a power of two that divides the heads of a die.  0: the ids cannot be dealt that way.
@@ -164,6 +181,11 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   }
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (s->dtype == MODA_BF16 && !tuning && fwd_few_tiles(s, p.heads_per_tile)) {
+    const int pos = moda::fwd_short_tile_pairs() / p.heads_per_tile;
+    p.n_qtiles = (s->T + pos - 1) / pos;
+    return launch_status(moda::launch_fwd_short(p, s->d, stream));
+  }
   return launch_status((s->dtype == MODA_BF16) ? moda::launch_fwd_bf16(p, s->d, waves, stream)
                                                : moda::launch_fwd_f32(p, s->d, stream));
 }

@@ -731,9 +731,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
   if (wave < n_items) issue(wave, 0);
   int stage = 0;
   for (int item = wave; item < n_items; item += 4, stage ^= 1) {
-    // (the wave's own copies into its own LDS: its wait publishes them.  The stage that the next
-    // copies overwrite was read for matrix instructions that have been issued: those reads are done)
-    wait_copies();
+    // (the wave's own copies into its own LDS: its wait publishes them, and the stage that the next
+    // copies overwrite may be refilled as soon as the wave's reads of it have returned)
+    wait_own_copies<0>();
+    wait_own_reads();
     if (item + 4 < n_items) issue(item + 4, stage ^ 1);
     const int q0 = (qt0 + item % span) * 32;
     const unsigned qtile = ring + stage * C::kStage;
@@ -1091,7 +1092,8 @@ __global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
 
   int stage = 0;
   for (int kt = wave; kt < nt; kt += 4, stage ^= 1) {
-    wait_copies();  // (the wave's own copies into its own LDS, as in the dK/dV kernel)
+    wait_own_copies<0>();  // (the wave's own copies into its own LDS, as in the dK/dV kernel)
+    wait_own_reads();
     if (kt + 4 < nt) issue(kt + 4, stage ^ 1);
     const unsigned ktile = ring + stage * C::kStage;
     const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;

@@ -23,6 +23,10 @@ inline bool grid_ok(long long blocks) { return blocks > 0 && blocks <= 0x7ffffff
 // must be the number of such tiles in p.T.
 int fwd_bf16_tile_rows(int waves);
 hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, hipStream_t stream);
+// The same for calls with few such tiles: tiles of fwd_short_tile_pairs() (position, head) pairs,
+// whose number per head (subset) is p.n_qtiles.
+int fwd_short_tile_pairs();
+hipError_t launch_fwd_short(const FwdParams& p, int d, hipStream_t stream);
 // fp32 forward kernel: tiles of fwd_f32_tile_rows() queries of one head; p.n_qtiles must be their number.
 int fwd_f32_tile_rows();
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream);

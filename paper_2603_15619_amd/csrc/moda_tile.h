@@ -122,6 +122,17 @@ __device__ __forceinline__ void tile_copy16(const i32x4& rsrc, int voff, int sof
 }
 __device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// For waves that copy into LDS of their own and need no workgroup barrier.  Between the request of
+// a copy and its first read: all but the COUNT youngest vector memory operations of the wave are
+// complete.  Between the last read of a tile and the request that overwrites it: every LDS read of the
+// wave has returned.  (Statements that clobber memory: neither reads nor copies move across them.)
+template <int COUNT>
+__device__ __forceinline__ void wait_own_copies() {
+  static_assert(COUNT >= 0 && COUNT < 64, "vmcnt immediate");
+  asm volatile("s_waitcnt vmcnt(%c0)" : : "n"(COUNT) : "memory");
+}
+__device__ __forceinline__ void wait_own_reads() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+
 // Copies rows [row0, row0+64) of a [n_rows, D] bf16 matrix (behind `rsrc`) into a tile, 1 KB
 // pieces (1024 / row bytes rows each), piece q by copy instruction q % kInstPerWave of wave
 // q / kInstPerWave.  The chunk permutation is applied by choosing which global chunk a lane

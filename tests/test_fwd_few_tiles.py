@@ -1,0 +1,46 @@
+"""GPU parity of the bf16 forward for calls with few tiles (32 (position, head) pairs per workgroup,
+key tiles and blocks of depth slots dealt out to its waves), and of the rule that picks it: both
+kernels on the same inputs.  Tolerances as in test_fwd_parity."""
+import pytest
+import torch
+
+from paper_2603_15619_amd import synth
+from test_fwd_parity import check_full, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La", [(1, 1, 1, 1, 64, 2, 3), (1, 2, 2, 31, 128, 5, None), (2, 2, 2, 32, 64, 6, 8),
+                                              (1, 3, 3, 33, 128, 11, None), (1, 2, 2, 129, 64, 31, None), (2, 4, 2, 63, 128, 3, 4),
+                                              (1, 8, 1, 97, 64, 9, 10), (1, 32, 1, 65, 128, 1, None), (1, 64, 1, 40, 64, 33, 34),
+                                              (1, 12, 2, 161, 128, 0, 2), (1, 4, 1, 1030, 64, 7, None)])
+def test_fwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1500 + T + L, device="cuda", depth_alloc=La)
+    if La is not None:  # unattended slots take no part
+        inp["Kdepth"][:, :, :, L:] = float("nan")
+        inp["Vdepth"][:, :, :, L:] = float("nan")
+    check_full(B, Hq, Hk, T, d, L, "bf16", 0, causal=causal, depth_alloc=La, inp=inp)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,causal", [(1, 8, 8, 700, 64, 4, True), (1, 8, 2, 513, 128, 6, True),
+                                                  (1, 16, 2, 300, 64, 0, False), (1, 2, 2, 4100, 128, 1, True)])
+def test_both_kernels_agree(B, Hq, Hk, T, d, L, causal):
+    """(an empty tuning keeps the other kernel).  Both round weights and outputs to bf16: 2e-2 on O."""
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1600 + T, device="cuda")
+    O0, L0 = run_gpu(inp, L, causal)
+    O1, L1 = run_gpu(inp, L, causal, tuning={})
+    assert (O0.float() - O1.float()).abs().max().item() <= 2e-2
+    assert (L0 - L1).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("T,d,at", [(70, 64, 37), (200, 128, 130)])
+def test_depth_values_that_are_not_finite_stay_in_their_row(T, d, at):
+    """One head per tile: an infinite value in a depth slot reaches its own position only."""
+    inp = synth.make_inputs(1, 2, 2, T, d, 3, dtype="bf16", seed=1700, device="cuda")
+    clean, _ = run_gpu(inp, 3)
+    inp["Vdepth"][:, :, at, 1] = float("inf")
+    O, _ = run_gpu(inp, 3)
+    keep = [t for t in range(T) if t != at]
+    assert torch.equal(O[:, :, keep], clean[:, :, keep])
+    assert not torch.isfinite(O[:, :, at].float()).any()
