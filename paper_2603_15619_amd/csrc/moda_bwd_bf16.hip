@@ -529,68 +529,158 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
     const int key = kw0 + l32;
     // all 64 queries exist and (when causal) none precedes any of this wave's 32 keys
     const bool all_visible = q0 + 64 <= T && (!p.causal || q0 >= kw0 + 31);
-    // one 32-query block at a time: S, dP (recomputed), P and dS for this lane's key and
-    // 16 queries, then dV^T += dO^T P and dK^T += Q^T dS over those 32 queries
+    if constexpr (D == 64) {
+      // Registers allow two 32-query blocks in flight: the exponentials of one are issued, four at a
+      // time, between the matrix instructions of the other (its scores, then the first block's output
+      // products), in whose shadow the vector ALUs then work.  The order is pinned step by step.
+      // (Matrix and vector time of this kernel used to add up: 45 % matrix-pipe busy.  B=1 Hq=64 Hk=8
+      // T=16384: 4.74 ms one block at a time; 4.61 so; 4.39 with the wave priority below, 1.0 PFLOP/s.)
+      f32x16 s[2], dp[2];
+      u32x4 pb[2][2], ds[2][2];  // P and dS packed to bf16: [block][16-query half]
+      auto mask = [&](int qb) {  // (a uniform branch around the comparisons, as below)
+        if (!all_visible) {
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      f32x16 s, dp;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
-#pragma unroll
-      for (int st = 0; st < Tl::kDSteps; ++st) {
-        const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
-        s = mfma_bf16(fa.row_frag(x, qb, 0), kf[st], s);
-        dp = mfma_bf16(fa.row_frag(x, qb, Tl::kBytes), vf[st], dp);
-      }
-      // Order for the scheduler: LDS reads run one step (two fragments) ahead of the matrix
-      // instructions that consume them, no further (the kernel has no registers to spare).
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-      for (int st = 0; st < Tl::kDSteps - 2; ++st) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      // Scores of (query, key) pairs that are not visible become -inf, i.e. weight zero.  Only
-      // the diagonal tile and rows past the end have such pairs: everywhere else this block is
-      // skipped (a uniform branch around the comparisons, not a second copy of the loop body).
-      if (!all_visible) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int q = q0 + qb * 32 + (i >> 2) * 8 + hi * 4 + (i & 3);
-          const bool vis = q < T && (!p.causal || key <= q);
-          s[i] = vis ? s[i] : -INFINITY;
-        }
-      }
-      // one 16-query half at a time: P and dS packed to bf16, then straight into the products
-      // that contract over those 16 queries (keeps few temporaries alive)
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        float pv[8], dsv[8];
-#pragma unroll
-        for (int b2 = 0; b2 < 2; ++b2) {
-          const int b4 = hf * 2 + b2;
-          const float* st4 = stat_s + (qb * 32 + b4 * 8 + hi * 4) * 2;
-          const f32x4 ld01 = *(const f32x4*)st4, ld23 = *(const f32x4*)(st4 + 4);
-          const float l4[4] = {ld01[0], ld01[2], ld23[0], ld23[2]};
-          const float d4[4] = {ld01[1], ld01[3], ld23[1], ld23[3]};
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int i = b4 * 4 + r;
-            const float pe = fast_exp2(s[i] * c2 - l4[r]);
-            pv[b2 * 4 + r] = pe;
-            dsv[b2 * 4 + r] = pe * (dp[i] - d4[r]);
+          for (int i = 0; i < 16; ++i) {
+            const int q = q0 + qb * 32 + (i >> 2) * 8 + hi * 4 + (i & 3);
+            const bool vis = q < T && (!p.causal || key <= q);
+            s[qb][i] = vis ? s[qb][i] : -INFINITY;
           }
         }
-        const bf16x8 pb = pack8(pv), dsb = pack8(dsv);
+      };
+      // (LSE log2 e, delta) of the lane's queries 4 b4 .. + 3 of a block
+      f32x4 stat[2];
+      auto read_stat = [&](int qb, int b4) {
+        const float* st4 = stat_s + (qb * 32 + b4 * 8 + hi * 4) * 2;
+        stat[0] = *(const f32x4*)st4;
+        stat[1] = *(const f32x4*)(st4 + 4);
+      };
+      // ... and their P and dS
+      auto weights = [&](int qb, int b4) {
+        const float l4[4] = {stat[0][0], stat[0][2], stat[1][0], stat[1][2]};
+        const float d4[4] = {stat[0][1], stat[0][3], stat[1][1], stat[1][3]};
+        float pv[4], dsv[4];
 #pragma unroll
-        for (int db = 0; db < Tl::kDBlocks; ++db) {
-          const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
-          dv[db] = mfma_bf16(fa.tr_frag(x0, x8, qb * 2 + hf, Tl::kBytes), pb, dv[db]);
-          dk[db] = mfma_bf16(fa.tr_frag(x0, x8, qb * 2 + hf, 0), dsb, dk[db]);
+        for (int r = 0; r < 4; ++r) {
+          pv[r] = fast_exp2(s[qb][b4 * 4 + r] * c2 - l4[r]);
+          dsv[r] = pv[r] * (dp[qb][b4 * 4 + r] - d4[r]);
         }
+        uint32_t o[4] = {pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]), pack_bf16(dsv[0], dsv[1]),
+                         pack_bf16(dsv[2], dsv[3])};
+        // (used here: else the computation sinks to the block of its products)
+        asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+        pb[qb][b4 >> 1][(b4 & 1) * 2] = o[0];
+        pb[qb][b4 >> 1][(b4 & 1) * 2 + 1] = o[1];
+        ds[qb][b4 >> 1][(b4 & 1) * 2] = o[2];
+        ds[qb][b4 >> 1][(b4 & 1) * 2 + 1] = o[3];
+      };
+      // Sixteen steps of two matrix instructions: 0..3 scores of block 0, 4..7 of block 1 (with the
+      // weights of block 0), 8..11 products of block 0 (with the weights of block 1; 16-query half
+      // (n - 8) / 2, channel block n % 2), 12..15 products of block 1.  Fragments are read two steps
+      // ahead, the weights' row scalars one.
+      bf16x8 fq[3], fg[3];
+      auto read_frags = [&](int n) {
+        if (n < 8) {
+          const unsigned x = (unsigned)xor_here((int)b_row, (n & 3) << 5);
+          fq[n % 3] = fa.row_frag(x, n >> 2, 0);
+          fg[n % 3] = fa.row_frag(x, n >> 2, Tl::kBytes);
+        } else {
+          const int db = n & 1, ks = (n - 8) >> 1;
+          const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
+          fq[n % 3] = fa.tr_frag(x0, x8, ks, 0);
+          fg[n % 3] = fa.tr_frag(x0, x8, ks, Tl::kBytes);
+        }
+      };
+      read_frags(0);
+      read_frags(1);
+#pragma unroll
+      for (int n = 0; n < 16; ++n) {
+        // (the wave whose instructions fill both pipes goes first; the other wave of the SIMD takes
+        // what is left)
+        if (n == 4) __builtin_amdgcn_s_setprio(1);
+        if (n == 12) __builtin_amdgcn_s_setprio(0);
+        if (n < 14) read_frags(n + 2);
+        if (n < 8) {
+          const int qb = n >> 2, st = n & 3;
+          if (st == 0)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[qb][i] = dp[qb][i] = 0.f;
+          s[qb] = mfma_bf16(fq[n % 3], kf[st], s[qb]);
+          dp[qb] = mfma_bf16(fg[n % 3], vf[st], dp[qb]);
+        } else {
+          const int qb = (n - 8) >> 2, hf = ((n - 8) >> 1) & 1, db = n & 1;
+          dv[db] = mfma_bf16(fg[n % 3], __builtin_bit_cast(bf16x8, pb[qb][hf]), dv[db]);
+          dk[db] = mfma_bf16(fq[n % 3], __builtin_bit_cast(bf16x8, ds[qb][hf]), dk[db]);
+        }
+        if (n >= 4 && n < 12) weights((n - 4) >> 2, n & 3);
+        if (n >= 3 && n < 11) read_stat((n - 3) >> 2, (n - 3) & 3);
+        __builtin_amdgcn_sched_barrier(0);
+        if (n == 3) mask(0);
+        if (n == 7) mask(1);
+      }
+    } else {
+      // one 32-query block at a time: S, dP (recomputed), P and dS for this lane's key and
+      // 16 queries, then dV^T += dO^T P and dK^T += Q^T dS over those 32 queries
+  #pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        f32x16 s, dp;
+  #pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+  #pragma unroll
+        for (int st = 0; st < Tl::kDSteps; ++st) {
+          const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
+          s = mfma_bf16(fa.row_frag(x, qb, 0), kf[st], s);
+          dp = mfma_bf16(fa.row_frag(x, qb, Tl::kBytes), vf[st], dp);
+        }
+        // Order for the scheduler: LDS reads run one step (two fragments) ahead of the matrix
+        // instructions that consume them, no further (the kernel has no registers to spare).
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+  #pragma unroll
+        for (int st = 0; st < Tl::kDSteps - 2; ++st) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        // Scores of (query, key) pairs that are not visible become -inf, i.e. weight zero.  Only
+        // the diagonal tile and rows past the end have such pairs: everywhere else this block is
+        // skipped (a uniform branch around the comparisons, not a second copy of the loop body).
+        if (!all_visible) {
+  #pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int q = q0 + qb * 32 + (i >> 2) * 8 + hi * 4 + (i & 3);
+            const bool vis = q < T && (!p.causal || key <= q);
+            s[i] = vis ? s[i] : -INFINITY;
+          }
+        }
+        // one 16-query half at a time: P and dS packed to bf16, then straight into the products
+        // that contract over those 16 queries (keeps few temporaries alive)
+  #pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          float pv[8], dsv[8];
+  #pragma unroll
+          for (int b2 = 0; b2 < 2; ++b2) {
+            const int b4 = hf * 2 + b2;
+            const float* st4 = stat_s + (qb * 32 + b4 * 8 + hi * 4) * 2;
+            const f32x4 ld01 = *(const f32x4*)st4, ld23 = *(const f32x4*)(st4 + 4);
+            const float l4[4] = {ld01[0], ld01[2], ld23[0], ld23[2]};
+            const float d4[4] = {ld01[1], ld01[3], ld23[1], ld23[3]};
+  #pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int i = b4 * 4 + r;
+              const float pe = fast_exp2(s[i] * c2 - l4[r]);
+              pv[b2 * 4 + r] = pe;
+              dsv[b2 * 4 + r] = pe * (dp[i] - d4[r]);
+            }
+          }
+          const bf16x8 pb = pack8(pv), dsb = pack8(dsv);
+  #pragma unroll
+          for (int db = 0; db < Tl::kDBlocks; ++db) {
+            const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
+            dv[db] = mfma_bf16(fa.tr_frag(x0, x8, qb * 2 + hf, Tl::kBytes), pb, dv[db]);
+            dk[db] = mfma_bf16(fa.tr_frag(x0, x8, qb * 2 + hf, 0), dsb, dk[db]);
+          }
 
+        }
       }
     }
   }
@@ -914,38 +1004,11 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
     const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
 
     f32x16 s[2], dp[2];  // S^T, dP^T: [key block]; a lane holds 16 keys of its query
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[kb][i] = dp[kb][i] = 0.f;
-    // four independent accumulation chains per channel step
-#pragma unroll
-    for (int st = 0; st < Tl::kDSteps; ++st) {
-      const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        s[kb] = mfma_bf16(fa.row_frag(x, kb, 0), qf[st], s[kb]);
-        dp[kb] = mfma_bf16(fa.row_frag(x, kb, Tl::kBytes), dof[st], dp[kb]);
-      }
-    }
-    // Order for the scheduler: the LDS reads run one channel step (four fragments) ahead of the
-    // matrix instructions that consume them.
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int st = 0; st < Tl::kDSteps - 1; ++st) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    __builtin_amdgcn_sched_barrier(0);
-
-    bf16x8 dsb[2][2];
+    u32x4 ds[2][2];      // dS^T packed to bf16: [key block][16-key half]
     const int k0 = kt * 64;
     // every key of the tile exists and is visible to every query of the wave
     const bool all_visible = k0 + 64 <= T && (!p.causal || k0 + 63 <= qw0);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      float dsv[16];
+    auto mask = [&](int kb) {
       if (!all_visible) {  // (uniform) diagonal tile, keys past the end: invisible pairs get weight zero
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -953,34 +1016,61 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
           s[kb][i] = key <= lim ? s[kb][i] : -INFINITY;
         }
       }
+    };
+    auto weights = [&](int kb, int b4) {  // dS of the lane's keys 4 b4 .. + 3 of a block
+      float a[4];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) dsv[i] = fast_exp2(s[kb][i] * c2 - lse2) * (dp[kb][i] - delta);
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        float a[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) a[k] = dsv[hf * 8 + k];
-        dsb[kb][hf] = pack8(a);
+      for (int r = 0; r < 4; ++r)
+        a[r] = fast_exp2(s[kb][b4 * 4 + r] * c2 - lse2) * (dp[kb][b4 * 4 + r] - delta);
+      uint32_t o[2] = {pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])};
+      asm volatile("" : "+v"(o[0]), "+v"(o[1]));  // (used here: else the computation sinks to its products)
+      ds[kb][b4 >> 1][(b4 & 1) * 2] = o[0];
+      ds[kb][b4 >> 1][(b4 & 1) * 2 + 1] = o[1];
+    };
+    // Steps: the scores of key block 0 (two matrix instructions each); those of block 1, with the
+    // exponentials of block 0 between them; the products dQ^T += K^T dS^T of block 0 (one matrix
+    // instruction each), with the exponentials of block 1; the products of block 1.  The vector ALUs
+    // thus work in the shadow of the matrix pipe for half of the tile.  Fragments are read kAhead
+    // steps ahead; the order is pinned step by step.  (Against scores, exponentials, products one
+    // after the other: B=8 H=16 T=4096 d=128 0.88 -> 0.83 ms; B=1 Hq=64 Hk=8 T=16384 d=64 3.01 ->
+    // 2.97 ms, where 1.11 PFLOP/s of matrix work hold the clock at 1.7 GHz.)
+    constexpr int NS = Tl::kDSteps, NP = 2 * Tl::kDBlocks, kAhead = 2, kBuf = kAhead + 1;
+    bf16x8 fk[kBuf], fv[kBuf];
+    auto read_frags = [&](int n) {
+      if (n < 2 * NS) {
+        const unsigned x = (unsigned)xor_here((int)b_row, (n % NS) << 5);
+        fk[n % kBuf] = fa.row_frag(x, n / NS, 0);
+        fv[n % kBuf] = fa.row_frag(x, n / NS, Tl::kBytes);
+      } else if (n < 2 * NS + 2 * NP) {
+        const int m = n - 2 * NS, db = m % Tl::kDBlocks;
+        fk[n % kBuf] = fa.tr_frag((unsigned)xor_here((int)b_tr, db << 6), (unsigned)xor_here((int)b_tr8, db << 6),
+                                  m / Tl::kDBlocks, 0);
       }
+    };
+#pragma unroll
+    for (int n = 0; n < kAhead; ++n) read_frags(n);
+#pragma unroll
+    for (int n = 0; n < 2 * NS + 2 * NP; ++n) {
+      if (n == NS) __builtin_amdgcn_s_setprio(1);  // (as in the dK/dV kernel)
+      if (n == 2 * NS + NP) __builtin_amdgcn_s_setprio(0);
+      read_frags(n + kAhead);
+      if (n < 2 * NS) {
+        const int kb = n / NS, st = n % NS;
+        if (st == 0)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[kb][i] = dp[kb][i] = 0.f;
+        s[kb] = mfma_bf16(fk[n % kBuf], qf[st], s[kb]);
+        dp[kb] = mfma_bf16(fv[n % kBuf], dof[st], dp[kb]);
+        if (kb == 1 && st % (NS / 4) == 0) weights(0, st / (NS / 4));
+      } else {
+        const int m = n - 2 * NS, ks = m / Tl::kDBlocks, db = m % Tl::kDBlocks;
+        dq[db] = mfma_bf16(fk[n % kBuf], __builtin_bit_cast(bf16x8, ds[ks >> 1][ks & 1]), dq[db]);
+        if (m < NP && m % (NP / 4) == 0) weights(1, m / (NP / 4));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (n == NS - 1) mask(0);
+      if (n == 2 * NS - 1) mask(1);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    // dQ^T += K^T dS^T  (contraction over the tile's 64 keys); transposed fragments two
-    // matrix instructions ahead
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int db = 0; db < Tl::kDBlocks; ++db)
-        dq[db] = mfma_bf16(fa.tr_frag((unsigned)xor_here((int)b_tr, db << 6), (unsigned)xor_here((int)b_tr8, db << 6), ks, 0),
-                           dsb[ks >> 1][ks & 1], dq[db]);
-    constexpr int NM = 4 * Tl::kDBlocks;
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int m = 0; m < NM - 2; ++m) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    __builtin_amdgcn_sched_barrier(0);
   };
 
   // Every wave takes part in the copies and barriers of all nt tiles, but computes only on the
