@@ -1,10 +1,16 @@
-"""ctypes binding of the libmoda C ABI (include/moda.h).
+"""Binding of the libmoda C ABI (include/moda.h).
 
 Argument marshalling only: torch tensors supply device memory and the stream;
 every step of the attention runs in the HIP kernels of libmoda.so.  There is no
 fallback: if the library is missing or a call is rejected, an exception is raised.
+
+Plain valid calls of moda_attn_fwd, moda_attn_bwd, moda_attn_decode and moda_depth_append are marshalled
+by moda_torch.so (bind_csrc/moda_torch.cpp); whatever it declines comes back as None and is taken here,
+through ctypes, with the same checks and an exception for the one that fails.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -12,6 +18,7 @@ import torch
 HERE = os.path.dirname(os.path.abspath(__file__))
 # MODA_LIB_PATH points at another build of the same library (e.g. an experiment)
 LIB_PATH = os.environ.get("MODA_LIB_PATH") or os.path.join(HERE, "libmoda.so")
+NATIVE_PATH = os.path.join(HERE, "moda_torch.so")
 
 MODA_F32, MODA_BF16 = 0, 1
 EXPORTS = ("moda_attn_fwd", "moda_attn_fwd_tuned", "moda_attn_bwd_workspace_bytes", "moda_attn_bwd", "moda_depth_append",
@@ -85,6 +92,27 @@ def lib():
     return _lib
 
 
+_native_module = None
+
+
+def _native():
+    """Load moda_torch.so and hand it the entry points of libmoda.so.  Raises if absent."""
+    global _native_module
+    if _native_module is None:
+        if not os.path.exists(NATIVE_PATH):
+            raise FileNotFoundError(
+                "%s not found: build it with `python -m paper_2603_15619_amd.build`" % NATIVE_PATH)
+        loader = importlib.machinery.ExtensionFileLoader("moda_torch", NATIVE_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("moda_torch", loader))
+        loader.exec_module(m)
+        L = lib()
+        m.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                 (L.moda_attn_fwd, L.moda_attn_bwd, L.moda_attn_bwd_workspace_bytes, L.moda_attn_decode,
+                  L.moda_attn_decode_workspace_bytes, L.moda_depth_append)))
+        _native_module = m
+    return _native_module
+
+
 def status_string(code: int) -> str:
     return lib().moda_status_string(code).decode()
 
@@ -92,6 +120,13 @@ def status_string(code: int) -> str:
 def _check(code):
     if code != 0:
         raise MODAError(code, status_string(code))
+
+
+def _outputs(r):
+    """What moda_torch returned: the outputs, or the status of a call that the library rejected."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 def _ptr(t):
@@ -142,6 +177,10 @@ def moda_attn_fwd(Q, Kseq, Vseq, Kdepth=None, Vdepth=None, depth_count=None, cau
     `tuning` = dict(waves=, heads_per_tile=, head_group=, depth_path=) calls moda_attn_fwd_tuned (the bf16
     kernel's launch geometry chosen by the caller; missing keys keep the library's choice).
     """
+    if tuning is None:
+        r = (_native_module or _native()).fwd(Q, Kseq, Vseq, Kdepth, Vdepth, depth_count, causal, scale, out, lse)
+        if r is not None:
+            return _outputs(r)
     s = make_shape(Q, Kseq, Kdepth, depth_count, causal, scale)
     dev, dt = Q.device, Q.dtype
     _require(Q, "Q", (s.B, s.Hq, s.T, s.d), dt, dev)
@@ -174,6 +213,9 @@ def moda_attn_bwd_workspace_bytes(shape: MODAShape) -> int:
 def moda_attn_bwd(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, dO, depth_count=None, causal=True,
                   scale=None, workspace=None):
     """(dQ, dKseq, dVseq, dKdepth, dVdepth) on the current stream of Q's device."""
+    r = (_native_module or _native()).bwd(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, dO, depth_count, causal, scale, workspace)
+    if r is not None:
+        return _outputs(r)
     s = make_shape(Q, Kseq, Kdepth, depth_count, causal, scale)
     dev, dt = Q.device, Q.dtype
     _require(Q, "Q", (s.B, s.Hq, s.T, s.d), dt, dev)
@@ -204,6 +246,10 @@ def moda_attn_bwd(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, dO, depth_count=None, c
 def moda_depth_append(K, V, Kdepth, Vdepth, slot):
     """Depth-stream write step, in place on the current stream: K, V [B,Hk,T,d] become slot
     `slot` of Kdepth, Vdepth [B,Hk,T,depth_alloc,d]."""
+    r = (_native_module or _native()).append(K, V, Kdepth, Vdepth, slot)
+    if r is not None:
+        _outputs(r)
+        return Kdepth, Vdepth
     B, Hk, T, d = K.shape
     dev, dt = K.device, K.dtype
     _require(K, "K", (B, Hk, T, d), dt, dev)
@@ -227,6 +273,10 @@ def moda_attn_decode(Q, Kseq, Vseq, Kdepth=None, Vdepth=None, T=None, depth_coun
     token's depth slots Kdepth/Vdepth [B,Hk,depth_alloc,d] or None.  noalloc=True calls
     moda_attn_decode_noalloc (the library's own scratch array instead of a workspace; `out`
     and `lse` must then be given, so that this wrapper allocates nothing either)."""
+    if not noalloc:
+        r = (_native_module or _native()).decode(Q, Kseq, Vseq, Kdepth, Vdepth, T, depth_count, scale, out, lse, workspace)
+        if r is not None:
+            return _outputs(r)
     B, Hq, d = Q.shape
     Hk, kv_alloc = Kseq.shape[1], Kseq.shape[2]
     T = kv_alloc if T is None else int(T)

@@ -12,6 +12,10 @@ LIB = os.path.join(HERE, "libmoda.so")
 SYNTH_SRC = os.path.join(HERE, "synth_csrc", "moda_synth.hip")
 SYNTH_LIB = os.path.join(HERE, "libmoda_synth.so")
 
+# the calls of binding.py in native code: a CPython module (host code only) against torch's headers
+BIND_SRC = os.path.join(HERE, "bind_csrc", "moda_torch.cpp")
+BIND_LIB = os.path.join(HERE, "moda_torch.so")
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
@@ -215,7 +219,27 @@ def build_libmoda() -> str:
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)
     build_synth()
+    build_binding()
     return LIB
+
+
+def build_binding() -> str:
+    """Compiles the native half of the binding into moda_torch.so (g++; no device code)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    inc = [x for d in (*include_paths(), sysconfig.get_paths()["include"], os.path.join(rocm, "include"))
+           for x in ("-isystem", d)]
+    libs = [x for d in library_paths() for x in ("-L" + d,)] + ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    tmp = BIND_LIB + ".tmp.%d" % os.getpid()
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *inc, BIND_SRC, "-o", tmp, *libs],
+                   check=True)
+    os.replace(tmp, BIND_LIB)
+    return BIND_LIB
 
 
 def build_synth() -> str:
