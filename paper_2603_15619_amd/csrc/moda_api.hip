@@ -92,6 +92,7 @@ moda::BwdParams bwd_dims(const moda_shape* s) {
   moda::BwdParams p{};
   p.B = s->B; p.Hq = s->Hq; p.Hk = s->Hk; p.T = s->T;
   p.depth_alloc = s->depth_alloc; p.depth_count = s->depth_count;
+  p.causal = s->causal;
   return p;
 }
 
@@ -118,7 +119,7 @@ int moda_kernels_per_call(const moda_shape* s, int which) {
   if (check_shape(s) != MODA_OK || s->B == 0 || s->T == 0) return 0;
   if (which == 0) return 1;
   if (s->dtype != MODA_BF16 || s->Hq / s->Hk > moda::bwd_bf16_max_group()) return 0;
-  return moda::bwd_bf16_kernels(bwd_dims(s));
+  return moda::bwd_bf16_kernels(bwd_dims(s), s->d);
 }
 
 moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,

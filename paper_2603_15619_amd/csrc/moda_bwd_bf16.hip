@@ -26,7 +26,8 @@
 // gradients of the shared keys and values sum over the group.  dkdv walks the query
 // tiles of all G heads; the depth-slot gradients are computed by a kernel of their own
 // (depth_gqa for G <= 8 on the vector ALUs, depth_group above that on the matrix pipe) that holds
-// the G heads of a position side by side, sums in fp32 and rounds every depth gradient once.
+// the G heads of a position side by side, sums in fp32 and rounds every depth gradient once, or inside
+// dkdv: up to 4 heads on the vector ALUs, 5 to 8 heads with enough slots on the matrix pipe.
 #include <type_traits>
 
 #include "moda_launch.h"
@@ -415,17 +416,253 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_depth_gqa_kernel(BwdParams p)
   depth_gqa_row<D, GT>(p, row < n_rows ? row : n_rows - 1, row < n_rows, threadIdx.x % LPR);
 }
 
+// Eight fp32 as two operands of packed bf16, x = hi + lo to 16 bits.
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& lo) {
+  u32x4 h, l;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    h[k] = pack_bf16(x[2 * k], x[2 * k + 1]);
+    l[k] = pack_bf16(x[2 * k] - bf16_lo(h[k]), x[2 * k + 1] - bf16_hi(h[k]));
+  }
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo = __builtin_bit_cast(bf16x8, l);
+}
+
+// ---------------------------------------------------------------- depth-slot gradients of 5 to 8 heads, matrix pipe
+// The depth slots of ROWS consecutive positions (row0 ...) of one key/value head, handled by one
+// wave, for groups of up to 8 heads (G): per position and 32 slots, as for the larger groups below,
+//   S^T, dP^T (slots x heads) -> E^T -> dQ_p += E Kd_p,   S, dP (heads x slots) -> P, E -> dVd_p, dKd_p.
+// On the vector ALUs (depth_gqa_row) the sums over heads and channels take longer than the slots
+// take to arrive at this group size, and inside the dK/dV kernel they cost what they cost alone;
+// here the vector ALUs only exponentiate, so that the phase is HBM's and the key-tile work of the
+// workgroup next door goes on beside it.  B=1 Hq=64 Hk=8 T=16384 d=64, 64 slots: 1.13 ms in a kernel of
+// its own + 4.39 -> 5.06 ms together (of which 0.9 would be the 4.3 GB at the rate of a large copy).
+// Columns (or rows) of the products past the group repeat heads that exist and get weight zero
+// (lse = +inf).  The weights P and E enter the products as the sum of two bf16 numbers, 16 bits of
+// them, so that the gradients are as exact as with 32-bit weights: the contractions over the heads
+// have room for the second number in the 8 of their 16 places that no head takes, the one over the
+// slots takes a second matrix instruction.
+// LDS of one wave: tiles of 32 rows of Kd and Vd (later of their gradients, so that those are stored
+// row by row, 16 bytes per lane), of 8 rows of Q and dO.  The next 32 slots, and the next position's
+// Q and dO, are in flight in registers meanwhile.
+template <int D>
+struct DepthWave {
+  static constexpr int kKV = 32 * D * 2, kQ = 8 * D * 2;
+  static constexpr int kBytes = 2 * kKV + 2 * kQ;
+};
+
+template <int D, int ROWS>
+__device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int row0, int lane, unsigned lds) {
+  using Tl = Tile<D>;
+  using W = DepthWave<D>;
+  constexpr int RB = D * 2, kInst = W::kKV / 1024, kQInst = W::kQ / 1024;
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int T = p.T, L = p.depth_count, La = p.depth_alloc, G = p.Hq / p.Hk;
+  const int bh0 = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G;
+  const int n_pos = min(ROWS, T - row0);
+  if (n_pos <= 0) return;  // (wave-uniform)
+  const float c2 = p.scale_log2;
+  const unsigned k_tile = lds, v_tile = lds + W::kKV, q_tile = lds + 2 * W::kKV, g_tile = q_tile + W::kQ;
+  const size_t drow = (size_t)La * RB;
+  const size_t dbase = ((size_t)bg * T + row0) * drow;
+  FragAddr<D> fa;
+  fa.init(lane);
+  const int q_row = Tl::off(l32 & 7, hi);
+  // this lane's 16 bytes of a 1 KB piece: row j, chunk position pc (the permutation of piece q differs
+  // by piece_xor(q) from piece 0's)
+  const int j = lane / Tl::kChunks, pc = lane % Tl::kChunks;
+  const int g_off = j * RB + ((pc ^ Tl::swz(j)) << 4);
+  auto lds_at = [](unsigned a) { return (u32x4 __attribute__((address_space(3)))*)(size_t)a; };
+
+  const int nch = (L + 31) / 32;
+  u32x4 kn[kInst], vn[kInst], qn[kQInst], gn[kQInst];
+  f32x2 sn;
+  auto issue_kv = [&](int pos, int c) {
+    const size_t base = dbase + (size_t)pos * drow;
+    const __amdgpu_buffer_rsrc_t kb =
+        __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p.Kdepth + base), 0, L * RB, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vb =
+        __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p.Vdepth + base), 0, L * RB, 0x00020000);
+#pragma unroll
+    for (int q = 0; q < kInst; ++q) {  // (slots past depth_count are not fetched: zeros)
+      const int voff = xor_here(g_off, TileLoader<D>::piece_xor(q));
+      kn[q] = __builtin_amdgcn_raw_buffer_load_b128(kb, voff, c * W::kKV + q * 1024, 2);
+      vn[q] = __builtin_amdgcn_raw_buffer_load_b128(vb, voff, c * W::kKV + q * 1024, 2);
+    }
+  };
+  auto issue_q = [&](int pos) {
+    const int t = row0 + pos;
+#pragma unroll
+    for (int q = 0; q < kQInst; ++q) {
+      const int r = q * (1024 / RB) + j;
+      const size_t off = ((size_t)(bh0 + min(r, G - 1)) * T + t) * RB + ((pc ^ Tl::swz(r)) << 4);
+      qn[q] = *(const u32x4*)((const char*)p.Q + off);
+      gn[q] = *(const u32x4*)((const char*)p.dO + off);
+    }
+    sn = *(const f32x2*)(p.rowstat + ((size_t)(bh0 + min(l32, G - 1)) * T + t) * 2);
+  };
+  if (nch > 0) {
+    issue_q(0);
+    issue_kv(0, 0);
+  }
+  for (int pos = 0; pos < n_pos; ++pos) {
+    const int t = row0 + pos;
+    const i32x4 dk_buf = make_tile_buffer((const char*)p.dKdepth + dbase + (size_t)pos * drow, (unsigned)(L * RB));
+    const i32x4 dv_buf = make_tile_buffer((const char*)p.dVdepth + dbase + (size_t)pos * drow, (unsigned)(L * RB));
+    f32x16 dqa[Tl::kDBlocks];  // dQ^T (depth share): lane = head, registers = channels
+#pragma unroll
+    for (int cb = 0; cb < Tl::kDBlocks; ++cb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dqa[cb][i] = 0.f;
+    float lse2 = INFINITY, delta = 0.f, l4[4], d4[4];
+    if (nch > 0) {
+#pragma unroll
+      for (int q = 0; q < kQInst; ++q) {
+        *lds_at(q_tile + q * 1024 + lane * 16) = qn[q];
+        *lds_at(g_tile + q * 1024 + lane * 16) = gn[q];
+      }
+      lse2 = l32 < G ? sn[0] : INFINITY;
+      delta = sn[1];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {  // heads 4 hi + r
+        l4[r] = __shfl(lse2, hi * 4 + r, 64);
+        d4[r] = __shfl(delta, hi * 4 + r, 64);
+      }
+      issue_q(min(pos + 1, n_pos - 1));
+    }
+    for (int c = 0; c < nch; ++c) {
+#pragma unroll
+      for (int q = 0; q < kInst; ++q) {
+        *lds_at(k_tile + q * 1024 + lane * 16) = kn[q];
+        *lds_at(v_tile + q * 1024 + lane * 16) = vn[q];
+      }
+      const bool last = c == nch - 1;  // (past the last position: its last slots again, not used)
+      issue_kv(last ? min(pos + 1, n_pos - 1) : pos, last ? (pos + 1 < n_pos ? 0 : c) : c + 1);
+      asm volatile("" ::: "memory");
+      const int c0 = c * 32;
+      // ---- slots x heads: E^T, dQ^T += Kd^T E^T
+      {
+        f32x16 s, dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+#pragma unroll
+        for (int st = 0; st < Tl::kDSteps; ++st) {
+          const unsigned xk = (unsigned)xor_here(fa.row + (int)k_tile, st << 5), xq = (unsigned)xor_here(q_row + (int)q_tile, st << 5);
+          s = mfma_bf16(FragAddr<D>::row_frag(xk, 0, 0), FragAddr<D>::row_frag(xq, 0, 0), s);
+          dp = mfma_bf16(FragAddr<D>::row_frag(xk, 0, W::kKV), FragAddr<D>::row_frag(xq, 0, W::kQ), dp);
+        }
+        float ev[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int slot = c0 + (i >> 2) * 8 + hi * 4 + (i & 3);
+          const float pe = slot < L ? fast_exp2(s[i] * c2 - lse2) : 0.f;
+          ev[i] = pe * (dp[i] - delta);
+        }
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          float a8[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) a8[k] = ev[hf * 8 + k];
+          bf16x8 e_hi, e_lo;
+          split8(a8, e_hi, e_lo);
+#pragma unroll
+          for (int cb = 0; cb < Tl::kDBlocks; ++cb) {
+            const bf16x8 kt = FragAddr<D>::tr_frag((unsigned)xor_here(fa.tr + (int)k_tile, cb << 6),
+                                                   (unsigned)xor_here(fa.tr8 + (int)k_tile, cb << 6), hf, 0);
+            dqa[cb] = mfma_bf16(kt, e_hi, dqa[cb]);
+            dqa[cb] = mfma_bf16(kt, e_lo, dqa[cb]);
+          }
+        }
+      }
+      // ---- heads x slots (lane = slot, registers 0..3 = heads 4 hi ..): P, E
+      bf16x8 pb, eb;
+      {
+        f32x16 s, dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+#pragma unroll
+        for (int st = 0; st < Tl::kDSteps; ++st) {
+          const unsigned xk = (unsigned)xor_here(fa.row + (int)k_tile, st << 5), xq = (unsigned)xor_here(q_row + (int)q_tile, st << 5);
+          s = mfma_bf16(FragAddr<D>::row_frag(xq, 0, 0), FragAddr<D>::row_frag(xk, 0, 0), s);
+          dp = mfma_bf16(FragAddr<D>::row_frag(xq, 0, W::kQ), FragAddr<D>::row_frag(xk, 0, W::kKV), dp);
+        }
+        const bool live = c0 + l32 < L;
+        u32x4 pw, ew;  // places 0..3: first numbers, 4..7: second numbers of the four heads
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+          float pv[2], ev[2];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            pv[u] = live ? fast_exp2(s[r + u] * c2 - l4[r + u]) : 0.f;
+            ev[u] = pv[u] * (dp[r + u] - d4[r + u]);
+          }
+          pw[r / 2] = pack_bf16(pv[0], pv[1]);
+          pw[2 + r / 2] = pack_bf16(pv[0] - bf16_lo(pw[r / 2]), pv[1] - bf16_hi(pw[r / 2]));
+          ew[r / 2] = pack_bf16(ev[0], ev[1]);
+          ew[2 + r / 2] = pack_bf16(ev[0] - bf16_lo(ew[r / 2]), ev[1] - bf16_hi(ew[r / 2]));
+        }
+        pb = __builtin_bit_cast(bf16x8, pw);
+        eb = __builtin_bit_cast(bf16x8, ew);
+      }
+      // ---- dVd^T = dO^T P, dKd^T = Q^T E (lane = slot), bf16 rows through the tiles, stored 16 bytes a lane
+      asm volatile("" ::: "memory");
+      auto gradient = [&](unsigned src, const bf16x8& w, float f, unsigned tile, const i32x4& buf) {
+#pragma unroll
+        for (int cb = 0; cb < Tl::kDBlocks; ++cb) {
+          // (one transposing read: 8 heads, for the first and for the second numbers)
+          const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (s16x4 __attribute__((address_space(3)))*)(size_t)(unsigned)xor_here(fa.tr + (int)src, cb << 6));
+          f32x16 acc;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+          acc = mfma_bf16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(a, a, 0, 1, 2, 3, 0, 1, 2, 3)), w, acc);
+#pragma unroll
+          for (int bq = 0; bq < 4; ++bq)
+            *(u32x2 __attribute__((address_space(3)))*)(size_t)(tile + Tl::off(l32, cb * 4 + bq) + hi * 8) =
+                (u32x2){pack_bf16(acc[4 * bq] * f, acc[4 * bq + 1] * f), pack_bf16(acc[4 * bq + 2] * f, acc[4 * bq + 3] * f)};
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < kInst; ++q) {  // (slots past depth_count lie outside the buffer: not stored)
+          const u32x4 x = *lds_at(tile + q * 1024 + lane * 16);
+          buffer_store16_nt(x, buf, xor_here(g_off, TileLoader<D>::piece_xor(q)),
+                            __builtin_amdgcn_readfirstlane(c * W::kKV + q * 1024));
+        }
+      };
+      gradient(g_tile, pb, 1.0f, v_tile, dv_buf);
+      gradient(q_tile, eb, p.scale, k_tile, dk_buf);
+      asm volatile("" ::: "memory");
+    }
+    // allocated but unattended slots get zero gradients
+    for (int i = L * (RB / 16) + lane; i < La * (RB / 16); i += 64) {
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      *(u32x4*)((char*)p.dKdepth + dbase + (size_t)pos * drow + (size_t)i * 16) = z;
+      *(u32x4*)((char*)p.dVdepth + dbase + (size_t)pos * drow + (size_t)i * 16) = z;
+    }
+    if (l32 < G) {
+      float* dst = p.dq_depth + ((size_t)(bh0 + l32) * T + t) * D;
+#pragma unroll
+      for (int cb = 0; cb < Tl::kDBlocks; ++cb)
+#pragma unroll
+        for (int bq = 0; bq < 4; ++bq)
+          *(f32x4*)(dst + cb * 32 + bq * 8 + hi * 4) =
+              (f32x4){dqa[cb][4 * bq], dqa[cb][4 * bq + 1], dqa[cb][4 * bq + 2], dqa[cb][4 * bq + 3]};
+    }
+  }
+}
+
 // ---------------------------------------------------------------- dK, dV
 // Workgroup = 128 keys (4 waves x 32 keys).  Accumulators hold dK^T, dV^T
 // ([channel][key]: a lane owns one key and 64 of its channels).
 // GT: 0 = one query head per key/value head, more than 4 heads per group, or no depth slots;
-// 2, 4 = the depth-slot gradients of a group of up to GT heads are taken here as well
-// (depth_gqa_row).
+// 2, 4, 8 = the depth-slot gradients of a group of up to GT heads are taken here as well
+// (depth_gqa_row; 8: depth_group_rows).
 template <int D, int GT>
 __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   using Tl = Tile<D>;
   using C = BwdCfg<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
+  constexpr int kSmem = GT == 8 && 4 * DepthWave<D>::kBytes > C::kLds ? 4 * DepthWave<D>::kBytes : C::kLds;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmem];
   float* aux = (float*)(smem + C::kLds - C::kAux);
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -454,7 +691,12 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   if (own_depth && depth_first) depth_grad_rows<D, 32>(p, bg, kw0, lane);
   // grouped queries: the workgroup's 128 positions, 256 / (d/8) at a time
   auto group_depth = [&]() {
-    if constexpr (GT > 0) {
+    if constexpr (GT == 8) {
+      __syncthreads();  // (the waves' parts of LDS are other waves' before and after)
+      depth_group_rows<D, 32>(p, bg, kw0, lane, (unsigned)(size_t)(lds_ptr)smem + wave * DepthWave<D>::kBytes);
+      wait_own_reads();
+      __syncthreads();
+    } else if constexpr (GT > 0) {
       constexpr int LPR = D / 8, ROWS = 256 / LPR;
       for (int r0 = 0; r0 < 128; r0 += ROWS) {
         const int t = j0 + r0 + tid / LPR;
@@ -1484,8 +1726,6 @@ size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d) {
 
 int bwd_bf16_max_group() { return 64; }
 
-int bwd_bf16_kernels(const BwdParams& p) { return 3 + ((p.Hq / p.Hk > 4 && p.depth_alloc > 0) ? 1 : 0); }
-
 // Where the short kernels take over, in workgroups of the other kernel (the chip holds 512 of them,
 // two per compute unit).  The lines lie between the sizes at which either side was seen ahead, whole
 // call timed (other kernel / short kernel, us):
@@ -1501,6 +1741,23 @@ static long long few_key_tiles(int D, int G, bool causal) {
   return causal ? 352 : 192;
 }
 static long long few_query_tiles(int D) { return D == 64 ? 257 : 192; }
+static bool few_keys(const BwdParams& p, int d) {
+  return (long long)p.B * p.Hk * ((p.T + 127) / 128) < few_key_tiles(d, p.Hq / p.Hk, p.causal != 0);
+}
+// Depth-slot gradients of 5 to 8 heads: inside dK/dV (depth_group_rows), or in a kernel of their own
+// (depth_gqa).  The former takes 32 slots at a time whether they exist or not, and a wave takes 32
+// positions one after the other: it needs mostly full blocks of slots, and enough key tiles.
+// Backward call, 8 heads per group (kernel of its own / inside, us):
+//   d=64   T=16384: 31 slots 7623 / 7485, 64 slots 8900 / 8070, 12 slots 7329 / 7412;
+//          T=1000:  31 slots 911 / 834, 64 slots 1234 / 1102, 12 slots 805 / 844
+//   d=128  T=16384: 31 slots 14494 / 14205, 12 slots 13982 / 14017;  T=2048: 64 slots 3073 / 2925, 31 slots
+//          2393 / 2354, 12 slots 1944 / 2152;  T=1000: 31 slots 1700 / 1724
+static bool own_depth_kernel(const BwdParams& p, int d) {
+  const int G = p.Hq / p.Hk, L = p.depth_count, blocks = (L + 31) / 32;
+  if (p.depth_alloc == 0 || G <= 4) return false;
+  return G > 8 || few_keys(p, d) || L * 8 < blocks * 32 * (d == 64 ? 5 : 7) || L == 0;
+}
+int bwd_bf16_kernels(const BwdParams& p, int d) { return 3 + (own_depth_kernel(p, d) ? 1 : 0); }
 
 template <int D>
 static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
@@ -1524,7 +1781,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   hipError_t e = launch_kernel(moda_bwd_delta_kernel<D>, dim3((unsigned)g_delta), dim3(256), stream, p.dO, p.O, p.LSE,
                                p.rowstat, rows);
   if (e != hipSuccess) return e;
-  if (G > 4 && p.depth_alloc > 0) {
+  if (own_depth_kernel(p, D)) {
     if (G <= 8) {
       e = launch_kernel(moda_bwd_depth_gqa_kernel<D, 8>, dim3((unsigned)g_depth), dim3(256), stream, p);
     } else {
@@ -1536,12 +1793,13 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   {
-    const bool few = g_dkdv < few_key_tiles(D, G, p.causal != 0);  // (see moda_bwd_dkdv_short_kernel)
+    const bool few = few_keys(p, D);  // (see moda_bwd_dkdv_short_kernel)
     const dim3 gk((unsigned)(few ? (long long)p.B * p.Hk * ((p.T + 31) / 32) : g_dkdv)), blk(256);
-    const bool grouped = G > 1 && G <= 4 && p.depth_alloc > 0;  // the depth-slot gradients of the group run inside dK/dV
+    const bool grouped = G > 1 && p.depth_alloc > 0 && !own_depth_kernel(p, D);  // the group's depth-slot gradients run inside dK/dV
     const auto kernel = !grouped ? (few ? moda_bwd_dkdv_short_kernel<D, 0> : moda_bwd_dkdv_kernel<D, 0>)
                         : G <= 2 ? (few ? moda_bwd_dkdv_short_kernel<D, 2> : moda_bwd_dkdv_kernel<D, 2>)
-                                 : (few ? moda_bwd_dkdv_short_kernel<D, 4> : moda_bwd_dkdv_kernel<D, 4>);
+                        : G <= 4 ? (few ? moda_bwd_dkdv_short_kernel<D, 4> : moda_bwd_dkdv_kernel<D, 4>)
+                                 : moda_bwd_dkdv_kernel<D, 8>;
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;

@@ -34,7 +34,7 @@ hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream);
 // Backward (bf16, Hq / Hk <= bwd_bf16_max_group()): delta, [depth slots of grouped queries,]
 // dK/dV and dQ(/depth) kernels on `stream`.
 int bwd_bf16_max_group();
-int bwd_bf16_kernels(const BwdParams& p);  // kernels one call enqueues
+int bwd_bf16_kernels(const BwdParams& p, int d);  // kernels one call enqueues
 size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d);
 hipError_t launch_bwd_bf16(const BwdParams& p, int d, hipStream_t stream);
 
