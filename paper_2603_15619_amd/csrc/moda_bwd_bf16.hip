@@ -340,16 +340,24 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
   char* dkd = (char*)p.dKdepth + (size_t)rc * drow + l16 * 16;
   char* dvd = (char*)p.dVdepth + (size_t)rc * drow + l16 * 16;
 
-  u32x4 kn = {0u, 0u, 0u, 0u}, vn = kn;
-  if (L > 0) {
-    kn = __builtin_nontemporal_load((const u32x4*)kd);
-    vn = __builtin_nontemporal_load((const u32x4*)vd);
+  // The next kAhead slots are in flight: each is only 2 KB of a wave's loads, and with one ahead a wave
+  // of few heads waited out the memory latency at every slot.  (No load past the last slot, whose branch
+  // is uniform.)  Backward call, one / four ahead: B=6 Hq=16 Hk=8 T=2048, 31 slots d=64 526 / 494 us, d=128
+  // 1018 / 964; B=2 T=1000, 12 slots d=128 116 / 102.  At 8 heads the arithmetic is the longer part.
+  constexpr int kAhead = GT > 4 ? 1 : 4;
+  u32x4 kn[kAhead], vn[kAhead];
+  auto request = [&](int u, int i) {
+    if (i < L) {
+      kn[u] = __builtin_nontemporal_load((const u32x4*)(kd + (size_t)i * RB));
+      vn[u] = __builtin_nontemporal_load((const u32x4*)(vd + (size_t)i * RB));
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    kn[u] = vn[u] = (u32x4){0u, 0u, 0u, 0u};
+    request(u, u);
   }
-  for (int i = 0; i < L; ++i) {
-    const u32x4 kv = kn, vv = vn;
-    const int inext = min(i + 1, L - 1);
-    kn = __builtin_nontemporal_load((const u32x4*)(kd + (size_t)inext * RB));
-    vn = __builtin_nontemporal_load((const u32x4*)(vd + (size_t)inext * RB));
+  auto slot = [&](int i, const u32x4& kv, const u32x4& vv) {
     float kx[8], ak[8], av[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -388,7 +396,16 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
       __builtin_nontemporal_store(o1, (u32x4*)(dvd + (size_t)i * RB));
       __builtin_nontemporal_store(o2, (u32x4*)(dkd + (size_t)i * RB));
     }
-  }
+  };
+  for (int i0 = 0; i0 < L; i0 += kAhead)
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int i = i0 + u;
+      if (i >= L) break;  // (uniform)
+      const u32x4 kv = kn[u], vv = vn[u];
+      request(u, i + kAhead);
+      slot(i, kv, vv);
+    }
   if (live) {
     const u32x4 z = {0u, 0u, 0u, 0u};
     for (int i = L; i < La; ++i) {  // allocated but unattended slots get zero gradients
@@ -1367,13 +1384,16 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
 // The same change of split for dQ when the kernel above would have fewer workgroups than the chip
 // takes: a workgroup = 32 queries, its 4 waves deal out the key tiles (32 keys, private LDS stages),
 // the four dQ^T and the depth share are summed at the end.
-// Whole backward call, B=1 H=8 T=2048, 4 slots: d=64 67 -> 47 us, d=128 104 -> 85 us; B=1 H=2
-// T=16384 d=64: 427 -> 328 us.
+// Whole backward call, B=1 H=8 T=2048, 4 slots: d=64 59 -> 46 us, d=128 97 -> 80 us; B=1 H=2
+// T=16384: d=64 365 -> 320 us, d=128 712 -> 636 us.
+// One LDS tile of K and one of V per wave (V is requested anew as soon as the scores are formed, K after
+// the products): twice the workgroups fit a compute unit that did with two stages.
 template <int D>
-__global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
+__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel(BwdParams p) {
   using Tl = Tile<D>;
   using C = BwdShortCfg<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
+  constexpr int kTiles = 4 * 2 * C::kTile, kExchange = 4 * C::kXWave * 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kTiles > kExchange ? kTiles : kExchange];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
@@ -1386,22 +1406,22 @@ __global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
   const float c2 = p.scale_log2;
 
   const int nt = ((p.causal ? min(T, q0 + 32) : T) + 31) / 32;
-  const unsigned ring = (unsigned)(size_t)(lds_ptr)smem + wave * 2 * C::kStage;
+  const unsigned ktile = (unsigned)(size_t)(lds_ptr)smem + wave * 2 * C::kTile, vtile = ktile + C::kTile;
   FragAddr<D> fa;
   fa.init(lane);
   const i32x4 k_buf = make_tile_buffer((const char*)p.Kseq + (size_t)bg * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
   const i32x4 v_buf = make_tile_buffer((const char*)p.Vseq + (size_t)bg * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
   const int goff = (lane / Tl::kChunks) * Tl::kRowBytes + (((lane % Tl::kChunks) ^ Tl::swz(lane / Tl::kChunks)) << 4);
-  auto issue = [&](int kt, int stage) {
-    const unsigned dst = ring + stage * C::kStage;
+  auto issue = [&](const i32x4& buf, int kt, unsigned dst) {  // (tiles past the end: zeros)
 #pragma unroll
-    for (int q = 0; q < C::kPieces; ++q) {
-      const int voff = xor_here(goff, TileLoader<D>::piece_xor(q));
-      tile_copy16(k_buf, voff, kt * C::kTile + q * 1024, dst + q * 1024);
-      tile_copy16(v_buf, voff, kt * C::kTile + q * 1024, dst + C::kTile + q * 1024);
-    }
+    for (int q = 0; q < C::kPieces; ++q)
+      tile_copy16(buf, xor_here(goff, TileLoader<D>::piece_xor(q)), (int)((unsigned)kt * (unsigned)C::kTile) + q * 1024,
+                  dst + q * 1024);
   };
-  if (wave < nt) issue(wave, 0);
+  if (wave < nt) {
+    issue(k_buf, wave, ktile);
+    issue(v_buf, wave, vtile);
+  }
 
   const int qrow = min(q0 + l32, T - 1);
   bf16x8 qf[Tl::kDSteps], dof[Tl::kDSteps];
@@ -1422,13 +1442,9 @@ __global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
 
-  int stage = 0;
-  for (int kt = wave; kt < nt; kt += 4, stage ^= 1) {
-    wait_own_copies<0>();  // (the wave's own copies into its own LDS, as in the dK/dV kernel)
-    wait_own_reads();
-    if (kt + 4 < nt) issue(kt + 4, stage ^ 1);
-    const unsigned ktile = ring + stage * C::kStage;
-    const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
+  const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
+  for (int kt = wave; kt < nt; kt += 4) {
+    wait_own_copies<0>();
     f32x16 s, dp;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
@@ -1438,6 +1454,8 @@ __global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
       s = mfma_bf16(FragAddr<D>::row_frag(x, 0, 0), qf[st], s);
       dp = mfma_bf16(FragAddr<D>::row_frag(x, 0, C::kTile), dof[st], dp);
     }
+    wait_own_reads();
+    if (kt + 4 < nt) issue(v_buf, kt + 4, vtile);
     const int k0 = kt * 32;
     if (k0 + 32 > T || (p.causal && k0 + 31 > q0)) {  // (uniform) the diagonal, keys past the end
 #pragma unroll
@@ -1458,6 +1476,8 @@ __global__ __launch_bounds__(256) void moda_bwd_dq_short_kernel(BwdParams p) {
         dq[db] = mfma_bf16(FragAddr<D>::tr_frag((unsigned)xor_here((int)b_tr, db << 6), (unsigned)xor_here((int)b_tr8, db << 6),
                                                 hf, 0), dsb, dq[db]);
     }
+    wait_own_reads();
+    if (kt + 4 < nt) issue(k_buf, kt + 4, ktile);
   }
 
   // ---- depth share + the four waves, row-major, 16-byte stores
@@ -1734,13 +1754,18 @@ int bwd_bf16_max_group() { return 64; }
 //          d=64   not causal:     256 wgs 346 / 312, 512 wgs 566 / 596
 //          d=128  causal:         320 wgs 927 / 775, 384 wgs 252 / 248 and 286 / 285, 512 wgs 676 / 788
 //          d=128  not causal:     128 wgs 306 / 216, 256 wgs 627 / 679
-//   dQ     d=64:                  256 wgs 427 / 328 and 60 / 60, 384 wgs 87 / 87, 512 wgs 122 / 131
-//          d=128:                 128 wgs 104 / 85, 256 wgs 243 / 247 and 117 / 128
+//   dQ     d=64   causal:         256 wgs 365 / 320 and 85 / 82, 384 wgs 81 / 79, 512 wgs 114 / 118
+//          d=64   not causal:     32 wgs 18 / 16, 256 wgs 88 / 92
+//          d=128  causal:         128 wgs 97 / 80, 256 wgs T >= 4096 712 / 636 and 232 / 212, else 103 / 103 and 145 / 149
+//          d=128  not causal:     32 wgs 25 / 22, 256 wgs 199 / 212
 static long long few_key_tiles(int D, int G, bool causal) {
   if (D == 64) return !causal ? 384 : G > 1 ? 704 : 448;
   return causal ? 352 : 192;
 }
-static long long few_query_tiles(int D) { return D == 64 ? 257 : 192; }
+static long long few_query_tiles(int D, int T, bool causal) {
+  if (!causal) return 129;
+  return D == 64 ? 385 : T >= 4096 ? 257 : 193;
+}
 static bool few_keys(const BwdParams& p, int d) {
   return (long long)p.B * p.Hk * ((p.T + 127) / 128) < few_key_tiles(d, p.Hq / p.Hk, p.causal != 0);
 }
@@ -1803,7 +1828,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;
-  if (g_dq < few_query_tiles(D))
+  if (g_dq < few_query_tiles(D, p.T, p.causal != 0))
     return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)((long long)p.B * p.Hq * ((p.T + 31) / 32))), dim3(256),
                          stream, p);
   return launch_kernel(moda_bwd_dq_kernel<D, kDqWaves>, dim3((unsigned)g_dq), dim3(kDqWaves * 64), stream, p);
