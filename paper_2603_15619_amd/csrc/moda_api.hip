@@ -56,20 +56,22 @@ int fwd_waves_per_workgroup(const moda_shape* s) {
 }
 
 // Calls that take the kernel for few tiles (moda_fwd_short.hip): n = tiles of 128 (position, head)
-// pairs, i.e. the other kernel's workgroups; the short kernel has 4 n, of which the chip holds 768
-// at d = 64 and 512 at d = 128.  As long as they fit, it is ahead (other / short kernel, us, whole
-// call):
-//   d=64   n=128 33/18 and (not causal) 61/40, n=192 25/23 and 65/43;  n=256 25/29 (T=1000, 7 slots)
-//   d=128  n=128 34/25 and 73/53 and (not causal) 68/54;               n=160 36/41, n=256 38/51
+// pairs, i.e. the other kernel's workgroups; the short kernel has 4 n, of which the chip holds 512 at
+// d = 128 and, at d = 64, 768 with depth slots of one head per tile and 1024 otherwise.  As long as they
+// fit, it is ahead (other / short kernel, us, whole call):
+//   d=64   one head, slots: n=128 33/18 and (not causal) 61/40, n=192 25/23 and 65/43;  n=256 25/29
+//          otherwise:       n=64 17/10, n=256 19/14 and 26/20, (not causal) 23/22 and 21/22;  n=512 24/25
+//   d=128  n=128 34/25 and 73/53 and (not causal) 68/54;                 n=160 36/41, n=256 38/51
 // A second round of its workgroups only pays when the other kernel's longest tile is long: causal
-// calls with n <= 256
-//   d=64   T=4096 59/49, T=16384 200/121, several heads per tile 25/23 and 32/26; (not causal) 22/25
-//   d=128  T=16384 248/207;                                        T=4096 77/80
+// calls with up to twice as many
+//   d=64   one head, slots, n=256: T=4096 59/49;  otherwise, n=512: T=4096 76/65, T=1024 27/27
+//   d=128  n=256: T=16384 248/207, T=4096 77/80
 bool fwd_few_tiles(const moda_shape* s, int heads_per_tile) {
   const long long n = (long long)s->B * s->Hq * ((s->T + 127) / 128);
-  if (n <= (s->d == 64 ? 192 : 128)) return true;
-  if (n > 256 || !s->causal) return false;
-  return s->d == 64 ? heads_per_tile > 1 || s->T >= 4096 : s->T >= 8192;
+  const bool rows = heads_per_tile == 1 && s->depth_count > 0;
+  const int fit = s->d == 128 ? 128 : rows ? 192 : 256;
+  if (n <= fit) return true;
+  return s->causal && n <= (s->d == 64 && !rows ? 512 : 256) && s->T >= (s->d == 64 ? 4096 : 8192);
 }
 
 // Heads that one die (workgroup ids equal mod 8) walks together, tile by tile: as many as have

@@ -16,7 +16,7 @@
 // the waves after the key tiles.
 //
 // Bound by a wave's chain copy -> products -> exponentials -> products on the key tiles and by HBM on
-// the depth slots.  B=1 H=8 T=2048, 4 slots: d=64 33 -> 18 us, d=128 43 -> 31 us (of which 15 are the
+// the depth slots.  B=1 H=8 T=2048, 4 slots: d=64 33 -> 18 us, d=128 43 -> 31 us (15 of them the
 // host's); B=1 H=2 T=16384 d=64: 200 -> 121 us.
 //
 // K and V have one LDS tile each per wave; the next tile's K is requested as soon as the scores of
@@ -30,21 +30,23 @@ namespace moda {
 constexpr int kShortCols = 32;  // (position, head) pairs per workgroup
 constexpr int kShortWaves = 4;
 
-template <int D>
+// ROWS: depth slots of one head per tile are taken on the vector ALUs, as a fifth partial state.
+template <int D, bool ROWS>
 struct FwdShortCfg {
   static constexpr int kTile = 32 * D * 2;           // a K or V tile of 32 keys
   static constexpr int kPieces = kTile / 1024;       // copy instructions per tile
   static constexpr int kXRow = 64 + 4;               // states are exchanged 64 channels at a time
   static constexpr int kXPart = kShortCols * kXRow;  // floats of one partial state
   static constexpr int kTiles = kShortWaves * 2 * kTile;
-  static constexpr int kExchange = (kShortWaves + 1) * kXPart * 4;
+  static constexpr int kExchange = (kShortWaves + (ROWS ? 1 : 0)) * kXPart * 4;
   static constexpr int kLds = kTiles > kExchange ? kTiles : kExchange;
 };
 
-template <int D>
-__global__ __launch_bounds__(kShortWaves * 64, D == 64 ? 3 : 2) void moda_fwd_short_kernel(FwdParams p) {
+// (at d = 64 without a fifth state four workgroups fit a compute unit)
+template <int D, bool ROWS>
+__global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void moda_fwd_short_kernel(FwdParams p) {
   using Tl = Tile<D>;
-  using C = FwdShortCfg<D>;
+  using C = FwdShortCfg<D, ROWS>;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
   __shared__ float stat_m[kShortWaves + 1][kShortCols], stat_l[kShortWaves + 1][kShortCols];
 
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 64 ? 3 : 2) void moda_fwd_sh
 
   // ---- depth slots, one head per tile: rows wave * 8 ... + 7, 64 / (d/8) at a time
   constexpr int LPR = Tl::kChunks, RPS = 64 / LPR, NIT = 8 / RPS;
-  const bool rows_on_valu = L > 0 && GT == 1;
+  constexpr bool rows_on_valu = ROWS;
   float d_o[NIT][8], d_m[NIT], d_l[NIT];
   auto depth_rows = [&]() {
     constexpr int kC = 5;  // slots per step, the next step's in flight
@@ -338,9 +340,11 @@ hipError_t launch_fwd_short(const FwdParams& p, int d, hipStream_t stream) {
   const long long blocks = (long long)p.B * (p.Hq / gt) * p.n_qtiles;
   if (!grid_ok(blocks)) return kGridTooLarge;
   dim3 grid((unsigned)blocks), block(kShortWaves * 64);
-  if (d == 128) return launch_kernel(moda_fwd_short_kernel<128>, grid, block, stream, p);
-  if (d == 64) return launch_kernel(moda_fwd_short_kernel<64>, grid, block, stream, p);
-  return hipErrorInvalidValue;
+  if (d != 64 && d != 128) return hipErrorInvalidValue;
+  const bool rows = p.depth_count > 0 && gt == 1;
+  const auto kernel = d == 128 ? (rows ? moda_fwd_short_kernel<128, true> : moda_fwd_short_kernel<128, false>)
+                               : (rows ? moda_fwd_short_kernel<64, true> : moda_fwd_short_kernel<64, false>);
+  return launch_kernel(kernel, grid, block, stream, p);
 }
 
 }  // namespace moda

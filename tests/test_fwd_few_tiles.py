@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,La", [(1, 1, 1, 1, 64, 2, 3), (1, 2, 2, 31, 128, 5, None), (2, 2, 2, 32, 64, 6, 8),
                                               (1, 3, 3, 33, 128, 11, None), (1, 2, 2, 129, 64, 31, None), (2, 4, 2, 63, 128, 3, 4),
-                                              (1, 8, 1, 97, 64, 9, 10), (1, 32, 1, 65, 128, 1, None), (1, 64, 1, 40, 64, 33, 34),
+                                              (1, 8, 1, 97, 64, 9, 10), (1, 32, 1, 65, 128, 1, None), (1, 64, 1, 40, 64, 33, 34), (3, 32, 8, 200, 64, 5, None),
                                               (1, 12, 2, 161, 128, 0, 2), (1, 4, 1, 1030, 64, 7, None)])
 def test_fwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
     inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1500 + T + L, device="cuda", depth_alloc=La)
