@@ -422,22 +422,27 @@ void moda_decode_partial_mfma_kernel(DecodeParams p) {
   }
 }
 
-// One workgroup of D threads per (batch, query head): thread = channel.  The slices are folded
-// eight at a time (their loads issued together), with a running reference like any other
-// online softmax.
-template <int D>
-__global__ __launch_bounds__(D) void moda_decode_merge_kernel(DecodeParams p) {
+// One workgroup of NG x D threads per (batch, query head): thread = channel, group g of D threads folds
+// the slices g, g + NG, ... eight at a time (their loads issued together), with a running reference
+// like any other online softmax; the groups' states are folded through LDS.  The fold of a head is
+// a chain of memory latencies, one per eight slices, hence NG = 4 where there are more than 16 (B=8
+// Hq=64, 49 slices of d=64: 7.6 -> 4.8 us; B=8 Hq=16, 17 slices of d=128: 5.1 -> 5.0 us).
+constexpr int kMergeOne = 16;
+
+template <int D, int NG>
+__global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams p) {
   constexpr int kU = 8;
-  const int ch = threadIdx.x;
+  __shared__ float red[NG > 1 ? NG : 1][D], stat[NG > 1 ? NG : 1][2];
+  const int ch = threadIdx.x % D, g = threadIdx.x / D;
   const int bh = blockIdx.x;
   const float c2 = p.scale_log2;
   const float* ws = p.ws + (size_t)bh * p.n_slices * (D + 2);
   float mm = -INFINITY, ll = 0.f, oo = 0.f;
-  for (int s0 = 0; s0 < p.n_slices; s0 += kU) {
+  for (int s0 = g; s0 < p.n_slices; s0 += kU * NG) {
     float mi[kU], li[kU], oi[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const float* w = ws + (size_t)min(s0 + u, p.n_slices - 1) * (D + 2);
+      const float* w = ws + (size_t)min(s0 + u * NG, p.n_slices - 1) * (D + 2);
       mi[u] = w[D];
       li[u] = w[D + 1];
       oi[u] = w[ch];
@@ -445,7 +450,7 @@ __global__ __launch_bounds__(D) void moda_decode_merge_kernel(DecodeParams p) {
     float mn = mm;
 #pragma unroll
     for (int u = 0; u < kU; ++u)
-      if (s0 + u < p.n_slices) mn = fmaxf(mn, mi[u]);
+      if (s0 + u * NG < p.n_slices) mn = fmaxf(mn, mi[u]);
     // (every slice holds at least one key: mn is finite; with mm = -inf the factor is 0)
     const float al = fast_exp2((mm - mn) * c2);
     mm = mn;
@@ -453,19 +458,43 @@ __global__ __launch_bounds__(D) void moda_decode_merge_kernel(DecodeParams p) {
     oo *= al;
 #pragma unroll
     for (int u = 0; u < kU; ++u)
-      if (s0 + u < p.n_slices) {
+      if (s0 + u * NG < p.n_slices) {
         const float f = fast_exp2((mi[u] - mm) * c2);
         ll += f * li[u];
         oo += f * oi[u];
       }
+  }
+  if constexpr (NG > 1) {  // (more slices than groups: every group holds a finite reference)
+    red[g][ch] = oo;
+    if (ch == 0) {
+      stat[g][0] = mm;
+      stat[g][1] = ll;
+    }
+    __syncthreads();
+    if (g > 0) return;
+    const float m0 = mm;
+#pragma unroll
+    for (int w = 1; w < NG; ++w) mm = fmaxf(mm, stat[w][0]);
+    const float f0 = fast_exp2((m0 - mm) * c2);
+    ll *= f0;
+    oo *= f0;
+#pragma unroll
+    for (int w = 1; w < NG; ++w) {
+      const float f = fast_exp2((stat[w][0] - mm) * c2);
+      ll += f * stat[w][1];
+      oo += f * red[w][ch];
+    }
   }
   ((__bf16*)p.O)[(size_t)bh * D + ch] = (__bf16)(oo / ll);
   if (ch == 0) p.LSE[bh] = mm * p.scale + __logf(ll);
 }
 
 // How a call is cut into slices.  One query head per key/value head: workgroups of 4 waves,
-// enough of them to fill 256 compute units a few times over, slices of at least 256 keys.
-// More than 4 query heads per key/value head (matrix-pipe kernel): one slice per wave.
+// enough of them to fill 256 compute units a few times over, slices of at least 256 keys (128 while
+// that makes no more than 8 slices: T=1003, 16 heads 7.4 -> 6.9 us; but 16 slices of 128 keys at T=2000,
+// 4 heads 6.8 -> 7.5 us).
+// More than 4 query heads per key/value head (matrix-pipe kernel): one slice per wave, of at least 128
+// keys (256 / 128: B=1 Hq=64 Hk=8 d=64 T=1003 13.2 / 10.1 us, T=4096 14.6 / 12.7; B=4 T=2000 d=128 22 / 16).
 struct DecodePlan {
   bool mfma;
   int n_split;
@@ -476,7 +505,11 @@ static DecodePlan decode_plan(int B, int Hq, int Hk, int T, int d) {
   const int G = Hq / Hk;
   // up to 4 heads per group the vector-ALU kernel is at the memory rate and ahead (measured)
   pl.mfma = G > 4;
-  const int most = (T + 255) / 256;
+  const int fine = (T + 127) / 128, coarse = (T + 255) / 256;
+  int most = pl.mfma || fine <= 8 ? fine : coarse > 8 ? coarse : 8;
+  // (never so many that the partial results outgrow the library's own scratch array where those of the
+  // coarser slices fit it)
+  if ((size_t)B * Hq * (most + 1) * (d + 2) * sizeof(float) > kDecodeScratchBytes) most = coarse;
   int want, step;
   if (pl.mfma) {
     const int n_gc = (G + 31) / 32;
@@ -521,7 +554,9 @@ static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream)
     else e = launch_kernel(moda_decode_partial_kernel<D, 1>, grid, block, stream, p);
   }
   if (e != hipSuccess) return e;
-  return launch_kernel(moda_decode_merge_kernel<D>, dim3((unsigned)(p.B * p.Hq)), dim3(D), stream, p);
+  if (p.n_slices <= kMergeOne)
+    return launch_kernel(moda_decode_merge_kernel<D, 1>, dim3((unsigned)(p.B * p.Hq)), dim3(D), stream, p);
+  return launch_kernel(moda_decode_merge_kernel<D, 4>, dim3((unsigned)(p.B * p.Hq)), dim3(4 * D), stream, p);
 }
 
 hipError_t launch_decode_bf16(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,

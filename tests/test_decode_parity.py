@@ -109,3 +109,25 @@ def test_decode_rejects_bad_arguments():
         moda_attn_decode(q, inp["Kseq"], inp["Vseq"], T=0)
     with pytest.raises(MODAError):
         moda_attn_decode(q.float(), inp["Kseq"].float(), inp["Vseq"].float())  # bf16 only
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L", [(1, 4, 4, 1024, 128, 3), (1, 2, 2, 1025, 64, 0), (1, 8, 1, 2047, 64, 4),
+                                           (1, 16, 2, 2176, 128, 5), (1, 8, 1, 128, 64, 0), (1, 1, 1, 40000, 64, 2)])
+def test_decode_slice_counts(B, Hq, Hk, T, d, L):
+    """Both sides of 8 slices of 128 keys, of one block per slice, and of the 16 slices up to which one
+    group of threads folds a head."""
+    check(B, Hq, Hk, T, d, L, 1900 + T)
+
+
+def test_slices_fit_the_scratch_array_where_coarser_ones_do():
+    """moda_attn_decode_noalloc takes what 256-key slices would let it take."""
+    import ctypes
+
+    from paper_2603_15619_amd.binding import MODAShape, lib
+
+    most = lib().moda_attn_decode_noalloc_max_bytes()
+    for B, Hk, G, T, d in [(8, 2, 32, 2000, 128), (30, 1, 8, 16000, 64), (400, 4, 1, 1000, 128), (6, 1, 64, 5000, 64)]:
+        s = MODAShape(B, G * Hk, Hk, T, d, 2, 2, 1, 0.0, 1)
+        coarse = B * G * Hk * ((T + 255) // 256 + 1) * (d + 2) * 4
+        if coarse <= most:
+            assert lib().moda_attn_decode_workspace_bytes(ctypes.byref(s)) <= most
