@@ -26,13 +26,13 @@ sys.path.insert(0, ROOT)
 
 WORKLOADS = {
     # name: (B, Hq, Hk, T, d, depth_count, dtype)
-    "long_context_64k": (1, 16, 16, 65536, 128, 15, "bf16"),   # BASELINE configs[2] (the metric's workload)
-    "layer_1p5b_4k": (8, 16, 16, 4096, 128, 15, "bf16"),       # BASELINE configs[1]
-    "tiny_fp32": (1, 2, 2, 256, 64, 4, "f32"),                 # BASELINE configs[0]
-    "bwd_layer_1p5b_4k": (8, 16, 16, 4096, 128, 15, "bf16"),   # BASELINE configs[4] (backward)
+    "long_context_64k": (1, 16, 16, 65536, 128, 15, "bf16"),   # the headline workload
+    "layer_1p5b_4k": (8, 16, 16, 4096, 128, 15, "bf16"),
+    "tiny_fp32": (1, 2, 2, 256, 64, 4, "f32"),    
+    "bwd_layer_1p5b_4k": (8, 16, 16, 4096, 128, 15, "bf16"),   # backward
     "copy_calibration": None,  # plain device copy of known size, for scaling the HBM byte counters
     "mfma_calibration": None,  # what the matrix pipe alone sustains (zero and N(0,1) bf16 operands)
-    "sweep": None,             # BASELINE configs[3]: B=4 H=16 d=128, T x depth_count grid
+    "sweep": None,             # B=4 H=16 d=128, T x depth_count grid
     "paper_table2": None,      # the paper's Table 2 shapes (d=64, grouped queries, 64..256 slots), fwd+bwd
     "decode": None,            # one new token per sequence against a 64K sequence cache
     "append": None,            # the depth stream's write step (a strided copy)
@@ -124,7 +124,7 @@ def run_mfma_calibration(args):
 
 
 def run_sweep(args):
-    """BASELINE configs[3]: TFLOP/s and depth-segment GB/s per (T, depth_count) point."""
+    """TFLOP/s and depth-segment GB/s per (T, depth_count) point."""
     from paper_2603_15619_amd import moda_attn_fwd, synth
 
     B, H, d = 4, 16, 128

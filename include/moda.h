@@ -103,7 +103,8 @@ moda_status moda_attn_fwd(const void* Q, const void* Kseq, const void* Vseq, con
  * The same forward pass with the launch geometry of the bf16 kernel chosen by the caller
  * instead of derived from the shape (for experiments and for tests that must reach every
  * code path; the result is the same operator whatever the geometry).  A field that is 0
- * keeps the library's own choice; `tuning` == NULL is moda_attn_fwd.
+ * keeps the library's own choice; `tuning` == NULL is moda_attn_fwd (which, unlike a call with a
+ * tuning, takes a kernel of another split where the problem has few tiles).
  *   waves           4 or 8: waves (of 32 queries each) per workgroup
  *   heads_per_tile  query heads of one group that share a tile (side by side in every wave): a
  *                   power of two up to 32 that divides Hq / Hk
