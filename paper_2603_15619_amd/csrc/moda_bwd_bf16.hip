@@ -1775,12 +1775,14 @@ static bool few_keys(const BwdParams& p, int d) {
 // Backward call, 8 heads per group (kernel of its own / inside, us):
 //   d=64   T=16384: 31 slots 7623 / 7485, 64 slots 8900 / 8070, 12 slots 7329 / 7412;
 //          T=1000:  31 slots 911 / 834, 64 slots 1234 / 1102, 12 slots 805 / 844
-//   d=128  T=16384: 31 slots 14494 / 14205, 12 slots 13982 / 14017;  T=2048: 64 slots 3073 / 2925, 31 slots
-//          2393 / 2354, 12 slots 1944 / 2152;  T=1000: 31 slots 1700 / 1724
+// d = 128 keeps the kernel of its own: beside the key tiles' registers the 32 slots and the next 32 do not
+// fit (91 registers went to scratch memory, reloaded at every position), and the gain was 2 to 5 % at best
+// (T=16384, 31 slots 14494 / 14205; T=2048, 64 slots 3073 / 2925) and a loss elsewhere (T=1000, 31 slots
+// 1700 / 1724; B=116 Hq=32 Hk=4 T=84, 31 slots 503 / 530).
 static bool own_depth_kernel(const BwdParams& p, int d) {
   const int G = p.Hq / p.Hk, L = p.depth_count, blocks = (L + 31) / 32;
   if (p.depth_alloc == 0 || G <= 4) return false;
-  return G > 8 || few_keys(p, d) || L * 8 < blocks * 32 * (d == 64 ? 5 : 7) || L == 0;
+  return G > 8 || d != 64 || few_keys(p, d) || L * 8 < blocks * 32 * 5 || L == 0;
 }
 int bwd_bf16_kernels(const BwdParams& p, int d) { return 3 + (own_depth_kernel(p, d) ? 1 : 0); }
 
@@ -1824,7 +1826,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     const auto kernel = !grouped ? (few ? moda_bwd_dkdv_short_kernel<D, 0> : moda_bwd_dkdv_kernel<D, 0>)
                         : G <= 2 ? (few ? moda_bwd_dkdv_short_kernel<D, 2> : moda_bwd_dkdv_kernel<D, 2>)
                         : G <= 4 ? (few ? moda_bwd_dkdv_short_kernel<D, 4> : moda_bwd_dkdv_kernel<D, 4>)
-                                 : moda_bwd_dkdv_kernel<D, 8>;
+                                 : moda_bwd_dkdv_kernel<D, D == 64 ? 8 : 4>;  // (d = 128: never more than 4 here)
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;

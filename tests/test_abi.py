@@ -146,3 +146,14 @@ def test_size_limits_without_gpu(L):
 
     assert tuned(waves=8, heads_per_tile=2, head_group=1) == 1   # accepted (then NULL output)
     assert tuned(waves=5) == 2 and tuned(heads_per_tile=4) == 2 and tuned(head_group=-2) == 2
+
+
+@pytest.mark.parametrize("d,kernels", [(64, 3), (128, 4)])
+def test_depth_gradients_of_5_to_8_heads_take_their_own_kernel_at_d_128(d, kernels):
+    """Many key tiles, full blocks of slots: inside dK/dV at d = 64 only (at d = 128 the registers do not
+    suffice and it would reload them from scratch memory at every position)."""
+    from paper_2603_15619_amd.binding import MODAShape, lib
+
+    for G in (5, 8):
+        s = MODAShape(8, 8 * G, 8, 4096, d, 64, 64, 1, 0.0, 1)
+        assert lib().moda_kernels_per_call(ctypes.byref(s), 1) == kernels
