@@ -433,16 +433,16 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_depth_gqa_kernel(BwdParams p)
   depth_gqa_row<D, GT>(p, row < n_rows ? row : n_rows - 1, row < n_rows, threadIdx.x % LPR);
 }
 
-// Eight fp32 as two operands of packed bf16, x = hi + lo to 16 bits.
-__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& lo) {
-  u32x4 h, l;
+// Two fp32 as three pairs of bf16 whose sum they are: the differences are exact, and three times 8 bits
+// hold the 24 of a float.  (x, y) become what the last pair leaves: zero for numbers whose third part
+// is representable, NaN where x is infinite, NaN or rounds to an infinite bf16.
+__device__ __forceinline__ void split2(float& x, float& y, uint32_t (&part)[3]) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    h[k] = pack_bf16(x[2 * k], x[2 * k + 1]);
-    l[k] = pack_bf16(x[2 * k] - bf16_lo(h[k]), x[2 * k + 1] - bf16_hi(h[k]));
+  for (int k = 0; k < 3; ++k) {
+    part[k] = pack_bf16(x, y);
+    x -= bf16_lo(part[k]);
+    y -= bf16_hi(part[k]);
   }
-  hi = __builtin_bit_cast(bf16x8, h);
-  lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // ---------------------------------------------------------------- depth-slot gradients of 5 to 8 heads, matrix pipe
@@ -455,10 +455,11 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& 
 // workgroup next door goes on beside it.  B=1 Hq=64 Hk=8 T=16384 d=64, 64 slots: 1.13 ms in a kernel of
 // its own + 4.39 -> 5.06 ms together (of which 0.9 would be the 4.3 GB at the rate of a large copy).
 // Columns (or rows) of the products past the group repeat heads that exist and get weight zero
-// (lse = +inf).  The weights P and E enter the products as the sum of two bf16 numbers, 16 bits of
-// them, so that the gradients are as exact as with 32-bit weights: the contractions over the heads
-// have room for the second number in the 8 of their 16 places that no head takes, the one over the
-// slots takes a second matrix instruction.
+// (lse = +inf).  The weights P and E enter the products as the sum of three bf16 numbers, i.e. with all
+// their 24 bits: the contractions over the heads have room for the second number in the 8 of their 16
+// places that no head takes and take a second matrix instruction for the third, the one over the slots
+// takes three.  A weight that is infinite or NaN has no such sum: the positions that show one (a logit
+// gradient E covers its P, Q, dO, K and V) are left to the vector ALUs at the end (depth_gqa_row).
 // LDS of one wave: tiles of 32 rows of Kd and Vd (later of their gradients, so that those are stored
 // row by row, 16 bytes per lane), of 8 rows of Q and dO.  The next 32 slots, and the next position's
 // Q and dO, are in flight in registers meanwhile.
@@ -522,8 +523,11 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
     issue_q(0);
     issue_kv(0, 0);
   }
+  static_assert(ROWS <= 32, "one bit per position");
+  unsigned again = 0;  // positions with weights that are not finite
   for (int pos = 0; pos < n_pos; ++pos) {
     const int t = row0 + pos;
+    float not_finite = 0.f;  // zero, or NaN
     const i32x4 dk_buf = make_tile_buffer((const char*)p.dKdepth + dbase + (size_t)pos * drow, (unsigned)(L * RB));
     const i32x4 dv_buf = make_tile_buffer((const char*)p.dVdepth + dbase + (size_t)pos * drow, (unsigned)(L * RB));
     f32x16 dqa[Tl::kDBlocks];  // dQ^T (depth share): lane = head, registers = channels
@@ -577,22 +581,28 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
         }
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
-          float a8[8];
+          u32x4 e[3];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) a8[k] = ev[hf * 8 + k];
-          bf16x8 e_hi, e_lo;
-          split8(a8, e_hi, e_lo);
+          for (int k = 0; k < 4; ++k) {
+            float& x = ev[hf * 8 + 2 * k];
+            float& y = ev[hf * 8 + 2 * k + 1];
+            uint32_t part[3];
+            split2(x, y, part);
+            not_finite = fmaf(x, 0.f, fmaf(y, 0.f, not_finite));
+#pragma unroll
+            for (int n = 0; n < 3; ++n) e[n][k] = part[n];
+          }
 #pragma unroll
           for (int cb = 0; cb < Tl::kDBlocks; ++cb) {
             const bf16x8 kt = FragAddr<D>::tr_frag((unsigned)xor_here(fa.tr + (int)k_tile, cb << 6),
                                                    (unsigned)xor_here(fa.tr8 + (int)k_tile, cb << 6), hf, 0);
-            dqa[cb] = mfma_bf16(kt, e_hi, dqa[cb]);
-            dqa[cb] = mfma_bf16(kt, e_lo, dqa[cb]);
+#pragma unroll
+            for (int n = 0; n < 3; ++n) dqa[cb] = mfma_bf16(kt, __builtin_bit_cast(bf16x8, e[n]), dqa[cb]);
           }
         }
       }
       // ---- heads x slots (lane = slot, registers 0..3 = heads 4 hi ..): P, E
-      bf16x8 pb, eb;
+      u32x4 pw[2], ew[2];  // [0] places 0..3: first numbers, 4..7: second numbers of the four heads; [1] third numbers
       {
         f32x16 s, dp;
 #pragma unroll
@@ -604,7 +614,7 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
           dp = mfma_bf16(FragAddr<D>::row_frag(xq, 0, W::kQ), FragAddr<D>::row_frag(xk, 0, W::kKV), dp);
         }
         const bool live = c0 + l32 < L;
-        u32x4 pw, ew;  // places 0..3: first numbers, 4..7: second numbers of the four heads
+        pw[1] = ew[1] = (u32x4){0u, 0u, 0u, 0u};
 #pragma unroll
         for (int r = 0; r < 4; r += 2) {
           float pv[2], ev[2];
@@ -613,26 +623,32 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
             pv[u] = live ? fast_exp2(s[r + u] * c2 - l4[r + u]) : 0.f;
             ev[u] = pv[u] * (dp[r + u] - d4[r + u]);
           }
-          pw[r / 2] = pack_bf16(pv[0], pv[1]);
-          pw[2 + r / 2] = pack_bf16(pv[0] - bf16_lo(pw[r / 2]), pv[1] - bf16_hi(pw[r / 2]));
-          ew[r / 2] = pack_bf16(ev[0], ev[1]);
-          ew[2 + r / 2] = pack_bf16(ev[0] - bf16_lo(ew[r / 2]), ev[1] - bf16_hi(ew[r / 2]));
+          uint32_t part[3];
+          split2(pv[0], pv[1], part);
+          pw[0][r / 2] = part[0];
+          pw[0][2 + r / 2] = part[1];
+          pw[1][r / 2] = part[2];
+          split2(ev[0], ev[1], part);
+          ew[0][r / 2] = part[0];
+          ew[0][2 + r / 2] = part[1];
+          ew[1][r / 2] = part[2];
         }
-        pb = __builtin_bit_cast(bf16x8, pw);
-        eb = __builtin_bit_cast(bf16x8, ew);
       }
       // ---- dVd^T = dO^T P, dKd^T = Q^T E (lane = slot), bf16 rows through the tiles, stored 16 bytes a lane
       asm volatile("" ::: "memory");
-      auto gradient = [&](unsigned src, const bf16x8& w, float f, unsigned tile, const i32x4& buf) {
+      auto gradient = [&](unsigned src, const u32x4 (&w)[2], float f, unsigned tile, const i32x4& buf) {
 #pragma unroll
         for (int cb = 0; cb < Tl::kDBlocks; ++cb) {
-          // (one transposing read: 8 heads, for the first and for the second numbers)
+          // (one transposing read: 8 heads, for the first and for the second numbers, and for the third)
           const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
               (s16x4 __attribute__((address_space(3)))*)(size_t)(unsigned)xor_here(fa.tr + (int)src, cb << 6));
           f32x16 acc;
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-          acc = mfma_bf16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(a, a, 0, 1, 2, 3, 0, 1, 2, 3)), w, acc);
+#pragma unroll
+          for (int n = 0; n < 2; ++n)
+            acc = mfma_bf16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(a, a, 0, 1, 2, 3, 0, 1, 2, 3)),
+                            __builtin_bit_cast(bf16x8, w[n]), acc);
 #pragma unroll
           for (int bq = 0; bq < 4; ++bq)
             *(u32x2 __attribute__((address_space(3)))*)(size_t)(tile + Tl::off(l32, cb * 4 + bq) + hi * 8) =
@@ -646,8 +662,8 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
                             __builtin_amdgcn_readfirstlane(c * W::kKV + q * 1024));
         }
       };
-      gradient(g_tile, pb, 1.0f, v_tile, dv_buf);
-      gradient(q_tile, eb, p.scale, k_tile, dk_buf);
+      gradient(g_tile, pw, 1.0f, v_tile, dv_buf);
+      gradient(q_tile, ew, p.scale, k_tile, dk_buf);
       asm volatile("" ::: "memory");
     }
     // allocated but unattended slots get zero gradients
@@ -664,6 +680,16 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
         for (int bq = 0; bq < 4; ++bq)
           *(f32x4*)(dst + cb * 32 + bq * 8 + hi * 4) =
               (f32x4){dqa[cb][4 * bq], dqa[cb][4 * bq + 1], dqa[cb][4 * bq + 2], dqa[cb][4 * bq + 3]};
+    }
+    if (__builtin_amdgcn_ballot_w64(not_finite != not_finite) != 0) again |= 1u << pos;
+  }
+  if (again != 0) {  // (wave-uniform)
+    constexpr int LPR = D / 8, RPS = 64 / LPR;
+    wait_own_copies<0>();  // (the stores that are replaced have been made)
+    for (int r0 = 0; r0 < n_pos; r0 += RPS) {
+      const int r = r0 + lane / LPR;
+      if (((again >> r0) & ((1u << RPS) - 1)) != 0)
+        depth_gqa_row<D, 8>(p, (long long)bg * T + row0 + min(r, n_pos - 1), r < n_pos && ((again >> r) & 1u) != 0, lane % LPR);
     }
   }
 }

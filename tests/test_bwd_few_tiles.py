@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import moda_ref as R
-from paper_2603_15619_amd import synth
+from paper_2603_15619_amd import moda_attn_bwd, moda_attn_fwd, synth
 from test_bwd_parity import NAMES, check_full, compare, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +48,55 @@ def test_bwd_depth_slots_of_5_to_8_heads_inside_dkdv(B, Hq, Hk, T, d, L, La, cau
             compare(name, g[b], r, n)
     for g in grads:
         assert torch.isfinite(g.float()).all()
+
+
+def test_depth_gradients_of_8_heads_use_32_bit_weights():
+    """Two heads whose weights on a slot differ by 2^-14 of them and whose dO are opposite: dVdepth is that
+    difference.  Each weight is 2^(s - lse) with both terms below 8 and rounded at 2^-22, an error of the
+    difference of some 2^-22 of the weight (root mean square); the bf16 result, 2^-14 of it, adds 2^-23.
+    Weights of 16 bits would be off by 2^-19 or 2^-20."""
+    B, Hk, G, L, d = 48, 8, 8, 32, 64
+    inp = synth.make_inputs(B, G * Hk, Hk, 1, d, L, dtype="bf16", seed=77, device="cuda", with_dO=True)
+    for k in ("Q", "Kseq", "Kdepth"):
+        inp[k] *= 0.25
+    inp["Kseq"][..., 0] = 0.0
+    inp["Kdepth"][..., 0] = 2.0 ** -12  # times a difference of 2 in Q's first channel, scaled by 1 / 8 ...
+    inp["Kdepth"][:, :, :, ::2, 0] *= -1  # ... up or down (a common shift would cancel in the weights)
+    Q, dO = (inp[k].view(B, Hk, G, d) for k in ("Q", "dO"))
+    Q[:, :, 1] = Q[:, :, 0]
+    Q[:, :, 0, 0], Q[:, :, 1, 0] = 1.0, -1.0
+    dO.zero_()
+    dO[:, :, 0], dO[:, :, 1] = 1.0, -1.0
+    q, kd, k = Q.double(), inp["Kdepth"].double()[:, :, 0], inp["Kseq"].double()[:, :, 0]
+    s = torch.cat([(kd[:, :, None] * q[:, :, :, None]).sum(-1), (k[:, :, None] * q).sum(-1, keepdim=True)], -1) / 8
+    P, LSE = torch.softmax(s, -1)[..., :L], torch.logsumexp(s, -1).float().view(B, G * Hk, 1)
+    O, _ = moda_attn_fwd(*(inp[n] for n in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), causal=False)
+    # (the rounded LSE's own error is no part of the kernel's)
+    P = P * torch.exp(torch.logsumexp(s, -1, keepdim=True) - LSE.double().view(B, Hk, G, 1))
+    dVd = moda_attn_bwd(*(inp[n] for n in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), O, LSE, inp["dO"],
+                        causal=False)[4].double()[:, :, 0]
+    ref = (P[:, :, 0] - P[:, :, 1])[..., None].expand_as(dVd)
+    rms = ((dVd - ref) / P[:, :, 0, :, None]).square().mean().sqrt().item()
+    print("rms error of the difference over the weight: 2^%.2f" % np.log2(rms), flush=True)
+    assert rms <= 2.0 ** -21
+
+
+@pytest.mark.parametrize("B,T,L", [(48, 1, 32), (89, 130, 48)])
+def test_infinite_dO_of_8_heads_stays_infinite(B, T, L):
+    """An infinite element of dO: dVdepth is infinite in that channel of that position (every weight is
+    positive), one bf16 rounding off at most in the others (another order of fp32 sums), and no other
+    position's depth gradients change."""
+    causal = T > 1
+    inp = synth.make_inputs(B, 64, 8, T, 64, L, dtype="bf16", seed=78, device="cuda", with_dO=True)
+    clean = run_gpu(inp, L, causal)
+    b, h, t, c = 3, 2, T // 2, 5
+    inp["dO"][b, h, t, c] = -float("inf")
+    grads = run_gpu(inp, L, causal)
+    at = (b, h // 8, t)
+    assert (grads[4][at][:, c] == -float("inf")).all()
+    others = [i for i in range(64) if i != c]
+    x, y = (g[4][at][:, others].float() for g in (grads, clean))
+    assert ((x - y).abs() <= 2.0 ** -7 * y.abs() + 2.0 ** -20).all()
+    for g, k in zip(grads[3:], clean[3:]):
+        g[at] = k[at]
+        assert torch.equal(g, k)
