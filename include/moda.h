@@ -175,6 +175,10 @@ moda_status moda_depth_append(const void* K, const void* V, void* Kdepth, void* 
  *   out: O                 [B, Hq, d], LSE [B, Hq] fp32
  *   workspace: device scratch of at least moda_attn_decode_workspace_bytes(s) bytes
  *        (partial results of the slices the sequence is split into), 16-byte aligned.
+ * moda_attn_decode_workspace_bytes never falls as T grows: what it reports for the longest context
+ * serves every shorter one.  A workspace that is smaller, e.g. because it was sized for a larger batch
+ * (fewer slices per sequence), is accepted down to what slices of 256 keys take (the cut is then that
+ * one, and the last bits of the result those of its sums), else MODA_ERR_WORKSPACE.
  * `s->T` is the attended length (>= 1), `s->causal` is ignored.  bf16 only.
  */
 size_t moda_attn_decode_workspace_bytes(const moda_shape* s);
@@ -189,8 +193,9 @@ moda_status moda_attn_decode(const void* Q, const void* Kseq, const void* Vseq, 
  * to a scratch array that is part of the library image (a file-scope device array of
  * moda_attn_decode_noalloc_max_bytes() = 8 MiB; every GPU the library runs on holds its own
  * copy until the process ends).  The call allocates nothing and frees nothing.  A shape whose
- * moda_attn_decode_workspace_bytes() exceeds that size is rejected with MODA_ERR_WORKSPACE
- * before anything is launched (use moda_attn_decode with a workspace then).  All calls on one
+ * partial results do not fit it, cut into slices of 256 keys, is rejected with MODA_ERR_WORKSPACE
+ * before anything is launched (use moda_attn_decode with a workspace then); every shape whose
+ * moda_attn_decode_workspace_bytes() is no larger is accepted.  All calls on one
  * GPU share that GPU's array: two such calls that overlap in time on the same GPU (different
  * streams, different threads) race and give wrong results; calls on one stream, or otherwise
  * ordered, are safe, and nothing in the array needs clearing between calls.  The array's device

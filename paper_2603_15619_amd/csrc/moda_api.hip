@@ -227,10 +227,13 @@ size_t moda_attn_decode_workspace_bytes(const moda_shape* s) {
   return moda::decode_workspace_bytes(s->B, s->Hq, s->Hk, s->T, s->d);
 }
 
+// The least that the partial results of a (validated, not empty) decoding step take.
+static size_t decode_least(const moda_shape* s) { return moda::decode_least_bytes(s->B, s->Hq, s->Hk, s->T, s->d); }
+
 // The decoding step with the slices' partial results in `workspace` (already validated).
 static moda_status decode_with(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
                                const void* Vdepth, void* O, float* LSE, int32_t kv_alloc, void* workspace,
-                               const moda_shape* s, void* hip_stream);
+                               size_t workspace_bytes, const moda_shape* s, void* hip_stream);
 
 moda_status moda_attn_decode(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
                              const void* Vdepth, void* O, float* LSE, int32_t kv_alloc, void* workspace,
@@ -243,8 +246,8 @@ moda_status moda_attn_decode(const void* Q, const void* Kseq, const void* Vseq, 
   const void* ptrs[] = {Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, workspace};
   for (const void* q : ptrs)
     if (!aligned16(q)) return MODA_ERR_ALIGN;
-  if (!workspace || workspace_bytes < moda_attn_decode_workspace_bytes(s)) return MODA_ERR_WORKSPACE;
-  return decode_with(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, kv_alloc, workspace, s, hip_stream);
+  if (!workspace || workspace_bytes < decode_least(s)) return MODA_ERR_WORKSPACE;
+  return decode_with(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, kv_alloc, workspace, workspace_bytes, s, hip_stream);
 }
 
 size_t moda_attn_decode_noalloc_max_bytes(void) { return moda::decode_static_scratch_bytes(); }
@@ -254,8 +257,8 @@ moda_status moda_attn_decode_noalloc(const void* Q, const void* Kseq, const void
                                      const moda_shape* s, void* hip_stream) {
   moda_status st = check_decode(s, kv_alloc);
   if (st != MODA_OK) return st;
-  if (moda_attn_decode_workspace_bytes(s) > moda::decode_static_scratch_bytes()) return MODA_ERR_WORKSPACE;
   if (s->B == 0) return MODA_OK;
+  if (decode_least(s) > moda::decode_static_scratch_bytes()) return MODA_ERR_WORKSPACE;
   if (!Q || !Kseq || !Vseq || !O || !LSE) return MODA_ERR_NULL;
   if (s->depth_count > 0 && (!Kdepth || !Vdepth)) return MODA_ERR_NULL;
   const void* ptrs[] = {Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE};
@@ -265,14 +268,15 @@ moda_status moda_attn_decode_noalloc(const void* Q, const void* Kseq, const void
   if (moda::decode_static_scratch(&ws) != hipSuccess) return MODA_ERR_LAUNCH;
   // Nothing in the scratch has to start at zero: the first kernel writes every partial result
   // that the second one reads.
-  return decode_with(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, kv_alloc, ws, s, hip_stream);
+  return decode_with(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, kv_alloc, ws, moda::decode_static_scratch_bytes(), s,
+                     hip_stream);
 }
 
 static moda_status decode_with(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
                                const void* Vdepth, void* O, float* LSE, int32_t kv_alloc, void* workspace,
-                               const moda_shape* s, void* hip_stream) {
+                               size_t workspace_bytes, const moda_shape* s, void* hip_stream) {
   return launch_status(moda::launch_decode_bf16(Q, Kseq, Vseq, Kdepth, Vdepth, O, LSE, static_cast<float*>(workspace),
-                                                s->B, s->Hq, s->Hk, s->T, kv_alloc, s->d, s->depth_alloc,
+                                                workspace_bytes, s->B, s->Hq, s->Hk, s->T, kv_alloc, s->d, s->depth_alloc,
                                                 s->depth_count, resolve_scale(s),
                                                 static_cast<hipStream_t>(hip_stream)));
 }

@@ -500,39 +500,74 @@ struct DecodePlan {
   int n_split;
   int keys_per_split;
 };
-static DecodePlan decode_plan(int B, int Hq, int Hk, int T, int d) {
-  DecodePlan pl;
+struct DecodeRule {
+  bool mfma;
+  int want;      // slices that fill the chip, whatever the length
+  int step;      // keys_per_split is a multiple of this
+  int most_fine;    // most slices of the finer cut
+  size_t slice_bytes;  // partial results of one slice of every (batch, head)
+};
+static DecodeRule decode_rule(int B, int Hq, int Hk, int d) {
+  DecodeRule r;
   const int G = Hq / Hk;
   // up to 4 heads per group the vector-ALU kernel is at the memory rate and ahead (measured)
-  pl.mfma = G > 4;
-  const int fine = (T + 127) / 128, coarse = (T + 255) / 256;
-  int most = pl.mfma || fine <= 8 ? fine : coarse > 8 ? coarse : 8;
-  // (never so many that the partial results outgrow the library's own scratch array where those of the
-  // coarser slices fit it)
-  if ((size_t)B * Hq * (most + 1) * (d + 2) * sizeof(float) > kDecodeScratchBytes) most = coarse;
-  int want, step;
-  if (pl.mfma) {
+  r.mfma = G > 4;
+  if (r.mfma) {
     const int n_gc = (G + 31) / 32;
     // 12 wave-slices per compute unit: all resident at once at d = 64, one and a half rounds
     // at d = 128 (measured better than exactly one round: the second half-round evens out the tail)
     const long long slots = 256ll * 12;
     const long long per = slots / ((long long)B * Hk * n_gc);
-    want = per < 1 ? 1 : (int)per;
-    step = kDecBlock;
+    r.want = per < 1 ? 1 : (int)per;
+    r.step = kDecBlock;
   } else {
-    want = (2048 + B * Hk - 1) / (B * Hk);
-    step = kDecWaves * (64 / (d / 8));  // key rows a workgroup takes per step (16 or 32)
+    r.want = (2048 + B * Hk - 1) / (B * Hk);
+    r.step = kDecWaves * (64 / (d / 8));  // key rows a workgroup takes per step (16 or 32)
   }
-  int s = want < most ? want : most;
+  r.slice_bytes = (size_t)B * Hq * (d + 2) * sizeof(float);
+  // (never so many that the partial results, with the depth slots' slice, outgrow the library's own scratch
+  // array where those of the coarser slices fit it)
+  r.most_fine = (int)(kDecodeScratchBytes / r.slice_bytes) - 1;
+  return r;
+}
+static int coarse_slices(int T) { return (T + 255) / 256; }
+static int fine_slices(bool mfma, int T) {
+  const int fine = (T + 127) / 128, coarse = coarse_slices(T);
+  return mfma || fine <= 8 ? fine : coarse > 8 ? coarse : 8;
+}
+static DecodePlan cut(const DecodeRule& r, int T, int most) {
+  int s = r.want < most ? r.want : most;
   if (s < 1) s = 1;
-  pl.keys_per_split = ((T + s - 1) / s + step - 1) / step * step;
+  DecodePlan pl;
+  pl.mfma = r.mfma;
+  pl.keys_per_split = ((T + s - 1) / s + r.step - 1) / r.step * r.step;
   pl.n_split = (T + pl.keys_per_split - 1) / pl.keys_per_split;
   return pl;
 }
+// The cut of a call whose partial results (of n_split slices and the depth slots) have `room` bytes: the finer
+// slices if they fit, else the coarser ones.
+static DecodePlan decode_plan(const DecodeRule& r, int T, size_t room) {
+  const int fine = fine_slices(r.mfma, T);
+  if (fine <= r.most_fine) {
+    const DecodePlan pl = cut(r, T, fine);
+    if ((size_t)(pl.n_split + 1) * r.slice_bytes <= room) return pl;
+  }
+  return cut(r, T, coarse_slices(T));
+}
 
+// What every length up to T needs at most for its finer cut, so that a workspace of the longest context
+// serves the shorter ones.  (A cut never has more than min(want, most) slices, and among the lengths up to
+// T the finer ones take every number of slices up to min(fine, most_fine).)
 size_t decode_workspace_bytes(int B, int Hq, int Hk, int T, int d) {
-  // (one slice more than the sequence is cut into: the depth slots)
-  return (size_t)B * Hq * (decode_plan(B, Hq, Hk, T, d).n_split + 1) * (d + 2) * sizeof(float);
+  const DecodeRule r = decode_rule(B, Hq, Hk, d);
+  int most = fine_slices(r.mfma, T);
+  if (most > r.most_fine) most = r.most_fine > coarse_slices(T) ? r.most_fine : coarse_slices(T);
+  return (size_t)((r.want < most ? r.want : most) + 1) * r.slice_bytes;
+}
+
+size_t decode_least_bytes(int B, int Hq, int Hk, int T, int d) {
+  const DecodeRule r = decode_rule(B, Hq, Hk, d);
+  return (size_t)(cut(r, T, coarse_slices(T)).n_split + 1) * r.slice_bytes;
 }
 
 template <int D>
@@ -560,15 +595,15 @@ static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream)
 }
 
 hipError_t launch_decode_bf16(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
-                              const void* Vdepth, void* O, float* LSE, float* ws, int B, int Hq, int Hk, int T,
-                              int T_alloc, int d, int depth_alloc, int depth_count, float scale,
+                              const void* Vdepth, void* O, float* LSE, float* ws, size_t ws_bytes, int B, int Hq,
+                              int Hk, int T, int T_alloc, int d, int depth_alloc, int depth_count, float scale,
                               hipStream_t stream) {
   DecodeParams p;
   p.Q = Q; p.Kseq = Kseq; p.Vseq = Vseq; p.Kdepth = Kdepth; p.Vdepth = Vdepth;
   p.O = O; p.LSE = LSE; p.ws = ws;
   p.B = B; p.Hq = Hq; p.Hk = Hk; p.T = T; p.T_alloc = T_alloc;
   p.depth_alloc = depth_alloc; p.depth_count = depth_count;
-  const DecodePlan pl = decode_plan(B, Hq, Hk, T, d);
+  const DecodePlan pl = decode_plan(decode_rule(B, Hq, Hk, d), T, ws_bytes);
   p.n_split = pl.n_split;
   p.keys_per_split = pl.keys_per_split;
   p.n_slices = pl.n_split + (depth_count > 0 ? 1 : 0);

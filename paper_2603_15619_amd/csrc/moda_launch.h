@@ -44,15 +44,17 @@ hipError_t launch_depth_append(const void* K, const void* V, void* Kdepth, void*
                                int row_bytes, int depth_alloc, int slot, hipStream_t stream);
 
 // Decoding step (one new token per sequence), bf16: partial kernel over slices of the sequence
-// cache + merge kernel; `ws` holds decode_workspace_bytes(...) bytes.
+// cache + merge kernel; `ws` holds ws_bytes >= decode_least_bytes(...) bytes.  With decode_workspace_bytes(...)
+// of this or any longer T the cache is cut as finely as the chip likes it, with less more coarsely.
 size_t decode_workspace_bytes(int B, int Hq, int Hk, int T, int d);
+size_t decode_least_bytes(int B, int Hq, int Hk, int T, int d);
 // The library's own scratch for the decoding step (a file-scope device array, one per GPU): its
 // size, and its device address on the current device.
 size_t decode_static_scratch_bytes();
 hipError_t decode_static_scratch(void** addr);
 hipError_t launch_decode_bf16(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
-                              const void* Vdepth, void* O, float* LSE, float* ws, int B, int Hq, int Hk, int T,
-                              int T_alloc, int d, int depth_alloc, int depth_count, float scale,
+                              const void* Vdepth, void* O, float* LSE, float* ws, size_t ws_bytes, int B, int Hq,
+                              int Hk, int T, int T_alloc, int d, int depth_alloc, int depth_count, float scale,
                               hipStream_t stream);
 
 // Matrix-pipe calibration kernel (moda_calibrate.hip).

@@ -157,3 +157,16 @@ def test_depth_gradients_of_5_to_8_heads_take_their_own_kernel_at_d_128(d, kerne
     for G in (5, 8):
         s = MODAShape(8, 8 * G, 8, 4096, d, 64, 64, 1, 0.0, 1)
         assert lib().moda_kernels_per_call(ctypes.byref(s), 1) == kernels
+
+
+@pytest.mark.parametrize("B,Hq,Hk,d", [(8, 64, 8, 64), (8, 64, 8, 128), (4, 64, 8, 128), (2, 32, 4, 128), (1, 16, 16, 128),
+                                       (3, 4, 2, 64), (600, 8, 1, 64), (64, 256, 4, 64), (5000, 8, 8, 64)])
+def test_decode_workspace_of_the_longest_context_serves_shorter_ones(L, B, Hq, Hk, d):
+    """The size never falls as the context grows."""
+    from paper_2603_15619_amd.binding import MODAShape
+
+    last = 0
+    for T in [*range(1, 10000, 3), *range(10000, 70000, 61)]:
+        n = L.moda_attn_decode_workspace_bytes(ctypes.byref(MODAShape(B, Hq, Hk, T, d, 4, 4, 1, 0.0, 1)))
+        assert n >= last, (T, n, last)
+        last = n

@@ -131,3 +131,27 @@ def test_slices_fit_the_scratch_array_where_coarser_ones_do():
         coarse = B * G * Hk * ((T + 255) // 256 + 1) * (d + 2) * 4
         if coarse <= most:
             assert lib().moda_attn_decode_workspace_bytes(ctypes.byref(s)) <= most
+
+
+@pytest.mark.parametrize("B,Hq,Hk,d,T_max,calls", [(8, 64, 8, 64, 8192, [(8, 4097), (8, 6000), (8, 7808)]),
+                                                   (8, 64, 8, 128, 4096, [(8, 2049), (8, 3840), (7, 4096), (4, 4096)]),
+                                                   (12, 8, 8, 64, 3000, [(12, 1999), (5, 3000), (1, 1001)])])
+def test_one_workspace_for_a_serving_loop(B, Hq, Hk, d, T_max, calls):
+    """A workspace sized once, for the largest batch at its longest context, serves every call of the loop, and
+    the results are those of a call with a workspace of its own (both to the forward's tolerance)."""
+    import ctypes
+
+    from paper_2603_15619_amd import moda_attn_decode
+    from paper_2603_15619_amd.binding import MODAShape, lib
+
+    size = lib().moda_attn_decode_workspace_bytes(ctypes.byref(MODAShape(B, Hq, Hk, T_max, d, 3, 3, 1, 0.0, 1)))
+    for b, T in calls:
+        inp = synth.make_inputs(b, Hq, Hk, T, d, 0, dtype="bf16", seed=2000 + T, device="cuda")
+        one = synth.make_inputs(b, Hq, Hk, 1, d, 3, dtype="bf16", seed=2001 + T, device="cuda")
+        args = [one["Q"][:, :, 0].contiguous(), inp["Kseq"], inp["Vseq"], *(one[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))]
+        both = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")  # (nothing is written past the workspace)
+        O, LSE = moda_attn_decode(*args, workspace=both[:size])
+        O1, LSE1 = moda_attn_decode(*args)
+        torch.cuda.synchronize()
+        assert (both[size:] == 0x5a).all()
+        assert (O.float() - O1.float()).abs().max().item() <= 2e-2 and (LSE - LSE1).abs().max().item() <= 1e-3
