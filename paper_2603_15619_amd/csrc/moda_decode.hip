@@ -353,12 +353,12 @@ void moda_decode_partial_mfma_kernel(DecodeParams p) {
     // The reference m of the exponentials is raised lazily: only when a block's maximum exceeds
     // it by more than 8 powers of two (weights then stay below 2^8, which fp32 sums and bf16
     // weights hold; any reference gives the same quotient).  The first block always raises it
-    // (m = -inf; every block holds at least one key of the slice, so bm is finite, and the
-    // factor exp2(-inf) = 0 scales the empty state).
+    // (m = -inf, and the factor exp2(-inf) = 0 scales the empty state), unless all its scores are -inf: the
+    // state then stays empty and the weights are zero.
     const bool raise = bm > m + lazy || m == -INFINITY;
     if (__builtin_amdgcn_ballot_w64(raise) != 0) {  // (uniform)
       const float mn = raise ? bm : m;
-      const float al = fast_exp2((m - mn) * c2);
+      const float al = mn == m ? 1.f : fast_exp2((m - mn) * c2);
       m = mn;
       l *= al;
 #pragma unroll
@@ -366,7 +366,7 @@ void moda_decode_partial_mfma_kernel(DecodeParams p) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) oa[cb][i] *= al;
     }
-    const float mc = m * c2;
+    const float mc = m == -INFINITY ? 0.f : m * c2;
 #pragma unroll
     for (int sb = 0; sb < NB; ++sb)
 #pragma unroll
@@ -438,6 +438,8 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
   const float c2 = p.scale_log2;
   const float* ws = p.ws + (size_t)bh * p.n_slices * (D + 2);
   float mm = -INFINITY, ll = 0.f, oo = 0.f;
+  // (a slice or a group of them whose scores are all -inf is an empty state: reference -inf, weight zero)
+  auto factor = [&](float m, float ref) { return m == -INFINITY ? 0.f : fast_exp2((m - ref) * c2); };
   for (int s0 = g; s0 < p.n_slices; s0 += kU * NG) {
     float mi[kU], li[kU], oi[kU];
 #pragma unroll
@@ -451,20 +453,19 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
 #pragma unroll
     for (int u = 0; u < kU; ++u)
       if (s0 + u * NG < p.n_slices) mn = fmaxf(mn, mi[u]);
-    // (every slice holds at least one key: mn is finite; with mm = -inf the factor is 0)
-    const float al = fast_exp2((mm - mn) * c2);
+    const float al = factor(mm, mn);
     mm = mn;
     ll *= al;
     oo *= al;
 #pragma unroll
     for (int u = 0; u < kU; ++u)
       if (s0 + u * NG < p.n_slices) {
-        const float f = fast_exp2((mi[u] - mm) * c2);
+        const float f = factor(mi[u], mm);
         ll += f * li[u];
         oo += f * oi[u];
       }
   }
-  if constexpr (NG > 1) {  // (more slices than groups: every group holds a finite reference)
+  if constexpr (NG > 1) {
     red[g][ch] = oo;
     if (ch == 0) {
       stat[g][0] = mm;
@@ -475,12 +476,12 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
     const float m0 = mm;
 #pragma unroll
     for (int w = 1; w < NG; ++w) mm = fmaxf(mm, stat[w][0]);
-    const float f0 = fast_exp2((m0 - mm) * c2);
+    const float f0 = factor(m0, mm);
     ll *= f0;
     oo *= f0;
 #pragma unroll
     for (int w = 1; w < NG; ++w) {
-      const float f = fast_exp2((stat[w][0] - mm) * c2);
+      const float f = factor(stat[w][0], mm);
       ll += f * stat[w][1];
       oo += f * red[w][ch];
     }

@@ -155,3 +155,21 @@ def test_one_workspace_for_a_serving_loop(B, Hq, Hk, d, T_max, calls):
         torch.cuda.synchronize()
         assert (both[size:] == 0x5a).all()
         assert (O.float() - O1.float()).abs().max().item() <= 2e-2 and (LSE - LSE1).abs().max().item() <= 1e-3
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,lo,hi", [(1, 2, 2, 8192, 64, 512, 8192), (2, 4, 2, 9000, 128, 0, 8000), (1, 1, 1, 700, 64, 128, 256),
+                                               (1, 8, 1, 1003, 64, 128, 160), (1, 16, 2, 5000, 128, 96, 4900)])
+def test_decode_keys_of_weight_zero(B, Hq, Hk, T, d, lo, hi):
+    """Keys whose scores are -inf weigh nothing, also where a block, a slice or a group of slices holds no
+    other: the result is that of a cache without them (to the forward's tolerance, both sides)."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    inp = synth.make_inputs(B, Hq, Hk, T, d, 0, dtype="bf16", seed=2200 + T, device="cuda")
+    K, V, Q = inp["Kseq"], inp["Vseq"], inp["Q"][:, :, 0].abs().contiguous() + 0.1  # (positive: -inf, not NaN)
+    keep = [t for t in range(T) if t < lo or t >= hi]
+    O1, LSE1 = moda_attn_decode(Q, K[:, :, keep].contiguous(), V[:, :, keep].contiguous())
+    K[:, :, lo:hi] = -float("inf")
+    O, LSE = moda_attn_decode(Q, K, V)
+    torch.cuda.synchronize()
+    assert (O.float() - O1.float()).abs().max().item() <= 2e-2
+    assert (LSE - LSE1).abs().max().item() <= 1e-3
