@@ -103,7 +103,8 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
           s[u] = c * kC + u < L ? a : -INFINITY;
           mn = fmaxf(mn, s[u]);
         }
-        const float al = fast_exp2((m - mn) * c2), mc = mn * c2;
+        // (no slot of finite score so far: the state stays empty, the weights are exp2(-inf) = 0)
+        const float al = mn == -INFINITY ? 0.f : fast_exp2((m - mn) * c2), mc = mn == -INFINITY ? 0.f : mn * c2;
         m = mn;
         l *= al;
 #pragma unroll

@@ -44,3 +44,19 @@ def test_depth_values_that_are_not_finite_stay_in_their_row(T, d, at):
     keep = [t for t in range(T) if t != at]
     assert torch.equal(O[:, :, keep], clean[:, :, keep])
     assert not torch.isfinite(O[:, :, at].float()).any()
+
+
+@pytest.mark.parametrize("T,d,L,dead", [(200, 64, 6, 6), (130, 128, 12, 12), (200, 64, 12, 7), (97, 128, 5, 5)])
+def test_depth_slots_of_weight_zero(T, d, L, dead):
+    """One head per tile: slots whose scores are -inf, all of a row's or a whole step's among them, weigh
+    nothing: the result is that without them (the other slots' weights round to bf16 as before: 2e-2 on O)."""
+    inp = synth.make_inputs(1, 2, 2, T, d, L, dtype="bf16", seed=1800, device="cuda")
+    inp["Q"] = inp["Q"].abs() + 0.1  # (positive: -inf, not NaN)
+    rest = dict(inp, Kdepth=inp["Kdepth"][:, :, :, dead:].contiguous(), Vdepth=inp["Vdepth"][:, :, :, dead:].contiguous())
+    if dead == L:
+        rest["Kdepth"] = rest["Vdepth"] = None
+    O1, L1 = run_gpu(rest, L - dead)
+    inp["Kdepth"][:, :, :, :dead] = -float("inf")
+    O, LSE = run_gpu(inp, L)
+    assert (O.float() - O1.float()).abs().max().item() <= 2e-2
+    assert (LSE - L1).abs().max().item() <= 1e-4
