@@ -55,8 +55,10 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
 
 // exp(scale * (a - b)) of raw scores a, b; the difference is formed before it is scaled, so that
 // a large common part of the scores costs no precision.  b = -inf (an empty state) counts as 0.
+// (exp2f, not the bare instruction, which returns zero for weights below 2^-126: a value of 2^127 still
+// counts with them.)
 __device__ __forceinline__ float weight(float a, float b, float c2) {
-  return fast_exp2((a - (b == -INFINITY ? 0.f : b)) * c2);
+  return exp2f((a - (b == -INFINITY ? 0.f : b)) * c2);
 }
 
 template <int D>
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
     f32x4 q[NV], o[NV];
     float m = -INFINITY, l = 0.f;
     auto fold = [&](int c, const Chunk& x) {
-      float s[kC], mn = m;
+      float s[kC], mn = m, least = INFINITY;
 #pragma unroll
       for (int u = 0; u < kC; ++u) {
         float a = 0.f;
@@ -125,21 +127,31 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
         a = group_sum<16>(a);
         s[u] = c * kC + u < L ? a : -INFINITY;
         mn = fmaxf(mn, s[u]);
+        least = fminf(least, a);
       }
       const float al = weight(m, mn, c2);
       m = mn;
       l *= al;
 #pragma unroll
       for (int n = 0; n < NV; ++n) o[n] *= al;
+      const bool tiny = __builtin_amdgcn_ballot_w64((least - mn) * c2 < -126.f) != 0;  // (uniform; as for the key tiles)
+      float w[kC];
+      if (tiny) {
+#pragma unroll
+        for (int u = 0; u < kC; ++u) w[u] = weight(s[u], mn, c2);
+      } else {
+        const float ref = mn == -INFINITY ? 0.f : mn;
+#pragma unroll
+        for (int u = 0; u < kC; ++u) w[u] = fast_exp2((s[u] - ref) * c2);
+      }
 #pragma unroll
       for (int u = 0; u < kC; ++u) {
         if (c * kC + u >= L) break;  // (uniform)
-        const float w = weight(s[u], mn, c2);
-        l += w;
+        l += w[u];
 #pragma unroll
         for (int n = 0; n < NV; ++n)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[n][e] = fmaf(w, x.v[u][n][e], o[n][e]);
+          for (int e = 0; e < 4; ++e) o[n][e] = fmaf(w[u], x.v[u][n][e], o[n][e]);
       }
     };
     int it = 0, c = 0, iti = 0, ci = 0;
@@ -273,6 +285,12 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] += s1[i];
     const int k0 = kt * kF32Keys;
+    // exp2f takes four instructions more than the bare instruction, 3 to 8 % of the call if taken for every
+    // weight: only tiles with a weight below 2^-126 take it (masked scores count as they are: their weights
+    // are zero either way)
+    float least = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) least = fminf(least, s[i]);
     if constexpr (partial) {
       int past = lim - k0 - hi * 4;  // (evaluated here: the loop has no registers for 16 constants)
       asm volatile("" : "+v"(past));
@@ -293,11 +311,16 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[cb][i] *= al;
     }
+    if (__builtin_amdgcn_ballot_w64((least - m) * c2 < -126.f) != 0) {  // (uniform)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      s[i] = weight(s[i], m, c2);
-      l += s[i];
+      for (int i = 0; i < 16; ++i) s[i] = weight(s[i], m, c2);
+    } else {
+      const float ref = m == -INFINITY ? 0.f : m;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = fast_exp2((s[i] - ref) * c2);
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) l += s[i];
     // O^T += V^T P^T.  On a tile that the diagonal crosses a key's weight is zero for the queries
     // before it, but zero times an infinite or NaN value is not: if the tile holds such values the
     // visible (key, query) pairs are taken one by one.

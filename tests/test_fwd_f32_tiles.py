@@ -48,3 +48,26 @@ def test_f32_value_that_is_not_finite_stays_behind_the_diagonal(T, d, at, value)
     if at:
         assert np.abs(O[:, :, :at] - Oref[:, :, :at]).max() <= TOL
     assert not np.isfinite(O[:, :, at:]).any()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("depth", [False, True])
+def test_f32_weights_below_the_smallest_normal_number(d, depth):
+    """A key or a slot of weight e^-90 = 2^-129.8 and value 2^127 adds e^-90 2^127 / n = 0.14 / n to the
+    output of the n other keys' zeros.  (The weight has 20 bits left: 1e-6 of the result.)"""
+    T = 40
+    z = torch.zeros(1, 2, T, d, device="cuda")
+    Q, K, V = z.clone(), z.clone(), z.clone()
+    Q[..., 0] = 1.0
+    Kd = Vd = None
+    if depth:
+        Kd, Vd = (torch.zeros(1, 2, T, 8, d, device="cuda") for _ in range(2))
+        Kd[:, :, :, 6, 0], Vd[:, :, :, 6] = -90.0, 2.0 ** 127
+    else:
+        K[:, :, 3, 0], V[:, :, 3] = -90.0, 2.0 ** 127
+    O, _ = moda_attn_fwd(Q, K, V, Kd, Vd, scale=1.0)
+    torch.cuda.synchronize()
+    t = np.arange(T)
+    n = t + 1 + 7 if depth else t.astype(float)
+    want = np.where(depth | (t >= 3), np.exp(-90.0) * 2.0 ** 127 / np.maximum(n, 1), 0.0)
+    assert np.abs(synth.to_f64(O) - want[None, None, :, None]).max() <= 2e-6
