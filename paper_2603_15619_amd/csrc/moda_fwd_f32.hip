@@ -432,6 +432,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 int fwd_f32_tile_rows() { return kF32Rows; }
 
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream) {
+  if (fwd_f32_by_rows(p)) return launch_fwd_f32_rows(p, d, stream);
   if (p.n_qtiles != (p.T + kF32Rows - 1) / kF32Rows) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * p.Hq * p.n_qtiles;
   if (!grid_ok(blocks)) return kGridTooLarge;

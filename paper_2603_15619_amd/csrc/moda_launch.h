@@ -30,6 +30,9 @@ hipError_t launch_fwd_short(const FwdParams& p, int d, hipStream_t stream);
 // fp32 forward kernel: tiles of fwd_f32_tile_rows() queries of one head; p.n_qtiles must be their number.
 int fwd_f32_tile_rows();
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream);
+// The same for short sequences, one wave per query (launch_fwd_f32 hands over what fwd_f32_by_rows says).
+bool fwd_f32_by_rows(const FwdParams& p);
+hipError_t launch_fwd_f32_rows(const FwdParams& p, int d, hipStream_t stream);
 
 // Backward (bf16, Hq / Hk <= bwd_bf16_max_group()): delta, [depth slots of grouped queries,]
 // dK/dV and dQ(/depth) kernels on `stream`.

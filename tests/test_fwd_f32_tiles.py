@@ -39,7 +39,7 @@ def test_f32_tile_edges(B, Hq, Hk, T, d, L, La, causal):
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-@pytest.mark.parametrize("T,d,at", [(70, 64, 37), (130, 128, 129), (64, 128, 0)])
+@pytest.mark.parametrize("T,d,at", [(70, 64, 37), (130, 128, 129), (64, 128, 0), (6, 64, 3)])
 def test_f32_value_that_is_not_finite_stays_behind_the_diagonal(T, d, at, value):
     """A value row that is infinite or NaN reaches the queries that see it and no other, those that
     share its tile with a weight of zero among them."""
@@ -52,10 +52,10 @@ def test_f32_value_that_is_not_finite_stays_behind_the_diagonal(T, d, at, value)
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("depth", [False, True])
-def test_f32_weights_below_the_smallest_normal_number(d, depth):
+@pytest.mark.parametrize("T", [5, 40])
+def test_f32_weights_below_the_smallest_normal_number(T, d, depth):
     """A key or a slot of weight e^-90 = 2^-129.8 and value 2^127 adds e^-90 2^127 / n = 0.14 / n to the
     output of the n other keys' zeros.  (The weight has 20 bits left: 1e-6 of the result.)"""
-    T = 40
     z = torch.zeros(1, 2, T, d, device="cuda")
     Q, K, V = z.clone(), z.clone(), z.clone()
     Q[..., 0] = 1.0
@@ -71,3 +71,27 @@ def test_f32_weights_below_the_smallest_normal_number(d, depth):
     n = t + 1 + 7 if depth else t.astype(float)
     want = np.where(depth | (t >= 3), np.exp(-90.0) * 2.0 ** 127 / np.maximum(n, 1), 0.0)
     assert np.abs(synth.to_f64(O) - want[None, None, :, None]).max() <= 2e-6
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La", [(300, 16, 4, 1, 64, 3, None), (9, 64, 8, 8, 128, 2, 4), (9, 64, 8, 9, 64, 2, None),
+                                              (1, 4, 2, 6, 64, 70, 72), (2, 8, 8, 7, 128, 70, None), (3, 3, 1, 5, 128, 0, None),
+                                              (1, 2, 2, 2, 64, 0, 1)])
+def test_f32_short_sequences(B, Hq, Hk, T, d, L, La, causal):
+    """Both sides of the lines up to which a sequence's queries take a wave each; slots in one and in two steps
+    of 64."""
+    O, LSE, (Oref, Lref) = run(B, Hq, Hk, T, d, L, 300 + T + L, causal, La)
+    assert np.abs(O - Oref).max() <= TOL and np.abs(LSE - Lref).max() <= TOL
+
+
+@pytest.mark.parametrize("T,d,L,dead", [(4, 64, 3, 3), (6, 128, 70, 65), (200, 64, 12, 7)])
+def test_f32_depth_slots_of_weight_zero(T, d, L, dead):
+    """Slots whose scores are -inf weigh nothing, also where they are a row's first 64 or its only ones."""
+    inp = synth.make_inputs(1, 2, 2, T, d, L, dtype="f32", seed=500, device="cuda")
+    Q = inp["Q"].abs() + 0.1  # (positive: -inf, not NaN)
+    inp["Kdepth"][:, :, :, :dead] = -float("inf")
+    rest = [inp[k][:, :, :, dead:].contiguous() for k in ("Kdepth", "Vdepth")] if dead < L else [None, None]
+    O, LSE = moda_attn_fwd(Q, inp["Kseq"], inp["Vseq"], inp["Kdepth"], inp["Vdepth"])
+    O1, LSE1 = moda_attn_fwd(Q, inp["Kseq"], inp["Vseq"], *rest)
+    torch.cuda.synchronize()
+    assert (O - O1).abs().max().item() <= TOL and (LSE - LSE1).abs().max().item() <= TOL
