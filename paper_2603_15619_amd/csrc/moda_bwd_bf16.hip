@@ -1772,28 +1772,52 @@ size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d) {
 
 int bwd_bf16_max_group() { return 64; }
 
-// Where the short kernels take over, in workgroups of the other kernel (the chip holds 512 of them,
-// two per compute unit).  The lines lie between the sizes at which either side was seen ahead, whole
-// call timed (other kernel / short kernel, us):
-//   dK/dV  d=64   causal, G > 1:  640 wgs 333 / 294, 768 wgs 1110 / 1079 and 3062 / 3127, 1024 wgs 2015 / 2105
-//          d=64   causal, G = 1:  384 wgs 183 / 158, 448 wgs 144 / 147, 512 wgs 264 / 283
-//          d=64   not causal:     256 wgs 346 / 312, 512 wgs 566 / 596
-//          d=128  causal:         320 wgs 927 / 775, 384 wgs 252 / 248 and 286 / 285, 512 wgs 676 / 788
-//          d=128  not causal:     128 wgs 306 / 216, 256 wgs 627 / 679
-//   dQ     d=64   causal:         256 wgs 365 / 320 and 85 / 82, 384 wgs 81 / 79, 512 wgs 114 / 118
+// Which of the two dK/dV kernels a call takes: the one whose estimated time is shorter.  Either is bound by the
+// chain of its longest workgroup (few workgroups) or by what 256 compute units get done (many): a workgroup's
+// steps (64 queries x 128 keys; short kernel: 32 x 32 per wave, four side by side), its two ends, and the
+// depth slots of its positions, padding included.  The short kernel reads Q and dO four times as often, and
+// pays `undealt` more where the heads cannot be dealt to the 8 dies (head_blocked_id) and every L2 sees
+// them all.  Constants (us; per 256 units) fitted to both kernels' times at 7700 shapes, T = 2 to 16384, 1 to 2000
+// heads, 1 to 16 per group, 0 to 64 slots: 0.4 % behind the better kernel on average, more than 10 % at 1 of 100.
+// Whole call without slots, workgroups of the short kernel: other / short, us:
+//   d=64   causal      G=1 T=128: 512 16/15, 768 17/19;   T=512: 768 28/27, 1536 38/41;   T=2048: 1536 101/89, 2048 92/95
+//                      G=8 T=128: 1024 72/63, 2048 115/129;   T=1000: 2048 361/331, undealt 1216 265/214, 2400 379/536
+//          not causal  G=1 T=128: 512 15/15, 768 15/18;   T=1000: 512 42/34, 896 43/46;   T=4096: 768 133/126, 1280 192/194
+//   d=128  causal      G=1 T=128: 256 23/18, 512 24/24, 768 26/32;   T=512: 640 47/46, 1024 50/57;   T=2048: 1024 147/131, 1536 176/179
+//                      G=8 T=256: 1024 180/167, 1536 228/248;   T=1000: 1536 588/546, 2048 644/730
+//          not causal  G=2 T=128: 256 27/20, 512 30/32;   T=512: 512 70/57, 768 81/84;   T=2048: 768 259/240, 1024 274/307
+struct KeyCost {
+  double step, step_unit, ends, short_step, short_unit, undealt, slot, slot_unit;
+};
+static double fourth(double x) { return x * x * x * x; }
+static double undealt_share(long long heads) {  // 0: a multiple of 8; 1: odd
+  return (3 - (heads % 8 == 0 ? 3 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 1 : 0)) / 3.0;
+}
+static bool few_keys(const BwdParams& p, int d) {
+  const KeyCost c = d == 64 ? KeyCost{1.26, 1.12, 1.2, 0.90, 0.66, 0.16, 0.18, 0.0043}
+                            : KeyCost{2.7, 1.53, 3.9, 1.41, 1.58, 0.17, 0.36, 0.0076};
+  const long long heads = (long long)p.B * p.Hk;
+  const double G = p.Hq / p.Hk, n64 = (p.T + 63) / 64, n32 = (p.T + 31) / 32, n128 = (p.T + 127) / 128;
+  const double L = G <= 4 ? p.depth_count : 0;  // (larger groups: a kernel of their own, or the same in both)
+  const double slot = G > 1 ? 2 * c.slot : c.slot, odd = p.Hq / p.Hk % 4 ? 0.375 : 0.0;
+  const double steps = G * n128 * (p.causal ? n64 - n128 + 1 : n64);
+  const double short_steps = n32 * (G * (p.causal ? n32 + 1 : 2 * n32) / 8 + odd);
+  const double chain = G * n64 * c.step + 4 * L * slot;
+  const double load = heads * (steps * c.step_unit + n128 * (c.ends + 128 * L * c.slot_unit)) / 256;
+  const double short_chain = (G * n32 / 4 + odd) * c.short_step + L * slot;
+  const double short_load = heads * (short_steps * c.short_unit * (1 + c.undealt * undealt_share(heads)) +
+                                     n32 * (c.ends + 32 * L * c.slot_unit)) / 256;
+  return fourth(short_chain) + fourth(short_load) < fourth(chain) + fourth(load);  // (a smooth maximum of each pair)
+}
+// ... and the short dQ kernel, in workgroups of the other kernel (128 queries each), whole call timed (other
+// kernel / short kernel, us):
+//          d=64   causal:         256 wgs 365 / 320 and 85 / 82, 384 wgs 81 / 79, 512 wgs 114 / 118
 //          d=64   not causal:     32 wgs 18 / 16, 256 wgs 88 / 92
 //          d=128  causal:         128 wgs 97 / 80, 256 wgs T >= 4096 712 / 636 and 232 / 212, else 103 / 103 and 145 / 149
 //          d=128  not causal:     32 wgs 25 / 22, 256 wgs 199 / 212
-static long long few_key_tiles(int D, int G, bool causal) {
-  if (D == 64) return !causal ? 384 : G > 1 ? 704 : 448;
-  return causal ? 352 : 192;
-}
 static long long few_query_tiles(int D, int T, bool causal) {
   if (!causal) return 129;
   return D == 64 ? 385 : T >= 4096 ? 257 : 193;
-}
-static bool few_keys(const BwdParams& p, int d) {
-  return (long long)p.B * p.Hk * ((p.T + 127) / 128) < few_key_tiles(d, p.Hq / p.Hk, p.causal != 0);
 }
 // Depth-slot gradients of 5 to 8 heads: inside dK/dV (depth_group_rows), or in a kernel of their own
 // (depth_gqa).  The former takes 32 slots at a time whether they exist or not, and a wave takes 32

@@ -170,3 +170,13 @@ def test_decode_workspace_of_the_longest_context_serves_shorter_ones(L, B, Hq, H
         n = L.moda_attn_decode_workspace_bytes(ctypes.byref(MODAShape(B, Hq, Hk, T, d, 4, 4, 1, 0.0, 1)))
         assert n >= last, (T, n, last)
         last = n
+
+
+@pytest.mark.parametrize("T,B,kernels", [(1024, 4, 4), (512, 8, 4), (512, 20, 3), (1024, 9, 3), (1024, 8, 4)])
+def test_few_key_tiles(L, T, B, kernels):
+    """Few workgroups of 32 keys (2048 at most, fewer for short walks) take the dK/dV kernel that does without
+    the depth slots of 8 heads: one kernel more."""
+    from paper_2603_15619_amd.binding import MODAShape
+
+    s = MODAShape(B, 64, 8, T, 64, 64, 64, 1, 0.0, 1)
+    assert L.moda_kernels_per_call(ctypes.byref(s), 1) == kernels
