@@ -1809,15 +1809,26 @@ static bool few_keys(const BwdParams& p, int d) {
                                      n32 * (c.ends + 32 * L * c.slot_unit)) / 256;
   return fourth(short_chain) + fourth(short_load) < fourth(chain) + fourth(load);  // (a smooth maximum of each pair)
 }
-// ... and the short dQ kernel, in workgroups of the other kernel (128 queries each), whole call timed (other
-// kernel / short kernel, us):
-//          d=64   causal:         256 wgs 365 / 320 and 85 / 82, 384 wgs 81 / 79, 512 wgs 114 / 118
-//          d=64   not causal:     32 wgs 18 / 16, 256 wgs 88 / 92
-//          d=128  causal:         128 wgs 97 / 80, 256 wgs T >= 4096 712 / 636 and 232 / 212, else 103 / 103 and 145 / 149
-//          d=128  not causal:     32 wgs 25 / 22, 256 wgs 199 / 212
-static long long few_query_tiles(int D, int T, bool causal) {
-  if (!causal) return 129;
-  return D == 64 ? 385 : T >= 4096 ? 257 : 193;
+// The two dQ kernels likewise (32 queries against 128 per workgroup, key tiles dealt to the four waves; 3700
+// shapes, 0.2 % behind the better one on average).  Whole call, one head, workgroups of the short kernel: other /
+// short, us:
+//   d=64   causal      T=128: 512 17/16, 1200 21/23;   T=512: 512 27/25, 896 29/31;   T=2048: 1216 79/74, 2048 90/93;   T=8192: 1536 285/264
+//          not causal  T=128: 384 15/16;   T=512: 512 25/24, 896 27/30;   T=2048: 768 72/70, 1216 107/113
+//   d=128  causal      T=128: 256 23/21, 576 25/27;   T=512: 576 47/46, 896 49/56;   T=2048: 1024 142/136, 1216 149/158
+//          not causal  T=128: 256 21/21, 576 23/27;   T=512: 448 45/45, 576 46/54;   T=2048: 512 138/129, 768 140/153
+struct QueryCost {
+  double step, step_unit, ends, short_step, short_unit, undealt, short_ends;
+};
+static bool few_queries(const BwdParams& p, int d) {
+  const QueryCost c = d == 64 ? QueryCost{0.49, 0.28, 0.94, 0.13, 0.23, 0.25, 0.56} : QueryCost{0.94, 0.66, 2.1, 0.67, 0.59, 0.21, 1.6};
+  const double heads = (double)p.B * p.Hq, n64 = (p.T + 63) / 64, n32 = (p.T + 31) / 32, n128 = (p.T + 127) / 128;
+  const double steps = n128 * (p.causal ? n64 - n128 + 1 : n64);
+  const double short_steps = n32 * ((p.causal ? n32 + 1 : 2 * n32) / 8 + 0.375);
+  const double chain = n64 * c.step, load = heads * (steps * c.step_unit + n128 * c.ends) / 256;
+  const double short_chain = (n32 / 4 + 0.375) * c.short_step;
+  const double short_load = heads * (short_steps * c.short_unit * (1 + c.undealt * undealt_share((long long)p.B * p.Hk)) +
+                                     n32 * c.short_ends) / 256;
+  return fourth(short_chain) + fourth(short_load) < fourth(chain) + fourth(load);
 }
 // Depth-slot gradients of 5 to 8 heads: inside dK/dV (depth_group_rows), or in a kernel of their own
 // (depth_gqa).  The former takes 32 slots at a time whether they exist or not, and a wave takes 32
@@ -1880,7 +1891,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;
-  if (g_dq < few_query_tiles(D, p.T, p.causal != 0))
+  if (few_queries(p, D))
     return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)((long long)p.B * p.Hq * ((p.T + 31) / 32))), dim3(256),
                          stream, p);
   return launch_kernel(moda_bwd_dq_kernel<D, kDqWaves>, dim3((unsigned)g_dq), dim3(kDqWaves * 64), stream, p);
