@@ -1833,9 +1833,11 @@ static bool few_queries(const BwdParams& p, int d) {
 // Depth-slot gradients of 5 to 8 heads: inside dK/dV (depth_group_rows), or in a kernel of their own
 // (depth_gqa).  The former takes 32 slots at a time whether they exist or not, and a wave takes 32
 // positions one after the other: it needs mostly full blocks of slots, and enough key tiles.
-// Backward call, 8 heads per group (kernel of its own / inside, us):
-//   d=64   T=16384: 31 slots 7623 / 7485, 64 slots 8900 / 8070, 12 slots 7329 / 7412;
-//          T=1000:  31 slots 911 / 834, 64 slots 1234 / 1102, 12 slots 805 / 844
+// d = 64, backward call, inside / kernel of its own, 8 heads per group (5 heads the same within 3 %):
+//   slots       16    18    20    22    24    28    32    36    44    48    56    64
+//   T=1000    1.07  1.05  1.02  0.99  0.98  0.94  0.93  1.06  1.00  0.97  0.93  0.88
+//   T=2048    1.05  1.03  1.01  0.99  0.98  0.95  0.92  1.02  0.98  0.97  0.92  0.90
+//   T=16384   1.01  1.01  1.00  1.00  1.00  0.99  0.98  1.01  1.00  0.99  0.98  0.96
 // d = 128 keeps the kernel of its own: beside the key tiles' registers the 32 slots and the next 32 do not
 // fit (91 registers went to scratch memory, reloaded at every position), and the gain was 2 to 5 % at best
 // (T=16384, 31 slots 14494 / 14205; T=2048, 64 slots 3073 / 2925) and a loss elsewhere (T=1000, 31 slots
@@ -1843,7 +1845,7 @@ static bool few_queries(const BwdParams& p, int d) {
 static bool own_depth_kernel(const BwdParams& p, int d) {
   const int G = p.Hq / p.Hk, L = p.depth_count, blocks = (L + 31) / 32;
   if (p.depth_alloc == 0 || G <= 4) return false;
-  return G > 8 || d != 64 || few_keys(p, d) || L * 8 < blocks * 32 * 5 || L == 0;
+  return G > 8 || d != 64 || few_keys(p, d) || L * 16 < blocks * 32 * 11 || L == 0;
 }
 int bwd_bf16_kernels(const BwdParams& p, int d) { return 3 + (own_depth_kernel(p, d) ? 1 : 0); }
 

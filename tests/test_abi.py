@@ -180,3 +180,11 @@ def test_few_key_tiles(L, T, B, kernels):
 
     s = MODAShape(B, 64, 8, T, 64, 64, 64, 1, 0.0, 1)
     assert L.moda_kernels_per_call(ctypes.byref(s), 1) == kernels
+
+
+@pytest.mark.parametrize("L_slots,kernels", [(21, 4), (22, 3), (32, 3), (33, 4), (43, 4), (44, 3), (64, 3), (0, 4)])
+def test_depth_gradients_of_8_heads_inside_dkdv_where_blocks_of_32_slots_are_filled(L, L_slots, kernels):
+    from paper_2603_15619_amd.binding import MODAShape
+
+    s = MODAShape(8, 64, 8, 4096, 64, 64, L_slots, 1, 0.0, 1)
+    assert L.moda_kernels_per_call(ctypes.byref(s), 1) == kernels
