@@ -496,6 +496,10 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
 // 4 heads 6.8 -> 7.5 us).
 // More than 4 query heads per key/value head (matrix-pipe kernel): one slice per wave, of at least 128
 // keys (256 / 128: B=1 Hq=64 Hk=8 d=64 T=1003 13.2 / 10.1 us, T=4096 14.6 / 12.7; B=4 T=2000 d=128 22 / 16).
+// The finer slices of either only where they make no more rounds of workgroups than slices of 256 keys, i.e. where
+// compute units would be left over: 288 workgroups instead of 256 (B=4 Hq=16 Hk=8 T=1662 d=128) took 12.0 us
+// instead of 9.3, 512 instead of 384 (B=64 Hk=2 T=281) 0.88 of the time.  Over 900 random calls, caches just read
+// and from memory, this is 0.3 % behind the better cut on average; always the finer one 1.6 %.
 struct DecodePlan {
   bool mfma;
   int n_split;
@@ -507,7 +511,15 @@ struct DecodeRule {
   int step;      // keys_per_split is a multiple of this
   int most_fine;    // most slices of the finer cut
   size_t slice_bytes;  // partial results of one slice of every (batch, head)
+  long long groups;    // workgroups per slice (matrix pipe: per kDecMWaves slices)
+  int round;           // workgroups that make one round
+  long long rounds(int slices) const {
+    return (groups * (mfma ? (slices + kDecMWaves - 1) / kDecMWaves : slices) + round - 1) / round;
+  }
 };
+static int decode_heads_per_chunk(int G) {  // of the vector-ALU kernel (3 heads: one chunk of 4 with a padded head, not two)
+  return G >= 3 ? 4 : G >= 2 ? 2 : 1;
+}
 static DecodeRule decode_rule(int B, int Hq, int Hk, int d) {
   DecodeRule r;
   const int G = Hq / Hk;
@@ -521,9 +533,14 @@ static DecodeRule decode_rule(int B, int Hq, int Hk, int d) {
     const long long per = slots / ((long long)B * Hk * n_gc);
     r.want = per < 1 ? 1 : (int)per;
     r.step = kDecBlock;
+    r.groups = (long long)B * Hk * n_gc;
+    r.round = d == 128 ? 512 : 256;  // (d = 128: two workgroups per compute unit run side by side at no loss)
   } else {
     r.want = (2048 + B * Hk - 1) / (B * Hk);
     r.step = kDecWaves * (64 / (d / 8));  // key rows a workgroup takes per step (16 or 32)
+    const int gt = decode_heads_per_chunk(G);
+    r.groups = (long long)B * Hk * ((G + gt - 1) / gt);
+    r.round = 256;
   }
   r.slice_bytes = (size_t)B * Hq * (d + 2) * sizeof(float);
   // (never so many that the partial results, with the depth slots' slice, outgrow the library's own scratch
@@ -546,18 +563,18 @@ static DecodePlan cut(const DecodeRule& r, int T, int most) {
   return pl;
 }
 // The cut of a call whose partial results (of n_split slices and the depth slots) have `room` bytes: the finer
-// slices if they fit, else the coarser ones.
-static DecodePlan decode_plan(const DecodeRule& r, int T, size_t room) {
-  const int fine = fine_slices(r.mfma, T);
-  if (fine <= r.most_fine) {
-    const DecodePlan pl = cut(r, T, fine);
-    if ((size_t)(pl.n_split + 1) * r.slice_bytes <= room) return pl;
-  }
-  return cut(r, T, coarse_slices(T));
+// slices if they fit and make no more rounds, else the coarser ones.  `depth`: 1 if there are depth slots.
+static DecodePlan decode_plan(const DecodeRule& r, int T, int depth, size_t room) {
+  const DecodePlan coarse = cut(r, T, coarse_slices(T));
+  const int most = fine_slices(r.mfma, T);
+  if (most > r.most_fine) return coarse;
+  const DecodePlan fine = cut(r, T, most);
+  const bool fits = (size_t)(fine.n_split + 1) * r.slice_bytes <= room;
+  return fits && r.rounds(fine.n_split + depth) <= r.rounds(coarse.n_split + depth) ? fine : coarse;
 }
 
-// What every length up to T needs at most for its finer cut, so that a workspace of the longest context
-// serves the shorter ones.  (A cut never has more than min(want, most) slices, and among the lengths up to
+// What every length up to T needs at most for its finer cut, taken or not, so that a workspace of the longest
+// context serves the shorter ones.  (A cut never has more than min(want, most) slices, and among the lengths up to
 // T the finer ones take every number of slices up to min(fine, most_fine).)
 size_t decode_workspace_bytes(int B, int Hq, int Hk, int T, int d) {
   const DecodeRule r = decode_rule(B, Hq, Hk, d);
@@ -581,7 +598,7 @@ static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream)
     if (!grid_ok(blocks)) return kGridTooLarge;
     e = launch_kernel(moda_decode_partial_mfma_kernel<D>, dim3((unsigned)blocks), dim3(kDecMWaves * 64), stream, p);
   } else {
-    const int gt = G >= 3 ? 4 : G >= 2 ? 2 : 1;  // (3 heads: one chunk of 4 with a padded head, not two chunks)
+    const int gt = decode_heads_per_chunk(G);
     const long long blocks = (long long)p.B * p.Hk * ((G + gt - 1) / gt) * p.n_slices;
     if (!grid_ok(blocks)) return kGridTooLarge;
     dim3 grid((unsigned)blocks), block(kDecWaves * 64);
@@ -604,7 +621,7 @@ hipError_t launch_decode_bf16(const void* Q, const void* Kseq, const void* Vseq,
   p.O = O; p.LSE = LSE; p.ws = ws;
   p.B = B; p.Hq = Hq; p.Hk = Hk; p.T = T; p.T_alloc = T_alloc;
   p.depth_alloc = depth_alloc; p.depth_count = depth_count;
-  const DecodePlan pl = decode_plan(decode_rule(B, Hq, Hk, d), T, ws_bytes);
+  const DecodePlan pl = decode_plan(decode_rule(B, Hq, Hk, d), T, depth_count > 0, ws_bytes);
   p.n_split = pl.n_split;
   p.keys_per_split = pl.keys_per_split;
   p.n_slices = pl.n_split + (depth_count > 0 ? 1 : 0);

@@ -173,3 +173,22 @@ def test_decode_keys_of_weight_zero(B, Hq, Hk, T, d, lo, hi):
     torch.cuda.synchronize()
     assert (O.float() - O1.float()).abs().max().item() <= 2e-2
     assert (LSE - LSE1).abs().max().item() <= 1e-3
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,slices", [(4, 16, 8, 1662, 128, 12, 7), (3, 16, 8, 1662, 128, 12, 8), (1, 16, 16, 1003, 128, 2, 8),
+                                                  (36, 2, 2, 1271, 64, 7, 5), (64, 2, 2, 281, 128, 3, 3), (64, 2, 2, 281, 128, 0, 2),
+                                                  (23, 128, 16, 430, 64, 1, 2), (16, 128, 16, 380, 64, 4, 3),
+                                                  (16, 128, 16, 470, 64, 4, 2), (16, 128, 16, 470, 128, 4, 4)])
+def test_finer_slices_only_where_they_make_no_more_rounds(B, Hq, Hk, T, d, L, slices):
+    """The partial results that a call writes tell its slices: of at most 256 keys, or finer ones where these
+    leave no more workgroups than rounds of 256 (512 for groups of more than 4 heads at d = 128) hold already."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    one = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2300, device="cuda")
+    seq = synth.make_inputs(B, Hq, Hk, T, d, 0, dtype="bf16", seed=2301, device="cuda")
+    kd, vd = (None if L == 0 else one[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))
+    ws = torch.full((B * Hq * 20 * (d + 2),), float("nan"), device="cuda")
+    moda_attn_decode(one["Q"][:, :, 0].contiguous(), seq["Kseq"], seq["Vseq"], kd, vd, workspace=ws)
+    torch.cuda.synchronize()
+    written = int((~torch.isnan(ws)).sum().item())
+    assert written == B * Hq * (slices + (L > 0)) * (d + 2)
