@@ -433,7 +433,8 @@ template <int D, int NG>
 __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams p) {
   constexpr int kU = 8;
   __shared__ float red[NG > 1 ? NG : 1][D], stat[NG > 1 ? NG : 1][2];
-  const int ch = threadIdx.x % D, g = threadIdx.x / D;
+  // (the group is the same for a wave: what it reads of a slice besides its channel comes by scalar loads)
+  const int ch = threadIdx.x % D, g = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / D);
   const int bh = blockIdx.x;
   const float c2 = p.scale_log2;
   const float* ws = p.ws + (size_t)bh * p.n_slices * (D + 2);
