@@ -494,7 +494,8 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
 // How a call is cut into slices.  One query head per key/value head: workgroups of 4 waves,
 // enough of them to fill 256 compute units a few times over, slices of at least 256 keys (128 while
 // that makes no more than 8 slices: T=1003, 16 heads 7.4 -> 6.9 us; but 16 slices of 128 keys at T=2000,
-// 4 heads 6.8 -> 7.5 us).
+// 4 heads 6.8 -> 7.5 us; 8 slices instead of 5 to 7 of 256 keys 0 to 4 % longer at d = 64, at d = 128 5 % shorter
+// instead of 5 or 6, 3 % longer instead of 7).
 // More than 4 query heads per key/value head (matrix-pipe kernel): one slice per wave, of at least 128
 // keys (256 / 128: B=1 Hq=64 Hk=8 d=64 T=1003 13.2 / 10.1 us, T=4096 14.6 / 12.7; B=4 T=2000 d=128 22 / 16).
 // The finer slices of either only where they make no more rounds of workgroups than slices of 256 keys, i.e. where
@@ -514,6 +515,7 @@ struct DecodeRule {
   size_t slice_bytes;  // partial results of one slice of every (batch, head)
   long long groups;    // workgroups per slice (matrix pipe: per kDecMWaves slices)
   int round;           // workgroups that make one round
+  int most_for_8;      // (vector ALUs) 8 slices in place of up to so many of 256 keys, where finer ones make more than 8
   long long rounds(int slices) const {
     return (groups * (mfma ? (slices + kDecMWaves - 1) / kDecMWaves : slices) + round - 1) / round;
   }
@@ -543,6 +545,7 @@ static DecodeRule decode_rule(int B, int Hq, int Hk, int d) {
     r.groups = (long long)B * Hk * ((G + gt - 1) / gt);
     r.round = 256;
   }
+  r.most_for_8 = d == 128 ? 6 : 0;
   r.slice_bytes = (size_t)B * Hq * (d + 2) * sizeof(float);
   // (never so many that the partial results, with the depth slots' slice, outgrow the library's own scratch
   // array where those of the coarser slices fit it)
@@ -568,7 +571,7 @@ static DecodePlan cut(const DecodeRule& r, int T, int most) {
 static DecodePlan decode_plan(const DecodeRule& r, int T, int depth, size_t room) {
   const DecodePlan coarse = cut(r, T, coarse_slices(T));
   const int most = fine_slices(r.mfma, T);
-  if (most > r.most_fine) return coarse;
+  if (most > r.most_fine || (!r.mfma && T > 1024 && coarse_slices(T) > r.most_for_8)) return coarse;
   const DecodePlan fine = cut(r, T, most);
   const bool fits = (size_t)(fine.n_split + 1) * r.slice_bytes <= room;
   return fits && r.rounds(fine.n_split + depth) <= r.rounds(coarse.n_split + depth) ? fine : coarse;

@@ -175,13 +175,15 @@ def test_decode_keys_of_weight_zero(B, Hq, Hk, T, d, lo, hi):
     assert (LSE - LSE1).abs().max().item() <= 1e-3
 
 
-@pytest.mark.parametrize("B,Hq,Hk,T,d,L,slices", [(4, 16, 8, 1662, 128, 12, 7), (3, 16, 8, 1662, 128, 12, 8), (1, 16, 16, 1003, 128, 2, 8),
-                                                  (36, 2, 2, 1271, 64, 7, 5), (64, 2, 2, 281, 128, 3, 3), (64, 2, 2, 281, 128, 0, 2),
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,slices", [(4, 16, 8, 1500, 128, 12, 6), (3, 16, 8, 1500, 128, 12, 8), (1, 16, 16, 1003, 128, 2, 8),
+                                                  (36, 2, 2, 1271, 64, 7, 5), (1, 4, 4, 1024, 64, 1, 8), (1, 4, 4, 1025, 64, 1, 5),
+                                                  (1, 4, 4, 1536, 128, 1, 8), (1, 4, 4, 1537, 128, 1, 7), (64, 2, 2, 281, 128, 3, 3), (64, 2, 2, 281, 128, 0, 2),
                                                   (23, 128, 16, 430, 64, 1, 2), (16, 128, 16, 380, 64, 4, 3),
                                                   (16, 128, 16, 470, 64, 4, 2), (16, 128, 16, 470, 128, 4, 4)])
 def test_finer_slices_only_where_they_make_no_more_rounds(B, Hq, Hk, T, d, L, slices):
     """The partial results that a call writes tell its slices: of at most 256 keys, or finer ones where these
-    leave no more workgroups than rounds of 256 (512 for groups of more than 4 heads at d = 128) hold already."""
+    leave no more workgroups than rounds of 256 (512 for groups of more than 4 heads at d = 128) hold already, up to
+    8 of them for groups of up to 4 heads."""
     from paper_2603_15619_amd import moda_attn_decode
 
     one = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2300, device="cuda")
