@@ -156,25 +156,25 @@ def check_named_acc_registers(src) -> None:
             raise RuntimeError("%s: register spill to scratch memory (%s)" % (asm, line.strip()))
 
 
-# Kernels whose key loop keeps global -> LDS copies in flight while it computes must not
-# touch scratch memory inside that loop: memory operations complete in order, so waiting for a
-# reload also waits for the copies (measured on the dK/dV kernel: 1.9 ms with 100 bytes of
-# scratch per lane reloaded in the loop, 1.55 ms without).  A value parked in scratch before
-# the loops and fetched after them is harmless.
-# (source file, substring of the mangled kernel name)
-NO_SCRATCH_IN_LOOPS = (("moda_bwd_bf16.hip", "moda_bwd_dkdv_kernel"), ("moda_bwd_bf16.hip", "moda_bwd_dq_kernel"))
+# A loop that keeps global -> LDS copies or slot loads in flight while it computes must not touch
+# scratch memory: memory operations complete in order, so waiting for a reload also waits for the
+# copies (measured on the dK/dV kernel: 1.9 ms with 100 bytes of scratch per lane reloaded in the
+# loop, 1.55 ms without).  Every kernel of every source is held to it, in each loop that encloses
+# matrix instructions at any depth (the loop over positions around them is such a loop too) and, where
+# a kernel has no matrix instructions, in each loop.  A value parked in scratch before the loops and
+# fetched after them is harmless.
 
 
-def check_no_scratch_in_loops(src, name_part) -> None:
+def check_no_scratch_in_loops(src) -> None:
     asm = os.path.join(OBJ, os.path.basename(src)[:-4] + ".s")
     subprocess.run([HIPCC, *FLAGS, "--cuda-device-only", "-S", src, "-o", asm], check=True,
                    stderr=subprocess.DEVNULL)
-    scan_scratch_in_key_loops(asm, name_part)
+    scan_scratch_in_key_loops(asm)
 
 
-def scan_scratch_in_key_loops(asm, name_part) -> None:
+def scan_scratch_in_key_loops(asm, name_part="") -> None:
     """Raises if a kernel of assembly file `asm` whose name contains `name_part` touches scratch
-    memory inside a loop that issues matrix instructions."""
+    memory inside a loop that encloses matrix instructions (any loop, if it has none)."""
     import re
 
     found = 0
@@ -182,25 +182,40 @@ def scan_scratch_in_key_loops(asm, name_part) -> None:
         if name_part not in name:
             continue
         found += 1
-        # the compiler annotates every basic block of a loop with the header of its innermost loop;
-        # the loops that matter are those that issue matrix instructions (the key loops)
-        header, per_line = None, []
+        # the compiler annotates every basic block of a loop with the header of its innermost loop,
+        # and the header of a nested loop with the loops around it
+        header, per_line, parent = None, [], {}
+        block, around = None, {}
         for n, line in body:
-            if re.match(r"^(\.LBB\d+_\d+:|; %bb\.\d+:)", line):
-                m = re.search(r"Header=(BB\d+_\d+)", line)
-                if m:
-                    header = m.group(1)
+            m = re.match(r"^(?:\.L(BB\d+_\d+):|; %bb\.\d+:)", line)
+            if m:
+                block, header, around = m.group(1), None, {}
+            elif not re.match(r"^\s*;", line):
+                block = None  # (the annotations of a block stand in the comment lines at its label)
+            if m or block:
+                around.update((int(d), h) for h, d in re.findall(r"Parent Loop (BB\d+_\d+) Depth=(\d+)", line))
+                inside = re.search(r"in Loop: Header=(BB\d+_\d+)", line)
+                if inside:
+                    header = inside.group(1)
                 elif "Loop Header" in line:
-                    header = re.match(r"^\.L(BB\d+_\d+):", line).group(1)
-                else:
-                    header = None
+                    header = block
+                    parent[block] = around[max(around)] if around else None
             per_line.append((n, line, header))
-        hot = {h for _, line, h in per_line if h and re.match(r"^\s*v_mfma", line)}
+        has_mfma = any(re.match(r"^\s*v_mfma", line) for _, line, _ in per_line)
+        hot = set()
+        for _, line, h in per_line:
+            if h and (not has_mfma or re.match(r"^\s*v_mfma", line)):
+                while h and h not in hot:
+                    hot.add(h)
+                    h = parent.get(h)
         for n, line, h in per_line:
-            if h in hot and re.match(r"^\s*scratch_", line):
+            # (a loop inside a hot one runs as often)
+            while h and h not in hot:
+                h = parent.get(h)
+            if h and re.match(r"^\s*scratch_", line):
                 raise RuntimeError("%s:%d: %s touches scratch memory inside a key loop: %s"
                                    % (asm, n, name, line.strip()))
-    if found == 0:
+    if found == 0 and name_part:
         raise RuntimeError("%s: no kernel named *%s*" % (asm, name_part))
 
 
@@ -210,11 +225,11 @@ def build_libmoda() -> str:
     for src in sources():
         if os.path.basename(src) in NAMED_ACC_SOURCES:
             check_named_acc_registers(src)
-        for fname, part in NO_SCRATCH_IN_LOOPS:
-            if os.path.basename(src) == fname:
-                check_no_scratch_in_loops(src, part)
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        checks = [ex.submit(check_no_scratch_in_loops, src) for src in sources()]
         objs = list(ex.map(_compile, sources()))
+        for c in checks:
+            c.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB)

@@ -86,3 +86,74 @@ def test_scratch_inside_a_key_loop_is_rejected(tmp_path):
         B.scan_scratch_in_key_loops(str(f), "my_kernel")
     with pytest.raises(RuntimeError, match="no kernel named"):
         B.scan_scratch_in_key_loops(str(f), "other_kernel")
+
+
+NESTED = """\
+_Z9my_kernelv:
+.LBB0_1:                                ; =>This Loop Header: Depth=1
+                                        ;     Child Loop BB0_2 Depth 2
+                                        ;     Child Loop BB0_4 Depth 2
+%s
+.LBB0_2:                                ;   Parent Loop BB0_1 Depth=1
+                                        ; =>  This Inner Loop Header: Depth=2
+\tv_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], v[0:15]
+\ts_cbranch_scc1 .LBB0_2
+; %%bb.3:                                ;   in Loop: Header=BB0_1 Depth=1
+%s
+.LBB0_4:                                ;   Parent Loop BB0_1 Depth=1
+                                        ; =>  This Inner Loop Header: Depth=2
+%s
+\ts_cbranch_scc1 .LBB0_4
+; %%bb.5:                                ;   in Loop: Header=BB0_1 Depth=1
+\ts_cbranch_scc1 .LBB0_1
+; %%bb.6:
+%s
+.LBB0_7:                                ; =>This Inner Loop Header: Depth=1
+%s
+\ts_cbranch_scc1 .LBB0_7
+\ts_endpgm
+.Lfunc_end0:
+"""
+
+
+@pytest.mark.parametrize("place", range(5))
+def test_scratch_around_a_nested_key_loop(tmp_path, place):
+    """In the outer loop before (0) or behind (1) the loop of matrix instructions, or in another loop
+    inside it (2), scratch is rejected; behind the loops (3) or in a later loop (4) it is not."""
+    lines = ["\tv_add_f32_e32 v1, v2, v3"] * 5
+    f = tmp_path / "n.s"
+    f.write_text(NESTED % tuple(lines))
+    B.scan_scratch_in_key_loops(str(f))
+    lines[place] = "\tscratch_load_dword v3, off, off offset:4"
+    f.write_text(NESTED % tuple(lines))
+    if place < 3:
+        with pytest.raises(RuntimeError, match="inside a key loop"):
+            B.scan_scratch_in_key_loops(str(f), "my_kernel")
+    else:
+        B.scan_scratch_in_key_loops(str(f), "my_kernel")
+
+
+def test_scratch_in_a_loop_of_a_kernel_without_matrix_instructions_is_rejected(tmp_path):
+    text = (NESTED % tuple(["\tv_add_f32_e32 v1, v2, v3"] * 4 + ["\tscratch_load_dword v3, off, off"]))
+    f = tmp_path / "v.s"
+    f.write_text("\n".join(x for x in text.split("\n") if "v_mfma" not in x))
+    with pytest.raises(RuntimeError, match="inside a key loop"):
+        B.scan_scratch_in_key_loops(str(f))
+
+
+def test_every_source_is_checked(monkeypatch, tmp_path):
+    """The build hands every kernel source to the check, and a refusal ends the build."""
+    seen = []
+
+    def refuse_last(src):
+        seen.append(src)
+        if len(seen) == len(B.sources()):
+            raise RuntimeError("refused")
+
+    monkeypatch.setattr(B, "OBJ", str(tmp_path))
+    monkeypatch.setattr(B, "check_named_acc_registers", lambda src: None)
+    monkeypatch.setattr(B, "check_no_scratch_in_loops", refuse_last)
+    monkeypatch.setattr(B, "_compile", lambda src: src)
+    with pytest.raises(RuntimeError, match="refused"):
+        B.build_libmoda()
+    assert sorted(seen) == B.sources()
