@@ -40,6 +40,22 @@ def test_init_checks_its_arguments():
         m.init(0, 1, 1, 1, 1, 1)
 
 
+class Takes:
+    """The native half, with the names of the calls that it took."""
+
+    def __init__(self, native):
+        self.native, self.taken = native, []
+
+    def __getattr__(self, name):
+        def call(*a):
+            r = getattr(self.native, name)(*a)
+            if r is not None:
+                self.taken.append(name)
+            return r
+
+        return call
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_same_results_as_through_ctypes(monkeypatch, dtype):
@@ -58,7 +74,11 @@ def test_same_results_as_through_ctypes(monkeypatch, dtype):
         torch.cuda.synchronize()
         return r
 
+    takes = Takes(binding._native())
+    monkeypatch.setattr(binding, "_native_module", takes)
     native = calls()
+    assert takes.taken == (["fwd", "fwd", "fwd", "bwd", "fwd", "bwd", "decode", "append"] if dtype == "bf16"
+                           else ["fwd", "fwd", "append"])
     monkeypatch.setattr(binding, "_native_module", Declines())
     other = calls()
     assert len(native) == len(other)
@@ -96,6 +116,55 @@ def test_forms_that_the_native_half_leaves_to_the_other(monkeypatch):
         O2, _ = binding.moda_attn_fwd(*a, depth_count=2)
     s.synchronize()
     assert torch.equal(O, O2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_runs_on_the_current_stream(monkeypatch, native):
+    """Each call is captured on a stream of its own and replayed behind new inputs: work put on another stream would
+    not be part of the graph."""
+    mods = Takes(binding._native()) if native else Declines()
+    inp = synth.make_inputs(1, 4, 2, 90, 64, 2, dtype="bf16", seed=8, device="cuda", with_dO=True)
+    a = tuple(inp[k] for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth"))
+    q = a[0][:, :, -1].contiguous()
+    kd, vd = (x[:, :, -1].contiguous() for x in a[3:])
+    O, LSE = binding.moda_attn_fwd(*a, depth_count=2)
+    out = dict(O=torch.empty_like(O), LSE=torch.empty_like(LSE), dec=torch.empty_like(q),
+               dec_lse=torch.empty(1, 4, dtype=torch.float32, device="cuda"), grads=None)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+
+    def calls():
+        binding.moda_attn_fwd(*a, depth_count=2, out=out["O"], lse=out["LSE"])
+        out["grads"] = binding.moda_attn_bwd(*a, out["O"], out["LSE"], inp["dO"], depth_count=2)
+        binding.moda_attn_decode(q, a[1], a[2], kd, vd, depth_count=2, out=out["dec"], lse=out["dec_lse"], workspace=ws)
+
+    def results():
+        return [x.clone() for x in (out["O"], out["LSE"], out["dec"], out["dec_lse"], *out["grads"])]
+
+    calls()
+    torch.cuda.synchronize()
+    monkeypatch.setattr(binding, "_native_module", mods)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        calls()
+    if native:
+        assert mods.taken == ["fwd", "bwd", "decode"]
+    captured = out["grads"]
+    for seed in (9, 10, 11):
+        fresh = synth.make_inputs(1, 4, 2, 90, 64, 2, dtype="bf16", seed=seed, device="cuda", with_dO=True)
+        for k, x in zip(("Q", "Kseq", "Vseq", "Kdepth", "Vdepth"), a):
+            x.copy_(fresh[k])
+        q.copy_(a[0][:, :, -1])
+        calls()
+        torch.cuda.synchronize()
+        want = results()
+        for x in (*captured, out["O"], out["LSE"], out["dec"], out["dec_lse"]):
+            x.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        out["grads"] = captured
+        for x, y in zip(results(), want):
+            assert torch.equal(x, y)
 
 
 @pytest.mark.gpu
