@@ -120,12 +120,18 @@ def test_decode_slice_counts(B, Hq, Hk, T, d, L):
 
 
 def test_slices_fit_the_scratch_array_where_coarser_ones_do():
-    """moda_attn_decode_noalloc takes what 256-key slices would let it take."""
+    """moda_attn_decode_noalloc takes what 256-key slices would let it take (the first three: 128-key slices, of
+    every (batch, head) and with the depth slots' slice, would not fit)."""
     import ctypes
 
     from paper_2603_15619_amd.binding import MODAShape, lib
 
     most = lib().moda_attn_decode_noalloc_max_bytes()
+    for B, Hk, G, T, d in [(8, 8, 8, 4000, 128), (8, 16, 8, 2000, 128), (1, 16, 16, 16000, 64)]:
+        one = B * G * Hk * (d + 2) * 4
+        assert ((T + 127) // 128 + 1) * one > most >= ((T + 255) // 256 + 1) * one
+        s = MODAShape(B, G * Hk, Hk, T, d, 2, 2, 1, 0.0, 1)
+        assert lib().moda_attn_decode_workspace_bytes(ctypes.byref(s)) <= most
     for B, Hk, G, T, d in [(8, 2, 32, 2000, 128), (30, 1, 8, 16000, 64), (400, 4, 1, 1000, 128), (6, 1, 64, 5000, 64)]:
         s = MODAShape(B, G * Hk, Hk, T, d, 2, 2, 1, 0.0, 1)
         coarse = B * G * Hk * ((T + 255) // 256 + 1) * (d + 2) * 4
