@@ -28,7 +28,7 @@ WORKLOADS = {
     # name: (B, Hq, Hk, T, d, depth_count, dtype)
     "long_context_64k": (1, 16, 16, 65536, 128, 15, "bf16"),   # the headline workload
     "layer_1p5b_4k": (8, 16, 16, 4096, 128, 15, "bf16"),
-    "tiny_fp32": (1, 2, 2, 256, 64, 4, "f32"),    
+    "tiny_fp32": (1, 2, 2, 256, 64, 4, "f32"),    # the fp32 accuracy configuration
     "bwd_layer_1p5b_4k": (8, 16, 16, 4096, 128, 15, "bf16"),   # backward
     "copy_calibration": None,  # plain device copy of known size, for scaling the HBM byte counters
     "mfma_calibration": None,  # what the matrix pipe alone sustains (zero and N(0,1) bf16 operands)

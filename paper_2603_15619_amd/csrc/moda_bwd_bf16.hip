@@ -6,8 +6,8 @@
 //   p_c = exp(scale <q_t, k_c> - LSE_t),  delta_t = <dO_t, O_t>,
 //   dV_c += p_c dO_t,  e_c = p_c (<dO_t, v_c> - delta_t),
 //   dQ_t = scale sum_c e_c k_c,  dK_c += scale e_c q_t.
-// Three kernels (four with grouped queries), no atomics, every output element written
-// exactly once:
+// Three kernels (four where the depth slots of a group have one of their own, see the end), no
+// atomics, every output element written exactly once:
 //   delta  : (LSE_t log2(e), delta_t) for every row (row-parallel, vector ALUs).
 //   dkdv   : one workgroup per 128 sequence keys; Q / dO tiles stream through LDS;
 //            S = Q K^T and dP = dO V^T are recomputed per 32x32 block on the MFMA
@@ -24,10 +24,12 @@
 //            element of dQ is rounded to bf16 once.
 // Grouped-query attention (G = Hq / Hk query heads per key/value head, G <= 64): the
 // gradients of the shared keys and values sum over the group.  dkdv walks the query
-// tiles of all G heads; the depth-slot gradients are computed by a kernel of their own
-// (depth_gqa for G <= 8 on the vector ALUs, depth_group above that on the matrix pipe) that holds
-// the G heads of a position side by side, sums in fp32 and rounds every depth gradient once, or inside
-// dkdv: up to 4 heads on the vector ALUs, 5 to 8 heads with enough slots on the matrix pipe.
+// tiles of all G heads; the depth-slot gradients hold the G heads of a position side by side, sum in
+// fp32 and round every depth gradient once:
+//   up to 4 heads  : inside dkdv (or dkdv_short), on the vector ALUs (depth_gqa_row);
+//   5 to 8 heads   : at d = 64 with blocks of 32 slots well filled, inside dkdv on the matrix pipe
+//                    (depth_group_rows); otherwise a kernel of their own on the vector ALUs (depth_gqa);
+//   9 heads and up : a kernel of their own on the matrix pipe (depth_group).
 #include <type_traits>
 
 #include "moda_launch.h"
@@ -304,8 +306,8 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
 // One row = one (batch, key/value head, position); d/8 lanes x 8 channels per row, `row` is
 // (b * Hk + g) * T + t of this thread's row (rows that do not exist: `live` false, they compute on
 // a clamped row and store nothing).  The GT (>= G) query heads of the group are resident (their Q
-// and dO rows, LSE, delta, and their depth share of dQ); the row's slots stream by, one prefetched
-// ahead.  Per slot i:
+// and dO rows, LSE, delta, and their depth share of dQ); the row's slots stream by, the next ones
+// prefetched.  Per slot i:
 //   dVdepth_i = sum_h p_{h,i} dO_h,  dKdepth_i = scale sum_h e_{h,i} q_h  (summed in fp32, one
 //                                    rounding each),
 //   dQ_h     += e_{h,i} k_i          (left in the workspace, fp32, unscaled, for the dQ kernel).
@@ -422,9 +424,9 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
   }
 }
 
-// The same rows as a kernel of its own: groups of 5 to 8 heads, where the arithmetic per fetched
-// byte (it grows with the group) makes the phase a vector-ALU job that the dK/dV kernel cannot
-// hide (measured at 8 heads: inside dK/dV it costs what it costs alone).
+// The same rows as a kernel of its own: groups of 5 to 8 heads (those that do not take
+// depth_group_rows, see own_depth_kernel).  The arithmetic per fetched byte grows with the group, and on
+// the vector ALUs the dK/dV kernel cannot hide it (measured at 8 heads: there it costs what it costs alone).
 template <int D, int GT>
 __global__ __launch_bounds__(256, 2) void moda_bwd_depth_gqa_kernel(BwdParams p) {
   constexpr int LPR = D / 8, ROWS = 256 / LPR;
@@ -453,7 +455,7 @@ __device__ __forceinline__ void split2(float& x, float& y, uint32_t (&part)[3]) 
 // take to arrive at this group size, and inside the dK/dV kernel they cost what they cost alone;
 // here the vector ALUs only exponentiate, so that the phase is HBM's and the key-tile work of the
 // workgroup next door goes on beside it.  B=1 Hq=64 Hk=8 T=16384 d=64, 64 slots: 1.13 ms in a kernel of
-// its own + 4.39 -> 5.06 ms together (of which 0.9 would be the 4.3 GB at the rate of a large copy).
+// its own + 4.46 -> 5.16 ms together (0.9 would be the 4.3 GB alone at the rate of a large copy).
 // Columns (or rows) of the products past the group repeat heads that exist and get weight zero
 // (lse = +inf).  The weights P and E enter the products as the sum of three bf16 numbers, i.e. with all
 // their 24 bits: the contractions over the heads have room for the second number in the 8 of their 16
@@ -697,9 +699,9 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
 // ---------------------------------------------------------------- dK, dV
 // Workgroup = 128 keys (4 waves x 32 keys).  Accumulators hold dK^T, dV^T
 // ([channel][key]: a lane owns one key and 64 of its channels).
-// GT: 0 = one query head per key/value head, more than 4 heads per group, or no depth slots;
-// 2, 4, 8 = the depth-slot gradients of a group of up to GT heads are taken here as well
-// (depth_gqa_row; 8: depth_group_rows).
+// GT: 2, 4, 8 = the depth-slot gradients of a group of up to GT heads are taken here as well (2, 4:
+// depth_gqa_row; 8, at d = 64: depth_group_rows); 0 = one query head per key/value head (depth_grad_rows), or
+// depth slots that have a kernel of their own, or none.
 template <int D, int GT>
 __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   using Tl = Tile<D>;
@@ -723,8 +725,8 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   const char* Kb = (const char*)p.Kseq + (size_t)bg * T * Tl::kRowBytes;
   const char* Vb = (const char*)p.Vseq + (size_t)bg * T * Tl::kRowBytes;
 
-  // ---- Depth-slot gradients (one query head per key/value head; grouped queries have a kernel
-  // of their own): row-local, bound by HBM (every depth slot read once, every gradient written
+  // ---- Depth-slot gradients (one query head per key/value head; groups: group_depth below, or a
+  // kernel of their own): row-local, bound by HBM (every depth slot read once, every gradient written
   // once), and independent of everything else this kernel does, which is bound by the matrix
   // pipe and leaves HBM idle.  Each workgroup takes the 128 positions of its key tile, before
   // its key-tile work (every other workgroup) or after it, so that at any time some compute

@@ -10,16 +10,17 @@
 // of the depth slots.  Dealing out keys instead of queries makes the unit of work 32 queries per
 // 4 SIMDs: a few thousand rows of causal attention then fill 256 compute units evenly (32 queries
 // per wave left the last query tiles of a T = 2000 call alone on the chip for twice the mean), and
-// a call of a few hundred rows walks its longest row in a quarter of the steps.
+// a call of a few hundred rows walks its longest row in a quarter of the steps.  (Sequences of a few
+// positions, which this would pad to tiles of 32, go to the kernel of moda_fwd_f32_rows.hip.)
 //
 // What bounds it: the fp32 matrix pipe (64 FLOP per cycle and SIMD) on the sequence keys, HBM on
 // the depth slots (4 bytes per FLOP); every other workgroup takes its slots before its key tiles,
 // the others after, so that both are busy.
-//   B=1 H=16 T=2000 d=128, 15 slots: 0.209 ms, 80 TFLOP/s and 2.7 TB/s (one wave per query on the
+//   B=1 H=16 T=2000 d=128, 15 slots: 0.211 ms, 79 TFLOP/s and 2.6 TB/s (one wave per query on the
 //                                    vector ALUs, the form before: 2.69 ms)
 //   B=1 H=16 T=8000 d=128, no slots: 1.95 ms, 134 TFLOP/s of the 154 that a library product of
 //                                    8192^3 reaches on the same card
-//   B=1 H=2 T=256 d=64, 4 slots:     10 us (36 us), most of it latency from one end to the other
+//   B=1 H=2 T=256 d=64, 4 slots:     10.7 us (36 us), most of it latency from one end to the other
 //
 // Operand layouts.  S^T = K Q^T (keys on M, queries on N): the contraction may take the channels
 // in any order that both operands share, so lane (l32, hi) holds channels 8 j + 4 hi .. + 3 of key

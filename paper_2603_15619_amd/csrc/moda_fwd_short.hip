@@ -16,8 +16,8 @@
 // the waves after the key tiles.
 //
 // Bound by a wave's chain copy -> products -> exponentials -> products on the key tiles and by HBM on
-// the depth slots.  B=1 H=8 T=2048, 4 slots: d=64 33 -> 18 us, d=128 43 -> 31 us (15 of them the
-// host's); B=1 H=2 T=16384 d=64: 200 -> 121 us.
+// the depth slots.  B=1 H=8 T=2048, 4 slots: d=64 33 -> 17 us, d=128 43 -> 29 us;
+// B=1 H=2 T=16384 d=64: 203 -> 123 us.
 //
 // K and V have one LDS tile each per wave; the next tile's K is requested as soon as the scores of
 // this one are formed and its V as soon as the output product has read it, so that several
