@@ -879,6 +879,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       MODA_PIN();
       MODA_NOP(15);  // the matrix results have landed before the vector ALUs read them
       MODA_NOP(15);
+      asm volatile("" : "+v"(sd.a[0]));  // (and no reader is moved up before the wait)
       // mask: key r of the block is attended by this lane's query iff it is a slot of its position
       const unsigned lo = (unsigned)((l32 >> gt_shift) * L - blk * 32);  // first key of the position, relative to the block
       float vmax = -INFINITY;
