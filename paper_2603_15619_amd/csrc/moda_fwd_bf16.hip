@@ -16,8 +16,8 @@
 //   O^T += V^T P^T with P^T taken straight from the S^T accumulators (no layout
 //                 round trip); the V^T operand comes from ds_read_b64_tr_b16.
 // The key loop is software pipelined: while tile kt-1's P V and tile kt+1's K Q^T run
-// on the matrix pipe, the vector ALUs take the row max of tile kt and exponentiate it,
-// a fixed slice after every MFMA.  The loop body is unrolled over the 4 ring stages, so
+// on the matrix pipe, the vector ALUs exponentiate tile kt, a fixed slice after every MFMA, with the
+// reference of the tiles before: no row maximum is taken unless a tile's sum asks for it (see `step`).  The loop body is unrolled over the 4 ring stages, so
 // every LDS address is a per-lane base register plus an immediate.  K / V^T fragments
 // are read from LDS straight into named accumulation registers a fixed number of MFMAs
 // ahead of their use (moda_fwd_regs.h), next to the Q fragments and the output
@@ -275,18 +275,71 @@ __device__ __forceinline__ void zero(PTile& t) {
       for (int i = 0; i < 4; ++i) asm volatile("v_mov_b32 %0, 0" : "=v"(t.a[kb][hf][i]));
 }
 
-// exp2 of two adjacent scores: pair Q of a tile, Q = kb*8 + j.
-template <int Q>
-__device__ __forceinline__ void exp_pair(const STile& s, PTile& pt, float mc, float& l_run, float c2) {
-  constexpr int kb = Q / 8, j = Q % 8;
-  const float e0 = fast_exp2(s.a[kb][2 * j] * c2 - mc);
-  const float e1 = fast_exp2(s.a[kb][2 * j + 1] * c2 - mc);
-  float l = l_run + (e0 + e1);
-  int pk = (int)pack_bf16(e0, e1);
-  MODA_ANCHOR(l);
-  MODA_ANCHOR(pk);
-  l_run = l;
-  pt.a[kb][j >> 2][j & 3] = pk;
+// The weights of a tile, exp2((score - reference) c2), 32 scores per lane spread evenly over the
+// NS = kNFV + kNFK matrix instructions of a step (kPer per instruction) as a pipeline over them: after
+// matrix instruction g the exponentials of scores g kPer ..., then the arguments of the next ones, then
+// the sums and packing of finished pairs, so that nothing waits for the instruction before it.
+// (B=1 H=16 T=65536 d=128 without slots 13.46 ms with the exponentials before the matrix instruction, 13.19
+// after it; B=1 Hq=64 Hk=8 T=16384 d=64 2.13 / 2.09 with the order pinned between arguments and sums.)
+struct Weights {
+  float x[2];   // arguments of the next exponentials
+  float e[2];   // the pair in progress
+  float sum;    // this lane's weights of the tile so far
+};
+template <class C>
+constexpr int kPer = 32 / (C::kNFV + C::kNFK);
+template <class C, int G>  // arguments for matrix instruction G of the step
+__device__ __forceinline__ void weight_args(const STile& s, Weights& w, float mc, float c2) {
+  static_for<kPer<C>>([&](auto U) {
+    constexpr int u = decltype(U)::value, n = G * kPer<C> + u;
+    w.x[u] = __builtin_fmaf(s.a[n / 16][n % 16], c2, -mc);
+    MODA_ANCHOR(w.x[u]);
+  });
+}
+template <class C, int G>  // after matrix instruction G ...
+__device__ __forceinline__ void weight_exps(Weights& w) {
+  static_for<kPer<C>>([&](auto U) {
+    constexpr int u = decltype(U)::value;
+    w.e[(G * kPer<C> + u) & 1] = fast_exp2(w.x[u]);
+    MODA_ANCHOR(w.e[(G * kPer<C> + u) & 1]);
+  });
+}
+template <class C, int G>  // ... and then
+__device__ __forceinline__ void weight_sums(const STile& s, PTile& pt, Weights& w, float mc, float c2) {
+  if constexpr (G + 1 < C::kNFV + C::kNFK) weight_args<C, G + 1>(s, w, mc, c2);
+  MODA_PIN();
+  constexpr int last = G * kPer<C> + kPer<C> - 1;
+  if constexpr (last & 1) {
+    constexpr int kb = last / 16, j = (last % 16) / 2;
+    const float both = w.e[0] + w.e[1];
+    w.sum = last == 1 ? both : w.sum + both;
+    int pk = (int)pack_bf16(w.e[0], w.e[1]);
+    MODA_ANCHOR(w.sum);
+    MODA_ANCHOR(pk);
+    pt.a[kb][j >> 2][j & 3] = pk;
+  }
+}
+// All of a tile at once (the rare path).
+__device__ __forceinline__ void weigh_tile(const STile& s, PTile& pt, Weights& w, float mc, float c2) {
+  w.sum = 0.f;
+  static_for<16>([&](auto Q) {
+    constexpr int kb = decltype(Q)::value / 8, j = decltype(Q)::value % 8;
+    const float e0 = fast_exp2(__builtin_fmaf(s.a[kb][2 * j], c2, -mc));
+    const float e1 = fast_exp2(__builtin_fmaf(s.a[kb][2 * j + 1], c2, -mc));
+    w.sum += e0 + e1;
+    int pk = (int)pack_bf16(e0, e1);
+    MODA_ANCHOR(w.sum);
+    MODA_ANCHOR(pk);
+    pt.a[kb][j >> 2][j & 3] = pk;
+    MODA_PIN();  // (not all pairs at once: there are no registers for them)
+  });
+}
+// Largest score of this lane's query in the tile (two lanes share a query).
+__device__ __forceinline__ float tile_max(const STile& s) {
+  float mx = s.a[0][0];
+#pragma unroll
+  for (int i = 1; i < 32; ++i) mx = fmaxf(mx, s.a[i / 16][i % 16]);
+  return pair_max(mx);
 }
 
 // The LDS reads form one stream per wave: V^T fragments 0..NFV-1 of a tile, then K
@@ -303,12 +356,13 @@ constexpr int ops_after() {
 }
 
 // ---- matrix phase 1: S^T(next) = K Q^T over the 64-key tile in K stage KS (kNFK
-// MFMAs), with exp2 of the CURRENT tile's second key block (pairs 8..15) spread
-// between the MFMAs when WITH_EXP.  The first kAhead K fragments were requested by the
+// MFMAs), with the second half of the CURRENT tile's weights between the MFMAs when WITH_EXP.
+// The first kAhead K fragments were requested by the
 // phase before; this one requests the first V^T fragments of stage VSN for the phase
 // after.  The hardware does not interlock a matrix result against a vector-ALU reader:
-// the caller keeps at least 12 issue slots between the end of this function and the
-// first read of `nxt` (an MFMA of the next phase counts 8).
+// the caller keeps at least 12 issue slots between an MFMA and the first read of its result (an MFMA
+// issued in between counts 8): key block 0 of `nxt` is complete one MFMA before the end, and the weights of
+// the tile start with it, after the last pair's sum and pack and the comparison of the tile's sum.
 // `hook(integral_constant<m>)` runs after MFMA number m: the caller spreads its
 // global->LDS copy instructions there, one at a time, so that their issue time is
 // hidden behind matrix work as well.
@@ -317,9 +371,8 @@ struct NoHook {
   __device__ __forceinline__ void operator()(I) const {}
 };
 template <class C, int KS, int VSN, bool WITH_EXP, class Hook = NoHook>
-__device__ __forceinline__ void qk_phase(STile& nxt, const STile& cur, PTile& pcur, float mc,
-                                         float& l_run, float c2, const FragBase<C>& fb,
-                                         Hook hook = Hook{}) {
+__device__ __forceinline__ void qk_phase(STile& nxt, const STile& cur, PTile& pcur, Weights& w, float mc, float c2,
+                                         const FragBase<C>& fb, Hook hook = Hook{}) {
   constexpr int NF = C::kNFK;
   static_for<NF>([&](auto F) {
     constexpr int f = decltype(F)::value;
@@ -329,64 +382,47 @@ __device__ __forceinline__ void qk_phase(STile& nxt, const STile& cur, PTile& pc
     else read_vfrag<C, VSN, (pf < NF ? 0 : pf - NF)>(fb);
     lds_wait<ops_after<f, NF, 1, 2>()>();
     mfma_s<f % kSlots, st, st == 0>(nxt.a[kb]);
+    MODA_PIN();
     if constexpr (WITH_EXP) {
-      constexpr int lo = 8 + (f * 8) / NF, up = 8 + ((f + 1) * 8) / NF;
-      static_for<up - lo>([&](auto Q) { exp_pair<lo + decltype(Q)::value>(cur, pcur, mc, l_run, c2); });
+      weight_exps<C, C::kNFV + f>(w);
+      MODA_PIN();
+      weight_sums<C, C::kNFV + f>(cur, pcur, w, mc, c2);
     }
     hook(F);
     MODA_PIN();
   });
 }
 
-// ---- matrix phase 2: O^T += V^T P^T over the 64-key tile in V stage VS, V^T fragments
-// FIRST..LAST-1 (one MFMA each); requests the first K fragments of stage KSN for the
-// phase after.  MODE 0: nothing else.  MODE 1 (head, fragments of the first 16 keys):
-// the row max of the current score tile is taken between the MFMAs, starting after the
-// second one (see qk_phase).  MODE 2 (tail): exp2 of the current tile's first key block
-// (pairs 0..7) is spread between the MFMAs.
+// ---- matrix phase 2: O^T += V^T P^T over the 64-key tile in V stage VS (kNFV MFMAs), with the first
+// half of the current tile's weights between the MFMAs and the first K fragments of stage KSN requested
+// for the phase after, unless it is the wave's LAST tile.
 // `before_k(...)` runs just before the first K fragment of stage KSN is requested (all V^T
 // fragments of this tile have been requested by then): where the 2-stage geometry awaits
 // the copies of that K tile and synchronises the workgroup.
-template <class C, int VS, int KSN, int FIRST, int LAST, int MODE, class BeforeK = NoHook>
-__device__ __forceinline__ void pv_phase(const PTile& pin, const STile& s, PTile& pout, float mc,
-                                         float& l_run, float& mx, float c2, const FragBase<C>& fb,
-                                         BeforeK before_k = BeforeK{}) {
-  static_assert((FIRST <= C::kNFV - kAhead && LAST > C::kNFV - kAhead) || std::is_same<BeforeK, NoHook>::value,
-                "only the call that requests the first K fragment takes the hook");
+template <class C, int VS, int KSN, bool LAST, class BeforeK = NoHook>
+__device__ __forceinline__ void pv_phase(const PTile& pin, const STile& s, PTile& pout, Weights& w, float mc, float c2,
+                                         const FragBase<C>& fb, BeforeK before_k = BeforeK{}) {
   constexpr int DB = C::kDBlocks;
   constexpr int NF = C::kNFV;
-  constexpr int NM = LAST - FIRST;  // MFMAs in this call
-  float vmax[2];                    // MODE 1: two independent chains of partial maxima
-  static_for<NM>([&](auto FI) {
-    constexpr int m = decltype(FI)::value;
-    constexpr int f = FIRST + m;
+  if constexpr (!LAST) weight_args<C, 0>(s, w, mc, c2);
+  static_for<NF>([&](auto F) {
+    constexpr int f = decltype(F)::value;
     constexpr int ks = f / DB, db = f % DB;
     constexpr int kb = ks >> 1, hf = ks & 1;
     constexpr int pf = f + kAhead;
-    if constexpr (pf == NF) before_k(FI);
+    if constexpr (pf == NF) before_k(F);
     if constexpr (pf < NF) read_vfrag<C, VS, (pf < NF ? pf : 0)>(fb);
-    else read_kfrag<C, KSN, (pf < NF ? 0 : pf - NF)>(fb);
-    lds_wait<ops_after<f, NF, 2, 1>()>();
+    else if constexpr (!LAST) read_kfrag<C, KSN, (pf < NF ? 0 : pf - NF)>(fb);
+    lds_wait<ops_after<f, NF, 2, LAST ? 0 : 1>()>();
     mfma_o<db, f % kSlots>(pin.a[kb][hf]);
-    if constexpr (MODE == 1 && m >= 1) {
-      // 32 score registers folded 2 at a time (v_max3): 16 steps spread over NM-1 slots
-      constexpr int lo = ((m - 1) * 16) / (NM - 1), up = (m * 16) / (NM - 1);
-      static_for<up - lo>([&](auto Z) {
-        constexpr int w = lo + decltype(Z)::value;  // step w folds registers 2w, 2w+1 of the 32
-        constexpr int kb2 = w >> 3, i0 = (w & 7) * 2;
-        constexpr int ch = w & 1;
-        if constexpr (w < 2) vmax[ch] = fmaxf(s.a[kb2][i0], s.a[kb2][i0 + 1]);
-        else vmax[ch] = fmaxf(fmaxf(vmax[ch], s.a[kb2][i0]), s.a[kb2][i0 + 1]);
-        MODA_ANCHOR(vmax[ch]);
-      });
-    }
-    if constexpr (MODE == 2) {
-      constexpr int lo = (m * 8) / NM, up = ((m + 1) * 8) / NM;
-      static_for<up - lo>([&](auto Q) { exp_pair<lo + decltype(Q)::value>(s, pout, mc, l_run, c2); });
+    MODA_PIN();
+    if constexpr (!LAST) {
+      weight_exps<C, f>(w);
+      MODA_PIN();
+      weight_sums<C, f>(s, pout, w, mc, c2);
     }
     MODA_PIN();
   });
-  if constexpr (MODE == 1) mx = pair_max(fmaxf(vmax[0], vmax[1]));
 }
 
 template <int D, int W>
@@ -745,14 +781,14 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const i32x4 k_buf = make_raw_buffer(Kb, (unsigned)T * C::kRowBytes);
   const i32x4 v_buf = make_raw_buffer(Vb, (unsigned)T * C::kRowBytes);
   // Copy instruction I (of kInstPerWave) of this wave's share of tile kt into the ring stage at
-  // byte offset STAGE_OFF: piece wave * kInstPerWave + I.  The wave-dependent parts of both
+  // byte offset STAGE_OFF + stage_off: piece wave * kInstPerWave + I.  The wave-dependent parts of both
   // addresses are two scalars; everything else is a compile-time constant.
   const int wave_lds = __builtin_amdgcn_readfirstlane((int)smem_addr + wave * C::kInstPerWave * C::kKPieceStride);
   const int wave_lds_v = __builtin_amdgcn_readfirstlane((int)smem_addr + wave * C::kInstPerWave * C::kVPieceStride);
   const int wave_goff = __builtin_amdgcn_readfirstlane(wave * C::kInstPerWave * 1024);
   // `kt` is the K tile index of the step; the V tile copied in the same step is
   // kStages - kVAhead tiles behind it.
-  auto issue_one = [&](auto IS_K, auto I, auto STAGE_OFF, const i32x4& buf, int kt) {
+  auto issue_one = [&](auto IS_K, auto I, auto STAGE_OFF, const i32x4& buf, int kt, int stage_off = 0) {
     constexpr bool is_k = decltype(IS_K)::value;
     constexpr int i = decltype(I)::value;
     constexpr int stride = is_k ? C::kKPieceStride : C::kVPieceStride;
@@ -766,7 +802,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     copy16_to_lds<decltype(STAGE_OFF)::value + i * (stride - 1024), i * 1024,
                   is_k ? 0 : -(kStages - C::kVAhead) * C::kGTileBytes>(
-        buf, goff, soff, is_k ? wave_lds : wave_lds_v);
+        buf, goff, soff, (is_k ? wave_lds : wave_lds_v) + stage_off);
   };
   auto issue_tile = [&](auto IS_K, auto STAGE_OFF, const i32x4& buf, int kt) {
     static_for<C::kInstPerWave>([&](auto I) { issue_one(IS_K, I, STAGE_OFF, buf, kt); });
@@ -797,7 +833,6 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
   FragBase<C> fb;
   fb.init(tid & 63, (int)smem_addr);
-  float mx = 0.f;
 
   // ---- The depth slots on the matrix pipe.  A wave's 32 queries are PW = 32 / GT consecutive
   // positions x GT heads; the attended depth slots of those positions, enumerated position by
@@ -950,137 +985,149 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
   STile sA, sB;
   PTile pA, pB;
+  Weights w;
   zero(pA);
   clear(pB);
   {
     static_for<kAhead>([&](auto I) { read_kfrag<C, 0, decltype(I)::value>(fb); });
-    qk_phase<C, 0, kStages - 1, false>(sA, sA, pA, 0.f, l_run, c2, fb);
+    qk_phase<C, 0, kStages - 1, false>(sA, sA, pA, w, 0.f, c2, fb);
     MODA_PIN();
     MODA_NOP(15);
     if (wave_last == 0 && needs_mask(0)) mask_tile(sA, 0);
+    // the first reference (a query whose scores are all -inf so far takes 0: weights 0, empty state)
+    const float mx = tile_max(sA);
+    if (m_run == -INFINITY) m_run = mx == -INFINITY ? 0.f : mx;
   }
 
   // ---- steady state.  Step kt, kt % 4 == S (scores of tile kt are in `cur`, P of tile
   // kt-1 in `pprev`):
-  //   matrix pipe : O += P V (tile kt-1)            | S(next) = K Q^T (tile kt+1)
-  //   vector ALUs : row max of tile kt, exp2 of its | exp2 of its second key block
-  //                 first key block                 |
+  //   matrix pipe : O += P V (tile kt-1)          | S(next) = K Q^T (tile kt+1)
+  //   vector ALUs : weights of tile kt, key block | ... key block 1
+  //                 0                             |
   //   in between  : wait for the copies issued two steps ago, barrier; the copies of
   //                 K tile kt+4 and V tile kt+2 into the stages just vacated ride along
   //                 with the second matrix phase.
-  // The reference max is only raised when some row's tile max exceeds it by more than
-  // 2^8 in the exp2 domain; P may then exceed 1 (bounded by 256), which fp32 sums and
-  // bf16 P hold without loss, and the final division is unchanged.  Raising it is the
-  // rare path: the pending P V is finished first, then the accumulators are rescaled.
+  // No row maximum is taken: the weights of a tile are formed with the reference of the tiles before,
+  // and their sum, which the normaliser needs anyway, tells afterwards whether that was good enough.  As
+  // long as a lane's 32 weights sum to at most 2^8, none exceeds 2^8, which fp32 sums and bf16 P hold
+  // without loss, and the final division is unchanged.  Otherwise (and for NaN) the rare path raises the
+  // reference to the row maximum, rescales the accumulators and forms the tile's weights anew, before they
+  // are multiplied with anything.  (The maximum, its exchange between two lanes, comparison and branch stood
+  // before the first exponential of every tile: 24 of 150 vector instructions, and nothing to overlap with.
+  // B=1 H=16 T=65536 d=128: 14.2 -> 13.2 ms, 1.33 PFLOP/s; B=1 Hq=64 Hk=8 T=16384 d=64: 2.49 -> 2.09 ms, 1.05.)
+  // Every step issues the same number of copies (tiles past the end of the tensor are
+  // out of range of the raw buffer: nothing is fetched), so "all but the newest
+  // kPending copies have landed" always means: K tile kt+1 and V tile kt, which are
+  // read next, are complete (with 4 stages K tile kt+2 too: one step of slack).
+  // The stages written are those of K tile kt (its scores were taken in step kt-1) and,
+  // with 4 stages, of V tile kt-2, with 2 stages of V tile kt-1 (consumed in the first
+  // half of this step): every wave is past those reads once it has passed the barrier.
+  //
+  // Where the barrier stands: with 4 stages between the two matrix phases.  With 2 stages
+  // K tile kt+1 was only requested in step kt-1, and its first fragments are read at the end
+  // of the first matrix phase: the synchronisation point moves to just before that read.  All
+  // V^T fragment reads of tile kt-1 have been issued by then (LDS serves requests in order, and a
+  // copy into that stage is only requested after the barrier, so it lands after them).
+  constexpr bool kEarlySync = kStages == 2;
+  auto sync_copies = [&]() {
+    wait_copies_but<C::kPending>();
+    __syncthreads();
+  };
+  // step kt <= wave_last
   auto step = [&](auto SI, int kt, STile& cur, STile& nxt, const PTile& pprev, PTile& pcur) {
     constexpr int S = decltype(SI)::value;
     constexpr int VS_PREV = (S + kStages - 1) % kStages;  // V tile kt-1
     constexpr int KS_NEXT = (S + 1) % kStages;            // K tile kt+1
     constexpr int VS_CUR = S % kStages;                   // V tile kt
-    constexpr int NFV = C::kNFV;
-    constexpr int HEAD = C::kDBlocks;  // V fragments of the first 16 keys
-    // Await this wave's copies and synchronise the workgroup.  With 4 stages this stands
-    // between the two matrix phases.  With 2 stages K tile kt+1 was only requested in step
-    // kt-1, and its first fragments are read at the end of the first matrix phase: the
-    // synchronisation point moves to just before that read.  All V^T fragment reads of tile
-    // kt-1 have been issued by then (LDS serves requests in order, and a copy into that
-    // stage is only requested after the barrier, so it lands after them).
-    constexpr bool kEarlySync = kStages == 2;
-    auto sync_copies = [&]() {
-      if (kt < nt) {
-        wait_copies_but<C::kPending>();
-        __syncthreads();
-      }
-    };
     auto before_k = [&](auto) {
       if constexpr (kEarlySync) sync_copies();
     };
-    if (kt <= wave_last) {
-      pv_phase<C, VS_PREV, KS_NEXT, 0, HEAD, 1>(pprev, cur, pcur, 0.f, l_run, mx, c2, fb);
-      const bool raise = (mx - m_run) * c2 > 8.f;
-      if (__builtin_amdgcn_ballot_w64(raise) != 0) {
-        // Rare path (always taken for the first tile, where m_run = -inf).
-        pv_phase<C, VS_PREV, KS_NEXT, HEAD, NFV, 0>(pprev, cur, pcur, 0.f, l_run, mx, c2, fb, before_k);
-        MODA_PIN();
-        MODA_NOP(15);  // every MFMA above has retired
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = fast_exp2((m_run - m_new) * c2);  // 0 when m_run = -inf
-        m_run = m_new;
-        l_run *= alpha;
-        static_for<C::kDBlocks * 16>([&](auto R) { scale_acc<kAccO + decltype(R)::value>(alpha); });
-        MODA_PIN();
-        MODA_NOP(7);  // register writes settle before the next MFMA
-        const float mc = m_run * c2;
-        static_for<8>([&](auto Q) { exp_pair<decltype(Q)::value>(cur, pcur, mc, l_run, c2); });
-      } else {
-        const float mc = m_run * c2;
-        pv_phase<C, VS_PREV, KS_NEXT, HEAD, NFV, 2>(pprev, cur, pcur, mc, l_run, mx, c2, fb, before_k);
-      }
-      // (for this wave's last tile the next K tile is not needed; it is read and
-      //  multiplied all the same, which keeps the loop body free of branches)
-    } else if (kt == wave_last + 1) {
-      // this wave's last tile: only its P V is left (the K fragments it requests are never used)
-      pv_phase<C, VS_PREV, KS_NEXT, 0, NFV, 0>(pprev, cur, pcur, 0.f, l_run, mx, c2, fb, before_k);
-      clear(pcur);
-    } else {
-      clear(pcur);
-      if constexpr (kEarlySync) sync_copies();
-    }
-
-    // Every step issues the same number of copies (tiles past the end of the tensor are
-    // out of range of the raw buffer: nothing is fetched), so "all but the newest
-    // kPending copies have landed" always means: K tile kt+1 and V tile kt, which are
-    // read next, are complete (with 4 stages K tile kt+2 too: one step of slack).
-    // The stages written are those of K tile kt (its scores were taken in step kt-1) and,
-    // with 4 stages, of V tile kt-2, with 2 stages of V tile kt-1 (consumed in the first
-    // half of this step): every wave is past those reads once it has passed the barrier.
-    const int kt_k = kt + kStages;  // the V tile of this step is kt + kVAhead
+    const float mc = m_run * c2;
+    pv_phase<C, VS_PREV, KS_NEXT, false>(pprev, cur, pcur, w, mc, c2, fb, before_k);
+    if constexpr (!kEarlySync) sync_copies();
+    // this step's copies ride along, spread evenly over the MFMAs of the phase; the V tile is kt + kVAhead
+    // (for this wave's last tile the next K tile is not needed; it is read and
+    //  multiplied all the same, which keeps the loop body free of branches)
     constexpr auto so_k = k_stage_off(std::integral_constant<int, S % kStages>{});
     constexpr auto so_v = v_stage_off(std::integral_constant<int, (S + C::kVAhead) % kStages>{});
-    if constexpr (!kEarlySync) sync_copies();
-    // every wave is past the reads of the stages that this step's copies overwrite
-    if (kt < nt && kt > wave_last) {
-      issue_tile(kIsK, so_k, k_buf, kt_k);
-      issue_tile(kIsV, so_v, v_buf, kt_k);
-    }
-
-    if (kt <= wave_last) {
-      const float mc = m_run * c2;
-      // this step's copies ride along, spread evenly over the MFMAs of the phase
-      auto hook = [&](auto M) {
-        constexpr int m = decltype(M)::value;
-        constexpr int every = C::kNFK / (2 * C::kInstPerWave) >= 4 ? 4 : C::kNFK / (2 * C::kInstPerWave);
-        static_assert(every >= 1, "at most one copy per MFMA");
-        if constexpr (m % every == every / 2 && m / every < 2 * C::kInstPerWave) {
-          constexpr int i = m / every;
-          if constexpr (i < C::kInstPerWave)
-            issue_one(kIsK, std::integral_constant<int, i>{}, so_k, k_buf, kt_k);
-          else
-            issue_one(kIsV, std::integral_constant<int, (i < C::kInstPerWave ? 0 : i - C::kInstPerWave)>{}, so_v,
-                      v_buf, kt_k);
-        }
-      };
-      qk_phase<C, KS_NEXT, VS_CUR, true>(nxt, cur, pcur, mc, l_run, c2, fb, hook);
-      if (kt + 1 == wave_last && needs_mask(kt + 1)) {
-        MODA_PIN();
-        MODA_NOP(15);
-        mask_tile(nxt, kt + 1);
+    auto hook = [&](auto M) {
+      constexpr int m = decltype(M)::value;
+      constexpr int every = C::kNFK / (2 * C::kInstPerWave) >= 4 ? 4 : C::kNFK / (2 * C::kInstPerWave);
+      static_assert(every >= 1, "at most one copy per MFMA");
+      if constexpr (m % every == every / 2 && m / every < 2 * C::kInstPerWave) {
+        constexpr int i = m / every;
+        if constexpr (i < C::kInstPerWave)
+          issue_one(kIsK, std::integral_constant<int, i>{}, so_k, k_buf, kt + kStages);
+        else
+          issue_one(kIsV, std::integral_constant<int, (i < C::kInstPerWave ? 0 : i - C::kInstPerWave)>{}, so_v,
+                    v_buf, kt + kStages);
       }
-    } else {
-      clear(nxt);
+    };
+    qk_phase<C, KS_NEXT, VS_CUR, true>(nxt, cur, pcur, w, mc, c2, fb, hook);
+    if (__builtin_amdgcn_ballot_w64(!(w.sum <= 256.f)) != 0) {
+      // Rare path.  (The products of the tiles before have long retired.)
+      MODA_PIN();
+      MODA_NOP(15);
+      const float m_new = fmaxf(m_run, tile_max(cur));
+      const float alpha = m_new == m_run ? 1.0f : fast_exp2((m_run - m_new) * c2);
+      m_run = m_new;
+      l_run *= alpha;
+      static_for<C::kDBlocks * 16>([&](auto R) { scale_acc<kAccO + decltype(R)::value>(alpha); });
+      MODA_PIN();
+      MODA_NOP(7);  // register writes settle before the next MFMA
+      weigh_tile(cur, pcur, w, m_new * c2, c2);
+    }
+    l_run += w.sum;
+    if (kt + 1 == wave_last && needs_mask(kt + 1)) {
+      MODA_PIN();
+      MODA_NOP(15);
+      mask_tile(nxt, kt + 1);
     }
   };
   static_assert(kUnroll == 4, "the four steps below");
-  for (int kt = 0; kt <= nt; kt += 4) {
+  // (One exit, and the remainder as branches one after the other: an exit after each of the four
+  // steps made the compiler merge all of them, with registers it does not have.)
+  int kt = 0;
+  for (; kt + 3 <= wave_last; kt += 4) {
     step(std::integral_constant<int, 0>{}, kt, sA, sB, pA, pB);
-    if (kt + 1 <= nt) step(std::integral_constant<int, 1>{}, kt + 1, sB, sA, pB, pA);
-    if (kt + 2 <= nt) step(std::integral_constant<int, 2>{}, kt + 2, sA, sB, pA, pB);
-    if (kt + 3 <= nt) step(std::integral_constant<int, 3>{}, kt + 3, sB, sA, pB, pA);
+    step(std::integral_constant<int, 1>{}, kt + 1, sB, sA, pB, pA);
+    step(std::integral_constant<int, 2>{}, kt + 2, sA, sB, pA, pB);
+    step(std::integral_constant<int, 3>{}, kt + 3, sB, sA, pB, pA);
+  }
+  if (kt <= wave_last) {
+    step(std::integral_constant<int, 0>{}, kt, sA, sB, pA, pB);
+  } else {
+    clear(sB);
+    clear(pB);
+  }
+  if (kt + 1 <= wave_last) step(std::integral_constant<int, 1>{}, kt + 1, sB, sA, pB, pA);
+  if (kt + 2 <= wave_last) step(std::integral_constant<int, 2>{}, kt + 2, sA, sB, pA, pB);
+  // The products of the wave's last tile, whose P is in pB if an odd number of steps remained.
+  if (((wave_last + 1) & 1) != 0) pA = pB;
+  {
+    const int off = (wave_last % kStages) * C::kVTileBytes;
+    FragBase<C> at = fb;
+#pragma unroll
+    for (int db = 0; db < C::kDBlocks; ++db) at.v[db] += off;
+    pv_phase<C, 0, 0, true>(pA, sA, pB, w, 0.f, c2, at);
+  }
+  // (the score tiles are declared used only here: the last one, which nobody reads, is written while the
+  // instructions above are issued, and nothing else may be put into its registers)
+  asm volatile("" : : "v"(sA.a[0]), "v"(sA.a[1]), "v"(sB.a[0]), "v"(sB.a[1]));
+  // the steps in which this wave only helps copy the tiles that the other waves still need
+  for (kt = wave_last + 1; kt < nt; ++kt) {
+    sync_copies();
+    const int off_k = (kt % kStages) * C::kKTileBytes, off_v = ((kt + C::kVAhead) % kStages) * C::kVTileBytes;
+    static_for<C::kInstPerWave>([&](auto I) {
+      issue_one(kIsK, I, std::integral_constant<int, 0>{}, k_buf, kt + kStages, off_k);
+      issue_one(kIsV, I, std::integral_constant<int, C::kVBase>{}, v_buf, kt + kStages, off_v);
+    });
   }
   MODA_PIN();
   MODA_NOP(15);          // accumulators final before they are read out
   lds_wait<0>();         // fragment reads requested but never used have landed
   wait_copies_but<0>();  // the ring is reused below: no copy may still be landing in it
+  if (pair_sum(l_run) == 0.f) m_run = -INFINITY;  // (no weight so far: any reference may follow)
   __syncthreads();
   if (L > 0 && !depth_first && depth_on_mfma) {
     depth_blocks();

@@ -1,0 +1,57 @@
+"""GPU parity: bf16 forward kernel (through the C ABI) where the reference of the exponentials, which the
+key loop takes from the tiles before, is far too low for a tile: scores that jump by hundreds of
+powers of two at single keys (weights formed with the old reference overflow to infinity), in every ring
+stage, in the first, the last and the remaining tiles of a wave; and first tiles whose scores are all
+-inf.  The oracle is the checker's fp64 forward.
+
+Tolerance: one key carries a row, so |O| reaches max|V|: weights and output rounded to bf16, 2 * 2^-8 *
+max|V|.  LSE (up to 1000 in size): the 1e-3 of the task plus four fp32 roundings of its size.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moda_ref as R
+from paper_2603_15619_amd import synth
+
+from test_fwd_parity import run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def check(inp, B, Hq, Hk, T, d, L, causal, tuning, first_row=0):
+    print("case", dict(Hq=Hq, Hk=Hk, T=T, d=d, L=L, causal=causal, tuning=tuning), flush=True)
+    O, LSE = run_gpu(inp, L, causal, None, tuning)
+    with np.errstate(invalid="ignore"):
+        Oref, Lref = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")),
+                           depth_count=L, causal=causal)
+    vmax = max(float(inp[k].abs().max()) for k in (("Vseq", "Vdepth") if L else ("Vseq",)))
+    o, l = synth.to_f64(O)[:, :, first_row:], synth.to_f64(LSE)[:, :, first_row:]
+    Oref, Lref = Oref[:, :, first_row:], Lref[:, :, first_row:]
+    assert np.isfinite(o).all() and np.isfinite(l).all()
+    assert np.abs(o - Oref).max() <= 2 * 2.0 ** -8 * vmax
+    assert (np.abs(l - Lref) <= 1e-3 + 4 * 2.0 ** -24 * np.abs(Lref)).all()
+
+
+@pytest.mark.parametrize("waves", [4, 8])
+@pytest.mark.parametrize("Hk,T,d,L,causal", [(4, 580, 64, 0, True), (4, 711, 128, 3, True), (2, 650, 64, 6, True),
+                                             (2, 523, 128, 0, False), (4, 390, 64, 5, False), (1, 777, 128, 2, True)])
+def test_scores_that_jump(waves, Hk, T, d, L, causal):
+    B, Hq = 2, 4
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=900 + T, device="cuda")
+    for pos, factor in ((0, 8.0), (40, 30.0), (63, 60.0), (70, 200.0), (130, 250.0), (200, 300.0), (290, 350.0),
+                        (350, 20.0), (T - 1, 400.0)):
+        inp["Kseq"][:, :, pos] *= factor
+    check(inp, B, Hq, Hk, T, d, L, causal, dict(waves=waves))
+
+
+@pytest.mark.parametrize("waves", [4, 8])
+@pytest.mark.parametrize("T,d,L", [(300, 64, 0), (450, 128, 0), (330, 128, 4)])
+def test_first_tiles_of_minus_infinity(waves, T, d, L):
+    """70 keys (the first tile and a few more) of score -inf: rows that see others are as if those keys were not
+    there.  (Without depth slots the first rows see nothing else: their softmax is not defined.)"""
+    B, Hq, Hk, blocked = 2, 2, 2, 70
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=950 + T, device="cuda")
+    inp["Q"][..., 0] = inp["Q"][..., 0].abs() + 0.25
+    inp["Kseq"][:, :, :blocked, 0] = -float("inf")
+    check(inp, B, Hq, Hk, T, d, L, True, dict(waves=waves), first_row=0 if L else blocked)
