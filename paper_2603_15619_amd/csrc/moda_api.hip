@@ -321,7 +321,7 @@ moda_status moda_attn_bwd(const void* Q, const void* Kseq, const void* Vseq, con
   p.Q = Q; p.Kseq = Kseq; p.Vseq = Vseq; p.Kdepth = Kdepth; p.Vdepth = Vdepth;
   p.O = O; p.LSE = LSE; p.dO = dO;
   p.dQ = dQ; p.dKseq = dKseq; p.dVseq = dVseq; p.dKdepth = dKdepth; p.dVdepth = dVdepth;
-  p.rowstat = static_cast<float*>(workspace);
+  p.lse2 = static_cast<float*>(workspace);
   p.causal = s->causal;
   p.scale = resolve_scale(s);
   p.scale_log2 = p.scale * 1.4426950408889634f;

@@ -8,7 +8,7 @@
 //   dQ_t = scale sum_c e_c k_c,  dK_c += scale e_c q_t.
 // Three kernels (four where the depth slots of a group have one of their own, see the end), no
 // atomics, every output element written exactly once:
-//   delta  : (LSE_t log2(e), delta_t) for every row (row-parallel, vector ALUs).
+//   delta  : LSE_t log2(e) and -delta_t for every row (row-parallel, vector ALUs).
 //   dkdv   : one workgroup per 128 sequence keys; Q / dO tiles stream through LDS;
 //            S = Q K^T and dP = dO V^T are recomputed per 32x32 block on the MFMA
 //            pipe, P and dS = P (dP - delta) are packed to bf16 straight out of the
@@ -40,12 +40,16 @@ namespace moda {
 constexpr float kLog2e = 1.4426950408889634f;
 
 // ---------------------------------------------------------------- per-row scalars
-// rowstat[row] = (LSE_row * log2(e), delta_row = <dO_row, O_row>), interleaved, for the other
-// kernels (they exponentiate with exp2; the pairs of a query tile are one contiguous block
-// that is copied to LDS without passing through registers).
+// lse2[row] = LSE_row * log2(e) and minus_delta[row] = -<dO_row, O_row> for the other kernels: they
+// exponentiate with exp2, and start the accumulators of dP = dO V^T from -delta, so that dP - delta
+// comes out of the matrix pipe (a query tile's values are copied to LDS without passing through
+// registers and read from there as accumulators).  The matrix kernels below are bound by power (on all-zero
+// inputs they take the same cycles at 2.3 GHz instead of 1.5 to 1.7): a subtraction less per weight, one
+// vector instruction in four, let the clock rise.  d = 64, B=1 Hq=64 Hk=8 T=16384: dK/dV 4.49 -> 4.25 ms, dQ
+// 3.04 -> 2.93; d = 128, B=8 H=16 T=4096 without slots: whole call 1.87 -> 1.81 ms.
 template <int D>
 __global__ __launch_bounds__(256) void moda_bwd_delta_kernel(const void* dO, const void* O, const float* LSE,
-                                                             float* rowstat, long long rows) {
+                                                             float* lse2, float* minus_delta, long long rows) {
   constexpr int LPR = D / 8;  // lanes per row, 8 channels each
   const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / LPR;
   const int l = threadIdx.x % LPR;
@@ -56,7 +60,10 @@ __global__ __launch_bounds__(256) void moda_bwd_delta_kernel(const void* dO, con
 #pragma unroll
   for (int k = 0; k < 4; ++k) s = dot2_bf16(a[k], b[k], s);
   s = group_sum<LPR>(s);
-  if (l == 0 && row < rows) *(f32x2*)(rowstat + 2 * row) = (f32x2){LSE[row] * kLog2e, s};
+  if (l == 0 && row < rows) {
+    lse2[row] = LSE[row] * kLog2e;
+    minus_delta[row] = -s;
+  }
 }
 
 template <int D, int NW = 4>
@@ -65,7 +72,7 @@ struct BwdCfg {
   static constexpr int kXWave = 32 * kXRow;       // 32 rows per wave
   static constexpr int kXBytes = NW * kXWave;
   static constexpr int kStageBytes = 2 * Tile<D>::kBytes;  // two tiles per stage
-  static constexpr int kAux = 2 * 2 * 64 * 4;     // per stage: (lse2, delta) of 64 queries (dkdv only)
+  static constexpr int kAux = 2 * 2 * 64 * 4;     // per stage: lse2, then -delta of 64 queries (dkdv only)
   static constexpr int kRing = 2 * kStageBytes;
   static constexpr int kLds = (kRing > kXBytes ? kRing : kXBytes) + kAux;
 };
@@ -96,7 +103,8 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
   const float c2 = p.scale_log2;
   const char* Qb = (const char*)p.Q + (size_t)bh * T * Tl::kRowBytes;
   const char* dOb = (const char*)p.dO + (size_t)bh * T * Tl::kRowBytes;
-  const float* statb = p.rowstat + (size_t)bh * T * 2;
+  const float* lseb = p.lse2 + (size_t)bh * T;
+  const float* deltab = p.minus_delta + (size_t)bh * T;
   const int rg = lane / LPR, l16 = lane % LPR;
   const size_t drow = (size_t)La * Tl::kRowBytes;
   // (this phase only runs when every key/value head serves one query head: bg == bh)
@@ -120,7 +128,7 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
 
   struct Item {
     u32x4 q, g;   // the row's Q and dO channels of this lane
-    float l2, dl;  // LSE * log2(e), delta
+    float l2, md;  // LSE * log2(e), -delta
     u32x4 k[kChunk], v[kChunk];
   };
   float acc[8];
@@ -155,9 +163,8 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
     const int tc = min(qw0 + it * RPS + rg, T - 1);  // rows past the end use row T-1; nothing of them is stored
     b.q = *(const u32x4*)(Qb + (size_t)tc * Tl::kRowBytes + l16 * 16);
     b.g = *(const u32x4*)(dOb + (size_t)tc * Tl::kRowBytes + l16 * 16);
-    const f32x2 st = *(const f32x2*)(statb + 2 * tc);
-    b.l2 = st[0];
-    b.dl = st[1];
+    b.l2 = lseb[tc];
+    b.md = deltab[tc];
     const int voff = (int)((unsigned)(tc - rbase) * (unsigned)drow + (unsigned)l16 * 16u);  // 32 positions' slots: far below 4 GiB
     // slots of the chunk past depth_count re-read the last attended slot (a cache hit, ignored)
 #pragma unroll
@@ -196,7 +203,7 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
         sdot = group_sum<LPR>(sdot);
         gdot = group_sum<LPR>(gdot);
         pe[i] = fast_exp2(sdot * c2 - b.l2);
-        e[i] = pe[i] * (gdot - b.dl);
+        e[i] = pe[i] * (gdot + b.md);
       }
 #pragma unroll
       for (int i = 0; i < kChunk; ++i) {
@@ -236,7 +243,7 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
         }
       } else {
         const float pe = fast_exp2(sdot * c2 - b.l2);
-        const float e = pe * (gdot - b.dl);
+        const float e = pe * (gdot + b.md);
         const float es = e * p.scale;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -324,15 +331,14 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
   const int bh0 = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G;
   const float c2 = p.scale_log2;
   u32x4 q[GT], g[GT];
-  float l2[GT], dl[GT], dq[GT][8];
+  float l2[GT], md[GT], dq[GT][8];
 #pragma unroll
   for (int j = 0; j < GT; ++j) {
     const int bh = bh0 + min(j, G - 1);  // heads past the group repeat the last one with weight zero
     q[j] = *(const u32x4*)((const char*)p.Q + ((size_t)bh * T + t) * RB + l16 * 16);
     g[j] = *(const u32x4*)((const char*)p.dO + ((size_t)bh * T + t) * RB + l16 * 16);
-    const f32x2 st = *(const f32x2*)(p.rowstat + ((size_t)bh * T + t) * 2);
-    l2[j] = st[0];
-    dl[j] = st[1];
+    l2[j] = p.lse2[(size_t)bh * T + t];
+    md[j] = p.minus_delta[(size_t)bh * T + t];
 #pragma unroll
     for (int k = 0; k < 8; ++k) dq[j][k] = 0.f;
   }
@@ -379,7 +385,7 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
       sdot = group_sum<LPR>(sdot);
       gdot = group_sum<LPR>(gdot);
       const float pe = j < G ? fast_exp2(sdot * c2 - l2[j]) : 0.f;
-      const float e = pe * (gdot - dl[j]);
+      const float e = pe * (gdot + md[j]);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         av[2 * k] += pe * bf16_lo(g[j][k]);
@@ -519,7 +525,8 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
       qn[q] = *(const u32x4*)((const char*)p.Q + off);
       gn[q] = *(const u32x4*)((const char*)p.dO + off);
     }
-    sn = *(const f32x2*)(p.rowstat + ((size_t)(bh0 + min(l32, G - 1)) * T + t) * 2);
+    const size_t row = (size_t)(bh0 + min(l32, G - 1)) * T + t;
+    sn = (f32x2){p.lse2[row], p.minus_delta[row]};
   };
   if (nch > 0) {
     issue_q(0);
@@ -537,7 +544,7 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
     for (int cb = 0; cb < Tl::kDBlocks; ++cb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dqa[cb][i] = 0.f;
-    float lse2 = INFINITY, delta = 0.f, l4[4], d4[4];
+    float lse2 = INFINITY, m_delta = 0.f, l4[4], d4[4];  // d4, m_delta: -delta
     if (nch > 0) {
 #pragma unroll
       for (int q = 0; q < kQInst; ++q) {
@@ -545,11 +552,11 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
         *lds_at(g_tile + q * 1024 + lane * 16) = gn[q];
       }
       lse2 = l32 < G ? sn[0] : INFINITY;
-      delta = sn[1];
+      m_delta = sn[1];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {  // heads 4 hi + r
         l4[r] = __shfl(lse2, hi * 4 + r, 64);
-        d4[r] = __shfl(delta, hi * 4 + r, 64);
+        d4[r] = __shfl(m_delta, hi * 4 + r, 64);
       }
       issue_q(min(pos + 1, n_pos - 1));
     }
@@ -579,7 +586,7 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
         for (int i = 0; i < 16; ++i) {
           const int slot = c0 + (i >> 2) * 8 + hi * 4 + (i & 3);
           const float pe = slot < L ? fast_exp2(s[i] * c2 - lse2) : 0.f;
-          ev[i] = pe * (dp[i] - delta);
+          ev[i] = pe * (dp[i] + m_delta);
         }
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
@@ -623,7 +630,7 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
             pv[u] = live ? fast_exp2(s[r + u] * c2 - l4[r + u]) : 0.f;
-            ev[u] = pv[u] * (dp[r + u] - d4[r + u]);
+            ev[u] = pv[u] * (dp[r + u] + d4[r + u]);
           }
           uint32_t part[3];
           split2(pv[0], pv[1], part);
@@ -784,17 +791,12 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
     const i32x4 do_buf = make_tile_buffer((const char*)p.dO + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
     ld.issue(q_buf, qt * 64, smem_addr + stage * C::kStageBytes);
     ld.issue(do_buf, qt * 64, smem_addr + stage * C::kStageBytes + Tl::kBytes);
-    // (lse2, delta) of the tile's 64 queries: 512 contiguous bytes, copied like the tiles (no
+    // lse2 and -delta of the tile's 64 queries: 256 contiguous bytes each, copied like the tiles (no
     // load whose result a wave would have to wait for while the tile copies are in flight:
-    // memory operations complete in order); waves 0 and 1 copy 256 bytes each
+    // memory operations complete in order) by waves 0 and 1
     if (wave < 2) {
-      const i32x4 st_buf = make_tile_buffer(p.rowstat + (size_t)bh * T * 2, (unsigned)T * 8);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-                   :
-                   : "s"(__builtin_amdgcn_readfirstlane((int)(smem_addr + (unsigned)(C::kLds - C::kAux) +
-                                                               stage * 512 + wave * 256))),
-                     "v"(lane * 4), "s"(st_buf), "s"(__builtin_amdgcn_readfirstlane(qt * 512 + wave * 256))
-                   : "memory");
+      const i32x4 st_buf = make_tile_buffer((wave == 0 ? p.lse2 : p.minus_delta) + (size_t)bh * T, (unsigned)T * 4);
+      copy4(st_buf, lane * 4, qt * 256, smem_addr + (unsigned)(C::kLds - C::kAux) + stage * 512 + wave * 256);
     }
   };
 
@@ -811,7 +813,18 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
     // per-lane fragment bases inside this stage (Q tile; the dO tile sits Tl::kBytes after it)
     const unsigned qtile = smem_addr + stage * C::kStageBytes;
     const unsigned b_row = fa.row + qtile, b_tr = fa.tr + qtile, b_tr8 = fa.tr8 + qtile;
-    const float* stat_s = aux + stage * 128;  // (lse2, delta) pairs of the tile's queries
+    const float* lse_s = aux + stage * 128;  // of the tile's queries
+    const float* delta_s = lse_s + 64;       // (-delta)
+    // -delta of the lane's queries of a 32-query block, in the order of the accumulators
+    auto minus_delta = [&](int qb) {
+      f32x16 r;
+#pragma unroll
+      for (int b4 = 0; b4 < 4; ++b4) {
+        const f32x4 x = *(const f32x4*)(delta_s + qb * 32 + b4 * 8 + hi * 4);
+        r[4 * b4] = x[0]; r[4 * b4 + 1] = x[1]; r[4 * b4 + 2] = x[2]; r[4 * b4 + 3] = x[3];
+      }
+      return r;
+    };
 
     const int key = kw0 + l32;
     // all 64 queries exist and (when causal) none precedes any of this wave's 32 keys
@@ -822,7 +835,7 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
       // products), in whose shadow the vector ALUs then work.  The order is pinned step by step.
       // (Matrix and vector time of this kernel used to add up: 45 % matrix-pipe busy.  B=1 Hq=64 Hk=8
       // T=16384: 4.74 ms one block at a time; 4.61 so; 4.39 with the wave priority below, 1.0 PFLOP/s.)
-      f32x16 s[2], dp[2];
+      f32x16 s[2], dp[2];        // S, dP - delta
       u32x4 pb[2][2], ds[2][2];  // P and dS packed to bf16: [block][16-query half]
       auto mask = [&](int qb) {  // (a uniform branch around the comparisons, as below)
         if (!all_visible) {
@@ -834,22 +847,16 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
           }
         }
       };
-      // (LSE log2 e, delta) of the lane's queries 4 b4 .. + 3 of a block
-      f32x4 stat[2];
-      auto read_stat = [&](int qb, int b4) {
-        const float* st4 = stat_s + (qb * 32 + b4 * 8 + hi * 4) * 2;
-        stat[0] = *(const f32x4*)st4;
-        stat[1] = *(const f32x4*)(st4 + 4);
-      };
+      // LSE log2 e of the lane's queries 4 b4 .. + 3 of a block
+      f32x4 l4;
+      auto read_stat = [&](int qb, int b4) { l4 = *(const f32x4*)(lse_s + qb * 32 + b4 * 8 + hi * 4); };
       // ... and their P and dS
       auto weights = [&](int qb, int b4) {
-        const float l4[4] = {stat[0][0], stat[0][2], stat[1][0], stat[1][2]};
-        const float d4[4] = {stat[0][1], stat[0][3], stat[1][1], stat[1][3]};
         float pv[4], dsv[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           pv[r] = fast_exp2(s[qb][b4 * 4 + r] * c2 - l4[r]);
-          dsv[r] = pv[r] * (dp[qb][b4 * 4 + r] - d4[r]);
+          dsv[r] = pv[r] * dp[qb][b4 * 4 + r];
         }
         uint32_t o[4] = {pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]), pack_bf16(dsv[0], dsv[1]),
                          pack_bf16(dsv[2], dsv[3])};
@@ -877,10 +884,12 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
           fg[n % 3] = fa.tr_frag(x0, x8, ks, Tl::kBytes);
         }
       };
+      dp[0] = minus_delta(0);
       read_frags(0);
       read_frags(1);
 #pragma unroll
       for (int n = 0; n < 16; ++n) {
+        if (n == 2) dp[1] = minus_delta(1);
         // (the wave whose instructions fill both pipes goes first; the other wave of the SIMD takes
         // what is left)
         if (n == 4) __builtin_amdgcn_s_setprio(1);
@@ -890,7 +899,7 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
           const int qb = n >> 2, st = n & 3;
           if (st == 0)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[qb][i] = dp[qb][i] = 0.f;
+            for (int i = 0; i < 16; ++i) s[qb][i] = 0.f;
           s[qb] = mfma_bf16(fq[n % 3], kf[st], s[qb]);
           dp[qb] = mfma_bf16(fg[n % 3], vf[st], dp[qb]);
         } else {
@@ -909,9 +918,9 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
       // 16 queries, then dV^T += dO^T P and dK^T += Q^T dS over those 32 queries
   #pragma unroll
       for (int qb = 0; qb < 2; ++qb) {
-        f32x16 s, dp;
+        f32x16 s, dp = minus_delta(qb);
   #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
   #pragma unroll
         for (int st = 0; st < Tl::kDSteps; ++st) {
           const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
@@ -947,16 +956,13 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   #pragma unroll
           for (int b2 = 0; b2 < 2; ++b2) {
             const int b4 = hf * 2 + b2;
-            const float* st4 = stat_s + (qb * 32 + b4 * 8 + hi * 4) * 2;
-            const f32x4 ld01 = *(const f32x4*)st4, ld23 = *(const f32x4*)(st4 + 4);
-            const float l4[4] = {ld01[0], ld01[2], ld23[0], ld23[2]};
-            const float d4[4] = {ld01[1], ld01[3], ld23[1], ld23[3]};
+            const f32x4 l4 = *(const f32x4*)(lse_s + qb * 32 + b4 * 8 + hi * 4);
   #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const int i = b4 * 4 + r;
               const float pe = fast_exp2(s[i] * c2 - l4[r]);
               pv[b2 * 4 + r] = pe;
-              dsv[b2 * 4 + r] = pe * (dp[i] - d4[r]);
+              dsv[b2 * 4 + r] = pe * dp[i];
             }
           }
           const bf16x8 pb = pack8(pv), dsb = pack8(dsv);
@@ -1026,7 +1032,7 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
 template <int D>
 struct BwdShortCfg {
   static constexpr int kTile = 32 * D * 2;               // 32 rows of Q or dO
-  static constexpr int kStage = 2 * kTile + 32 * 8;      // Q, dO, (LSE log2 e, delta)
+  static constexpr int kStage = 2 * kTile + 64 * 8;      // Q, dO, LSE log2 e, -delta (of 64 rows, 32 of them used)
   static constexpr int kPieces = kTile / 1024;           // copy instructions per tile
   static constexpr int kXRow = D + 4;                    // floats per row of the exchange buffer
   static constexpr int kXWave = 32 * kXRow;
@@ -1092,18 +1098,16 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     const unsigned dst = ring + stage * C::kStage;
     const i32x4 q_buf = make_tile_buffer((const char*)p.Q + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
     const i32x4 do_buf = make_tile_buffer((const char*)p.dO + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
-    const i32x4 st_buf = make_tile_buffer(p.rowstat + (size_t)bh * T * 2, (unsigned)T * 8);
+    const i32x4 l_buf = make_tile_buffer(p.lse2 + (size_t)bh * T, (unsigned)T * 4);
+    const i32x4 d_buf = make_tile_buffer(p.minus_delta + (size_t)bh * T, (unsigned)T * 4);
 #pragma unroll
     for (int q = 0; q < C::kPieces; ++q) {
       const int voff = xor_here(goff, Ld::piece_xor(q));
       tile_copy16(q_buf, voff, qt * C::kTile + q * 1024, dst + q * 1024);
       tile_copy16(do_buf, voff, qt * C::kTile + q * 1024, dst + C::kTile + q * 1024);
     }
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-                 :
-                 : "s"(__builtin_amdgcn_readfirstlane((int)(dst + 2 * C::kTile))), "v"(lane * 4), "s"(st_buf),
-                   "s"(__builtin_amdgcn_readfirstlane(qt * 256))
-                 : "memory");
+    copy4(l_buf, lane * 4, qt * 128, dst + 2 * C::kTile);
+    copy4(d_buf, lane * 4, qt * 128, dst + 2 * C::kTile + 256);
   };
   if (wave < n_items) issue(wave, 0);
   int stage = 0;
@@ -1116,10 +1120,17 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     const int q0 = (qt0 + item % span) * 32;
     const unsigned qtile = ring + stage * C::kStage;
     const unsigned b_row = fa.row + qtile, b_tr = fa.tr + qtile, b_tr8 = fa.tr8 + qtile;
-    const float* stat_s = (const float*)(smem + (qtile - (unsigned)(size_t)(lds_ptr)smem) + 2 * C::kTile);
-    f32x16 s, dp;
+    const float* lse_s = (const float*)(smem + (qtile - (unsigned)(size_t)(lds_ptr)smem) + 2 * C::kTile);
+    f32x16 s, dp;  // S, dP - delta
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+    for (int b4 = 0; b4 < 4; ++b4) {
+      const f32x4 x = *(const f32x4*)(lse_s + 64 + b4 * 8 + hi * 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[4 * b4 + r] = 0.f;
+        dp[4 * b4 + r] = x[r];
+      }
+    }
 #pragma unroll
     for (int st = 0; st < Tl::kDSteps; ++st) {
       const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
@@ -1140,16 +1151,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) {
         const int b4 = hf * 2 + b2;
-        const float* st4 = stat_s + (b4 * 8 + hi * 4) * 2;
-        const f32x4 ld01 = *(const f32x4*)st4, ld23 = *(const f32x4*)(st4 + 4);
-        const float l4[4] = {ld01[0], ld01[2], ld23[0], ld23[2]};
-        const float d4[4] = {ld01[1], ld01[3], ld23[1], ld23[3]};
+        const f32x4 l4 = *(const f32x4*)(lse_s + b4 * 8 + hi * 4);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int i = b4 * 4 + r;
           const float pe = fast_exp2(s[i] * c2 - l4[r]);
           pv[b2 * 4 + r] = pe;
-          dsv[b2 * 4 + r] = pe * (dp[i] - d4[r]);
+          dsv[b2 * 4 + r] = pe * dp[i];
         }
       }
       const bf16x8 pb = pack8(pv), dsb = pack8(dsv);
@@ -1227,7 +1235,6 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
   const char* Kb = (const char*)p.Kseq + (size_t)bg * T * Tl::kRowBytes;
   const char* Vb = (const char*)p.Vseq + (size_t)bg * T * Tl::kRowBytes;
   const char* dOb = (const char*)p.dO + (size_t)bh * T * Tl::kRowBytes;
-  const float* statb = p.rowstat + (size_t)bh * T * 2;  // (LSE * log2(e), delta) per row
 
   const int qi = qw0 + l32;
   const int qrow = min(qi, T - 1);
@@ -1265,8 +1272,10 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
     qf[st] = *(const bf16x8*)(Qb + (size_t)qrow * Tl::kRowBytes + st * 32 + hi * 16);
     dof[st] = *(const bf16x8*)(dOb + (size_t)qrow * Tl::kRowBytes + st * 32 + hi * 16);
   }
-  const f32x2 stat = *(const f32x2*)(statb + 2 * qrow);
-  const float lse2 = stat[0], delta = stat[1];
+  const float lse2 = p.lse2[(size_t)bh * T + qrow], md = p.minus_delta[(size_t)bh * T + qrow];
+  f32x16 minus_delta;  // dP - delta comes out of the matrix pipe: its accumulators start from here
+#pragma unroll
+  for (int i = 0; i < 16; ++i) minus_delta[i] = md;
 
   const int n_keys = p.causal ? min(T, q0 + kQT) : T;
   const int nt = (n_keys + 63) / 64;
@@ -1290,7 +1299,7 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
     const unsigned ktile = smem_addr + stage * C::kStageBytes;
     const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
 
-    f32x16 s[2], dp[2];  // S^T, dP^T: [key block]; a lane holds 16 keys of its query
+    f32x16 s[2], dp[2];  // S^T, dP^T - delta: [key block]; a lane holds 16 keys of its query
     u32x4 ds[2][2];      // dS^T packed to bf16: [key block][16-key half]
     const int k0 = kt * 64;
     // every key of the tile exists and is visible to every query of the wave
@@ -1308,7 +1317,7 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
       float a[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        a[r] = fast_exp2(s[kb][b4 * 4 + r] * c2 - lse2) * (dp[kb][b4 * 4 + r] - delta);
+        a[r] = fast_exp2(s[kb][b4 * 4 + r] * c2 - lse2) * dp[kb][b4 * 4 + r];
       uint32_t o[2] = {pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])};
       asm volatile("" : "+v"(o[0]), "+v"(o[1]));  // (used here: else the computation sinks to its products)
       ds[kb][b4 >> 1][(b4 & 1) * 2] = o[0];
@@ -1345,9 +1354,9 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
         const int kb = n / NS, st = n % NS;
         if (st == 0)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s[kb][i] = dp[kb][i] = 0.f;
+          for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
         s[kb] = mfma_bf16(fk[n % kBuf], qf[st], s[kb]);
-        dp[kb] = mfma_bf16(fv[n % kBuf], dof[st], dp[kb]);
+        dp[kb] = mfma_bf16(fv[n % kBuf], dof[st], st == 0 ? minus_delta : dp[kb]);
         if (kb == 1 && st % (NS / 4) == 0) weights(0, st / (NS / 4));
       } else {
         const int m = n - 2 * NS, ks = m / Tl::kDBlocks, db = m % Tl::kDBlocks;
@@ -1461,8 +1470,10 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
       dof[st] = *(const bf16x8*)((const char*)p.dO + row + st * 32);
     }
   }
-  const f32x2 stat = *(const f32x2*)(p.rowstat + ((size_t)bh * T + qrow) * 2);
-  const float lse2 = stat[0], delta = stat[1];
+  const float lse2 = p.lse2[(size_t)bh * T + qrow], md = p.minus_delta[(size_t)bh * T + qrow];
+  f32x16 minus_delta;  // (as above)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) minus_delta[i] = md;
   const int lim = p.causal ? qrow : T - 1;  // last visible key of this lane's query
   f32x16 dq[Tl::kDBlocks];
 #pragma unroll
@@ -1473,9 +1484,9 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
   const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
   for (int kt = wave; kt < nt; kt += 4) {
     wait_own_copies<0>();
-    f32x16 s, dp;
+    f32x16 s, dp = minus_delta;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
     for (int st = 0; st < Tl::kDSteps; ++st) {
       const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
@@ -1492,7 +1503,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
     }
     float ds[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) ds[i] = fast_exp2(s[i] * c2 - lse2) * (dp[i] - delta);
+    for (int i = 0; i < 16; ++i) ds[i] = fast_exp2(s[i] * c2 - lse2) * dp[i];
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
       float a[8];
@@ -1565,7 +1576,7 @@ __global__ __launch_bounds__(64) void moda_bwd_depth_group_kernel(BwdParams p) {
   constexpr int RB = D * 2;
   constexpr int kRowsPerInst = 1024 / RB;       // rows one copy instruction moves
   constexpr int kInst = 64 / kRowsPerInst;      // copy instructions per tile
-  constexpr int kStatOff = 4 * Tl::kBytes;      // (lse2, delta) per head row, after the four tiles
+  constexpr int kStatOff = 4 * Tl::kBytes;      // (lse2, -delta) per head row, after the four tiles
   __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * Tl::kBytes + 64 * 8];
   const int lane = threadIdx.x, l32 = lane & 31, hi = lane >> 5;
   const int T = p.T, L = p.depth_count, La = p.depth_alloc, G = p.Hq / p.Hk;
@@ -1599,7 +1610,8 @@ __global__ __launch_bounds__(64) void moda_bwd_depth_group_kernel(BwdParams p) {
     // heads past the group get lse2 = +inf: weight zero
     const int h = lane;
     f32x2 st = {INFINITY, 0.f};
-    if (h < G) st = *(const f32x2*)(p.rowstat + ((size_t)(bh0 + h) * T + t) * 2);
+    const size_t row = (size_t)(bh0 + min(h, G - 1)) * T + t;
+    if (h < G) st = (f32x2){p.lse2[row], p.minus_delta[row]};
     *(f32x2*)(stat + 2 * h) = st;
   }
   f32x16 dqa[NG][Tl::kDBlocks];  // dQ^T (depth share): [head block][channel block], lane = head
@@ -1669,7 +1681,7 @@ __global__ __launch_bounds__(64) void moda_bwd_depth_group_kernel(BwdParams p) {
           for (int i = 0; i < 16; ++i) {
             const int slot = c0 + sb * 32 + (i >> 2) * 8 + hi * 4 + (i & 3);
             const float pe = slot < L ? fast_exp2(s[i] * c2 - st_h[0]) : 0.f;
-            ev[i] = pe * (dp[i] - st_h[1]);
+            ev[i] = pe * (dp[i] + st_h[1]);
           }
 #pragma unroll
           for (int hf = 0; hf < 2; ++hf) {
@@ -1711,7 +1723,7 @@ __global__ __launch_bounds__(64) void moda_bwd_depth_group_kernel(BwdParams p) {
                 const int i = b4 * 4 + r;
                 const float pe = live ? fast_exp2(s[i] * c2 - l4[r]) : 0.f;
                 pv[b2 * 4 + r] = pe;
-                evv[b2 * 4 + r] = pe * (dp[i] - d4[r]);
+                evv[b2 * 4 + r] = pe * (dp[i] + d4[r]);  // (d4: -delta)
               }
             }
             const bf16x8 pb = pack8(pv), eb = pack8(evv);
@@ -1763,13 +1775,13 @@ __global__ __launch_bounds__(64) void moda_bwd_depth_group_kernel(BwdParams p) {
 }
 
 // ---------------------------------------------------------------- launchers
-// Workspace: (LSE log2 e, delta) per query row, then - when there are depth slots - the depth
+// Workspace: LSE log2 e, then -delta of every query row, then - when there are depth slots - the depth
 // share of dQ in fp32, [B, Hq, T, d].
-static size_t rowstat_bytes(const BwdParams& p) {
+static size_t row_scalar_bytes(const BwdParams& p) {
   return (((size_t)p.B * p.Hq * p.T * 2 * sizeof(float)) + 255) / 256 * 256;
 }
 size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d) {
-  return rowstat_bytes(p) + (p.depth_alloc > 0 ? (size_t)p.B * p.Hq * p.T * d * sizeof(float) : 0);
+  return row_scalar_bytes(p) + (p.depth_alloc > 0 ? (size_t)p.B * p.Hq * p.T * d * sizeof(float) : 0);
 }
 
 int bwd_bf16_max_group() { return 64; }
@@ -1869,9 +1881,10 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   if (G > bwd_bf16_max_group()) return hipErrorInvalidValue;
   // the group kernel gathers the G heads' rows of a position with 32-bit offsets from the first head
   if (G > 8 && p.depth_alloc > 0 && (unsigned long long)G * p.T * (D * 2) >= 0xffffff00ull) return kGridTooLarge;
-  p.dq_depth = (float*)((char*)p.rowstat + rowstat_bytes(p));
+  p.minus_delta = p.lse2 + rows;
+  p.dq_depth = (float*)((char*)p.lse2 + row_scalar_bytes(p));
   hipError_t e = launch_kernel(moda_bwd_delta_kernel<D>, dim3((unsigned)g_delta), dim3(256), stream, p.dO, p.O, p.LSE,
-                               p.rowstat, rows);
+                               p.lse2, p.minus_delta, rows);
   if (e != hipSuccess) return e;
   if (own_depth_kernel(p, D)) {
     if (G <= 8) {

@@ -53,7 +53,8 @@ struct BwdParams {
   void* dVseq;
   void* dKdepth;
   void* dVdepth;
-  float* rowstat;  // workspace: (LSE_t * log2(e), <dO_t, O_t>) per row, [B, Hq, T, 2]
+  float* lse2;         // workspace: LSE_t * log2(e) per row, [B, Hq, T]
+  float* minus_delta;  // workspace: -<dO_t, O_t> per row, [B, Hq, T]
   float* dq_depth;  // workspace: the depth slots' share of dQ, fp32, not yet scaled, [B, Hq, T, d]
   int B, Hq, Hk, T;
   int depth_alloc, depth_count;

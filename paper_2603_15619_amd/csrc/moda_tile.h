@@ -120,6 +120,14 @@ __device__ __forceinline__ void tile_copy16(const i32x4& rsrc, int voff, int sof
                  "s"(__builtin_amdgcn_readfirstlane(soff))
                : "memory");
 }
+// ... 4 bytes per lane, to lds_addr + 4 i
+__device__ __forceinline__ void copy4(const i32x4& rsrc, int voff, int soff, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)lds_addr)), "v"(voff), "s"(rsrc),
+                 "s"(__builtin_amdgcn_readfirstlane(soff))
+               : "memory");
+}
 __device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // For waves that copy into LDS of their own and need no workgroup barrier.  Between the request of
