@@ -785,28 +785,39 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   FragAddr<D> fa;
   fa.init(lane);
 
-  auto issue = [&](int item, int stage) {
-    const int bh = bh0 + item / span, qt = qt0 + item % span;
-    const i32x4 q_buf = make_tile_buffer((const char*)p.Q + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
-    const i32x4 do_buf = make_tile_buffer((const char*)p.dO + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
-    ld.issue(q_buf, qt * 64, smem_addr + stage * C::kStageBytes);
-    ld.issue(do_buf, qt * 64, smem_addr + stage * C::kStageBytes + Tl::kBytes);
+  // Work items are walked by counters (head, query tile): a division per tile, and the buffers built anew,
+  // were 60 scalar instructions between a tile's barrier and its first copy.
+  i32x4 q_buf, do_buf, st_buf;  // (st_buf: of waves 0 and 1)
+  auto at_head = [&](int h) {
+    const size_t row = (size_t)(bh0 + h) * T;
+    q_buf = make_tile_buffer((const char*)p.Q + row * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+    do_buf = make_tile_buffer((const char*)p.dO + row * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+    st_buf = make_tile_buffer((wave == 0 ? p.lse2 : p.minus_delta) + row, (unsigned)T * 4);
+  };
+  int next_head = 0, next_qt = qt0;
+  auto issue_next = [&](int stage) {
+    ld.issue(q_buf, next_qt * 64, smem_addr + stage * C::kStageBytes);
+    ld.issue(do_buf, next_qt * 64, smem_addr + stage * C::kStageBytes + Tl::kBytes);
     // lse2 and -delta of the tile's 64 queries: 256 contiguous bytes each, copied like the tiles (no
     // load whose result a wave would have to wait for while the tile copies are in flight:
     // memory operations complete in order) by waves 0 and 1
-    if (wave < 2) {
-      const i32x4 st_buf = make_tile_buffer((wave == 0 ? p.lse2 : p.minus_delta) + (size_t)bh * T, (unsigned)T * 4);
-      copy4(st_buf, lane * 4, qt * 256, smem_addr + (unsigned)(C::kLds - C::kAux) + stage * 512 + wave * 256);
+    if (wave < 2) copy4(st_buf, lane * 4, next_qt * 256, smem_addr + (unsigned)(C::kLds - C::kAux) + stage * 512 + wave * 256);
+    if (++next_qt == nq) {
+      next_qt = qt0;
+      if (++next_head < G) at_head(next_head);
     }
   };
 
-  if (n_items > 0) issue(0, 0);
-  for (int item = 0; item < n_items; ++item) {
+  int qt = qt0;  // of the item at hand
+  if (n_items > 0) {
+    at_head(0);
+    issue_next(0);
+  }
+  for (int item = 0; item < n_items; ++item, qt = qt + 1 == nq ? qt0 : qt + 1) {
     const int stage = item & 1;
-    const int qt = qt0 + item % span;
     wait_copies();
     __syncthreads();
-    if (item + 1 < n_items) issue(item + 1, stage ^ 1);
+    if (item + 1 < n_items) issue_next(stage ^ 1);
 
     const int q0 = qt * 64;
     if (p.causal && q0 + 63 < kw0) continue;  // every query of the tile precedes this wave's keys
@@ -1093,13 +1104,26 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
   FragAddr<D> fa;
   fa.init(lane);
   const int goff = (lane / Tl::kChunks) * Tl::kRowBytes + (((lane % Tl::kChunks) ^ Tl::swz(lane / Tl::kChunks)) << 4);
-  auto issue = [&](int item, int stage) {
-    const int bh = bh0 + item / span, qt = qt0 + item % span;
+  // (items are walked by counters, as above: head and query tile, counted from qt0, of the next item to request)
+  int head = 0, pos = wave;
+  i32x4 q_buf, do_buf, l_buf, d_buf;
+  auto at_head = [&]() {
+    const size_t row = (size_t)(bh0 + head) * T;
+    q_buf = make_tile_buffer((const char*)p.Q + row * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+    do_buf = make_tile_buffer((const char*)p.dO + row * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
+    l_buf = make_tile_buffer(p.lse2 + row, (unsigned)T * 4);
+    d_buf = make_tile_buffer(p.minus_delta + row, (unsigned)T * 4);
+  };
+  auto issue_next = [&](int stage) -> int {  // returns the first query of the item
+    if (pos >= span) {
+      do {
+        pos -= span;
+        ++head;
+      } while (pos >= span);
+      at_head();
+    }
+    const int qt = qt0 + pos;
     const unsigned dst = ring + stage * C::kStage;
-    const i32x4 q_buf = make_tile_buffer((const char*)p.Q + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
-    const i32x4 do_buf = make_tile_buffer((const char*)p.dO + (size_t)bh * T * Tl::kRowBytes, (unsigned)T * Tl::kRowBytes);
-    const i32x4 l_buf = make_tile_buffer(p.lse2 + (size_t)bh * T, (unsigned)T * 4);
-    const i32x4 d_buf = make_tile_buffer(p.minus_delta + (size_t)bh * T, (unsigned)T * 4);
 #pragma unroll
     for (int q = 0; q < C::kPieces; ++q) {
       const int voff = xor_here(goff, Ld::piece_xor(q));
@@ -1108,16 +1132,22 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     }
     copy4(l_buf, lane * 4, qt * 128, dst + 2 * C::kTile);
     copy4(d_buf, lane * 4, qt * 128, dst + 2 * C::kTile + 256);
+    pos += 4;
+    return qt * 32;
   };
-  if (wave < n_items) issue(wave, 0);
+  int q_next = 0;
+  if (wave < n_items) {
+    at_head();
+    q_next = issue_next(0);
+  }
   int stage = 0;
   for (int item = wave; item < n_items; item += 4, stage ^= 1) {
     // (the wave's own copies into its own LDS: its wait publishes them, and the stage that the next
     // copies overwrite may be refilled as soon as the wave's reads of it have returned)
     wait_own_copies<0>();
     wait_own_reads();
-    if (item + 4 < n_items) issue(item + 4, stage ^ 1);
-    const int q0 = (qt0 + item % span) * 32;
+    const int q0 = q_next;
+    if (item + 4 < n_items) q_next = issue_next(stage ^ 1);
     const unsigned qtile = ring + stage * C::kStage;
     const unsigned b_row = fa.row + qtile, b_tr = fa.tr + qtile, b_tr8 = fa.tr8 + qtile;
     const float* lse_s = (const float*)(smem + (qtile - (unsigned)(size_t)(lds_ptr)smem) + 2 * C::kTile);
