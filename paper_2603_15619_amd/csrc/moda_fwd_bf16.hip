@@ -702,7 +702,13 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   // depth slots FIRST: half of the units stream, at the full per-unit rate, while the other
   // half computes.  The result does not depend on the order (one softmax over the union).
   // Workgroup ids are dealt round-robin to the 8 dies: the role alternates within a die.
-  const bool depth_first = L > 0 && ((blockIdx.x >> 3) & 1) != 0;
+  // A grid that is resident all at once has no workgroups that follow: there the light half of the tiles
+  // streams first, while the heavy half, which is to end last, computes (alternating / so, us: B=2 H=16 T=1800
+  // d=128, 15 slots 105.8 / 99.5; B=3 H=16 T=1000 d=64, 12 slots 46.9 / 43.2; B=1 H=5 T=6000 d=128, 31
+  // slots 142 / 135; with two rounds and more of workgroups up to 11 % slower: B=4 H=16 T=2000 d=64, 24 slots
+  // 165 / 183).
+  const bool one_round = (int)gridDim.x <= (W == 8 ? 256 : 512);
+  const bool depth_first = L > 0 && (one_round ? 2 * tile_idx >= p.n_qtiles : ((blockIdx.x >> 3) & 1) != 0);
   // Two implementations of the depth slots: on the vector ALUs in the row-major mapping
   // (depth_phase above), or on the matrix pipe as extra key blocks (depth_blocks below).
   const bool depth_on_mfma = p.depth_mfma != 0;
