@@ -46,32 +46,46 @@ moda_status launch_status(hipError_t e) {
   return e == moda::kGridTooLarge ? MODA_ERR_UNSUPPORTED : MODA_ERR_LAUNCH;
 }
 
-// Geometry of the bf16 forward kernel (see moda_fwd_bf16.hip): 8 waves (256 queries) per
-// workgroup, one workgroup per compute unit, unless that grid would leave compute units
-// without work: then 4 waves (128 queries), two workgroups per unit, twice as many
-// workgroups.
-int fwd_waves_per_workgroup(const moda_shape* s) {
-  const long long tiles8 = (long long)s->B * s->Hq * ((s->T + 255) / 256);
-  return tiles8 < 256 ? 4 : 8;
+// Geometry of the bf16 forward kernel (see moda_fwd_bf16.hip): 8 waves (256 (position, head) pairs) per
+// workgroup, one workgroup per compute unit, or 4 waves (128 pairs), two workgroups per unit.  Long
+// sequences in large grids take 8: every K/V tile is copied from the L2 half as often.  4 waves take
+//   - grids that would leave compute units without work;
+//   - sequences of up to 512 pairs, which 8 waves pad to 256, and whose ends weigh more than their copies
+//     (4 / 8 waves, us, one head per tile: d=64 T=100, 4096 tiles of 128: 55 / 109, T=256 2048 tiles 39 / 44,
+//     T=384 4095 tiles 78 / 110; d=128 12 slots T=128, 768 tiles: 127 / 171; T=500 and more tiles 0.88 to 1.02);
+//   - one and a half rounds of workgroups of 8 waves, whose last half round 4 waves spread over all units
+//     (768 tiles: d=64 T=1000 27 / 29, not causal 36 / 40; d=128 12 slots T=2000 not causal 168 / 187, causal
+//     T=1000 138 / 150; causal and longer 0.92 to 1.14: not there).
+int fwd_waves_per_workgroup(const moda_shape* s, int heads_per_tile) {
+  const long long heads = (long long)s->B * s->Hq / heads_per_tile, pairs = (long long)s->T * heads_per_tile;
+  const long long n = heads * ((pairs + 255) / 256);
+  if (n < 256 || pairs <= 512) return 4;
+  return n > 256 && n <= 448 && (!s->causal || s->T <= 1024) ? 4 : 8;
 }
 
 // Calls that take the kernel for few tiles (moda_fwd_short.hip): n = tiles of 128 (position, head)
-// pairs, i.e. the other kernel's workgroups; the short kernel has 4 n, of which the chip holds 512 at
-// d = 128 and, at d = 64, 768 with depth slots of one head per tile and 1024 otherwise.  As long as they
-// fit, it is ahead (other / short kernel, us, whole call):
-//   d=64   one head, slots: n=128 33/18 and (not causal) 61/40, n=192 25/23 and 65/43;  n=256 25/29
-//          otherwise:       n=64 17/10, n=256 19/14 and 26/20, (not causal) 23/22 and 21/22;  n=512 24/25
-//   d=128  n=128 34/25 and 73/53 and (not causal) 68/54;                 n=160 36/41, n=256 38/51
-// A second round of its workgroups only pays when the other kernel's longest tile is long: causal
-// calls with up to twice as many
-//   d=64   one head, slots, n=256: T=4096 59/49;  otherwise, n=512: T=4096 76/65, T=1024 27/27
-//   d=128  n=256: T=16384 248/207, T=4096 77/80
+// pairs; the short kernel has 4 n workgroups, of which the chip holds 512 at d = 128 and, at d = 64, 768
+// with depth slots of one head per tile and 1024 otherwise.  It is ahead while they fit, on causal calls
+// (half of whose tiles are short) somewhat longer, on others somewhat less (other / short kernel, us,
+// whole call; 12 slots where there are any):
+//   d=64, no slots or several heads per tile, causal:  T=128 n=384 13/10;   n=256: T=512 13/10, T=2048 26/20, T=8192 81/64;
+//                     n=384: T=512 15/16, T=4096 45/48
+//     not causal:     T=512 n=256 13/13;   T=1024 n=160 15.5/15.5;   T=2048 n=128 25/21, n=192 25/27 (several heads 30/29)
+//   d=64, slots of one head:  n=192: T=128 21/19, T=1024 28/28, T=4096 56/42;   n=256: T=512 26/30, T=4096 56/57, T=8192 92/82
+//   d=128, causal:    n=128: T=100 13/8, T=512 15/11, T=900 19/15;   n=160: T=512 15/17, T=1024 20/19;
+//                     n=192: T=1024 21/23, T=2048 32/31, T=8192 103/93;   n=256: T=8192 105/115
+//     slots of one head:  n=128: T=512 35/28, T=8192 120/93;   n=160: T=1024 41/47, T=4096 75/65;   n=192: T=4096 76/76
+//     not causal:     n=128: T=512 15/14, T=4096 55/58 (12 slots 76/70);   n=96: T=4096 55/53
 bool fwd_few_tiles(const moda_shape* s, int heads_per_tile) {
   const long long n = (long long)s->B * s->Hq * ((s->T + 127) / 128);
   const bool rows = heads_per_tile == 1 && s->depth_count > 0;
-  const int fit = s->d == 128 ? 128 : rows ? 192 : 256;
-  if (n <= fit) return true;
-  return s->causal && n <= (s->d == 64 && !rows ? 512 : 256) && s->T >= (s->d == 64 ? 4096 : 8192);
+  const int T = s->T;
+  int most;
+  if (s->d == 64 && s->causal) most = rows ? (T >= 8192 ? 256 : 192) : T <= 256 ? 384 : 256;
+  else if (s->d == 64) most = rows ? 192 : T <= 512 ? 256 : heads_per_tile > 1 ? 192 : 160;
+  else if (s->causal) most = rows ? (T >= 4096 ? 192 : 128) : T >= 2048 ? 192 : T >= 1024 ? 160 : 128;
+  else most = heads_per_tile == 1 && !rows && T > 1024 ? 96 : 128;
+  return n <= most;
 }
 
 // Heads that one die (workgroup ids equal mod 8) walks together, tile by tile: as many as have
@@ -130,10 +144,8 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   moda_status st = check_shape(s);
   if (st != MODA_OK) return st;
   const int G = s->Hq / s->Hk;
-  int waves = fwd_waves_per_workgroup(s);
   if (tuning && s->dtype == MODA_BF16) {
     if (tuning->waves != 0 && tuning->waves != 4 && tuning->waves != 8) return MODA_ERR_SHAPE;
-    if (tuning->waves != 0) waves = tuning->waves;
     const int gt = tuning->heads_per_tile;
     if (gt < 0 || gt > 32 || (gt & (gt - 1)) != 0 || (gt > 0 && G % gt != 0)) return MODA_ERR_SHAPE;
     if (tuning->head_group < 0) return MODA_ERR_SHAPE;
@@ -175,6 +187,7 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   if (tuning && s->dtype == MODA_BF16 && tuning->depth_path != 0)
     p.depth_mfma = (tuning->depth_path == 2 && s->depth_count > 0) ? 1 : 0;
   p.depth_magic = s->depth_count > 1 ? (unsigned)((1ull << 32) / (unsigned)s->depth_count) + 1u : 0u;
+  const int waves = tuning && s->dtype == MODA_BF16 && tuning->waves != 0 ? tuning->waves : fwd_waves_per_workgroup(s, p.heads_per_tile);
   const int rows = moda::fwd_bf16_tile_rows(waves) / p.heads_per_tile;  // positions per tile
   p.n_qtiles = (s->T + rows - 1) / rows;
 

@@ -1,9 +1,11 @@
 """GPU parity of the bf16 forward for calls with few tiles (32 (position, head) pairs per workgroup,
 key tiles and blocks of depth slots dealt out to its waves), and of the rule that picks it: both
 kernels on the same inputs.  Tolerances as in test_fwd_parity."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import moda_ref as R
 from paper_2603_15619_amd import synth
 from test_fwd_parity import check_full, run_gpu
 
@@ -60,3 +62,20 @@ def test_depth_slots_of_weight_zero(T, d, L, dead):
     O, LSE = run_gpu(inp, L)
     assert (O.float() - O1.float()).abs().max().item() <= 2e-2
     assert (LSE - L1).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,causal", [(64, 16, 16, 100, 64, 3, True), (40, 8, 8, 384, 128, 0, False),
+                                                  (40, 16, 4, 128, 64, 5, True), (12, 16, 16, 500, 64, 2, True),
+                                                  (6, 8, 8, 1800, 128, 0, False), (8, 16, 16, 513, 128, 1, True)])
+def test_workgroups_of_four_waves(B, Hq, Hk, T, d, L, causal):
+    """Short sequences in large grids and one and a half rounds of workgroups take four waves (the last
+    case just does not): against eight on the same inputs, rows of whole heads against the oracle."""
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1900 + T, device="cuda")
+    O0, L0 = run_gpu(inp, L, causal)
+    O1, L1 = run_gpu(inp, L, causal, tuning=dict(waves=8))
+    assert (O0.float() - O1.float()).abs().max().item() <= 2e-2
+    assert (L0 - L1).abs().max().item() <= 1e-4
+    one = {k: None if v is None else v[B - 1:].contiguous() for k, v in inp.items()}
+    Oref, Lref = R.fwd(*(synth.to_f64(one[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), depth_count=L, causal=causal)
+    assert np.abs(synth.to_f64(O0[B - 1:]) - Oref).max() <= 2e-2
+    assert np.abs(synth.to_f64(L0[B - 1:]) - Lref).max() <= 1e-3
