@@ -1,8 +1,13 @@
-// MoDA attention forward, fp32 inputs, fp32 arithmetic throughout, gfx950 fp32 MFMA.
+// MoDA attention forward, fp32 inputs, fp32 precision throughout, on the gfx950 matrix pipe.
 //
 // The accuracy path (max abs error 1e-5 against an fp64 evaluation is the target).  Its products
-// run on v_mfma_f32_32x32x2_f32 (fp32 operands, fp32 accumulation, twice the rate of the vector
-// ALUs' fused multiply-adds), and its depth slots on the vector ALUs at the memory rate.
+// run on the bf16 matrix instructions with every fp32 factor as the sum of THREE bf16 numbers, which hold
+// its 24 bits: x y = x1 y1 + (x1 y2 + x2 y1 + x1 y3 + x3 y1 + x2 y2) + what is below 2^-24 of it.  bf16
+// products are exact in fp32 and 16 of them are summed per instruction: six such instructions take 192
+// cycles where the fp32 ones (64 FLOP per cycle and SIMD) take 512, and there are fewer roundings: error of
+// O against 64 bits 2.05e-7 -> 1.70e-7 (T=700 d=64), 2.83e-7 -> 2.25e-7 (T=1500 d=128, 15 slots), with
+// softmax scale 1 8.6e-7 -> 5.0e-7.  Factors that have no such parts take the fp32 instructions (see
+// fold_tile).  The depth slots run on the vector ALUs at the memory rate.
 //
 // A workgroup = 32 queries of one head; its 4 waves share the queries and DEAL OUT THE KEYS: key
 // tile kt (32 keys) belongs to wave kt % 4, every wave keeps a running (max, normaliser, output) of
@@ -13,20 +18,22 @@
 // a call of a few hundred rows walks its longest row in a quarter of the steps.  (Sequences of a few
 // positions, which this would pad to tiles of 32, go to the kernel of moda_fwd_f32_rows.hip.)
 //
-// What bounds it: the fp32 matrix pipe (64 FLOP per cycle and SIMD) on the sequence keys, HBM on
-// the depth slots (4 bytes per FLOP); every other workgroup takes its slots before its key tiles,
-// the others after, so that both are busy.
-//   B=1 H=16 T=2000 d=128, 15 slots: 0.211 ms, 79 TFLOP/s and 2.6 TB/s (one wave per query on the
-//                                    vector ALUs, the form before: 2.69 ms)
-//   B=1 H=16 T=8000 d=128, no slots: 1.95 ms, 134 TFLOP/s of the 154 that a library product of
-//                                    8192^3 reaches on the same card
-//   B=1 H=2 T=256 d=64, 4 slots:     10.7 us (36 us), most of it latency from one end to the other
+// What bounds it: the vector ALUs that form the parts (11 instructions per two numbers: 800 of a tile's
+// 900 at d = 128) and the matrix pipe, of different waves, on the sequence keys; HBM on the depth slots (4 bytes
+// per FLOP); every other workgroup takes its slots before its key tiles, the others after, so that both
+// are busy.
+//   B=1 H=16 T=2000 d=128, 15 slots: 0.190 ms, 88 TFLOP/s and 2.9 TB/s (fp32 matrix instructions: 0.226 ms; one
+//                                    wave per query on the vector ALUs: 2.69 ms); no slots 0.162 -> 0.119
+//   B=1 H=16 T=8000 d=128, no slots: 1.59 ms, 165 TFLOP/s (1.97; a library product of 8192^3 reaches 154)
+//   B=1 H=2 T=256 d=64, 4 slots:     9.8 us (10.8), most of it latency from one end to the other
+// (Splitting the next operand between the matrix instructions of one wave: no change; subtracting the
+// parts with packed dot products, 7 instructions per two numbers instead of 11: 2 to 6 % slower.)
 //
 // Operand layouts.  S^T = K Q^T (keys on M, queries on N): the contraction may take the channels
 // in any order that both operands share, so lane (l32, hi) holds channels 8 j + 4 hi .. + 3 of key
-// l32 and one 128-bit load feeds four matrix instructions; K comes straight from global memory
+// l32 and two 128-bit loads make an operand; K comes straight from global memory
 // (four consecutive loads use up a 128-byte line), Q from LDS.  A lane then owns 16 scores of one
-// query, and register i of them is, as it stands, the B operand of O^T += V^T P^T for the keys
+// query, and registers 8 h .. 8 h + 7 of them are, as they stand, the B operand of O^T += V^T P^T for the keys
 // 8 (i / 4) + i % 4 (lanes < 32) and 4 more (lanes >= 32).  Channels are dealt to the output blocks
 // so that one load of a V row feeds them all: block cb, row r is channel r * (d / 32) + cb.
 #include <type_traits>
@@ -38,17 +45,52 @@ namespace moda {
 constexpr int kF32Rows = 32;   // queries per workgroup
 constexpr int kF32Keys = 32;   // keys per tile (of one wave)
 constexpr int kF32Waves = 4;
+constexpr float kTiny = -100.f, kSmallest = 0x1p-100f;  // weights below are taken with care
+constexpr float kLargest = 3.38e38f;  // (values beyond round to an infinite bf16)
+constexpr float kLeast = 0x1p-80f;    // (the last parts of values far below would be subnormal)
 
 template <int D>
 struct F32Cfg {
   static constexpr int kRow = D + 4;                 // floats per LDS row (16 consecutive rows hit 16 bank groups)
   static constexpr int kBlocks = D / 32;             // output blocks of 32 channels
   static constexpr int kFrags = D / 8;               // 128-bit K fragments per tile and lane
+  static constexpr int kSteps = D / 16;              // bf16 matrix instructions per product of parts
   static constexpr int kRounds = D / 64;             // the waves' outputs are summed 64 channels at a time
   static constexpr int kXRow = 64 + 4;
   static constexpr int kXWave = kF32Rows * kXRow;    // floats of one wave's share in a round
-  static constexpr int kShared = kF32Rows * kRow > kF32Waves * kXWave ? kF32Rows * kRow : kF32Waves * kXWave;
+  static constexpr int kQRow = D + 8;                // bf16 numbers per LDS row of a part of the queries
+  static constexpr int kQPart = kF32Rows * kQRow;
+  static constexpr int kShared = kF32Waves * kXWave; // floats: the queries (three parts), later the outputs
+  static_assert(3 * kQPart * 2 <= kShared * 4, "the queries fit");
 };
+
+// Eight fp32 as three operands of packed bf16 whose sum they are: each part is the part before's remainder
+// rounded to 8 bits, the remainders are exact, and three times 8 bits hold the 24 of a float.  (An
+// infinite number, or one that rounds to an infinite bf16, leaves NaN in the second part.)
+struct Parts {
+  bf16x8 p[3];
+};
+__device__ __forceinline__ Parts split8(const float (&v)[8]) {
+  Parts r;
+  u32x4 w[3];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float x = v[2 * k], y = v[2 * k + 1];
+    asm volatile("" : "+v"(x), "+v"(y));  // (split here: else all operands of a loop are split at once)
+#pragma unroll
+    for (int n = 0; n < 3; ++n) {
+      w[n][k] = pack_bf16(x, y);
+      x -= bf16_lo(w[n][k]);
+      y -= bf16_hi(w[n][k]);
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 3; ++n) r.p[n] = __builtin_bit_cast(bf16x8, w[n]);
+  return r;
+}
+__device__ __forceinline__ f32x16 mfma_16(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
@@ -82,11 +124,24 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
   const int T = p.T, L = p.depth_count;
   const float c2 = p.scale_log2;
 
-  // ---- queries -> LDS (rows past the end repeat the last one; nothing of them is stored)
+  // ---- queries -> LDS, as three parts of bf16 (rows past the end repeat the last one; nothing of them is
+  // stored).  The 16 channels of a matrix instruction stand in the order in which a lane holds those of a
+  // key: 4 hi .. + 3, then 8 + 4 hi .. + 3 at place 8 hi.
+  unsigned short* q_parts = (unsigned short*)shared;
   for (int i = tid; i < kF32Rows * (D / 4); i += kF32Waves * 64) {
     const int r = i / (D / 4), c = i % (D / 4);
-    *(f32x4*)(shared + r * C::kRow + c * 4) =
-        *(const f32x4*)((const float*)p.Q + ((size_t)bh * T + min(q0 + r, T - 1)) * D + c * 4);
+    const f32x4 q = *(const f32x4*)((const float*)p.Q + ((size_t)bh * T + min(q0 + r, T - 1)) * D + c * 4);
+    float x[4] = {q[0], q[1], q[2], q[3]};
+    unsigned short* dst = q_parts + r * C::kQRow + (c >> 2) * 16 + (c & 1) * 8 + ((c >> 1) & 1) * 4;
+#pragma unroll
+    for (int n = 0; n < 3; ++n) {
+      const u32x2 w = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+      *(u32x2*)(dst + n * C::kQPart) = w;
+      x[0] -= bf16_lo(w[0]);
+      x[1] -= bf16_hi(w[0]);
+      x[2] -= bf16_lo(w[1]);
+      x[3] -= bf16_hi(w[1]);
+    }
   }
   __syncthreads();
 
@@ -253,38 +308,60 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
   }
   auto fold_tile = [&](int kt, auto PARTIAL) {
     constexpr bool partial = decltype(PARTIAL)::value;
-    // loads in flight: half of the tile's V during the scores; then its other half and half of the
-    // next tile's K; the rest of that K from the middle of the output products on (all of K and V
-    // at once do not fit 256 registers)
+    // loads in flight: half of the tile's V during the scores; then its other half; half of the next
+    // tile's K from the output products on, the rest from their middle (all of K and V at once do
+    // not fit 256 registers)
     const int k_next = kt + kF32Waves;  // (past the last tile: rows that exist or zeros, not used)
     load_v(kt, 0);
     __builtin_amdgcn_sched_barrier(0);
-    // S^T = K Q^T: two accumulation chains (even and odd fragments)
-    // (issued strictly in turn: left to itself the scheduler runs one chain after the other)
+    // S^T = K Q^T: the products of the first parts in one chain, the five others down to 2^-16 of them in
+    // another (those left out are 2^-24 of a product)
     f32x16 s, s1;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
-    const float* q_row = shared + l32 * C::kRow + hi * 4;
-    f32x4 qa = *(const f32x4*)q_row, qb = *(const f32x4*)(q_row + 8);
+    const unsigned short* q_row = q_parts + l32 * C::kQRow + hi * 8;
+    auto k_parts = [&](int st) {
+      const float x[8] = {kf[2 * st][0], kf[2 * st][1], kf[2 * st][2], kf[2 * st][3],
+                          kf[2 * st + 1][0], kf[2 * st + 1][1], kf[2 * st + 1][2], kf[2 * st + 1][3]};
+      return split8(x);
+    };
 #pragma unroll
-    for (int j = 0; j < C::kFrags; j += 2) {
-      const int jn = j + 2 < C::kFrags ? j + 2 : 0;  // Q fragments are read one step ahead
-      const f32x4 na = *(const f32x4*)(q_row + jn * 8), nb = *(const f32x4*)(q_row + jn * 8 + 8);
+    for (int st = 0; st < C::kSteps; ++st) {
+      bf16x8 q[3];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        __builtin_amdgcn_sched_barrier(0);
-        s = mfma_f32(kf[j][e], qa[e], s);
-        s1 = mfma_f32(kf[j + 1][e], qb[e], s1);
+      for (int n = 0; n < 3; ++n) q[n] = *(const bf16x8*)(q_row + n * C::kQPart + st * 16);
+      const Parts ka = k_parts(st);
+      s = mfma_16(ka.p[0], q[0], s);
+      s1 = mfma_16(ka.p[0], q[1], s1);
+      s1 = mfma_16(ka.p[1], q[0], s1);
+      s1 = mfma_16(ka.p[0], q[2], s1);
+      s1 = mfma_16(ka.p[2], q[0], s1);
+      s1 = mfma_16(ka.p[1], q[1], s1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] += s1[i];
+    // numbers that have no such parts (infinite, NaN, about to overflow) leave NaN or infinity in the scores of
+    // their key or query: the tile is then taken on the fp32 matrix instructions
+    float sum = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) sum += s[i];
+    if (__builtin_amdgcn_ballot_w64(!(fabsf(sum) < INFINITY)) != 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = 0.f;
+      const float* q = (const float*)p.Q + ((size_t)bh * T + min(q0 + l32, T - 1)) * D + hi * 4;
+#pragma unroll 1
+      for (int j = 0; j < C::kFrags; ++j) {
+        const f32x4 qj = *(const f32x4*)(q + j * 8);
+        const f32x4 kj = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+            k_buf, k_off + j * 32, (int)((unsigned)kt * (unsigned)(kF32Keys * D * 4)), 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = mfma_f32(kj[e], qj[e], s);
       }
-      qa = na;
-      qb = nb;
     }
     __builtin_amdgcn_sched_barrier(0);
     load_v(kt, 1);
-    load_k(k_next, 0);
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] += s1[i];
     const int k0 = kt * kF32Keys;
     // exp2f takes four instructions more than the bare instruction, 3 to 8 % of the call if taken for every
     // weight: only tiles with a weight below 2^-126 take it (masked scores count as they are: their weights
@@ -312,7 +389,8 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[cb][i] *= al;
     }
-    if (__builtin_amdgcn_ballot_w64((least - m) * c2 < -126.f) != 0) {  // (uniform)
+    const bool tiny = __builtin_amdgcn_ballot_w64((least - m) * c2 < kTiny) != 0;  // (uniform)
+    if (tiny) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = weight(s[i], m, c2);
     } else {
@@ -322,51 +400,90 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) l += s[i];
-    // O^T += V^T P^T.  On a tile that the diagonal crosses a key's weight is zero for the queries
-    // before it, but zero times an infinite or NaN value is not: if the tile holds such values the
-    // visible (key, query) pairs are taken one by one.
-    bool plain = true;
-    if (partial && p.causal) {  // (uniform)
-      bool finite = true;
+    // O^T += V^T P^T.  Values that are infinite, NaN or about to overflow have no parts, and the last parts of the
+    // smallest weights, or of a channel's values that are all minute, would be lost: those are taken on the
+    // fp32 matrix instructions first, and left out below.
+    bool has_parts = true;
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
+    for (int cb = 0; cb < C::kBlocks; ++cb) {  // (a lane's channels, one by one)
+      float largest = 0.f;
 #pragma unroll
-        for (int cb = 0; cb < C::kBlocks; ++cb) finite = finite && fabsf(vf[i][cb]) < INFINITY;
-      plain = __builtin_amdgcn_ballot_w64(!finite) == 0;
+      for (int i = 0; i < 16; ++i) largest = __builtin_elementwise_maximum(largest, fabsf(vf[i][cb]));
+      has_parts = has_parts && largest < kLargest && (largest == 0.f || largest > kLeast);
     }
-    auto fold_v = [&](int first) {
+    const bool plain = __builtin_amdgcn_ballot_w64(!has_parts) == 0;
+    if (tiny || !plain) {
+      float w[16];
 #pragma unroll
-      for (int i = first; i < first + 8; ++i)
-#pragma unroll
-        for (int cb = 0; cb < C::kBlocks; ++cb) o[cb] = mfma_f32(vf[i][cb], s[i], o[cb]);
-    };
-    if (plain) {
-      fold_v(0);
-    } else {
-      // (one tile per workgroup at most is crossed by the diagonal: one wave uses p_tile)
-      int h = hi, q = l32;  // (addresses formed here, not kept across the loop)
-      asm volatile("" : "+v"(h), "+v"(q));
-#pragma unroll
-      for (int i = 0; i < 16; ++i) p_tile[(i >> 2) * 8 + h * 4 + (i & 3)][q] = s[i];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      for (int key = k0; key < min(T, k0 + kF32Keys); ++key) {
-        const float w = p_tile[key - k0][q];
-        const float* vr = Vb + (size_t)key * D;
+      for (int i = 0; i < 16; ++i) {
+        const bool here = !plain || s[i] < kSmallest;
+        w[i] = here ? s[i] : 0.f;
+        s[i] = here ? 0.f : s[i];
+      }
+      if (plain || !(partial && p.causal)) {  // (uniform)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
 #pragma unroll
-          for (int cb = 0; cb < C::kBlocks; ++cb) {
-            const float x = fmaf(w, vr[((i >> 2) * 8 + h * 4 + (i & 3)) * C::kBlocks + cb], o[cb][i]);
-            o[cb][i] = key <= lim ? x : o[cb][i];
-          }
+          for (int cb = 0; cb < C::kBlocks; ++cb) o[cb] = mfma_f32(vf[i][cb], w[i], o[cb]);
+      } else {
+        // On a tile that the diagonal crosses a key's weight is zero for the queries before it, but zero times
+        // an infinite or NaN value is not: the visible (key, query) pairs are taken one by one.  (One tile
+        // per workgroup at most is crossed by the diagonal: one wave uses p_tile.)
+        int h = hi, q = l32;  // (addresses formed here, not kept across the loop)
+        asm volatile("" : "+v"(h), "+v"(q));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) p_tile[(i >> 2) * 8 + h * 4 + (i & 3)][q] = w[i];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int key = k0; key < min(T, k0 + kF32Keys); ++key) {
+          const float wk = p_tile[key - k0][q];
+          const float* vr = Vb + (size_t)key * D;
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int cb = 0; cb < C::kBlocks; ++cb) {
+              const float x = fmaf(wk, vr[((i >> 2) * 8 + h * 4 + (i & 3)) * C::kBlocks + cb], o[cb][i]);
+              o[cb][i] = key <= lim ? x : o[cb][i];
+            }
+        }
+      }
+      if (!plain) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int cb = 0; cb < C::kBlocks; ++cb) vf[i][cb] = 0.f;
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    load_k(k_next, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (plain) fold_v(8);
+    auto p_parts = [&](int hf) {
+      const float x[8] = {s[8 * hf], s[8 * hf + 1], s[8 * hf + 2], s[8 * hf + 3],
+                          s[8 * hf + 4], s[8 * hf + 5], s[8 * hf + 6], s[8 * hf + 7]};
+      return split8(x);
+    };
+    auto v_parts = [&](int hf, int cb) {
+      const float x[8] = {vf[8 * hf][cb], vf[8 * hf + 1][cb], vf[8 * hf + 2][cb], vf[8 * hf + 3][cb],
+                          vf[8 * hf + 4][cb], vf[8 * hf + 5][cb], vf[8 * hf + 6][cb], vf[8 * hf + 7][cb]};
+      return split8(x);
+    };
+    load_k(k_next, 0);
+    Parts pp = p_parts(0);
+#pragma unroll
+    for (int n = 0; n < 2 * C::kBlocks; ++n) {
+      const int cb = n % C::kBlocks;
+      const Parts va = v_parts(n / C::kBlocks, cb);
+      o[cb] = mfma_16(va.p[0], pp.p[0], o[cb]);
+      o[cb] = mfma_16(va.p[0], pp.p[1], o[cb]);
+      o[cb] = mfma_16(va.p[1], pp.p[0], o[cb]);
+      o[cb] = mfma_16(va.p[0], pp.p[2], o[cb]);
+      o[cb] = mfma_16(va.p[2], pp.p[0], o[cb]);
+      o[cb] = mfma_16(va.p[1], pp.p[1], o[cb]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n + 1 == C::kBlocks) {
+        pp = p_parts(1);
+        load_k(k_next, 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   };
   int kt = wave;
   for (; kt < n_full; kt += kF32Waves) fold_tile(kt, std::false_type{});

@@ -95,3 +95,37 @@ def test_f32_depth_slots_of_weight_zero(T, d, L, dead):
     O1, LSE1 = moda_attn_fwd(Q, inp["Kseq"], inp["Vseq"], *rest)
     torch.cuda.synchronize()
     assert (O - O1).abs().max().item() <= TOL and (LSE - LSE1).abs().max().item() <= TOL
+
+
+@pytest.mark.parametrize("T,d,causal", [(100, 64, True), (70, 128, False), (161, 128, True)])
+def test_f32_factors_without_three_parts(T, d, causal):
+    """Factors that are not the sum of three finite bf16 numbers of normal size, in some tiles: keys of score
+    -inf, a channel of values of 2^-120, a value that rounds to an infinite bf16.  (Channels are independent:
+    1e-5 of each channel's largest value; scores, hence LSE, as everywhere.)"""
+    inp = synth.make_inputs(1, 2, 1, T, d, 3, dtype="f32", seed=600 + T, device="cuda")
+    inp["Q"][..., 0] = inp["Q"][..., 0].abs() + 0.1
+    inp["Kseq"][:, :, 33:40, 0] = -float("inf")
+    inp["Vseq"][..., 5] *= 2.0 ** -120
+    inp["Vdepth"][..., 5] *= 2.0 ** -120
+    inp["Vseq"][:, :, 20, 7] = 3.4e38
+    O, LSE = moda_attn_fwd(inp["Q"], inp["Kseq"], inp["Vseq"], inp["Kdepth"], inp["Vdepth"], causal=causal)
+    torch.cuda.synchronize()
+    Oref, Lref = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), causal=causal)
+    assert np.abs(synth.to_f64(LSE) - Lref).max() <= TOL
+    scale = np.abs(Oref).max(axis=(0, 1, 2))
+    assert (np.abs(synth.to_f64(O) - Oref).max(axis=(0, 1, 2)) <= TOL * scale.clip(min=2.0 ** -125)).all()
+
+
+@pytest.mark.parametrize("T,d", [(300, 64), (200, 128)])
+def test_f32_wide_scores(T, d):
+    """Softmax scale 1: weights down to 2^-200.  An error of a score is an error of its weight: (d + 6) roundings
+    of 2^-24 of sum |q k|, on both sides of the quotient."""
+    inp = synth.make_inputs(1, 2, 2, T, d, 2, dtype="f32", seed=650 + T, device="cuda")
+    O, LSE = moda_attn_fwd(inp["Q"], inp["Kseq"], inp["Vseq"], inp["Kdepth"], inp["Vdepth"], scale=1.0)
+    torch.cuda.synchronize()
+    q, k, kd = (np.abs(synth.to_f64(inp[n])) for n in ("Q", "Kseq", "Kdepth"))
+    size = max((q @ k.transpose(0, 1, 3, 2)).max(), (kd * q[:, :, :, None]).sum(-1).max())
+    delta = (d + 6) * 2.0 ** -24 * size
+    Oref, Lref = R.fwd(*(synth.to_f64(inp[n]) for n in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), scale=1.0)
+    assert np.abs(synth.to_f64(O) - Oref).max() <= 2 * delta * float(max(inp["Vseq"].abs().max(), inp["Vdepth"].abs().max()))
+    assert np.abs(synth.to_f64(LSE) - Lref).max() <= delta + TOL
