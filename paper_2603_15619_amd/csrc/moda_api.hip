@@ -1,4 +1,5 @@
 // libmoda C ABI: argument validation and kernel dispatch (host code only).
+#include <algorithm>
 #include <math.h>
 
 #include "../../include/moda.h"
@@ -46,21 +47,37 @@ moda_status launch_status(hipError_t e) {
   return e == moda::kGridTooLarge ? MODA_ERR_UNSUPPORTED : MODA_ERR_LAUNCH;
 }
 
-// Geometry of the bf16 forward kernel (see moda_fwd_bf16.hip): 8 waves (256 (position, head) pairs) per
-// workgroup, one workgroup per compute unit, or 4 waves (128 pairs), two workgroups per unit.  Long
-// sequences in large grids take 8: every K/V tile is copied from the L2 half as often.  4 waves take
+// Geometry of the bf16 forward kernel (see moda_fwd_bf16.hip): workgroups of 8 waves (256 (position, head)
+// pairs) or of 4 (128 pairs), which copy every K/V tile from the L2 twice as often.
+// d = 128: two waves per SIMD, so one workgroup of 8 or two of 4 per compute unit.  Long
+// sequences in large grids take 8.  4 waves take
 //   - grids that would leave compute units without work;
 //   - sequences of up to 512 pairs, which 8 waves pad to 256, and whose ends weigh more than their copies
-//     (4 / 8 waves, us, one head per tile: d=64 T=100, 4096 tiles of 128: 55 / 109, T=256 2048 tiles 39 / 44,
-//     T=384 4095 tiles 78 / 110; d=128 12 slots T=128, 768 tiles: 127 / 171; T=500 and more tiles 0.88 to 1.02);
+//     (4 / 8 waves, us, one head per tile: 12 slots T=128, 768 tiles of 128: 127 / 171);
 //   - one and a half rounds of workgroups of 8 waves, whose last half round 4 waves spread over all units
-//     (768 tiles: d=64 T=1000 27 / 29, not causal 36 / 40; d=128 12 slots T=2000 not causal 168 / 187, causal
-//     T=1000 138 / 150; causal and longer 0.92 to 1.14: not there).
+//     (768 tiles: 12 slots T=2000 not causal 168 / 187, causal T=1000 138 / 150; causal and longer 0.92 to 1.14:
+//     not there).
+// d = 64: four waves per SIMD, two workgroups of 8 or four of 4 per unit, and 4 waves up to one and a half rounds
+//   of 8 (B=5 H=16 T=1020, 640 tiles, 15 slots 68 / 82 us; T=4720 32 heads on 4, 1184 tiles 108 / 114; T=11652 16 on 4, 1472
+//   tiles 303 / 311; T=4570, 1728 tiles 143.3 / 143.7; B=8 H=16 T=2048, 2048 tiles 93 / 89) and for up to 1024 pairs
+//   (B=16 H=16 T=1024, 2048 tiles 53.0 / 53.5; B=15 32 on 8 T=515 37 / 40).
 int fwd_waves_per_workgroup(const moda_shape* s, int heads_per_tile) {
   const long long heads = (long long)s->B * s->Hq / heads_per_tile, pairs = (long long)s->T * heads_per_tile;
   const long long n = heads * ((pairs + 255) / 256);
+  if (s->d == 64) return n <= 768 || pairs <= 1024 ? 4 : 8;
   if (n < 256 || pairs <= 512) return 4;
   return n > 256 && n <= 448 && (!s->causal || s->T <= 1024) ? 4 : 8;
+}
+
+// Waves that share a SIMD in the bf16 forward kernel: four at d = 64, but two while two workgroups of 4 waves
+// per unit hold the grid: a third and fourth wave are not there then, and the step for two, of a whole tile, is
+// a little faster (two / four, us: T=1338, 352 tiles 19.1 / 20.4; T=13133, 412 tiles 143 / 147; T=900, 512 tiles 16.2 / 16.6;
+// T=4096, 512 tiles 49 / 53; 640 tiles 25.4 / 25.3; with slots of one head per tile 440 tiles 96.6 / 101.5, 512 tiles 53.7 / 52.5, 640
+// tiles 75.8 / 68.3).
+int fwd_waves_per_simd(const moda_shape* s, int heads_per_tile, int waves) {
+  if (s->d == 128) return 2;
+  const long long n = (long long)s->B * s->Hq / heads_per_tile * (((long long)s->T * heads_per_tile + 127) / 128);
+  return waves == 4 && n <= (heads_per_tile == 1 && s->depth_count > 0 ? 448 : 512) ? 2 : 4;
 }
 
 // Calls that take the kernel for few tiles (moda_fwd_short.hip): n = tiles of 128 (position, head)
@@ -91,10 +108,14 @@ bool fwd_few_tiles(const moda_shape* s, int heads_per_tile) {
 // Heads that one die (workgroup ids equal mod 8) walks together, tile by tile: as many as have
 // their streamed tensors (2 * T * d bf16 elements each: K and V, or Q and dO) in its 4 MB L2, at
 // least one; a power of two that divides the heads of a die.  0: the ids cannot be dealt that way.
-int heads_per_die_at_a_time(long long n_heads, int T, int d) {
+// Forward with four waves per SIMD (d = 64): a die holds twice the workgroups, and with few heads at a time its
+// last rounds are the tiles of one head; two to eight heads in up to 8 MB (us, heads as for 4 MB / so: H=16
+// T=16384 604 / 537; B=2 H=16 T=8192 305 / 272; B=8 H=16 T=4096 303 / 288; B=16 H=16 T=1024 56.0 / 53.5).
+int heads_per_die_at_a_time(long long n_heads, int T, int d, bool four_per_simd = false) {
   if (n_heads % 8 != 0) return 0;
   const long long per_die = n_heads / 8;
-  const long long fit = (4ll << 20) / (4ll * T * d);
+  long long fit = (4ll << 20) / (4ll * T * d);
+  if (four_per_simd) fit = std::min(8ll, std::max(2ll, 2 * fit));
   int hg = 1;
   while (hg * 2 <= fit && per_die % (hg * 2) == 0) hg *= 2;
   return hg;
@@ -178,8 +199,6 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   //  slower than one head per tile at G = 2, equal or faster from 4 heads on)
   if (s->depth_count == 0 && p.heads_per_tile < 4) p.heads_per_tile = 1;
   if (tuning && tuning->heads_per_tile > 0) p.heads_per_tile = tuning->heads_per_tile;
-  p.head_group = heads_per_die_at_a_time((long long)s->B * s->Hk * (G / p.heads_per_tile), s->T, s->d);
-  if (tuning && tuning->head_group > 0) p.head_group = tuning->head_group;
   // depth slots: on the matrix pipe when several heads share a position's slots (the block
   // products are then dense enough to beat the vector ALUs), else on the vector ALUs, where the
   // phase already runs at the rate a compute unit can fetch
@@ -188,6 +207,9 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
     p.depth_mfma = (tuning->depth_path == 2 && s->depth_count > 0) ? 1 : 0;
   p.depth_magic = s->depth_count > 1 ? (unsigned)((1ull << 32) / (unsigned)s->depth_count) + 1u : 0u;
   const int waves = tuning && s->dtype == MODA_BF16 && tuning->waves != 0 ? tuning->waves : fwd_waves_per_workgroup(s, p.heads_per_tile);
+  const int per_simd = fwd_waves_per_simd(s, p.heads_per_tile, waves);
+  p.head_group = heads_per_die_at_a_time((long long)s->B * s->Hk * (G / p.heads_per_tile), s->T, s->d, per_simd == 4);
+  if (tuning && tuning->head_group > 0) p.head_group = tuning->head_group;
   const int rows = moda::fwd_bf16_tile_rows(waves) / p.heads_per_tile;  // positions per tile
   p.n_qtiles = (s->T + rows - 1) / rows;
 
@@ -202,7 +224,7 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
     p.n_qtiles = (s->T + pos - 1) / pos;
     return launch_status(moda::launch_fwd_short(p, s->d, stream));
   }
-  return launch_status((s->dtype == MODA_BF16) ? moda::launch_fwd_bf16(p, s->d, waves, stream)
+  return launch_status((s->dtype == MODA_BF16) ? moda::launch_fwd_bf16(p, s->d, waves, per_simd, stream)
                                                : moda::launch_fwd_f32(p, s->d, stream));
 }
 

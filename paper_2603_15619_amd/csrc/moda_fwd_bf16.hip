@@ -1,12 +1,12 @@
 // MoDA attention forward, bf16 inputs, fp32 online-softmax state, gfx950 MFMA.
 //
-// One workgroup = 8 waves (two per SIMD) = one tile of 256 (position, query head) pairs of
-// one key/value head (256 positions of one head without grouped queries); each wave owns 32
-// of them.  (A second geometry, 4 waves and 2-stage rings, serves small grids.)  Two waves
-// per SIMD matter: a single wave issues a vector-ALU
+// One workgroup = 8 or 4 waves = one tile of 256 or 128 (position, query head) pairs of
+// one key/value head (positions of one head without grouped queries); each wave owns 32
+// of them.  Two waves share a SIMD at d = 128, four at d = 64, where the registers allow it.  The number of
+// waves matters: a single wave issues a vector-ALU
 // instruction only every ~8 cycles and an exp2 every ~24, two waves together reach
 // ~5.7 and ~9.4 (measured), and the softmax arithmetic of this operator needs about as
-// many vector-ALU cycles as its matrix products need matrix-pipe cycles.
+// many vector-ALU cycles as its matrix products need matrix-pipe cycles (more at d = 64).
 // Sequence K/V tiles of 64 keys are copied global -> LDS without passing through
 // registers, into rings of 4 stages each, two iterations ahead of their use, and
 // consumed by v_mfma_f32_32x32x16_bf16:
@@ -16,12 +16,13 @@
 //   O^T += V^T P^T with P^T taken straight from the S^T accumulators (no layout
 //                 round trip); the V^T operand comes from ds_read_b64_tr_b16.
 // The key loop is software pipelined: while tile kt-1's P V and tile kt+1's K Q^T run
-// on the matrix pipe, the vector ALUs exponentiate tile kt, a fixed slice after every MFMA, with the
+// on the matrix pipe (at d = 64 with four waves per SIMD: the halves of tiles before and after), the vector
+// ALUs exponentiate tile kt (the half between), a fixed slice after every MFMA, with the
 // reference of the tiles before: no row maximum is taken unless a tile's sum asks for it (see `step`).  The loop body is unrolled over the 4 ring stages, so
 // every LDS address is a per-lane base register plus an immediate.  K / V^T fragments
 // are read from LDS straight into named accumulation registers a fixed number of MFMAs
 // ahead of their use (moda_fwd_regs.h), next to the Q fragments and the output
-// accumulators; score tiles, P and the softmax state live in the 128 vector registers.
+// accumulators; scores, P and the softmax state live in the vector registers.
 // Tiles above the diagonal are never loaded; only the diagonal tile is masked
 // (Algorithm 1's split into fully visible and boundary blocks).
 // The depth slots of the query's own position -- one contiguous L*d block in the
@@ -47,18 +48,14 @@ constexpr int kUnroll = 4;               // the key loop is unrolled over 4 step
 // cache policy of loads whose data is used exactly once (depth K/V): non-temporal, so
 // that the stream does not push the re-used sequence K/V tiles out of the L2
 constexpr int kStreamOnce = 2;
-constexpr int kDepthChunk = 5;           // depth slots per work item of the depth phase
-constexpr int kAhead = 4;                // fragments read from LDS ahead of the MFMA that consumes them
-static_assert(kAhead < kSlots - 1, "a slot is refilled only after the MFMA that read it was issued");
-
-// Two geometries:
-//   W = 8: one workgroup of 8 waves (256 queries) per compute unit, K and V rings of 4 stages
-//          (128 KB at d = 128); copies run two steps ahead of their use.
-//   W = 4: workgroups of 4 waves (128 queries), rings of 2 stages (64 KB), so that TWO
-//          workgroups share a compute unit (still two waves per SIMD): while one of them is in
-//          its depth phase, which is bound by memory latency, the other keeps the matrix pipe
-//          busy.  Copies run one step ahead; every K/V tile is fetched from L2 twice as often.
-template <int D, int W>
+// Geometries, PS waves per SIMD (D = 64 for 4):
+//   W = 8: workgroups of 8 waves (256 queries), PS / 2 per compute unit, K and V rings of 4 stages
+//          (128 KB at d = 128, 64 KB at d = 64); copies run two tiles ahead of their use.
+//   W = 4: workgroups of 4 waves (128 queries), PS per unit, rings of 2 stages (half of that): while
+//          one of them is in
+//          its depth phase, which is bound by memory latency, the others keep the matrix pipe
+//          busy.  Copies run one tile ahead; every K/V tile is fetched from L2 twice as often.
+template <int D, int W, int PS>
 struct FwdCfg {
   static constexpr int kD = D;
   static constexpr int kWaves = W;
@@ -71,19 +68,26 @@ struct FwdCfg {
   static constexpr int kRowBytes = D * 2;
   static constexpr int kGTileBytes = kBN * kRowBytes;  // a tile in global memory
   // A tile in LDS is made of 1 KB pieces (what one wave copy instruction moves: 4 rows at
-  // d = 128, 8 at d = 64); the pieces of a K tile at d = 128 are 64 bytes apart (see the
-  // layout comment), all others adjacent.
+  // d = 128, 8 at d = 64); the pieces of a K tile are 64 bytes apart (see the
+  // layout comment), those of a V tile adjacent.
   static constexpr int kPieceRows = 1024 / kRowBytes;
-  static constexpr int kKPieceStride = 1024 + (D == 128 ? 64 : 0);
+  static constexpr int kKPieceStride = 1024 + 64;
   static constexpr int kVPieceStride = 1024;
   static constexpr int kKTileBytes = kBN / kPieceRows * kKPieceStride;  // a K tile (ring stage) in LDS
   static constexpr int kVTileBytes = kBN / kPieceRows * kVPieceStride;  // a V tile (ring stage) in LDS
-  static constexpr int kKRegs = D == 128 ? 2 : D / 16;  // per-lane K fragment base addresses
   static constexpr int kDSteps = D / 16;         // MFMA k-steps over the head dim
   static constexpr int kDBlocks = D / 32;        // 32-wide output blocks over the head dim
-  static constexpr int kNFK = kDSteps * 2;       // K fragments (= MFMAs of S^T = K Q^T) per tile
-  static constexpr int kNFV = 4 * kDBlocks;      // V^T fragments (= MFMAs of O^T += V^T P^T) per tile
-  static_assert(kNFK % kSlots == 0 && kNFV % kSlots == 0, "fragment f always uses slot f % kSlots");
+  static constexpr int kWavesPerSimd = PS;
+  static_assert(PS == 2 || (PS == 4 && D == 64), "registers");
+  static constexpr int kKB = PS == 2 ? 2 : 1;      // 32-key blocks per step of the key loop (registers allow one at four waves per SIMD)
+  static constexpr int kNFK = kDSteps * kKB;       // K fragments (= MFMAs of S^T = K Q^T) per step
+  static constexpr int kNFV = 2 * kDBlocks * kKB;  // V^T fragments (= MFMAs of O^T += V^T P^T) per step
+  static constexpr int kNF = kNFK + kNFV;
+  using Acc = AccMap<D, PS>;
+  static constexpr int kAhead = PS == 2 ? 4 : 2;  // fragments read from LDS ahead of the MFMA that consumes them
+  static_assert(kAhead < Acc::kSlots - 1, "a slot is refilled only after the MFMA that read it was issued");
+  static_assert(kNF % Acc::kSlots == 0 && kAhead % 2 == 0, "the fragment at place g of a step always uses slot g % kSlots");
+  static constexpr int kDepthChunk = PS == 2 ? 5 : 3;  // depth slots per work item of the depth phase
   // fp32 exchange buffer: 32 query rows x D floats per wave, rows padded by 16 B
   static constexpr int kXRow = D * 4 + 16;
   static constexpr int kXWave = 32 * kXRow + 32 * 8;  // + (m, l) per row
@@ -91,14 +95,17 @@ struct FwdCfg {
   static constexpr int kVBase = kStages * kKTileBytes;  // V ring follows the K ring
   static constexpr int kRingBytes = kStages * (kKTileBytes + kVTileBytes);
   static constexpr int kLds = kRingBytes > kXBytes ? kRingBytes : kXBytes;
-  static_assert((W == 8 ? 1 : 2) * kLds <= 160 * 1024, "workgroups per compute unit x LDS");
+  static_assert((W == 8 ? 1 : 2) * (kWavesPerSimd / 2) * kLds <= 160 * 1024, "workgroups per compute unit x LDS");
   static constexpr int kInstPerWave = kBN / kPieceRows / kWaves;  // copy instructions (pieces) per wave per tile
   // copy instructions of a wave that may still be in flight at a step's barrier: with 4 stages
   // the copies of the step before (needed one step later), with 2 stages none
   static constexpr int kPending = W == 8 ? 2 * kInstPerWave : 0;
+  // the matrix instruction of a step before which they are awaited and the workgroup synchronises (see the key loop)
+  static constexpr int kSyncAt = kKB == 1 ? kNF - kAhead : kStages == 2 ? kNFV - kAhead : kNFV;
   // V tile: segment permutation of row r (see the layout comment below)
   static constexpr int kSegs = kRowBytes / 64;        // 64-byte segments per row (4 or 2)
   static constexpr int kRowsPer256 = 256 / kRowBytes; // rows per sweep over all banks (1 or 2)
+  __device__ __host__ static constexpr int kswz(int r) { return (r / kRowsPer256) & 3; }  // (repeats from piece to piece)
   __device__ __host__ static constexpr int vswz(int r) { return (r / kRowsPer256) & (kSegs - 1); }
   static_assert(kInstPerWave >= 1, "every wave copies part of every tile");
 };
@@ -181,16 +188,14 @@ __device__ __forceinline__ void wait_copies_but() {  // all but the N most recen
 // piece r / kPieceRows; a piece is 1 KB, contiguous (the global -> LDS copy writes it with
 // one instruction), and pieces are kPieceStride bytes apart.  Inside a row the 16-byte
 // chunks are permuted so that fragment reads spread over all 64 banks (256 B):
-//   K tile, d = 128: chunk c of row r sits at chunk position c ^ (r & 3) (only the two
+//   K tile: chunk c of row r sits at chunk position c ^ kswz(r) (only the two
 //           low bits are permuted), and pieces are 1024 + 64 bytes apart.  The MFMA
-//           A-operand read (16 consecutive lanes = 16 consecutive rows = 4 pieces x 4 rows,
-//           same c) then touches 64-byte bank group (piece + c / 4) mod 4 and, inside it,
-//           chunk (c ^ row) & 3: 16 different 16-byte bank groups, conflict free.  Because
-//           only two chunk bits depend on the lane, the address of fragment (st, kb) is one
-//           of TWO per-lane registers (st even / odd) plus an immediate.
-//   K tile, d = 64:  chunk c of row r at chunk position c ^ ((r >> 1) & 7), pieces adjacent
-//           (two 128-byte rows span the banks, so 16 consecutive rows need 8 different
-//           positions per row parity); one per-lane register per k-step.
+//           A-operand read (16 consecutive lanes = 16 consecutive rows, same c) then touches
+//           64-byte bank group (piece + c / 4) mod 4 at d = 128 (4 pieces x 4 rows), (piece + 2 row + c / 4) mod 4
+//           at d = 64 (2 pieces x 8 rows, two rows to a sweep over the banks), and, inside it,
+//           chunk (c ^ kswz) & 3: 16 different 16-byte bank groups, conflict free.  Because
+//           only two chunk bits depend on the lane, the address of a fragment is one
+//           of TWO per-lane registers (k-step even / odd) plus an immediate.
 //   V tile: the 64-byte segment (c >> 2) sits at segment position (c >> 2) ^ vswz(r).  The
 //           transposing read takes 2 cycles of 32 lanes; in one cycle the lanes read 4
 //           consecutive rows x one 64-byte segment, and vswz spreads those 4 rows over the
@@ -200,21 +205,14 @@ __device__ __forceinline__ void wait_copies_but() {  // all but the N most recen
 // the instruction's immediate.
 template <class C>
 struct FragBase {
-  int k[C::kKRegs];    // K ring
+  int k[2];            // K ring
   int v[C::kDBlocks];  // V ring: (lane base ^ (db << 6)) + offset of the V ring
   __device__ __forceinline__ void init(int lane, int smem_addr) {
     const int l32 = lane & 31, hi = lane >> 5;
-    // K fragment (st, kb): row kb*32 + l32, logical chunk 2*st + hi
-    if constexpr (C::kD == 128) {
-      const int j = l32 & 3;
-      const int kbase = (l32 >> 2) * C::kKPieceStride + j * C::kRowBytes;
+    // K fragment st of a half: row l32 of it, logical chunk 2*st + hi
+    const int kbase = l32 / C::kPieceRows * C::kKPieceStride + l32 % C::kPieceRows * C::kRowBytes;
 #pragma unroll
-      for (int e = 0; e < 2; ++e) k[e] = smem_addr + kbase + ((((e << 1) | hi) ^ j) << 4);
-    } else {
-      const int kbase = l32 * C::kRowBytes + ((((l32 >> 1) & (C::kChunks - 1)) ^ hi) << 4);
-#pragma unroll
-      for (int st = 0; st < C::kDSteps; ++st) k[st] = smem_addr + (kbase ^ (st << 5));
-    }
+    for (int e = 0; e < 2; ++e) k[e] = smem_addr + kbase + ((((e << 1) | hi) ^ C::kswz(l32)) << 4);
     // V fragment (ks, db): transposing read, see read_vfrag
     const int r8 = hi * 4 + ((lane & 15) >> 2);  // row inside the 16-key group (first read)
     const int grp = (lane >> 4) & 1;             // which 16 channels of the 32-channel block
@@ -228,55 +226,67 @@ struct FragBase {
   }
 };
 
-// K fragment F = st*2 + kb of the tile in ring stage KS: 32 keys x 16 channels; this
-// lane reads 8 channels of one key.
-template <class C, int KS, int F>
+// K fragment F = st * kKB + kb of block kb of the tile in ring stage KS, counted from block H: 32 keys x 16
+// channels; this lane reads 8 channels of one key.
+template <class C, int KS, int H, int SLOT, int F>
 __device__ __forceinline__ void read_kfrag(const FragBase<C>& fb) {
-  constexpr int st = F >> 1, kb = F & 1;
-  constexpr int blk = KS * C::kKTileBytes + kb * (32 / C::kPieceRows) * C::kKPieceStride;
-  if constexpr (C::kD == 128) read_k_slot<F % kSlots, blk + (st >> 1) * 64>(fb.k[st & 1]);
-  else read_k_slot<F % kSlots, blk>(fb.k[st]);
+  constexpr int ST = F / C::kKB;
+  constexpr int blk = KS * C::kKTileBytes + (H + F % C::kKB) * (32 / C::kPieceRows) * C::kKPieceStride;
+  read_k_slot<typename C::Acc, SLOT, blk + (ST >> 1) * 64>(fb.k[ST & 1]);
 }
-// V^T fragment F = ks*kDBlocks + db of the tile in ring stage VS: 16 keys x 32 channels.
+// V^T fragment F = ks*kDBlocks + db of the tile in ring stage VS, from block H on: 16 keys x 32 channels.
 // Transposing read: within 16 lanes, lane i supplies row (i/4), 8-byte piece (i%4)
 // of a 4-key x 16-channel block and receives channel i of the 4 keys.  MFMA k-slots
 // 0..7 (lanes < 32) are keys {0..3, 8..11} of the 16-key group and slots 8..15
 // (lanes >= 32) keys {4..7, 12..15}: how the S^T accumulators hold P^T.
-template <class C, int VS, int F>
+template <class C, int VS, int H, int SLOT, int F>
 __device__ __forceinline__ void read_vfrag(const FragBase<C>& fb) {
-  constexpr int ks = F / C::kDBlocks, db = F % C::kDBlocks;
-  read_v_slot<F % kSlots, VS * C::kVTileBytes + ks * (16 / C::kPieceRows) * C::kVPieceStride,
+  constexpr int ks = 2 * H + F / C::kDBlocks, db = F % C::kDBlocks;
+  read_v_slot<typename C::Acc, SLOT, VS * C::kVTileBytes + ks * (16 / C::kPieceRows) * C::kVPieceStride,
               8 / C::kPieceRows * C::kVPieceStride>(fb.v[db]);
 }
 
-// One wave's share of a 64-key x 32-query score tile (vector registers).
-struct STile {
-  f32x16 a[2];  // [key block of 32]
+// One wave's scores of a step's keys x 32 queries (vector registers).
+template <class C>
+struct SBlock {
+  f32x16 a[C::kKB];  // [block of 32 keys]
 };
-// P^T (packed bf16) of one tile as MFMA B operands.
-struct PTile {
-  i32x4 a[2][2];  // [key block of 32][16-key half]
+// P^T (packed bf16) of the same keys as MFMA B operands.
+template <class C>
+struct PBlock {
+  i32x4 a[2 * C::kKB];  // [16 keys]
 };
 
 // Values that are not produced on some control path are declared overwritten there
 // (with unspecified contents that nothing reads), so that the compiler does not have
 // to keep their stale contents alive.
-__device__ __forceinline__ void clear(STile& s) { asm volatile("" : "=v"(s.a[0]), "=v"(s.a[1])); }
-__device__ __forceinline__ void clear(PTile& t) {
-  asm volatile("" : "=v"(t.a[0][0]), "=v"(t.a[0][1]), "=v"(t.a[1][0]), "=v"(t.a[1][1]));
+__device__ __forceinline__ void clear(f32x16& s) { asm volatile("" : "=v"(s)); }
+template <class C>
+__device__ __forceinline__ void clear(SBlock<C>& s) {
+#pragma unroll
+  for (int kb = 0; kb < C::kKB; ++kb) clear(s.a[kb]);
+}
+template <class C>
+__device__ __forceinline__ void used(const SBlock<C>& s) {
+#pragma unroll
+  for (int kb = 0; kb < C::kKB; ++kb) asm volatile("" : : "v"(s.a[kb]));
+}
+template <class C>
+__device__ __forceinline__ void clear(PBlock<C>& t) {
+#pragma unroll
+  for (int i = 0; i < 2 * C::kKB; ++i) asm volatile("" : "=v"(t.a[i]));
 }
 // All-zero P (multiplied with the zero-filled V stage that stands in for "tile -1").
-__device__ __forceinline__ void zero(PTile& t) {
+template <class C>
+__device__ __forceinline__ void zero(PBlock<C>& t) {
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int hf = 0; hf < 2 * C::kKB; ++hf)
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) asm volatile("v_mov_b32 %0, 0" : "=v"(t.a[kb][hf][i]));
+    for (int i = 0; i < 4; ++i) asm volatile("v_mov_b32 %0, 0" : "=v"(t.a[hf][i]));
 }
 
-// The weights of a tile, exp2((score - reference) c2), 32 scores per lane spread evenly over the
-// NS = kNFV + kNFK matrix instructions of a step (kPer per instruction) as a pipeline over them: after
+// The weights of a step's keys, exp2((score - reference) c2), 16 scores per lane and block spread evenly over
+// the kNF matrix instructions of a step (kPer per instruction) as a pipeline over them: after
 // matrix instruction g the exponentials of scores g kPer ..., then the arguments of the next ones, then
 // the sums and packing of finished pairs, so that nothing waits for the instruction before it.
 // (B=1 H=16 T=65536 d=128 without slots 13.46 ms with the exponentials before the matrix instruction, 13.19
@@ -284,12 +294,12 @@ __device__ __forceinline__ void zero(PTile& t) {
 struct Weights {
   float x[2];   // arguments of the next exponentials
   float e[2];   // the pair in progress
-  float sum;    // this lane's weights of the tile so far
+  float sum;    // this lane's weights of the step so far
 };
 template <class C>
-constexpr int kPer = 32 / (C::kNFV + C::kNFK);
+constexpr int kPer = 16 * C::kKB / C::kNF;
 template <class C, int G>  // arguments for matrix instruction G of the step
-__device__ __forceinline__ void weight_args(const STile& s, Weights& w, float mc, float c2) {
+__device__ __forceinline__ void weight_args(const SBlock<C>& s, Weights& w, float mc, float c2) {
   static_for<kPer<C>>([&](auto U) {
     constexpr int u = decltype(U)::value, n = G * kPer<C> + u;
     w.x[u] = __builtin_fmaf(s.a[n / 16][n % 16], c2, -mc);
@@ -305,132 +315,115 @@ __device__ __forceinline__ void weight_exps(Weights& w) {
   });
 }
 template <class C, int G>  // ... and then
-__device__ __forceinline__ void weight_sums(const STile& s, PTile& pt, Weights& w, float mc, float c2) {
-  if constexpr (G + 1 < C::kNFV + C::kNFK) weight_args<C, G + 1>(s, w, mc, c2);
+__device__ __forceinline__ void weight_sums(const SBlock<C>& s, PBlock<C>& pt, Weights& w, float mc, float c2) {
+  if constexpr (G + 1 < C::kNF) weight_args<C, G + 1>(s, w, mc, c2);
   MODA_PIN();
   constexpr int last = G * kPer<C> + kPer<C> - 1;
   if constexpr (last & 1) {
-    constexpr int kb = last / 16, j = (last % 16) / 2;
+    constexpr int j = last / 2;
     const float both = w.e[0] + w.e[1];
     w.sum = last == 1 ? both : w.sum + both;
     int pk = (int)pack_bf16(w.e[0], w.e[1]);
     MODA_ANCHOR(w.sum);
     MODA_ANCHOR(pk);
-    pt.a[kb][j >> 2][j & 3] = pk;
+    pt.a[j >> 2][j & 3] = pk;
   }
 }
-// All of a tile at once (the rare path).
-__device__ __forceinline__ void weigh_tile(const STile& s, PTile& pt, Weights& w, float mc, float c2) {
+// All of them at once (the rare path).
+template <class C>
+__device__ __forceinline__ void weigh_block(const SBlock<C>& s, PBlock<C>& pt, Weights& w, float mc, float c2) {
   w.sum = 0.f;
-  static_for<16>([&](auto Q) {
-    constexpr int kb = decltype(Q)::value / 8, j = decltype(Q)::value % 8;
-    const float e0 = fast_exp2(__builtin_fmaf(s.a[kb][2 * j], c2, -mc));
-    const float e1 = fast_exp2(__builtin_fmaf(s.a[kb][2 * j + 1], c2, -mc));
+  static_for<8 * C::kKB>([&](auto Q) {
+    constexpr int j = decltype(Q)::value, kb = j / 8, i = j % 8 * 2;
+    const float e0 = fast_exp2(__builtin_fmaf(s.a[kb][i], c2, -mc));
+    const float e1 = fast_exp2(__builtin_fmaf(s.a[kb][i + 1], c2, -mc));
     w.sum += e0 + e1;
     int pk = (int)pack_bf16(e0, e1);
     MODA_ANCHOR(w.sum);
     MODA_ANCHOR(pk);
-    pt.a[kb][j >> 2][j & 3] = pk;
+    pt.a[j >> 2][j & 3] = pk;
     MODA_PIN();  // (not all pairs at once: there are no registers for them)
   });
 }
-// Largest score of this lane's query in the tile (two lanes share a query).
-__device__ __forceinline__ float tile_max(const STile& s) {
+// Largest score of this lane's query (two lanes share a query).
+template <class C>
+__device__ __forceinline__ float block_max(const SBlock<C>& s) {
   float mx = s.a[0][0];
 #pragma unroll
-  for (int i = 1; i < 32; ++i) mx = fmaxf(mx, s.a[i / 16][i % 16]);
+  for (int i = 1; i < 16 * C::kKB; ++i) mx = fmaxf(mx, s.a[i / 16][i % 16]);
   return pair_max(mx);
 }
 
-// The LDS reads form one stream per wave: V^T fragments 0..NFV-1 of a tile, then K
-// fragments 0..NFK-1 of the next score tile, then V^T fragments again, ...; the read
-// of the fragment kAhead places further on is issued just before each MFMA, and every
-// fragment lands in slot (its index % kSlots).  LDS operations issued after the read of
-// the fragment that MFMA number F of a phase consumes (kAhead fragments, of 1 or 2
-// reads each):
-template <int F, int NF, int OPS_THIS, int OPS_NEXT>
+// ---- One step: the matrix instructions O^T += V^T P^T of the keys before (kNFV) and S^T = K Q^T of the
+// keys after (kNFK), with the weights of the current keys between them.  Their order at d = 128, where a step
+// has two blocks of 32 keys: all of the first, then all of the second, the blocks in turn; at d = 64, with
+// one block: the two alternate (the second are a chain of dependent ones), the last of the second in
+// front of the last of the first, so that the scores of all but a step's last instruction are complete.  The LDS
+// reads form one stream per wave in the same order: the read of
+// the fragment kAhead places further on is issued just before each MFMA, and every
+// fragment lands in slot (its place in the step % kSlots).
+template <class C, int G>
+struct Place {  // of matrix instruction G of a step (or, from kNF on, of the step after)
+  static constexpr int g = G % C::kNF;
+  static_assert(C::kNFK == C::kNFV, "they alternate");
+  static constexpr bool phases = C::kKB == 2;
+  static constexpr bool is_k = phases ? g >= C::kNFV : g < C::kNF - 2 ? (g & 1) != 0 : g == C::kNF - 2;
+  static constexpr int index = phases ? g % C::kNFV : g / 2;
+};
+// LDS operations issued after the read of the fragment that matrix instruction G consumes: kAhead
+// fragments, of 1 (K) or 2 (V^T) reads each.
+template <class C, int G, int J = 1>
 constexpr int ops_after() {
-  int n = 0;
-  for (int j = 1; j <= kAhead; ++j) n += (F + j < NF) ? OPS_THIS : OPS_NEXT;
-  return n;
+  if constexpr (J > C::kAhead) return 0;
+  else return (Place<C, G + J>::is_k ? 1 : 2) + ops_after<C, G, J + 1>();
 }
-
-// ---- matrix phase 1: S^T(next) = K Q^T over the 64-key tile in K stage KS (kNFK
-// MFMAs), with the second half of the CURRENT tile's weights between the MFMAs when WITH_EXP.
-// The first kAhead K fragments were requested by the
-// phase before; this one requests the first V^T fragments of stage VSN for the phase
-// after.  The hardware does not interlock a matrix result against a vector-ALU reader:
-// the caller keeps at least 12 issue slots between an MFMA and the first read of its result (an MFMA
-// issued in between counts 8): key block 0 of `nxt` is complete one MFMA before the end, and the weights of
-// the tile start with it, after the last pair's sum and pack and the comparison of the tile's sum.
-// `hook(integral_constant<m>)` runs after MFMA number m: the caller spreads its
-// global->LDS copy instructions there, one at a time, so that their issue time is
-// hidden behind matrix work as well.
 struct NoHook {
   template <class I>
   __device__ __forceinline__ void operator()(I) const {}
 };
-template <class C, int KS, int VSN, bool WITH_EXP, class Hook = NoHook>
-__device__ __forceinline__ void qk_phase(STile& nxt, const STile& cur, PTile& pcur, Weights& w, float mc, float c2,
-                                         const FragBase<C>& fb, Hook hook = Hook{}) {
-  constexpr int NF = C::kNFK;
-  static_for<NF>([&](auto F) {
-    constexpr int f = decltype(F)::value;
-    constexpr int st = f >> 1, kb = f & 1;
-    constexpr int pf = f + kAhead;
-    if constexpr (pf < NF) read_kfrag<C, KS, (pf < NF ? pf : 0)>(fb);
-    else read_vfrag<C, VSN, (pf < NF ? 0 : pf - NF)>(fb);
-    lds_wait<ops_after<f, NF, 1, 2>()>();
-    mfma_s<f % kSlots, st, st == 0>(nxt.a[kb]);
+// H: block of their tiles that the V and K fragments start with; HN: those of the step after.  VS / KS: ring
+// stage of the V / K tile; VSN, KSN: of the step after.
+// The hardware does not interlock a matrix result against a vector-ALU reader:
+// the caller keeps at least 12 issue slots between an MFMA and the first read of its result (an MFMA
+// issued in between counts 8): the scores that the step after starts with are complete one MFMA before the end,
+// and behind it come the last exponentials, sums and packs, and the comparison of the sum.
+// `before(integral_constant<g>)` runs before the LDS read that precedes MFMA number g, `after` behind it: the
+// caller spreads its global->LDS copy instructions there, one at a time, so that their issue time is
+// hidden behind matrix work as well.
+template <class C, int H, int VS, int KS, int HN, int VSN, int KSN, class Before, class After>
+__device__ __forceinline__ void block_step(const SBlock<C>& cur, SBlock<C>& nxt, const PBlock<C>& pprev, PBlock<C>& pcur,
+                                           Weights& w, float mc, float c2, const FragBase<C>& fb, Before before, After after) {
+  using M = typename C::Acc;
+  weight_args<C, 0>(cur, w, mc, c2);
+  static_for<C::kNF>([&](auto GI) {
+    constexpr int g = decltype(GI)::value;
+    constexpr int pf = g + C::kAhead;
+    using At = Place<C, g>;
+    using Next = Place<C, pf>;
+    constexpr int h = pf < C::kNF ? H : HN;
+    before(GI);
+    if constexpr (Next::is_k) read_kfrag<C, (pf < C::kNF ? KS : KSN), h, pf % M::kSlots, Next::index>(fb);
+    else read_vfrag<C, (pf < C::kNF ? VS : VSN), h, pf % M::kSlots, Next::index>(fb);
+    lds_wait<ops_after<C, g>()>();
+    if constexpr (At::is_k) mfma_s<M, g % M::kSlots, At::index / C::kKB, At::index / C::kKB == 0>(nxt.a[At::index % C::kKB]);
+    else mfma_o<M, At::index % C::kDBlocks, g % M::kSlots>(pprev.a[At::index / C::kDBlocks]);
     MODA_PIN();
-    if constexpr (WITH_EXP) {
-      weight_exps<C, C::kNFV + f>(w);
-      MODA_PIN();
-      weight_sums<C, C::kNFV + f>(cur, pcur, w, mc, c2);
-    }
-    hook(F);
+    weight_exps<C, g>(w);
     MODA_PIN();
-  });
-}
-
-// ---- matrix phase 2: O^T += V^T P^T over the 64-key tile in V stage VS (kNFV MFMAs), with the first
-// half of the current tile's weights between the MFMAs and the first K fragments of stage KSN requested
-// for the phase after, unless it is the wave's LAST tile.
-// `before_k(...)` runs just before the first K fragment of stage KSN is requested (all V^T
-// fragments of this tile have been requested by then): where the 2-stage geometry awaits
-// the copies of that K tile and synchronises the workgroup.
-template <class C, int VS, int KSN, bool LAST, class BeforeK = NoHook>
-__device__ __forceinline__ void pv_phase(const PTile& pin, const STile& s, PTile& pout, Weights& w, float mc, float c2,
-                                         const FragBase<C>& fb, BeforeK before_k = BeforeK{}) {
-  constexpr int DB = C::kDBlocks;
-  constexpr int NF = C::kNFV;
-  if constexpr (!LAST) weight_args<C, 0>(s, w, mc, c2);
-  static_for<NF>([&](auto F) {
-    constexpr int f = decltype(F)::value;
-    constexpr int ks = f / DB, db = f % DB;
-    constexpr int kb = ks >> 1, hf = ks & 1;
-    constexpr int pf = f + kAhead;
-    if constexpr (pf == NF) before_k(F);
-    if constexpr (pf < NF) read_vfrag<C, VS, (pf < NF ? pf : 0)>(fb);
-    else if constexpr (!LAST) read_kfrag<C, KSN, (pf < NF ? 0 : pf - NF)>(fb);
-    lds_wait<ops_after<f, NF, 2, LAST ? 0 : 1>()>();
-    mfma_o<db, f % kSlots>(pin.a[kb][hf]);
-    MODA_PIN();
-    if constexpr (!LAST) {
-      weight_exps<C, f>(w);
-      MODA_PIN();
-      weight_sums<C, f>(s, pout, w, mc, c2);
-    }
+    weight_sums<C, g>(cur, pcur, w, mc, c2);
+    after(GI);
     MODA_PIN();
   });
 }
 
-template <int D, int W>
-__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void moda_fwd_bf16_kernel(FwdParams p) {
-  using C = FwdCfg<D, W>;
+template <int D, int W, int PS>
+__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))) void moda_fwd_bf16_kernel(FwdParams p) {
+  using C = FwdCfg<D, W, PS>;
   constexpr int kThreads = C::kThreads, kBM = C::kBM, kStages = C::kStages;
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::kLds];
-  reserve_acc_registers();
+  using M = typename C::Acc;
+  constexpr int kAccO = M::kO;
+  reserve_acc_registers<PS>();
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -455,10 +448,20 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   // K/V of the heads in progress fit its L2 (measured at T = 65536, 2 heads per die: one at
   // a time -4 %; at T = 4096, 16 heads per die: two at a time -4 %, one at a time slower
   // again, because the heaviest tiles of a head then start late).
-  int tbh = blockIdx.x % NBH;
-  int tile_idx = blockIdx.x / NBH;
+  //
+  // A grid that is resident all at once fills the 32 units of a die in layers (ids equal mod 8, 32 at a
+  // time).  Every other layer takes its tiles in reverse order there: a heavy tile shares its unit with a light one.
+  const bool one_round = (int)gridDim.x <= (W == 8 ? 256 : 512) * (PS / 2);
+  int id = blockIdx.x;
+  if (one_round && p.causal && ((id >> 8) & 1)) {
+    const int die = id & 7, r = id >> 3, r0 = r & ~31;
+    const int layer = min(32, (((int)gridDim.x - die + 7) >> 3) - r0);
+    id = (r0 + layer - 1 - (r - r0)) * 8 + die;
+  }
+  int tbh = id % NBH;
+  int tile_idx = id / NBH;
   if (p.head_group > 0 && NBH % (8 * p.head_group) == 0) {
-    const int die = blockIdx.x & 7, r = blockIdx.x >> 3;       // r-th workgroup of this die
+    const int die = id & 7, r = id >> 3;       // r-th workgroup of this die
     const int per_group = p.head_group * p.n_qtiles;
     const int grp = r / per_group, w = r % per_group;
     tile_idx = w / p.head_group;
@@ -510,6 +513,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     constexpr int LPR = C::kChunks;   // lanes per query row: each owns 8 channels (16 B)
     constexpr int RPS = 64 / LPR;     // query rows per wave step
     constexpr int NIT = 32 / RPS;     // row steps of the wave's 32 rows
+    constexpr int kDepthChunk = C::kDepthChunk;
     const int rg = lane / LPR;
     const int l16 = lane % LPR;       // owns channels 8*l16 .. 8*l16+7
     const size_t drow = (size_t)p.depth_alloc * C::kRowBytes;  // bytes of one position's slots
@@ -707,7 +711,6 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   // d=128, 15 slots 105.8 / 99.5; B=3 H=16 T=1000 d=64, 12 slots 46.9 / 43.2; B=1 H=5 T=6000 d=128, 31
   // slots 142 / 135; with two rounds and more of workgroups up to 11 % slower: B=4 H=16 T=2000 d=64, 24 slots
   // 165 / 183).
-  const bool one_round = (int)gridDim.x <= (W == 8 ? 256 : 512);
   const bool depth_first = L > 0 && (one_round ? 2 * tile_idx >= p.n_qtiles : ((blockIdx.x >> 3) & 1) != 0);
   // Two implementations of the depth slots: on the vector ALUs in the row-major mapping
   // (depth_phase above), or on the matrix pipe as extra key blocks (depth_blocks below).
@@ -766,23 +769,22 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
   // ---- global -> LDS copies of one K or V tile.  One wave instruction moves one 1 KB
   // piece, so the chunk permutation is applied by choosing which global chunk each lane
-  // fetches; one per-lane offset serves all K copies and one all V copies (at d = 128 the
-  // permutations only look at the row index inside a piece; at d = 64 the K permutation also
-  // looks at the parity of the piece, a constant XOR for a wave's odd pieces).
+  // fetches; one per-lane offset serves all K copies and one all V copies (the
+  // permutations only look at the row index inside a piece).
   // A wave copies pieces wave * kInstPerWave + i, i < kInstPerWave, of every tile.
   int k_goff, v_goff;
   {
     const int lane = tid & 63;
     const int j = lane / C::kChunks;   // row inside the piece
     const int pc = lane % C::kChunks;  // chunk position this lane fills
-    const int piece0 = wave * C::kInstPerWave;  // the wave's first piece
-    const int kc = C::kD == 128 ? (pc ^ (j & 3)) : (pc ^ ((((piece0 & 1) * C::kPieceRows + j) >> 1) & (C::kChunks - 1)));
+    const int kc = pc ^ C::kswz(j);
     const int vc = (((pc >> 2) ^ C::vswz(j)) << 2) | (pc & 3);
     k_goff = j * C::kRowBytes + kc * 16;
     v_goff = j * C::kRowBytes + vc * 16;
   }
-  static_assert(C::vswz(0) == C::vswz(C::kPieceRows) && C::vswz(1) == C::vswz(1 + C::kPieceRows),
-                "the V permutation repeats from piece to piece");
+  static_assert(C::vswz(0) == C::vswz(C::kPieceRows) && C::vswz(1) == C::vswz(1 + C::kPieceRows) &&
+                    C::kswz(0) == C::kswz(C::kPieceRows) && C::kswz(2) == C::kswz(2 + C::kPieceRows),
+                "the permutations repeat from piece to piece");
   const unsigned smem_addr = (unsigned)(size_t)(lds_ptr)smem;
   const i32x4 k_buf = make_raw_buffer(Kb, (unsigned)T * C::kRowBytes);
   const i32x4 v_buf = make_raw_buffer(Vb, (unsigned)T * C::kRowBytes);
@@ -799,16 +801,9 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     constexpr int i = decltype(I)::value;
     constexpr int stride = is_k ? C::kKPieceStride : C::kVPieceStride;
     const int soff = __builtin_amdgcn_readfirstlane(kt * C::kGTileBytes) + wave_goff;
-    int goff = is_k ? k_goff : v_goff;
-    if constexpr (is_k && C::kD == 64 && (i & 1) != 0) {
-      // odd piece of an even first piece (kInstPerWave is even whenever it is not 1): the row
-      // index has bit 3 set, which flips bit 2 of the chunk permutation
-      static_assert(C::kInstPerWave % 2 == 0, "a wave's first piece is even");
-      asm volatile("v_xor_b32 %0, %1, %2" : "=v"(goff) : "n"(4 << 4), "v"(k_goff));
-    }
     copy16_to_lds<decltype(STAGE_OFF)::value + i * (stride - 1024), i * 1024,
                   is_k ? 0 : -(kStages - C::kVAhead) * C::kGTileBytes>(
-        buf, goff, soff, (is_k ? wave_lds : wave_lds_v) + stage_off);
+        buf, is_k ? k_goff : v_goff, soff, (is_k ? wave_lds : wave_lds_v) + stage_off);
   };
   auto issue_tile = [&](auto IS_K, auto STAGE_OFF, const i32x4& buf, int kt) {
     static_for<C::kInstPerWave>([&](auto I) { issue_one(IS_K, I, STAGE_OFF, buf, kt); });
@@ -822,13 +817,12 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     return std::integral_constant<int, C::kVBase + decltype(STAGE)::value * C::kVTileBytes>{};
   };
 
-  auto mask_tile = [&](STile& s, int kt) {
-    const int k0 = kt * kBN;
+  auto mask_block = [&](SBlock<C>& s, int k0) {
     const int lane = lane_id(), l32 = lane & 31, hi = lane >> 5;
     const int qi = qw0 + (l32 >> gt_shift);
     const int lim = p.causal ? min(qi, T - 1) : T - 1;  // last visible key
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < C::kKB; ++kb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int key = k0 + kb * 32 + (i >> 2) * 8 + hi * 4 + (i & 3);
@@ -858,7 +852,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     constexpr int PR = C::kPieceRows, NP = 32 / PR;  // rows per 1 KB piece, pieces per block
     constexpr int kDK = NP * C::kKPieceStride, kDV = NP * C::kVPieceStride, kDWave = kDK + kDV;
     static_assert(W * kDWave <= C::kLds, "one block per wave fits the rings");
-    static_assert(C::kDSteps <= kSlots && 2 * C::kDBlocks <= kSlots, "a block's fragments fit the slots");
+    static_assert(C::kDSteps <= M::kSlots && 2 * C::kDBlocks <= M::kSlots, "a block's fragments fit the slots");
     const int lane = lane_id(), l32 = lane & 31, hi = lane >> 5;
     const int nkeys = PW * L;
     const int nblk = (nkeys + 31) >> 5;
@@ -884,7 +878,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       constexpr bool is_k = decltype(IS_K)::value;
       static_for<NP>([&](auto P) {
         constexpr int pi = decltype(P)::value;
-        const int kc = C::kD == 128 ? (pc ^ (j & 3)) : (pc ^ (((pi & 1) * 4 + (j >> 1)) & (C::kChunks - 1)));
+        const int kc = pc ^ C::kswz(j);
         const unsigned kk = (unsigned)(blk * 32 + pi * PR + j);          // key in the wave's enumeration
         const unsigned pos = L == 1 ? kk : __umulhi(kk, p.depth_magic);  // kk / L (exact for kk * L < 2^32)
         const unsigned slot = kk - pos * (unsigned)L;
@@ -905,22 +899,22 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       const bool more = blk + 1 < nblk;
       // S^T = K Q^T over the block's 32 keys (the V copies of this block were issued after its K copies)
       wait_copies_but<NP>();
-      STile sd;
+      f32x16 sd;
+      clear(sd);
       static_for<C::kDSteps>([&](auto ST) {
         constexpr int st = decltype(ST)::value;
-        if constexpr (C::kD == 128) read_k_slot<st % kSlots, (st >> 1) * 64>(fb.k[st & 1] + dwave);
-        else read_k_slot<st % kSlots, 0>(fb.k[st] + dwave);
+        read_k_slot<M, st % M::kSlots, (st >> 1) * 64>(fb.k[st & 1] + dwave);
       });
       lds_wait<0>();
       static_for<C::kDSteps>([&](auto ST) {
         constexpr int st = decltype(ST)::value;
-        mfma_s<st % kSlots, st, st == 0>(sd.a[0]);
+        mfma_s<M, st % M::kSlots, st, st == 0>(sd);
       });
       if (more) copy_half(kHalfK, blk + 1);  // the K region has been read
       MODA_PIN();
       MODA_NOP(15);  // the matrix results have landed before the vector ALUs read them
       MODA_NOP(15);
-      asm volatile("" : "+v"(sd.a[0]));  // (and no reader is moved up before the wait)
+      asm volatile("" : "+v"(sd));  // (and no reader is moved up before the wait)
       // mask: key r of the block is attended by this lane's query iff it is a slot of its position
       const unsigned lo = (unsigned)((l32 >> gt_shift) * L - blk * 32);  // first key of the position, relative to the block
       float vmax = -INFINITY;
@@ -928,8 +922,8 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       for (int i = 0; i < 16; ++i) {
         const unsigned r = (unsigned)((i >> 2) * 8 + hi * 4 + (i & 3));
         const bool vis = (r - lo) < (unsigned)L;
-        sd.a[0][i] = vis ? sd.a[0][i] : -INFINITY;
-        vmax = fmaxf(vmax, sd.a[0][i]);
+        sd[i] = vis ? sd[i] : -INFINITY;
+        vmax = fmaxf(vmax, sd[i]);
       }
       const float mxd = pair_max(vmax);
       const bool raise = (mxd - m_run) * c2 > 8.f;  // false when the query has no key in this block
@@ -944,14 +938,14 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         MODA_NOP(7);
       }
       const float mc = m_run == -INFINITY ? 0.f : m_run * c2;
-      PTile pd;
+      i32x4 pd[2];
       float lsum = 0.f;
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const float e0 = fast_exp2(sd.a[0][2 * q] * c2 - mc);
-        const float e1 = fast_exp2(sd.a[0][2 * q + 1] * c2 - mc);
+        const float e0 = fast_exp2(sd[2 * q] * c2 - mc);
+        const float e1 = fast_exp2(sd[2 * q + 1] * c2 - mc);
         lsum += e0 + e1;
-        pd.a[0][q >> 2][q & 3] = (int)pack_bf16(e0, e1);
+        pd[q >> 2][q & 3] = (int)pack_bf16(e0, e1);
       }
       l_run += lsum;
       // O^T += V^T P^T (the next block's K copies, if any, were issued after this block's V copies)
@@ -959,13 +953,13 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       else wait_copies_but<0>();
       static_for<2 * C::kDBlocks>([&](auto F) {
         constexpr int f = decltype(F)::value, ks = f / C::kDBlocks, db = f % C::kDBlocks;
-        read_v_slot<f % kSlots, ks * (16 / PR) * C::kVPieceStride, 8 / PR * C::kVPieceStride>(
+        read_v_slot<M, f % M::kSlots, ks * (16 / PR) * C::kVPieceStride, 8 / PR * C::kVPieceStride>(
             fb.v[db] + (dwave + kDK - C::kVBase));
       });
       lds_wait<0>();
       static_for<2 * C::kDBlocks>([&](auto F) {
         constexpr int f = decltype(F)::value, ks = f / C::kDBlocks, db = f % C::kDBlocks;
-        mfma_o<db, f % kSlots>(pd.a[0][ks]);
+        mfma_o<M, db, f % M::kSlots>(pd[ks]);
       });
       if (more) copy_half(kHalfV, blk + 1);  // the V region has been read
       MODA_PIN();
@@ -989,78 +983,120 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   wait_copies_but<0>();
   __syncthreads();
 
-  STile sA, sB;
-  PTile pA, pB;
+  // Steps alternate between sA / pA (scores and weights of the step's keys) and sB / pB, the first in sA.
+  SBlock<C> sA, sB;
+  PBlock<C> pA, pB;
   Weights w;
-  zero(pA);
-  clear(pB);
+  clear(sA);
+  clear(sB);
+  zero(pB);
+  clear(pA);
   {
-    static_for<kAhead>([&](auto I) { read_kfrag<C, 0, decltype(I)::value>(fb); });
-    qk_phase<C, 0, kStages - 1, false>(sA, sA, pA, w, 0.f, c2, fb);
+    static_assert(C::kDSteps <= M::kSlots, "a block's fragments fit the slots");
+    static_for<C::kKB>([&](auto KB) {
+      constexpr int kb = decltype(KB)::value;
+      static_for<C::kDSteps>([&](auto ST) {
+        constexpr int st = decltype(ST)::value;
+        read_kfrag<C, 0, 0, st, st * C::kKB + kb>(fb);
+      });
+      lds_wait<0>();
+      static_for<C::kDSteps>([&](auto ST) {
+        constexpr int st = decltype(ST)::value;
+        mfma_s<M, st, st, st == 0>(sA.a[kb]);
+      });
+    });
     MODA_PIN();
     MODA_NOP(15);
-    if (wave_last == 0 && needs_mask(0)) mask_tile(sA, 0);
+    MODA_ANCHOR(sA.a[0]);
+    MODA_ANCHOR(sA.a[C::kKB - 1]);
+    if (wave_last == 0 && needs_mask(0)) mask_block(sA, 0);
     // the first reference (a query whose scores are all -inf so far takes 0: weights 0, empty state)
-    const float mx = tile_max(sA);
+    const float mx = block_max(sA);
     if (m_run == -INFINITY) m_run = mx == -INFINITY ? 0.f : mx;
+    static_for<C::kAhead>([&](auto I) {  // the first fragments of the first step
+      constexpr int i = decltype(I)::value, h = C::kKB == 1;
+      if constexpr (Place<C, i>::is_k) read_kfrag<C, 0, h, i, Place<C, i>::index>(fb);
+      else read_vfrag<C, kStages - 1, h, i, Place<C, i>::index>(fb);
+    });
   }
 
-  // ---- steady state.  Step kt, kt % 4 == S (scores of tile kt are in `cur`, P of tile
-  // kt-1 in `pprev`):
-  //   matrix pipe : O += P V (tile kt-1)          | S(next) = K Q^T (tile kt+1)
-  //   vector ALUs : weights of tile kt, key block | ... key block 1
-  //                 0                             |
-  //   in between  : wait for the copies issued two steps ago, barrier; the copies of
-  //                 K tile kt+4 and V tile kt+2 into the stages just vacated ride along
-  //                 with the second matrix phase.
-  // No row maximum is taken: the weights of a tile are formed with the reference of the tiles before,
+  // ---- steady state, a step per tile (d = 128) or per block of 32 keys (d = 64); scores of its keys in `cur`,
+  // P of the keys before in `pprev`:
+  //   matrix pipe : O += P V (keys before) and S(next) = K Q^T (keys after)
+  //   vector ALUs : weights of the keys
+  // At d = 64 a step of half a tile lets a wave do with 128 registers, so that FOUR waves share a SIMD: a
+  // wave's own chain of instructions (8 cycles from one to the next, 24 per exponential) takes nearly as long
+  // as two waves have between them (matrix pipe and vector ALUs each idle half of the time).  B=1 Hq=64 Hk=8 T=16384
+  // d=64: 2.14 -> 1.97 ms, with 64 slots 2.42 -> 2.19.  At d = 128 the same step is 1.5 % slower (13.28 -> 13.49 ms at
+  // T=65536), and there are no registers for a third wave.
+  // No row maximum is taken: the weights of a step are formed with the reference of the steps before,
   // and their sum, which the normaliser needs anyway, tells afterwards whether that was good enough.  As
-  // long as a lane's 32 weights sum to at most 2^8, none exceeds 2^8, which fp32 sums and bf16 P hold
+  // long as a lane's weights sum to at most 2^8, none exceeds 2^8, which fp32 sums and bf16 P hold
   // without loss, and the final division is unchanged.  Otherwise (and for NaN) the rare path raises the
-  // reference to the row maximum, rescales the accumulators and forms the tile's weights anew, before they
+  // reference to the row maximum, rescales the accumulators and forms the step's weights anew, before they
   // are multiplied with anything.  (The maximum, its exchange between two lanes, comparison and branch stood
   // before the first exponential of every tile: 24 of 150 vector instructions, and nothing to overlap with.
   // B=1 H=16 T=65536 d=128: 14.2 -> 13.2 ms, 1.33 PFLOP/s; B=1 Hq=64 Hk=8 T=16384 d=64: 2.49 -> 2.09 ms, 1.05.)
-  // Every step issues the same number of copies (tiles past the end of the tensor are
+  // Once per tile: wait for the copies issued two tiles ago, barrier (kSyncAt); the copies of
+  // K tile kt+4 and V tile kt+2 into the stages just vacated ride along with the instructions after it.
+  // Every tile issues the same number of copies (tiles past the end of the tensor are
   // out of range of the raw buffer: nothing is fetched), so "all but the newest
   // kPending copies have landed" always means: K tile kt+1 and V tile kt, which are
-  // read next, are complete (with 4 stages K tile kt+2 too: one step of slack).
-  // The stages written are those of K tile kt (its scores were taken in step kt-1) and,
-  // with 4 stages, of V tile kt-2, with 2 stages of V tile kt-1 (consumed in the first
-  // half of this step): every wave is past those reads once it has passed the barrier.
-  //
-  // Where the barrier stands: with 4 stages between the two matrix phases.  With 2 stages
-  // K tile kt+1 was only requested in step kt-1, and its first fragments are read at the end
-  // of the first matrix phase: the synchronisation point moves to just before that read.  All
-  // V^T fragment reads of tile kt-1 have been issued by then (LDS serves requests in order, and a
-  // copy into that stage is only requested after the barrier, so it lands after them).
-  constexpr bool kEarlySync = kStages == 2;
+  // read next, are complete (with 4 stages K tile kt+2 too: one tile of slack).
+  // The stages written are those of K tile kt and, with 4 stages, of V tile kt-2, with 2 stages of V tile
+  // kt-1.  Where the barrier stands: d = 64, in the step of the tile's first half, before the first read of V
+  // tile kt; d = 128, with 4 stages between the two phases, with 2 stages before the first read of K tile
+  // kt+1, which was only requested in the step before.  Every read of the stages that are written after it has been
+  // issued by then (LDS serves requests in order, and a copy is only requested after the barrier, so it
+  // lands after them).
   auto sync_copies = [&]() {
     wait_copies_but<C::kPending>();
     __syncthreads();
   };
-  // step kt <= wave_last
-  auto step = [&](auto SI, int kt, STile& cur, STile& nxt, const PTile& pprev, PTile& pcur) {
+  // the step's sum is in; `k_next`: first key of the step after, whose scores were taken
+  auto end_step = [&](const SBlock<C>& cur, SBlock<C>& nxt, PBlock<C>& pcur, int k_next) __attribute__((always_inline)) {
+    if (__builtin_amdgcn_ballot_w64(!(w.sum <= 256.f)) != 0) {
+      // Rare path.  (The products of the steps before have retired.)
+      MODA_PIN();
+      MODA_NOP(15);
+      MODA_NOP(15);
+      const float m_new = fmaxf(m_run, block_max(cur));
+      const float alpha = m_new == m_run ? 1.0f : fast_exp2((m_run - m_new) * c2);
+      m_run = m_new;
+      l_run *= alpha;
+      static_for<C::kDBlocks * 16>([&](auto R) { scale_acc<kAccO + decltype(R)::value>(alpha); });
+      MODA_PIN();
+      MODA_NOP(7);  // register writes settle before the next MFMA
+      weigh_block(cur, pcur, w, m_new * c2, c2);
+    }
+    l_run += w.sum;
+    if (k_next / kBN == wave_last && needs_mask(wave_last)) {
+      MODA_PIN();
+      MODA_NOP(15);
+      mask_block(nxt, k_next);
+    }
+    MODA_ANCHOR(nxt.a[0]);  // (no reader is moved up)
+    MODA_ANCHOR(nxt.a[C::kKB - 1]);
+  };
+  // tile kt <= wave_last
+  auto step = [&](auto SI, int kt) __attribute__((always_inline)) {
     constexpr int S = decltype(SI)::value;
     constexpr int VS_PREV = (S + kStages - 1) % kStages;  // V tile kt-1
     constexpr int KS_NEXT = (S + 1) % kStages;            // K tile kt+1
-    constexpr int VS_CUR = S % kStages;                   // V tile kt
-    auto before_k = [&](auto) {
-      if constexpr (kEarlySync) sync_copies();
+    constexpr int ST_CUR = S % kStages;                   // K tile kt, V tile kt
+    auto sync = [&](auto GI) {
+      if constexpr (decltype(GI)::value == C::kSyncAt) sync_copies();
     };
-    const float mc = m_run * c2;
-    pv_phase<C, VS_PREV, KS_NEXT, false>(pprev, cur, pcur, w, mc, c2, fb, before_k);
-    if constexpr (!kEarlySync) sync_copies();
-    // this step's copies ride along, spread evenly over the MFMAs of the phase; the V tile is kt + kVAhead
+    // this tile's copies ride along, spread evenly over the MFMAs from number `first` on; the V tile is kt + kVAhead
     // (for this wave's last tile the next K tile is not needed; it is read and
     //  multiplied all the same, which keeps the loop body free of branches)
-    constexpr auto so_k = k_stage_off(std::integral_constant<int, S % kStages>{});
+    constexpr auto so_k = k_stage_off(std::integral_constant<int, ST_CUR>{});
     constexpr auto so_v = v_stage_off(std::integral_constant<int, (S + C::kVAhead) % kStages>{});
-    auto hook = [&](auto M) {
-      constexpr int m = decltype(M)::value;
-      constexpr int every = C::kNFK / (2 * C::kInstPerWave) >= 4 ? 4 : C::kNFK / (2 * C::kInstPerWave);
+    auto copies = [&](auto GI) {
+      constexpr int first = C::kKB == 1 ? 0 : C::kNFV, m = decltype(GI)::value - first;
+      constexpr int every = (C::kNF - first) / (2 * C::kInstPerWave) >= 4 ? 4 : (C::kNF - first) / (2 * C::kInstPerWave);
       static_assert(every >= 1, "at most one copy per MFMA");
-      if constexpr (m % every == every / 2 && m / every < 2 * C::kInstPerWave) {
+      if constexpr (m >= 0 && m % every == every / 2 && m / every < 2 * C::kInstPerWave) {
         constexpr int i = m / every;
         if constexpr (i < C::kInstPerWave)
           issue_one(kIsK, std::integral_constant<int, i>{}, so_k, k_buf, kt + kStages);
@@ -1069,25 +1105,16 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                     v_buf, kt + kStages);
       }
     };
-    qk_phase<C, KS_NEXT, VS_CUR, true>(nxt, cur, pcur, w, mc, c2, fb, hook);
-    if (__builtin_amdgcn_ballot_w64(!(w.sum <= 256.f)) != 0) {
-      // Rare path.  (The products of the tiles before have long retired.)
-      MODA_PIN();
-      MODA_NOP(15);
-      const float m_new = fmaxf(m_run, tile_max(cur));
-      const float alpha = m_new == m_run ? 1.0f : fast_exp2((m_run - m_new) * c2);
-      m_run = m_new;
-      l_run *= alpha;
-      static_for<C::kDBlocks * 16>([&](auto R) { scale_acc<kAccO + decltype(R)::value>(alpha); });
-      MODA_PIN();
-      MODA_NOP(7);  // register writes settle before the next MFMA
-      weigh_tile(cur, pcur, w, m_new * c2, c2);
-    }
-    l_run += w.sum;
-    if (kt + 1 == wave_last && needs_mask(kt + 1)) {
-      MODA_PIN();
-      MODA_NOP(15);
-      mask_tile(nxt, kt + 1);
+    if constexpr (C::kKB == 1) {
+      block_step<C, 1, VS_PREV, ST_CUR, 0, ST_CUR, KS_NEXT>(sA, sB, pB, pA, w, m_run * c2, c2, fb, sync, NoHook{});
+      end_step(sA, sB, pA, kt * kBN + 32);
+      block_step<C, 0, ST_CUR, KS_NEXT, 1, ST_CUR, KS_NEXT>(sB, sA, pA, pB, w, m_run * c2, c2, fb, NoHook{}, copies);
+      end_step(sB, sA, pB, kt * kBN + 64);
+    } else {
+      SBlock<C>&cur = S % 2 == 0 ? sA : sB, &nxt = S % 2 == 0 ? sB : sA;
+      PBlock<C>&pcur = S % 2 == 0 ? pA : pB, &pprev = S % 2 == 0 ? pB : pA;
+      block_step<C, 0, VS_PREV, KS_NEXT, 0, ST_CUR, KS_NEXT>(cur, nxt, pprev, pcur, w, m_run * c2, c2, fb, sync, copies);
+      end_step(cur, nxt, pcur, kt * kBN + 64);
     }
   };
   static_assert(kUnroll == 4, "the four steps below");
@@ -1095,31 +1122,47 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   // steps made the compiler merge all of them, with registers it does not have.)
   int kt = 0;
   for (; kt + 3 <= wave_last; kt += 4) {
-    step(std::integral_constant<int, 0>{}, kt, sA, sB, pA, pB);
-    step(std::integral_constant<int, 1>{}, kt + 1, sB, sA, pB, pA);
-    step(std::integral_constant<int, 2>{}, kt + 2, sA, sB, pA, pB);
-    step(std::integral_constant<int, 3>{}, kt + 3, sB, sA, pB, pA);
+    step(std::integral_constant<int, 0>{}, kt);
+    step(std::integral_constant<int, 1>{}, kt + 1);
+    step(std::integral_constant<int, 2>{}, kt + 2);
+    step(std::integral_constant<int, 3>{}, kt + 3);
   }
-  if (kt <= wave_last) {
-    step(std::integral_constant<int, 0>{}, kt, sA, sB, pA, pB);
-  } else {
-    clear(sB);
-    clear(pB);
-  }
-  if (kt + 1 <= wave_last) step(std::integral_constant<int, 1>{}, kt + 1, sB, sA, pB, pA);
-  if (kt + 2 <= wave_last) step(std::integral_constant<int, 2>{}, kt + 2, sA, sB, pA, pB);
-  // The products of the wave's last tile, whose P is in pB if an odd number of steps remained.
-  if (((wave_last + 1) & 1) != 0) pA = pB;
+  if (kt <= wave_last) step(std::integral_constant<int, 0>{}, kt);
+  if (kt + 1 <= wave_last) step(std::integral_constant<int, 1>{}, kt + 1);
+  if (kt + 2 <= wave_last) step(std::integral_constant<int, 2>{}, kt + 2);
+  // The products of the wave's last step, whose P is in pA if it has walked an odd number of steps.
+  if (C::kKB == 2 && (wave_last & 1) == 0) pB = pA;
   {
     const int off = (wave_last % kStages) * C::kVTileBytes;
     FragBase<C> at = fb;
 #pragma unroll
     for (int db = 0; db < C::kDBlocks; ++db) at.v[db] += off;
-    pv_phase<C, 0, 0, true>(pA, sA, pB, w, 0.f, c2, at);
+    // Of the fragments that the last step requested, the V^T ones are in their places; the others' slots are free.
+    constexpr int H = C::kKB == 1, have = Place<C, 1>::is_k ? C::kAhead / 2 : C::kAhead;
+    auto slot = [](auto F) {
+      constexpr int f = decltype(F)::value, step = C::kAhead / have;
+      return std::integral_constant<int, f < have ? f * step : f < C::kAhead ? (f - have) * step + 1 : f % M::kSlots>{};
+    };
+    auto fetch = [&](auto F) {
+      read_vfrag<C, 0, H, decltype(slot(F))::value, decltype(F)::value>(at);
+    };
+    constexpr int ahead = have < C::kAhead ? C::kNFV : C::kAhead;  // fragments requested before the first product
+    static_assert(ahead <= M::kSlots, "they fit the slots");
+    static_for<ahead - have>([&](auto I) { fetch(std::integral_constant<int, decltype(I)::value + have>{}); });
+    static_for<C::kNFV>([&](auto F) {
+      constexpr int f = decltype(F)::value;
+      constexpr int last = f + ahead < C::kNFV ? f + ahead : C::kNFV - 1;  // the newest request
+      constexpr int later = 2 * (last - (f < have && ahead > have ? have - 1 : f));
+      if constexpr (f + ahead < C::kNFV) fetch(std::integral_constant<int, f + ahead>{});
+      lds_wait<(later < 15 ? later : 15)>();
+      mfma_o<M, f % C::kDBlocks, decltype(slot(F))::value>(pB.a[f / C::kDBlocks]);
+      MODA_PIN();
+    });
   }
-  // (the score tiles are declared used only here: the last one, which nobody reads, is written while the
-  // instructions above are issued, and nothing else may be put into its registers)
-  asm volatile("" : : "v"(sA.a[0]), "v"(sA.a[1]), "v"(sB.a[0]), "v"(sB.a[1]));
+  // (the scores are declared used only here: the last ones, which nobody reads, are written while the
+  // instructions above are issued, and nothing else may be put into their registers)
+  used(sA);
+  used(sB);
   // the steps in which this wave only helps copy the tiles that the other waves still need
   for (kt = wave_last + 1; kt < nt; ++kt) {
     sync_copies();
@@ -1175,7 +1218,7 @@ namespace moda {
 
 int fwd_bf16_tile_rows(int waves) { return waves * kQPerWave; }
 
-hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, hipStream_t stream) {
+hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, int per_simd, hipStream_t stream) {
   const int gt = p.heads_per_tile;
   if ((waves != 4 && waves != 8) || gt < 1 || gt > kQPerWave || (gt & (gt - 1)) != 0 || (p.Hq / p.Hk) % gt != 0)
     return hipErrorInvalidValue;
@@ -1184,10 +1227,11 @@ hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, hipStream_t str
   const long long blocks = (long long)p.B * (p.Hq / gt) * p.n_qtiles;
   if (!grid_ok(blocks)) return kGridTooLarge;
   dim3 grid((unsigned)blocks), block(waves * 64);
-  if (d == 128 && waves == 8) return launch_kernel(moda_fwd_bf16_kernel<128, 8>, grid, block, stream, p);
-  if (d == 128) return launch_kernel(moda_fwd_bf16_kernel<128, 4>, grid, block, stream, p);
-  if (d == 64 && waves == 8) return launch_kernel(moda_fwd_bf16_kernel<64, 8>, grid, block, stream, p);
-  if (d == 64) return launch_kernel(moda_fwd_bf16_kernel<64, 4>, grid, block, stream, p);
+  if (d == 128 && per_simd == 2 && waves == 8) return launch_kernel(moda_fwd_bf16_kernel<128, 8, 2>, grid, block, stream, p);
+  if (d == 128 && per_simd == 2) return launch_kernel(moda_fwd_bf16_kernel<128, 4, 2>, grid, block, stream, p);
+  if (d == 64 && per_simd == 4 && waves == 8) return launch_kernel(moda_fwd_bf16_kernel<64, 8, 4>, grid, block, stream, p);
+  if (d == 64 && per_simd == 4) return launch_kernel(moda_fwd_bf16_kernel<64, 4, 4>, grid, block, stream, p);
+  if (d == 64 && per_simd == 2 && waves == 4) return launch_kernel(moda_fwd_bf16_kernel<64, 4, 2>, grid, block, stream, p);
   return hipErrorInvalidValue;
 }
 

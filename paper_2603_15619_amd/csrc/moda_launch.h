@@ -19,10 +19,11 @@ inline hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block
 constexpr hipError_t kGridTooLarge = hipErrorInvalidConfiguration;
 inline bool grid_ok(long long blocks) { return blocks > 0 && blocks <= 0x7fffffffLL; }
 
-// bf16 forward kernel: `waves` (8 or 4) waves per workgroup, 32 queries each; p.n_qtiles
+// bf16 forward kernel: `waves` (8 or 4) waves per workgroup, 32 queries each, per_simd (2, or at d = 64 4; 8 waves at
+// d = 64 go with 4) of them resident on a SIMD; p.n_qtiles
 // must be the number of such tiles in p.T.
 int fwd_bf16_tile_rows(int waves);
-hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, hipStream_t stream);
+hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, int per_simd, hipStream_t stream);
 // The same for calls with few such tiles: tiles of fwd_short_tile_pairs() (position, head) pairs,
 // whose number per head (subset) is p.n_qtiles.
 int fwd_short_tile_pairs();
