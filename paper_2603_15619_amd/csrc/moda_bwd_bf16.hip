@@ -1031,30 +1031,34 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
 // ---------------------------------------------------------------- dK, dV, few key tiles
 // The kernel above needs B * Hk * T / 128 workgroups to fill the chip; below that most compute units
 // idle while the first key tiles walk all query tiles of the group one after the other.  Here a
-// workgroup = 32 keys and its 4 waves DEAL OUT THE QUERIES: item i, 32 queries of one head of the
-// group, belongs to wave i % 4, which copies its Q / dO rows and their (LSE, delta) into LDS of its
-// own (two stages, no workgroup barrier in the loop); the four dK^T, dV^T are summed through LDS at
+// workgroup = 32 keys and its 4 or 8 waves (NW) DEAL OUT THE QUERIES: item i, 32 queries of one head of the
+// group, belongs to wave i % NW, which copies its Q / dO rows and their (LSE, delta) into LDS of its
+// own (two stages, no workgroup barrier in the loop); their dK^T, dV^T are summed through LDS at
 // the end, in wave order.  Four times the workgroups with a quarter of the steps each, for four
 // times the reads of Q and dO, which the L2 serves.  The depth slots of the 32 positions are taken
 // here as well.
 // Bound by the latency of a wave's serial chain copy -> products -> exponentials -> products:
 // B=2 Hq=16 Hk=8 T=1000 d=64, 12 slots: 82 -> 34 us; whole backward call at B=1 Hq=64 Hk=8 T=1024
 // d=64, 64 slots: 293 -> 160 us, d=128: 530 -> 282 us.
-template <int D>
+// Eight waves (d = 64; the LDS of a unit holds one such workgroup, or two of four waves): the first key tiles,
+// which see all queries of a large group, take half as long, where they are what the call waits for.  Backward
+// call, 4 / 8 waves, us: B=1 Hq=8 Hk=1 T=16384 1404 / 1035; Hq=64 Hk=8 T=1000 75.5 / 60.8; Hq=32 Hk=4 T=3000, 24
+// slots 260 / 220; but Hq=16 Hk=8 B=2 T=1000, 12 slots 46.1 / 50.9 (dkdv_waves draws the line).
+template <int D, int NW = 4>
 struct BwdShortCfg {
   static constexpr int kTile = 32 * D * 2;               // 32 rows of Q or dO
   static constexpr int kStage = 2 * kTile + 64 * 8;      // Q, dO, LSE log2 e, -delta (of 64 rows, 32 of them used)
   static constexpr int kPieces = kTile / 1024;           // copy instructions per tile
   static constexpr int kXRow = D + 4;                    // floats per row of the exchange buffer
   static constexpr int kXWave = 32 * kXRow;
-  static constexpr int kRing = 4 * 2 * kStage;
-  static constexpr int kLds = kRing > 4 * kXWave * 4 ? kRing : 4 * kXWave * 4;
+  static constexpr int kRing = NW * 2 * kStage;
+  static constexpr int kLds = kRing > NW * kXWave * 4 ? kRing : NW * kXWave * 4;
 };
 
-template <int D, int GT>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kernel(BwdParams p) {
+template <int D, int GT, int NW>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kernel(BwdParams p) {
   using Tl = Tile<D>;
-  using C = BwdShortCfg<D>;
+  using C = BwdShortCfg<D, NW>;
   using Ld = TileLoader<D>;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1070,13 +1074,14 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
   // depth slots of the 32 positions, before or after the key tile (alternating, as above)
   auto depth = [&]() {
     if constexpr (GT > 0) {
-      constexpr int LPR = D / 8, ROWS = 256 / LPR;
+      constexpr int LPR = D / 8, ROWS = NW * 64 / LPR;
       for (int r0 = 0; r0 < 32; r0 += ROWS) {
         const int t = j0 + r0 + tid / LPR;
+        if (ROWS > 32 && t >= j0 + 32) break;  // (whole waves)
         depth_gqa_row<D, GT>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR);
       }
     } else if (G == 1 && p.depth_alloc > 0) {
-      depth_grad_rows<D, 8>(p, bg, j0 + wave * 8, lane);
+      if (wave < 4) depth_grad_rows<D, 8>(p, bg, j0 + wave * 8, lane);
     }
   };
   const bool depth_first = ((blockIdx.x >> 3) & 1) != 0;
@@ -1132,7 +1137,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     }
     copy4(l_buf, lane * 4, qt * 128, dst + 2 * C::kTile);
     copy4(d_buf, lane * 4, qt * 128, dst + 2 * C::kTile + 256);
-    pos += 4;
+    pos += NW;
     return qt * 32;
   };
   int q_next = 0;
@@ -1141,13 +1146,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     q_next = issue_next(0);
   }
   int stage = 0;
-  for (int item = wave; item < n_items; item += 4, stage ^= 1) {
+  for (int item = wave; item < n_items; item += NW, stage ^= 1) {
     // (the wave's own copies into its own LDS: its wait publishes them, and the stage that the next
     // copies overwrite may be refilled as soon as the wave's reads of it have returned)
     wait_own_copies<0>();
     wait_own_reads();
     const int q0 = q_next;
-    if (item + 4 < n_items) q_next = issue_next(stage ^ 1);
+    if (item + NW < n_items) q_next = issue_next(stage ^ 1);
     const unsigned qtile = ring + stage * C::kStage;
     const unsigned b_row = fa.row + qtile, b_tr = fa.tr + qtile, b_tr8 = fa.tr8 + qtile;
     const float* lse_s = (const float*)(smem + (qtile - (unsigned)(size_t)(lds_ptr)smem) + 2 * C::kTile);
@@ -1200,7 +1205,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     }
   }
 
-  // ---- sum of the four waves, row-major, 16-byte stores
+  // ---- sum of the waves, row-major, 16-byte stores
   float* xb = (float*)smem;
   constexpr int LPR = Tl::kChunks;
 #pragma unroll
@@ -1217,11 +1222,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kern
     __syncthreads();
     char* outb = (char*)(which ? p.dVseq : p.dKseq) + (size_t)bg * T * Tl::kRowBytes;
     const float f = which ? 1.0f : p.scale;
-    for (int row = tid / LPR; row < 32; row += 256 / LPR) {
+    for (int row = tid / LPR; row < 32; row += NW * 64 / LPR) {
       const float* x = xb + row * C::kXRow + (tid % LPR) * 8;
       f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < NW; ++w) {
         a += *(const f32x4*)(x + w * C::kXWave);
         b += *(const f32x4*)(x + w * C::kXWave + 4);
       }
@@ -1816,13 +1821,16 @@ size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d) {
 
 int bwd_bf16_max_group() { return 64; }
 
-// Which of the two dK/dV kernels a call takes: the one whose estimated time is shorter.  Either is bound by the
+// Waves of the short dK/dV kernel that a call takes, 0: the other kernel; the one whose estimated time is shortest.
+// Each is bound by the
 // chain of its longest workgroup (few workgroups) or by what 256 compute units get done (many): a workgroup's
-// steps (64 queries x 128 keys; short kernel: 32 x 32 per wave, four side by side), its two ends, and the
+// steps (64 queries x 128 keys; short kernel: 32 x 32 per wave, its waves side by side), its two ends, and the
 // depth slots of its positions, padding included.  The short kernel reads Q and dO four times as often, and
 // pays `undealt` more where the heads cannot be dealt to the 8 dies (head_blocked_id) and every L2 sees
 // them all.  Constants (us; per 256 units) fitted to both kernels' times at 7700 shapes, T = 2 to 16384, 1 to 2000
 // heads, 1 to 16 per group, 0 to 64 slots: 0.4 % behind the better kernel on average, more than 10 % at 1 of 100.
+// Eight waves: one workgroup per unit, whose ends (and halves of its waves in the depth slots) nothing hides;
+// fitted to all three at 170 shapes of up to 3000 workgroups: 0.1 % behind the best on average, 4 % at most.
 // Whole call without slots, workgroups of the short kernel: other / short, us:
 //   d=64   causal      G=1 T=128: 512 16/15, 768 17/19;   T=512: 768 28/27, 1536 38/41;   T=2048: 1536 101/89, 2048 92/95
 //                      G=8 T=128: 1024 72/63, 2048 115/129;   T=1000: 2048 361/331, undealt 1216 265/214, 2400 379/536
@@ -1833,11 +1841,14 @@ int bwd_bf16_max_group() { return 64; }
 struct KeyCost {
   double step, step_unit, ends, short_step, short_unit, undealt, slot, slot_unit;
 };
+struct EightWaveCost {
+  double step, unit, ends, slot, slot_unit, once;
+};
 static double fourth(double x) { return x * x * x * x; }
 static double undealt_share(long long heads) {  // 0: a multiple of 8; 1: odd
   return (3 - (heads % 8 == 0 ? 3 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 1 : 0)) / 3.0;
 }
-static bool few_keys(const BwdParams& p, int d) {
+static int dkdv_waves(const BwdParams& p, int d) {
   const KeyCost c = d == 64 ? KeyCost{1.26, 1.12, 1.2, 0.90, 0.66, 0.16, 0.18, 0.0043}
                             : KeyCost{2.7, 1.53, 3.9, 1.41, 1.58, 0.17, 0.36, 0.0076};
   const long long heads = (long long)p.B * p.Hk;
@@ -1851,7 +1862,17 @@ static bool few_keys(const BwdParams& p, int d) {
   const double short_chain = (G * n32 / 4 + odd) * c.short_step + L * slot;
   const double short_load = heads * (short_steps * c.short_unit * (1 + c.undealt * undealt_share(heads)) +
                                      n32 * (c.ends + 32 * L * c.slot_unit)) / 256;
-  return fourth(short_chain) + fourth(short_load) < fourth(chain) + fourth(load);  // (a smooth maximum of each pair)
+  const double other = fourth(chain) + fourth(load), four = fourth(short_chain) + fourth(short_load);  // (smooth maxima)
+  if (d == 64) {
+    const EightWaveCost e{1.25, 1.31, 3.65, 0.196, 0.0064, 0.82};
+    const double odd8 = p.Hq / p.Hk % 8 ? 0.4375 : 0.0;
+    const double steps8 = n32 * (G * (p.causal ? n32 + 1 : 2 * n32) / 16 + odd8);
+    const double chain8 = (G * n32 / 8 + odd8) * e.step + (G > 1 ? 2 : 1) * L * e.slot + e.once;
+    const double load8 = heads * (steps8 * e.unit * (1 + c.undealt * undealt_share(heads)) + n32 * (e.ends + 32 * L * e.slot_unit)) / 256;
+    const double eight = fourth(chain8) + fourth(load8);
+    if (eight < other && eight < four) return 8;
+  }
+  return four < other ? 4 : 0;
 }
 // The two dQ kernels likewise (32 queries against 128 per workgroup, key tiles dealt to the four waves; 3700
 // shapes, 0.2 % behind the better one on average).  Whole call, one head, workgroups of the short kernel: other /
@@ -1889,7 +1910,7 @@ static bool few_queries(const BwdParams& p, int d) {
 static bool own_depth_kernel(const BwdParams& p, int d) {
   const int G = p.Hq / p.Hk, L = p.depth_count, blocks = (L + 31) / 32;
   if (p.depth_alloc == 0 || G <= 4) return false;
-  return G > 8 || d != 64 || few_keys(p, d) || L * 16 < blocks * 32 * 11 || L == 0;
+  return G > 8 || d != 64 || dkdv_waves(p, d) != 0 || L * 16 < blocks * 32 * 11 || L == 0;
 }
 int bwd_bf16_kernels(const BwdParams& p, int d) { return 3 + (own_depth_kernel(p, d) ? 1 : 0); }
 
@@ -1928,13 +1949,16 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   {
-    const bool few = few_keys(p, D);  // (see moda_bwd_dkdv_short_kernel)
-    const dim3 gk((unsigned)(few ? (long long)p.B * p.Hk * ((p.T + 31) / 32) : g_dkdv)), blk(256);
+    const int few = dkdv_waves(p, D);  // (see moda_bwd_dkdv_short_kernel)
+    constexpr int kEight = D == 64 ? 8 : 4;
+    const dim3 gk((unsigned)(few ? (long long)p.B * p.Hk * ((p.T + 31) / 32) : g_dkdv)), blk(few ? few * 64 : 256);
     const bool grouped = G > 1 && p.depth_alloc > 0 && !own_depth_kernel(p, D);  // the group's depth-slot gradients run inside dK/dV
-    const auto kernel = !grouped ? (few ? moda_bwd_dkdv_short_kernel<D, 0> : moda_bwd_dkdv_kernel<D, 0>)
-                        : G <= 2 ? (few ? moda_bwd_dkdv_short_kernel<D, 2> : moda_bwd_dkdv_kernel<D, 2>)
-                        : G <= 4 ? (few ? moda_bwd_dkdv_short_kernel<D, 4> : moda_bwd_dkdv_kernel<D, 4>)
-                                 : moda_bwd_dkdv_kernel<D, D == 64 ? 8 : 4>;  // (d = 128: never more than 4 here)
+    auto pick = [few](auto other, auto four, auto eight) { return few == 0 ? other : few == 4 ? four : eight; };
+    const auto kernel =
+        !grouped ? pick(moda_bwd_dkdv_kernel<D, 0>, moda_bwd_dkdv_short_kernel<D, 0, 4>, moda_bwd_dkdv_short_kernel<D, 0, kEight>)
+        : G <= 2 ? pick(moda_bwd_dkdv_kernel<D, 2>, moda_bwd_dkdv_short_kernel<D, 2, 4>, moda_bwd_dkdv_short_kernel<D, 2, kEight>)
+        : G <= 4 ? pick(moda_bwd_dkdv_kernel<D, 4>, moda_bwd_dkdv_short_kernel<D, 4, 4>, moda_bwd_dkdv_short_kernel<D, 4, kEight>)
+                 : moda_bwd_dkdv_kernel<D, D == 64 ? 8 : 4>;  // (d = 128: never more than 4 here)
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;

@@ -23,6 +23,14 @@ def test_bwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
     check_full(B, Hq, T, d, L, 1300 + T + L, causal=causal, depth_alloc=La, Hk=Hk)
 
 
+@pytest.mark.parametrize("B,Hq,Hk,T,L,La,causal", [(1, 8, 1, 777, 0, None, True), (1, 6, 2, 1500, 4, 5, True),
+                                                   (1, 4, 2, 1100, 7, None, True), (1, 3, 3, 2050, 5, 6, True), (2, 10, 1, 333, 2, None, False),
+                                                   (1, 8, 2, 1001, 24, None, False), (1, 8, 1, 97, 0, None, True), (3, 8, 1, 33, 9, 10, True)])
+def test_bwd_few_tiles_of_many_queries(B, Hq, Hk, T, L, La, causal):
+    """d = 64, few key tiles that see many queries: eight waves per key tile in the dK/dV kernel."""
+    check_full(B, Hq, T, 64, L, 1350 + T + L, causal=causal, depth_alloc=La, Hk=Hk)
+
+
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(89, 8, 8, 130, 64, 5, 6, True), (89, 16, 8, 131, 64, 3, None, True),
                                                      (45, 32, 8, 190, 64, 2, 3, True), (24, 16, 8, 257, 128, 6, None, False),
                                                      (24, 64, 16, 65, 128, 1, 2, True), (24, 40, 8, 130, 64, 2, None, False)])
