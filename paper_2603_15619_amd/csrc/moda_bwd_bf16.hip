@@ -723,7 +723,7 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   const int T = p.T;
   const int BHk = p.B * p.Hk;
   int bg, jt;  // (batch, key/value head); key tiles in natural order: the first ones see the most queries
-  head_blocked_id((int)blockIdx.x, BHk, (T + 127) / 128, bg, jt, p.head_group);
+  head_blocked_id(layered_id(p.causal, 2), BHk, (T + 127) / 128, bg, jt, p.head_group);
   const int j0 = jt * 128;
   const int kw0 = j0 + wave * 32;
   const int G = p.Hq / p.Hk;        // query heads per key/value head: their gradients add up here
@@ -1260,7 +1260,7 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
   // tile by query tile (heavy, i.e. late, tiles first).
   const int G = p.Hq / p.Hk;
   int bg, tile_idx;  // (batch, key/value head); position in the walk over (query tile, head of the group)
-  head_blocked_id((int)blockIdx.x, p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
+  head_blocked_id(layered_id(p.causal, 2), p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
   const int qt = n_qt - 1 - tile_idx / G;
   const int bh = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G;
   const int q0 = qt * kQT;

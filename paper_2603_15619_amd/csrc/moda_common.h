@@ -64,6 +64,20 @@ struct BwdParams {
   int head_group;  // heads that one die walks together, tile by tile (see head_blocked_id)
 };
 
+// Workgroup id of a grid whose workgroups are resident all at once (`per_unit` of them on a compute unit) and
+// whose tiles weigh less and less in walking order: they fill the 32 units of a die in layers (ids equal
+// mod 8, 32 at a time), and every other layer takes its tiles in reverse order, so that a heavy tile shares
+// its unit with a light one.  Other grids: the id as it is.  (As it is / so, us: fp32 forward H=8 T=2000 d=128, 15
+// slots 99 / 87.5, H=12 T=1300, 4 slots 58 / 52; backward H=16 T=4096 d=64 157 / 146, B=2 H=16 T=2000 d=128 161 / 155.  Not in
+// the kernels for few tiles: reading the grid's size costs short calls more, 15.3 / 15.9, than others gain.)
+__device__ __forceinline__ int layered_id(bool falling, int per_unit) {
+  const int id = blockIdx.x, n = gridDim.x;
+  if (!falling || n > 256 * per_unit || ((id >> 8) & 1) == 0) return id;
+  const int die = id & 7, r = id >> 3, r0 = r & ~31;
+  const int layer = min(32, ((n - die + 7) >> 3) - r0);
+  return (r0 + layer - 1 - (r - r0)) * 8 + die;
+}
+
 // Workgroup id -> (head index, tile position in the walking order).  Ids are dealt round-robin
 // to the 8 dies (each with its own L2).  With `n_heads` a multiple of 8, die x takes the heads
 // x, x + 8, x + 16, ... `group` AT A TIME, each with all its `n_tiles` tiles, instead of a tile

@@ -448,16 +448,9 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
   // K/V of the heads in progress fit its L2 (measured at T = 65536, 2 heads per die: one at
   // a time -4 %; at T = 4096, 16 heads per die: two at a time -4 %, one at a time slower
   // again, because the heaviest tiles of a head then start late).
-  //
-  // A grid that is resident all at once fills the 32 units of a die in layers (ids equal mod 8, 32 at a
-  // time).  Every other layer takes its tiles in reverse order there: a heavy tile shares its unit with a light one.
-  const bool one_round = (int)gridDim.x <= (W == 8 ? 256 : 512) * (PS / 2);
-  int id = blockIdx.x;
-  if (one_round && p.causal && ((id >> 8) & 1)) {
-    const int die = id & 7, r = id >> 3, r0 = r & ~31;
-    const int layer = min(32, (((int)gridDim.x - die + 7) >> 3) - r0);
-    id = (r0 + layer - 1 - (r - r0)) * 8 + die;
-  }
+  constexpr int kPerUnit = (W == 8 ? 1 : 2) * (PS / 2);  // workgroups that a compute unit holds
+  const bool one_round = (int)gridDim.x <= 256 * kPerUnit;
+  const int id = layered_id(p.causal, kPerUnit);
   int tbh = id % NBH;
   int tile_idx = id / NBH;
   if (p.head_group > 0 && NBH % (8 * p.head_group) == 0) {

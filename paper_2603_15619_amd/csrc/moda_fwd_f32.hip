@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int bh, tile;
-  head_blocked_id((int)blockIdx.x, p.B * p.Hq, p.n_qtiles, bh, tile, p.head_group);
+  head_blocked_id(layered_id(p.causal, D == 64 ? 3 : 2), p.B * p.Hq, p.n_qtiles, bh, tile, p.head_group);
   const int q0 = (p.n_qtiles - 1 - tile) * kF32Rows;  // heavy (late) tiles first
   const int b = bh / p.Hq, g = (bh - b * p.Hq) / (p.Hq / p.Hk);
   const size_t bg = (size_t)b * p.Hk + g;

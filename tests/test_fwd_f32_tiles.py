@@ -38,6 +38,14 @@ def test_f32_tile_edges(B, Hq, Hk, T, d, L, La, causal):
     assert np.abs(O - Oref).max() <= TOL and np.abs(LSE - Lref).max() <= TOL
 
 
+@pytest.mark.parametrize("Hq,T,d,L", [(5, 2000, 128, 2), (9, 1999, 64, 0)])
+def test_f32_grids_of_one_round(Hq, T, d, L):
+    """Between one and three workgroups per compute unit, a number that 8 does not divide: tiles of every
+    other layer in reverse."""
+    O, LSE, (Oref, Lref) = run(1, Hq, Hq, T, d, L, 60 + T)
+    assert np.abs(O - Oref).max() <= TOL and np.abs(LSE - Lref).max() <= TOL
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 @pytest.mark.parametrize("T,d,at", [(70, 64, 37), (130, 128, 129), (64, 128, 0), (6, 64, 3)])
 def test_f32_value_that_is_not_finite_stays_behind_the_diagonal(T, d, at, value):
