@@ -2,10 +2,10 @@
 key loop takes from the tiles before, is far too low for a tile: scores that jump by hundreds of
 powers of two at single keys (weights formed with the old reference overflow to infinity), in every ring
 stage, in the first, the last and the remaining tiles of a wave; and first tiles whose scores are all
--inf.  The oracle is the checker's fp64 forward.
+-inf.  The oracle is the fp64 forward in C.
 
 Tolerance: one key carries a row, so |O| reaches max|V|: weights and output rounded to bf16, 2 * 2^-8 *
-max|V|.  LSE (up to 1000 in size): the 1e-3 of the task plus four fp32 roundings of its size.
+max|V|.  LSE (up to 1000 in size): 1e-3 as in test_fwd_parity plus four fp32 roundings of its size.
 """
 import numpy as np
 import pytest
