@@ -623,10 +623,10 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
         sc[i] = (c * kDepthChunk + i < L) ? a : -INFINITY;
         mx2 = fmaxf(mx2, sc[i]);
       }
-      // (a chunk always holds at least one attended slot, so mx2 is finite; with m = -inf,
-      //  the state of an empty row, the factor is exp2(-inf) = 0)
-      const float al = fast_exp2((m - mx2) * c2);
-      const float mc = mx2 * c2;
+      // (a row whose slots so far all score -inf keeps its empty state, and they weigh nothing:
+      //  -inf - -inf must not become NaN)
+      const float al = m == mx2 ? 1.0f : fast_exp2((m - mx2) * c2);
+      const float mc = mx2 == -INFINITY ? 0.f : mx2 * c2;
       m = mx2;
       l *= al;
 #pragma unroll

@@ -1,8 +1,8 @@
 """GPU parity: bf16 forward kernel (through the C ABI) where the reference of the exponentials, which the
 key loop takes from the tiles before, is far too low for a tile: scores that jump by hundreds of
 powers of two at single keys (weights formed with the old reference overflow to infinity), in every ring
-stage, in the first, the last and the remaining tiles of a wave; and first tiles whose scores are all
--inf.  The oracle is the fp64 forward in C.
+stage, in the first, the last and the remaining tiles of a wave; and first tiles, or first depth slots, whose
+scores are all -inf.  The oracle is the fp64 forward in C.
 
 Tolerance: one key carries a row, so |O| reaches max|V|: weights and output rounded to bf16, 2 * 2^-8 *
 max|V|.  LSE (up to 1000 in size): 1e-3 as in test_fwd_parity plus four fp32 roundings of its size.
@@ -55,3 +55,26 @@ def test_first_tiles_of_minus_infinity(waves, T, d, L):
     inp["Q"][..., 0] = inp["Q"][..., 0].abs() + 0.25
     inp["Kseq"][:, :, :blocked, 0] = -float("inf")
     check(inp, B, Hq, Hk, T, d, L, True, dict(waves=waves), first_row=0 if L else blocked)
+
+
+# Both geometries of both head dimensions, at d = 64 two and four waves per SIMD (few and many workgroups);
+# workgroups that take their slots before the key loop and after it.
+KERNELS = [(2, 4, 300, 64, 4), (50, 4, 300, 64, 4), (50, 4, 300, 64, 8), (2, 4, 300, 128, 4), (2, 4, 300, 128, 8)]
+
+
+@pytest.mark.parametrize("L,dead", [(12, 12), (7, 3), (12, 5), (12, 10)])
+@pytest.mark.parametrize("B,H,T,d,waves", KERNELS)
+def test_depth_slots_of_weight_zero(B, H, T, d, waves, L, dead):
+    """One head per tile: slots whose scores are -inf, all of a row's or one or two whole work items (of 3 or 5
+    slots) among them, weigh nothing: the result is that without them (the other slots' weights round to
+    bf16 as before: 2e-2 on O)."""
+    inp = synth.make_inputs(B, H, H, T, d, L, dtype="bf16", seed=960 + L, device="cuda")
+    inp["Q"] = inp["Q"].abs() + 0.1  # (positive: -inf, not NaN)
+    rest = dict(inp, Kdepth=inp["Kdepth"][:, :, :, dead:].contiguous(), Vdepth=inp["Vdepth"][:, :, :, dead:].contiguous())
+    if dead == L:
+        rest["Kdepth"] = rest["Vdepth"] = None
+    O1, L1 = run_gpu(rest, L - dead, tuning=dict(waves=waves))
+    inp["Kdepth"][:, :, :, :dead] = -float("inf")
+    O, LSE = run_gpu(inp, L, tuning=dict(waves=waves))
+    assert (O.float() - O1.float()).abs().max().item() <= 2e-2
+    assert (LSE - L1).abs().max().item() <= 1e-4
