@@ -34,6 +34,7 @@
 // row-major state passes through LDS into the accumulators): the result is the same, and the
 // compute units then do not all stream from HBM at the same time.  O / LSE are stored with
 // 128-bit accesses.
+#include <cfloat>
 #include <type_traits>
 #include <utility>
 
@@ -1003,9 +1004,11 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
     MODA_ANCHOR(sA.a[0]);
     MODA_ANCHOR(sA.a[C::kKB - 1]);
     if (wave_last == 0 && needs_mask(0)) mask_block(sA, 0);
-    // the first reference (a query whose scores are all -inf so far takes 0: weights 0, empty state)
+    // The first reference.  A query whose scores are all -inf so far takes the lowest number that c2 does not
+    // carry past the range: its weights are zero, and its first finite score is so far above that the weight
+    // overflows and the rare path below raises the reference to it.
     const float mx = block_max(sA);
-    if (m_run == -INFINITY) m_run = mx == -INFINITY ? 0.f : mx;
+    if (m_run == -INFINITY) m_run = mx == -INFINITY ? -FLT_MAX / fmaxf(c2 * 1.0001f, 1.f) : mx;
     static_for<C::kAhead>([&](auto I) {  // the first fragments of the first step
       constexpr int i = decltype(I)::value, h = C::kKB == 1;
       if constexpr (Place<C, i>::is_k) read_kfrag<C, 0, h, i, Place<C, i>::index>(fb);

@@ -62,6 +62,33 @@ def test_first_tiles_of_minus_infinity(waves, T, d, L):
 KERNELS = [(2, 4, 300, 64, 4), (50, 4, 300, 64, 4), (50, 4, 300, 64, 8), (2, 4, 300, 128, 4), (2, 4, 300, 128, 8)]
 
 
+@pytest.mark.parametrize("offset", [-2048.0, 2048.0])
+@pytest.mark.parametrize("Hk,L", [(4, 0), (4, 5), (2, 5)])
+@pytest.mark.parametrize("B,H,T,d,waves", KERNELS)
+def test_far_scores_behind_first_tiles_of_minus_infinity(B, H, T, d, waves, Hk, L, offset):
+    """70 keys of score -inf, all other keys and slots `offset` away from zero (+-261 and +-369 powers of two):
+    the softmax is that without the offset, whatever reference the empty first tiles left."""
+    inp = synth.make_inputs(B, H, Hk, T, d, L, dtype="bf16", seed=970 + L, device="cuda")
+    blocked = 70
+    inp["Q"][..., 0] = inp["Q"][..., 0].abs() + 0.25
+    inp["Q"][..., 1] = 32.0
+    inp["Kseq"][..., 1] = offset / 32.0
+    inp["Kseq"][:, :, :blocked, 0] = -float("inf")
+    if L:
+        inp["Kdepth"][..., 1] = offset / 32.0
+    O, LSE = run_gpu(inp, L, True, None, dict(waves=waves))
+    for b in (0, B - 1):
+        one = {k: None if v is None else v[b:b + 1].contiguous() for k, v in inp.items()}
+        with np.errstate(invalid="ignore"):
+            Oref, Lref = R.fwd(*(synth.to_f64(one[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), depth_count=L)
+        rows = slice(0 if L else blocked, T)
+        o, l, Oref, Lref = (x[:, :, rows] for x in (synth.to_f64(O[b:b + 1]), synth.to_f64(LSE[b:b + 1]), Oref, Lref))
+        vmax = max(float(one[k].abs().max()) for k in (("Vseq", "Vdepth") if L else ("Vseq",)))
+        # (weights are formed from scores of size 2048 in fp32: 2^-13 of each, next to their rounding to bf16)
+        assert np.abs(o - Oref).max() <= 2 * 2.0 ** -8 * vmax
+        assert (np.abs(l - Lref) <= 1e-3 + 4 * 2.0 ** -24 * np.abs(Lref)).all()
+
+
 @pytest.mark.parametrize("L,dead", [(12, 12), (7, 3), (12, 5), (12, 10)])
 @pytest.mark.parametrize("B,H,T,d,waves", KERNELS)
 def test_depth_slots_of_weight_zero(B, H, T, d, waves, L, dead):
