@@ -48,6 +48,7 @@ constexpr int kF32Waves = 4;
 constexpr float kTiny = -100.f, kSmallest = 0x1p-100f;  // weights below are taken with care
 constexpr float kLargest = 3.38e38f;  // (values beyond round to an infinite bf16)
 constexpr float kLeast = 0x1p-80f;    // (the last parts of values far below would be subnormal)
+constexpr unsigned kLeastQ = (127 - 100) << 23;  // least query number that is split: 2^-100
 
 template <int D>
 struct F32Cfg {
@@ -127,12 +128,23 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
   // ---- queries -> LDS, as three parts of bf16 (rows past the end repeat the last one; nothing of them is
   // stored).  The 16 channels of a matrix instruction stand in the order in which a lane holds those of a
   // key: 4 hi .. + 3, then 8 + 4 hi .. + 3 at place 8 hi.
-  unsigned short* q_parts = (unsigned short*)shared;
+  // Where a query has a number that has not all of its 24 bits in three parts (below 2^-110 the last bits are none
+  // of a bf16), or one so large that it would show what a minute key lacks, one number is replaced by NaN: the
+  // tiles then take the fp32 matrix instructions (see fold_tile).  What is lost of the keys otherwise, 2^-134 of a
+  // number, is below 2^-32 of an exponent.
+  unsigned least_q = 0xffffffffu;
+  float largest_q = 0.f;
+  unsigned short *q_parts = (unsigned short*)shared, *dst;
   for (int i = tid; i < kF32Rows * (D / 4); i += kF32Waves * 64) {
     const int r = i / (D / 4), c = i % (D / 4);
     const f32x4 q = *(const f32x4*)((const float*)p.Q + ((size_t)bh * T + min(q0 + r, T - 1)) * D + c * 4);
     float x[4] = {q[0], q[1], q[2], q[3]};
-    unsigned short* dst = q_parts + r * C::kQRow + (c >> 2) * 16 + (c & 1) * 8 + ((c >> 1) & 1) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      least_q = min(least_q, 2 * __builtin_bit_cast(unsigned, x[e]) - 1);  // (of zeros the largest number)
+      largest_q = fmaxf(largest_q, fabsf(x[e]));
+    }
+    dst = q_parts + r * C::kQRow + (c >> 2) * 16 + (c & 1) * 8 + ((c >> 1) & 1) * 4;
 #pragma unroll
     for (int n = 0; n < 3; ++n) {
       const u32x2 w = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
@@ -143,6 +155,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
       x[3] -= bf16_hi(w[1]);
     }
   }
+  if (least_q < 2 * kLeastQ - 1 || largest_q > (c2 <= 0x1p30f ? 0x1p64f : 0.f)) *dst = 0x7fc0;
   __syncthreads();
 
   // ---- depth slots: 16 lanes per row, 4 (d = 64) or 8 (d = 128) channels each; a wave takes 8 of
@@ -341,8 +354,8 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] += s1[i];
-    // numbers that have no such parts (infinite, NaN, about to overflow) leave NaN or infinity in the scores of
-    // their key or query: the tile is then taken on the fp32 matrix instructions
+    // numbers that have no such parts (infinite, NaN, about to overflow; of the queries minute ones too) leave NaN or
+    // infinity in the scores of their key or query: the tile is then taken on the fp32 matrix instructions
     float sum = s[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) sum += s[i];

@@ -137,3 +137,19 @@ def test_f32_wide_scores(T, d):
     Oref, Lref = R.fwd(*(synth.to_f64(inp[n]) for n in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), scale=1.0)
     assert np.abs(synth.to_f64(O) - Oref).max() <= 2 * delta * float(max(inp["Vseq"].abs().max(), inp["Vdepth"].abs().max()))
     assert np.abs(synth.to_f64(LSE) - Lref).max() <= delta + TOL
+
+
+@pytest.mark.parametrize("which,exponent", [("Q", -120), ("K", -120), ("Q", -112), ("K", -112)])
+@pytest.mark.parametrize("T,d,causal", [(100, 64, True), (70, 128, False), (161, 128, True)])
+def test_f32_minute_queries_or_keys(T, d, causal, which, exponent):
+    """Queries of 2^-120 on keys of 2^120, and the other way round, for the heads of the first group: the last parts
+    of such factors are below the range of bf16, their scores are of size 1."""
+    inp = synth.make_inputs(1, 4, 2, T, d, 3, dtype="f32", seed=670 + T, device="cuda")
+    f = 2.0 ** (exponent if which == "Q" else -exponent)
+    inp["Q"][:, :2] *= f
+    inp["Kseq"][:, :1] /= f
+    inp["Kdepth"][:, :1] /= f
+    O, LSE = moda_attn_fwd(inp["Q"], inp["Kseq"], inp["Vseq"], inp["Kdepth"], inp["Vdepth"], causal=causal)
+    torch.cuda.synchronize()
+    Oref, Lref = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), causal=causal)
+    assert np.abs(synth.to_f64(O) - Oref).max() <= TOL and np.abs(synth.to_f64(LSE) - Lref).max() <= TOL
