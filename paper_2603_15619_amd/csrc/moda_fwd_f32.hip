@@ -47,8 +47,10 @@ constexpr int kF32Keys = 32;   // keys per tile (of one wave)
 constexpr int kF32Waves = 4;
 constexpr float kTiny = -100.f, kSmallest = 0x1p-100f;  // weights below are taken with care
 constexpr float kLargest = 3.38e38f;  // (values beyond round to an infinite bf16)
-constexpr float kLeast = 0x1p-80f;    // (the last parts of values far below would be subnormal)
-constexpr unsigned kLeastQ = (127 - 100) << 23;  // least query number that is split: 2^-100
+// A minute value (below 2^-110) loses its last bits, 2^-134 of a number: nothing next to a value above kLeast whose
+// weight is above 2^kWide, 2^-102 of an output.
+constexpr float kWide = -50.f, kLeast = 0x1p-52f;
+constexpr unsigned kLeastSplit = (127 - 100) << 23;  // numbers below 2^-100 are not split where they count by themselves
 
 template <int D>
 struct F32Cfg {
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
       x[3] -= bf16_hi(w[1]);
     }
   }
-  if (least_q < 2 * kLeastQ - 1 || largest_q > (c2 <= 0x1p30f ? 0x1p64f : 0.f)) *dst = 0x7fc0;
+  if (least_q < 2 * kLeastSplit - 1 || largest_q > (c2 <= 0x1p30f ? 0x1p64f : 0.f)) *dst = 0x7fc0;
   __syncthreads();
 
   // ---- depth slots: 16 lanes per row, 4 (d = 64) or 8 (d = 128) channels each; a wave takes 8 of
@@ -402,7 +404,8 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[cb][i] *= al;
     }
-    const bool tiny = __builtin_amdgcn_ballot_w64((least - m) * c2 < kTiny) != 0;  // (uniform)
+    const bool wide = __builtin_amdgcn_ballot_w64((least - m) * c2 < kWide) != 0;  // (uniform)
+    const bool tiny = wide && __builtin_amdgcn_ballot_w64((least - m) * c2 < kTiny) != 0;
     if (tiny) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = weight(s[i], m, c2);
@@ -414,8 +417,9 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
     for (int i = 0; i < 16; ++i) l += s[i];
     // O^T += V^T P^T.  Values that are infinite, NaN or about to overflow have no parts, and the last parts of the
-    // smallest weights, or of a channel's values that are all minute, would be lost: those are taken on the
-    // fp32 matrix instructions first, and left out below.
+    // smallest weights, or of minute values, would be lost: those are taken on the fp32 matrix instructions first,
+    // and left out below.  Minute values count by themselves where a channel has no others, or where
+    // queries give the others no weight (looked for on tiles with such weights, or masked ones, only).
     bool has_parts = true;
 #pragma unroll
     for (int cb = 0; cb < C::kBlocks; ++cb) {  // (a lane's channels, one by one)
@@ -423,6 +427,15 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
       for (int i = 0; i < 16; ++i) largest = __builtin_elementwise_maximum(largest, fabsf(vf[i][cb]));
       has_parts = has_parts && largest < kLargest && (largest == 0.f || largest > kLeast);
+    }
+    if (partial || wide) {
+      unsigned least_v = 0xffffffffu;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int cb = 0; cb < C::kBlocks; ++cb)
+          least_v = min(least_v, 2 * __builtin_bit_cast(unsigned, vf[i][cb]) - 1);  // (of zeros the largest number)
+      has_parts = has_parts && least_v >= 2 * kLeastSplit - 1;
     }
     const bool plain = __builtin_amdgcn_ballot_w64(!has_parts) == 0;
     if (tiny || !plain) {

@@ -153,3 +153,28 @@ def test_f32_minute_queries_or_keys(T, d, causal, which, exponent):
     torch.cuda.synchronize()
     Oref, Lref = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), causal=causal)
     assert np.abs(synth.to_f64(O) - Oref).max() <= TOL and np.abs(synth.to_f64(LSE) - Lref).max() <= TOL
+
+
+@pytest.mark.parametrize("T,d", [(100, 64), (161, 128)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_f32_minute_values_beside_others(T, d, causal):
+    """Values of 2^-120 with values of 1 in the same tile and channel, which the queries do not see (causal: rows
+    before them) or give no weight (e^-300): 1e-5 of each channel's largest output."""
+    inp = synth.make_inputs(1, 2, 1, T, d, 0, dtype="f32", seed=690 + T, device="cuda")
+    inp["Vseq"] *= 2.0 ** -120
+    for k0 in range(0, T, 32):
+        inp["Vseq"][:, :, k0 + 16:k0 + 24] = 1.0
+    rows = T
+    if causal:
+        rows = 16
+    else:
+        inp["Q"][..., 0] = 1.0
+        inp["Kseq"][..., 0] = 0.0
+        for k0 in range(0, T, 32):
+            inp["Kseq"][:, :, k0 + 16:k0 + 24, 0] = -300.0 * d ** 0.5
+    O, _ = moda_attn_fwd(inp["Q"], inp["Kseq"], inp["Vseq"], causal=causal)
+    torch.cuda.synchronize()
+    Oref = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq")), None, None, causal=causal)[0][:, :, :rows]
+    scale = np.abs(Oref).max(axis=(0, 1, 2))
+    assert scale.max() < 2.0 ** -110  # (the values of 1 take no part)
+    assert (np.abs(synth.to_f64(O)[:, :, :rows] - Oref).max(axis=(0, 1, 2)) <= TOL * scale).all()
