@@ -45,7 +45,7 @@ namespace moda {
 constexpr int kF32Rows = 32;   // queries per workgroup
 constexpr int kF32Keys = 32;   // keys per tile (of one wave)
 constexpr int kF32Waves = 4;
-constexpr float kTiny = -100.f, kSmallest = 0x1p-100f;  // weights below are taken with care
+constexpr float kTiny = -100.f;       // (2^kTiny: weights below have not all of their bits in three parts either)
 constexpr float kLargest = 3.38e38f;  // (values beyond round to an infinite bf16)
 // A minute value (below 2^-110) loses its last bits, 2^-134 of a number: nothing next to a value above kLeast whose
 // weight is above 2^kWide, 2^-102 of an output.
@@ -417,9 +417,12 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
     for (int i = 0; i < 16; ++i) l += s[i];
     // O^T += V^T P^T.  Values that are infinite, NaN or about to overflow have no parts, and the last parts of the
-    // smallest weights, or of minute values, would be lost: those are taken on the fp32 matrix instructions first,
-    // and left out below.  Minute values count by themselves where a channel has no others, or where
+    // smallest weights, or of minute values, would be lost: their tiles take the fp32 matrix instructions.
+    // Minute values count by themselves where a channel has no others, or where
     // queries give the others no weight (looked for on tiles with such weights, or masked ones, only).
+    // (Those tiles used to take both products, the smallest weights on one and the others on the other: T=2000 H=16,
+    // softmax scale 2, where nearly all tiles are of that kind: d=64 99 -> 78 us, d=128 173 -> 147; on fp32
+    // instructions throughout 84 and 165.)
     bool has_parts = true;
 #pragma unroll
     for (int cb = 0; cb < C::kBlocks; ++cb) {  // (a lane's channels, one by one)
@@ -438,19 +441,13 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
       has_parts = has_parts && least_v >= 2 * kLeastSplit - 1;
     }
     const bool plain = __builtin_amdgcn_ballot_w64(!has_parts) == 0;
-    if (tiny || !plain) {
-      float w[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const bool here = !plain || s[i] < kSmallest;
-        w[i] = here ? s[i] : 0.f;
-        s[i] = here ? 0.f : s[i];
-      }
+    const bool by_parts = plain && !tiny;  // (uniform)
+    if (!by_parts) {
       if (plain || !(partial && p.causal)) {  // (uniform)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
 #pragma unroll
-          for (int cb = 0; cb < C::kBlocks; ++cb) o[cb] = mfma_f32(vf[i][cb], w[i], o[cb]);
+          for (int cb = 0; cb < C::kBlocks; ++cb) o[cb] = mfma_f32(vf[i][cb], s[i], o[cb]);
       } else {
         // On a tile that the diagonal crosses a key's weight is zero for the queries before it, but zero times
         // an infinite or NaN value is not: the visible (key, query) pairs are taken one by one.  (One tile
@@ -458,7 +455,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
         int h = hi, q = l32;  // (addresses formed here, not kept across the loop)
         asm volatile("" : "+v"(h), "+v"(q));
 #pragma unroll
-        for (int i = 0; i < 16; ++i) p_tile[(i >> 2) * 8 + h * 4 + (i & 3)][q] = w[i];
+        for (int i = 0; i < 16; ++i) p_tile[(i >> 2) * 8 + h * 4 + (i & 3)][q] = s[i];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -474,12 +471,6 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
             }
         }
       }
-      if (!plain) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-#pragma unroll
-          for (int cb = 0; cb < C::kBlocks; ++cb) vf[i][cb] = 0.f;
-      }
     }
     auto p_parts = [&](int hf) {
       const float x[8] = {s[8 * hf], s[8 * hf + 1], s[8 * hf + 2], s[8 * hf + 3],
@@ -491,25 +482,25 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
                           vf[8 * hf + 4][cb], vf[8 * hf + 5][cb], vf[8 * hf + 6][cb], vf[8 * hf + 7][cb]};
       return split8(x);
     };
-    load_k(k_next, 0);
-    Parts pp = p_parts(0);
+    auto products = [&](int hf) {
+      const Parts pp = p_parts(hf);
 #pragma unroll
-    for (int n = 0; n < 2 * C::kBlocks; ++n) {
-      const int cb = n % C::kBlocks;
-      const Parts va = v_parts(n / C::kBlocks, cb);
-      o[cb] = mfma_16(va.p[0], pp.p[0], o[cb]);
-      o[cb] = mfma_16(va.p[0], pp.p[1], o[cb]);
-      o[cb] = mfma_16(va.p[1], pp.p[0], o[cb]);
-      o[cb] = mfma_16(va.p[0], pp.p[2], o[cb]);
-      o[cb] = mfma_16(va.p[2], pp.p[0], o[cb]);
-      o[cb] = mfma_16(va.p[1], pp.p[1], o[cb]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (n + 1 == C::kBlocks) {
-        pp = p_parts(1);
-        load_k(k_next, 1);
+      for (int cb = 0; cb < C::kBlocks; ++cb) {
+        const Parts va = v_parts(hf, cb);
+        o[cb] = mfma_16(va.p[0], pp.p[0], o[cb]);
+        o[cb] = mfma_16(va.p[0], pp.p[1], o[cb]);
+        o[cb] = mfma_16(va.p[1], pp.p[0], o[cb]);
+        o[cb] = mfma_16(va.p[0], pp.p[2], o[cb]);
+        o[cb] = mfma_16(va.p[2], pp.p[0], o[cb]);
+        o[cb] = mfma_16(va.p[1], pp.p[1], o[cb]);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
+    load_k(k_next, 0);
+    if (by_parts) products(0);
+    load_k(k_next, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (by_parts) products(1);
   };
   int kt = wave;
   for (; kt < n_full; kt += kF32Waves) fold_tile(kt, std::false_type{});
