@@ -46,7 +46,7 @@ constexpr int kF32Rows = 32;   // queries per workgroup
 constexpr int kF32Keys = 32;   // keys per tile (of one wave)
 constexpr int kF32Waves = 4;
 constexpr float kTiny = -100.f;       // (2^kTiny: weights below have not all of their bits in three parts either)
-constexpr float kLargest = 3.38e38f;  // (values beyond round to an infinite bf16)
+constexpr float kLargest = 0x1p120f;  // (the sums of first parts, rounded up, could overflow where those of the values do not)
 // A minute value (below 2^-110) loses its last bits, 2^-134 of a number: nothing next to a value above kLeast whose
 // weight is above 2^kWide, 2^-102 of an output.
 constexpr float kWide = -50.f, kLeast = 0x1p-52f;

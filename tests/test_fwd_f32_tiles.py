@@ -178,3 +178,19 @@ def test_f32_minute_values_beside_others(T, d, causal):
     scale = np.abs(Oref).max(axis=(0, 1, 2))
     assert scale.max() < 2.0 ** -110  # (the values of 1 take no part)
     assert (np.abs(synth.to_f64(O)[:, :, :rows] - Oref).max(axis=(0, 1, 2)) <= TOL * scale).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_values_at_the_end_of_the_range(d):
+    """253.6 * 2^120 with weights 1 and 0.0088: their sum is 255.8 * 2^120, below 2^128; that of the values rounded to
+    bf16, 254 * 2^120, is not."""
+    T, w, v = 40, 0.0088, 253.6 * 2.0 ** 120
+    z = torch.zeros(1, 2, T, d, device="cuda")
+    Q, K, V = z.clone(), z.clone(), z.clone()
+    Q[..., 0] = 1.0
+    K[..., 0] = -20.0  # (weights of 2e-9 on values of zero)
+    K[:, :, 0, 0], K[:, :, 1, 0] = 0.0, float(np.log(w))
+    V[:, :, :2] = v
+    O, _ = moda_attn_fwd(Q, K, V, causal=False, scale=1.0)
+    torch.cuda.synchronize()
+    assert (np.abs(synth.to_f64(O) - v) <= 4 * 2.0 ** -24 * v).all()
