@@ -105,3 +105,24 @@ def test_depth_slots_of_weight_zero(B, H, T, d, waves, L, dead):
     O, LSE = run_gpu(inp, L, tuning=dict(waves=waves))
     assert (O.float() - O1.float()).abs().max().item() <= 2e-2
     assert (LSE - L1).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("T,d", [(1000, 128), (1500, 64)])
+def test_rows_that_one_key_carries(T, d):
+    """A grid of one round, whose light tiles take their slots first: a key 6 to 7.5 powers of two above them weighs
+    exactly 1, whatever the slots' reference: |O| is off by its own rounding (2^-8) and that of the slots' weights
+    (2^-8 of the seven slots' share, 7 * 2^-6)."""
+    B, H, L = 2, 16, 7
+    inp = synth.make_inputs(B, H, H, T, d, L, dtype="bf16", seed=990, device="cuda")
+    jitter = 1.0 + 0.25 * torch.rand(B, H, T, device="cuda")
+    for k in ("Q", "Kseq", "Kdepth"):
+        inp[k].zero_()
+    inp["Q"][..., 0] = jitter.to(torch.bfloat16)
+    inp["Kseq"][:, :, :, 0] = -40.0
+    inp["Kseq"][:, :, 0, 0] = 6.0
+    inp["Vseq"][:, :, 0] = inp["Vseq"][:, :, 0].abs() + 1.0
+    inp["Vdepth"] = inp["Vdepth"].clamp(-1.0, 1.0)
+    scale = float(np.log(2.0))
+    O, _ = run_gpu(inp, L, True, scale)
+    Oref, _ = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), depth_count=L, scale=scale)
+    assert (np.abs(synth.to_f64(O) - Oref) <= 2.0 ** -8 * (np.abs(Oref) + 7 * 2.0 ** -6) + 1e-5).all()
