@@ -83,25 +83,28 @@ int fwd_waves_per_simd(const moda_shape* s, int heads_per_tile, int waves) {
 // Calls that take the kernel for few tiles (moda_fwd_short.hip): n = tiles of 128 (position, head)
 // pairs; the short kernel has 4 n workgroups, of which the chip holds 512 at d = 128 and, at d = 64, 768
 // with depth slots of one head per tile and 1024 otherwise.  It is ahead while they fit, on causal calls
-// (half of whose tiles are short) somewhat longer, on others somewhat less (other / short kernel, us,
-// whole call; 12 slots where there are any):
-//   d=64, no slots or several heads per tile, causal:  T=128 n=384 13/10;   n=256: T=512 13/10, T=2048 26/20, T=8192 81/64;
-//                     n=384: T=512 15/16, T=4096 45/48
-//     not causal:     T=512 n=256 13/13;   T=1024 n=160 15.5/15.5;   T=2048 n=128 25/21, n=192 25/27 (several heads 30/29)
-//   d=64, slots of one head:  n=192: T=128 21/19, T=1024 28/28, T=4096 56/42;   n=256: T=512 26/30, T=4096 56/57, T=8192 92/82
-//   d=128, causal:    n=128: T=100 13/8, T=512 15/11, T=900 19/15;   n=160: T=512 15/17, T=1024 20/19;
-//                     n=192: T=1024 21/23, T=2048 32/31, T=8192 103/93;   n=256: T=8192 105/115
-//     slots of one head:  n=128: T=512 35/28, T=8192 120/93;   n=160: T=1024 41/47, T=4096 75/65;   n=192: T=4096 76/76
-//     not causal:     n=128: T=512 15/14, T=4096 55/58 (12 slots 76/70);   n=96: T=4096 55/53
+// (half of whose tiles are short) somewhat longer, on others, whose workgroups all last equally long, mostly up to 192
+// (short / other kernel, us, whole call; 12 slots where there are any):
+//   d=64, no slots or several heads per tile, causal:  T=128 n=384 10/15;   T=512 n=256 10/13, n=384 16/15;
+//                     T=4096: n=256 32/43, n=320 42/48, n=384 45/46, n=448 54/50;   T=8192: n=320 72/91, n=384 88/89, n=448 105/95
+//     not causal:     T=512 n=256 13/13;   T=640: n=240 14/16;   T=768: n=192 13/16, n=240 17/16;   T=1024: n=192 15/16, n=208 19/16;
+//                     T=2048: n=176 25/28, n=192 25/25, n=208 31/28;   two heads: T=1024 n=224 23/24, n=256 24/24;  T=1536 n=240 29/28
+//   d=64, slots of one head, causal:  n=192: T=128 19/21, T=1024 28/28;   T=512 n=256 30/26;   T=4096: n=224 47/60, n=256 56/54;
+//                     T=8000 n=252 73/92
+//   d=128, causal:    n=128: T=100 8/13, T=512 11/15, T=900 15/19;   n=160: T=512 17/15, T=1024 18/20;
+//                     n=192: T=1024 23/21, T=2048 30/32, T=4096 47/57;   T=8192 n=256 107/107;   T=9000 n=213 97/113
+//     slots of one head:  n=128: T=512 28/35;   n=160: T=1024 47/41, T=4096 62/76;   n=192: T=4096 72/76;   T=9000 n=213 125/132;
+//                     T=8192 n=256 131/127
+//     not causal:     n=128: T=512 14/15, T=2048 32/34, T=4096 54/55 (12 slots 70/76), T=8192 102/104;   n=256: T=8192 192/134
 bool fwd_few_tiles(const moda_shape* s, int heads_per_tile) {
   const long long n = (long long)s->B * s->Hq * ((s->T + 127) / 128);
   const bool rows = heads_per_tile == 1 && s->depth_count > 0;
   const int T = s->T;
-  int most;
-  if (s->d == 64 && s->causal) most = rows ? (T >= 8192 ? 256 : 192) : T <= 256 ? 384 : 256;
-  else if (s->d == 64) most = rows ? 192 : T <= 512 ? 256 : heads_per_tile > 1 ? 192 : 160;
-  else if (s->causal) most = rows ? (T >= 4096 ? 192 : 128) : T >= 2048 ? 192 : T >= 1024 ? 160 : 128;
-  else most = heads_per_tile == 1 && !rows && T > 1024 ? 96 : 128;
+  int most = 128;
+  if (s->d == 64 && s->causal) most = rows ? (T >= 4096 ? 256 : 192) : T <= 256 || T >= 4096 ? 384 : 256;
+  else if (s->d == 64 && rows) most = 192;
+  else if (s->d == 64) most = T <= 512 || (heads_per_tile == 2 && T <= 1300) ? 256 : T <= 640 ? 240 : 192;
+  else if (s->causal) most = rows ? (T >= 8192 ? 240 : T >= 4096 ? 192 : 128) : T >= 8192 ? 256 : T >= 2048 ? 192 : T >= 1024 ? 160 : 128;
   return n <= most;
 }
 

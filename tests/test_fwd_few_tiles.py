@@ -26,7 +26,9 @@ def test_fwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
 
 
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,causal", [(1, 8, 8, 700, 64, 4, True), (1, 8, 2, 513, 128, 6, True),
-                                                  (1, 16, 2, 300, 64, 0, False), (1, 2, 2, 4100, 128, 1, True)])
+                                                  (1, 16, 2, 300, 64, 0, False), (1, 2, 2, 4100, 128, 1, True),
+                                                  (1, 12, 12, 4096, 64, 0, True), (1, 3, 3, 9000, 128, 2, True), (1, 12, 12, 2000, 64, 0, False),
+                                                  (1, 4, 4, 3900, 128, 0, False)])
 def test_both_kernels_agree(B, Hq, Hk, T, d, L, causal):
     """(an empty tuning keeps the other kernel).  Both round weights and outputs to bf16: 2e-2 on O."""
     inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1600 + T, device="cuda")
