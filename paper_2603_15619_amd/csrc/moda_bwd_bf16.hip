@@ -1243,8 +1243,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
 // Workgroup = NW waves x 32 queries.  Accumulators hold dQ^T ([channel][query]: a lane owns
 // one query).  Launched with NW = 4 (two workgroups per compute unit); NW = 8 (one workgroup
 // per unit, a K/V tile serving twice as many queries) measured 6 % slower at B=8 H=16 T=4096.
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
+// PS: workgroups per compute unit, i.e. waves per SIMD: 2, or at d = 64 3 (dq_per_unit draws the line).
+template <int D, int NW, int PS>
+__global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
   using Tl = Tile<D>;
   using C = BwdCfg<D, NW>;
   constexpr int kQT = NW * 32;  // queries per workgroup
@@ -1260,7 +1261,7 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
   // tile by query tile (heavy, i.e. late, tiles first).
   const int G = p.Hq / p.Hk;
   int bg, tile_idx;  // (batch, key/value head); position in the walk over (query tile, head of the group)
-  head_blocked_id(layered_id(p.causal, 2), p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
+  head_blocked_id(layered_id(p.causal, PS), p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
   const int qt = n_qt - 1 - tile_idx / G;
   const int bh = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G;
   const int q0 = qt * kQT;
@@ -1308,9 +1309,16 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
     dof[st] = *(const bf16x8*)(dOb + (size_t)qrow * Tl::kRowBytes + st * 32 + hi * 16);
   }
   const float lse2 = p.lse2[(size_t)bh * T + qrow], md = p.minus_delta[(size_t)bh * T + qrow];
-  f32x16 minus_delta;  // dP - delta comes out of the matrix pipe: its accumulators start from here
+  // dP - delta comes out of the matrix pipe: its accumulators start from here.  (Three waves per SIMD have no registers
+  // to keep that: formed anew for every block.)
+  auto minus_delta = [&]() {
+    float x = md;
+    if constexpr (PS > 2) asm volatile("" : "+v"(x));
+    f32x16 r;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) minus_delta[i] = md;
+    for (int i = 0; i < 16; ++i) r[i] = x;
+    return r;
+  };
 
   const int n_keys = p.causal ? min(T, q0 + kQT) : T;
   const int nt = (n_keys + 63) / 64;
@@ -1391,7 +1399,7 @@ __global__ __launch_bounds__(NW * 64, 2) void moda_bwd_dq_kernel(BwdParams p) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
         s[kb] = mfma_bf16(fk[n % kBuf], qf[st], s[kb]);
-        dp[kb] = mfma_bf16(fv[n % kBuf], dof[st], st == 0 ? minus_delta : dp[kb]);
+        dp[kb] = mfma_bf16(fv[n % kBuf], dof[st], st == 0 ? minus_delta() : dp[kb]);
         if (kb == 1 && st % (NS / 4) == 0) weights(0, st / (NS / 4));
       } else {
         const int m = n - 2 * NS, ks = m / Tl::kDBlocks, db = m % Tl::kDBlocks;
@@ -1895,6 +1903,19 @@ static bool few_queries(const BwdParams& p, int d) {
                                      n32 * c.short_ends) / 256;
   return fourth(short_chain) + fourth(short_load) < fourth(chain) + fourth(load);
 }
+// Workgroups of the dQ kernel of 128 queries that share a compute unit.  At d = 64 three fit in registers: ahead where
+// a workgroup's two ends weigh most, where three hold the grid and two do not (calls that are not causal; causal
+// ones, whose third layer has few light tiles to go with the heavy ones, while they are short), and in larger
+// grids of short sequences; otherwise two are as fast or faster, as the chip's power is what counts (three against
+// two, whole call, workgroups: T=40: 1024 0.97, 2048 0.91;  not causal: T=300 768 0.98, T=1500 768 0.98, T=5789 736 0.95,
+// T=2048 1024 1.02, 2048 1.00;  causal: T=300 768 0.97, T=700 768 0.97, T=1500 768 1.03, T=3000 768 1.05, T=512 1024 1.02,
+// T=1000 2048 0.98, T=2048 4096 0.98, T=4096 2048 1.01, T=16384 2048 1.03).
+static int dq_per_unit(const BwdParams& p, int d, long long workgroups) {
+  if (d != 64 || workgroups <= 512) return 2;
+  if (p.T <= 128) return 3;
+  if (workgroups <= 768) return !p.causal || p.T <= 700 ? 3 : 2;
+  return workgroups >= 2048 && p.T <= 2048 ? 3 : 2;
+}
 // Depth-slot gradients of 5 to 8 heads: inside dK/dV (depth_group_rows), or in a kernel of their own
 // (depth_gqa).  The former takes 32 slots at a time whether they exist or not, and a wave takes 32
 // positions one after the other: it needs mostly full blocks of slots, and enough key tiles.
@@ -1965,7 +1986,8 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   if (few_queries(p, D))
     return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)((long long)p.B * p.Hq * ((p.T + 31) / 32))), dim3(256),
                          stream, p);
-  return launch_kernel(moda_bwd_dq_kernel<D, kDqWaves>, dim3((unsigned)g_dq), dim3(kDqWaves * 64), stream, p);
+  return launch_kernel(dq_per_unit(p, D, g_dq) == 3 ? moda_bwd_dq_kernel<D, kDqWaves, D == 64 ? 3 : 2> : moda_bwd_dq_kernel<D, kDqWaves, 2>,
+                       dim3((unsigned)g_dq), dim3(kDqWaves * 64), stream, p);
 }
 
 hipError_t launch_bwd_bf16(const BwdParams& p, int d, hipStream_t stream) {

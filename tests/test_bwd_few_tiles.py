@@ -31,20 +31,33 @@ def test_bwd_few_tiles_of_many_queries(B, Hq, Hk, T, L, La, causal):
     check_full(B, Hq, T, 64, L, 1350 + T + L, causal=causal, depth_alloc=La, Hk=Hk)
 
 
-@pytest.mark.parametrize("B,Hq,T,d,L", [(3, 11, 1600, 128, 0), (1, 23, 2500, 64, 2), (5, 13, 610, 128, 3)])
-def test_bwd_grids_of_one_round(B, Hq, T, d, L):
-    """Between one and two workgroups per compute unit, a number that 8 does not divide: tiles of every other
-    layer in reverse.  The first and the last sequence (they differ in their data only)."""
-    inp = synth.make_inputs(B, Hq, Hq, T, d, L, dtype="bf16", seed=1380 + T, device="cuda", with_dO=True)
-    grads = run_gpu(inp, L, True)
+def check_ends(B, Hq, Hk, T, d, L, seed, causal):
+    """The first and the last sequence (they differ in their data only)."""
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=seed, device="cuda", with_dO=True)
+    grads = run_gpu(inp, L, causal)
     for b in {0, B - 1}:
         args = [None if inp[k] is None else synth.to_f64(inp[k][b:b + 1]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth", "dO")]
-        ref, noise = R.bwd(*args, depth_count=L, causal=True), R.bwd_noise(*args, depth_count=L, causal=True)
+        ref, noise = R.bwd(*args, depth_count=L, causal=causal), R.bwd_noise(*args, depth_count=L, causal=causal)
         for name, g, r, n in zip(NAMES, grads, ref, noise):
             if g is not None:
                 compare(name, g[b:b + 1], r, n)
     for g in grads:
         assert g is None or torch.isfinite(g.float()).all()
+
+
+@pytest.mark.parametrize("B,Hq,T,d,L", [(3, 11, 1600, 128, 0), (1, 23, 2500, 64, 2), (5, 13, 610, 128, 3)])
+def test_bwd_grids_of_one_round(B, Hq, T, d, L):
+    """Between one and two workgroups per compute unit, a number that 8 does not divide: tiles of every other
+    layer in reverse."""
+    check_ends(B, Hq, Hq, T, d, L, 1380 + T, True)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,L,causal", [(65, 8, 8, 33, 2, True), (75, 16, 2, 127, 0, False), (37, 6, 6, 321, 3, True), (17, 8, 4, 640, 0, True),
+                                                (8, 8, 8, 1100, 1, False), (19, 4, 2, 1100, 0, False), (70, 8, 8, 400, 0, True)])
+def test_bwd_three_workgroups_per_unit(B, Hq, Hk, T, L, causal):
+    """d = 64, the dQ kernel's grids that take three workgroups per compute unit: short sequences, one
+    round of three (in layers where causal; 8 does not divide it), many workgroups."""
+    check_ends(B, Hq, Hk, T, 64, L, 1390 + T, causal)
 
 
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(89, 8, 8, 130, 64, 5, 6, True), (89, 16, 8, 131, 64, 3, None, True),
