@@ -44,6 +44,7 @@ def _compile(src):
 #     register unless it sits inside one of the hand-written assembly statements,
 #   - no hand-written statement that names an accumulation register can execute before
 #     the acquire marker or after the release marker (there the registers are the compiler's),
+#   - nothing uses the result of a hand-written matrix instruction too early,
 #   - nothing was spilled to scratch memory.
 NAMED_ACC_SOURCES = ("moda_fwd_bf16.hip",)
 ACC_ACQUIRE_MARKER = "MODA_ACC_REGISTERS_ACQUIRED"
@@ -67,11 +68,11 @@ def _kernel_bodies(asm_path):
             body.append((n, line.rstrip("\n")))
 
 
-def _check_kernel(asm_path, name, body) -> None:
+def _instructions(body):
+    """The instruction stream of a function, [(line_no, text, hand_written)], with the markers as
+    instructions of their own, and its labels, {name: index}."""
     import re
 
-    acc = re.compile(r"\ba(?:\[\d+:\d+\]|\d+)\b")
-    # instruction stream: (line_no, text, hand_written)
     ins, labels, in_asm = [], {}, False
     for n, line in body:
         if "#ASMSTART" in line:
@@ -93,6 +94,79 @@ def _check_kernel(asm_path, name, body) -> None:
         if code.startswith("."):
             continue
         ins.append((n, code, in_asm))
+    return ins, labels
+
+
+def _successors(asm_path, ins, labels, i):
+    """Indices of the instructions that can execute right after instruction i."""
+    op = ins[i][1].split()[0]
+    if op in ("s_setpc_b64", "s_swappc_b64", "s_call_b64") or op.startswith("s_cbranch_i_fork"):
+        raise RuntimeError("%s:%d: indirect control flow: %s" % (asm_path, ins[i][0], ins[i][1]))
+    if op == "s_endpgm":
+        return []
+    if op == "s_branch":
+        return [labels[ins[i][1].split()[1]]]
+    out = [i + 1] if i + 1 < len(ins) else []
+    if op.startswith("s_cbranch"):
+        out.append(labels[ins[i][1].split()[1]])
+    return out
+
+
+# The compiler keeps other instructions away from a matrix instruction's result for as long as it takes, but not
+# from the result of one that is written as inline assembly, and the hardware does not wait either: such a
+# result (v_mfma_f32_32x32x16_bf16, 8 passes) may be read or overwritten no earlier than RESULT_SLOTS issue
+# slots later, except by a matrix instruction that accumulates in the same registers.  A matrix instruction
+# issued in between counts MFMA_SLOTS, s_nop N counts N + 1, any other one 1.
+RESULT_SLOTS = 12
+MFMA_SLOTS = 8
+
+
+def _registers(text):
+    """The vector and accumulation registers that an operand text names, as {("v" or "a", number)}."""
+    import re
+
+    out = set()
+    for file, lo, hi, one in re.findall(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)", text):
+        out.update((file, r) for r in (range(int(lo), int(hi) + 1) if lo else [int(one)]))
+    return out
+
+
+def _check_result_distance(asm_path, name, body) -> None:
+    ins, labels = _instructions(body)
+    regs = [_registers(code) for _, code, _ in ins]
+
+    def slots(i):
+        op = ins[i][1].split()
+        if op[0].startswith("v_mfma"):
+            return MFMA_SLOTS
+        return int(op[1], 0) + 1 if op[0] == "s_nop" else 1
+
+    for start, (n, code, hand) in enumerate(ins):
+        if not (hand and code.startswith("v_mfma")):
+            continue
+        result = _registers(code.split(None, 1)[1].split(",")[0])
+        nearest, todo = {}, [(j, 0) for j in _successors(asm_path, ins, labels, start)]
+        while todo:
+            i, passed = todo.pop()
+            if passed >= RESULT_SLOTS or nearest.get(i, RESULT_SLOTS) <= passed:
+                continue
+            nearest[i] = passed
+            if regs[i] & result:
+                operands = ins[i][1].split(None, 1)[1].split(", ") if ins[i][1].startswith("v_mfma") else []
+                if len(operands) >= 4 and _registers(operands[0]) == result and not (
+                        (_registers(operands[1]) | _registers(operands[2])) & result):
+                    continue  # accumulates on; its own result is looked at in turn
+                raise RuntimeError("%s:%d: %s: the result of line %d is used %d issue slots after it instead of %d: %s"
+                                   % (asm_path, ins[i][0], name, n, passed, RESULT_SLOTS, ins[i][1]))
+            todo.extend((j, passed + slots(i)) for j in _successors(asm_path, ins, labels, i))
+
+
+def _check_kernel(asm_path, name, body) -> None:
+    import re
+
+    acc = re.compile(r"\ba(?:\[\d+:\d+\]|\d+)\b")
+    ins, labels = _instructions(body)
+
     def the_marker(text):
         found = [i for i, x in enumerate(ins) if x[1] == text]
         if len(found) != 1:
@@ -102,17 +176,7 @@ def _check_kernel(asm_path, name, body) -> None:
     acquire, marker = the_marker(ACC_ACQUIRE_MARKER), the_marker(ACC_RELEASE_MARKER)
 
     def successors(i):
-        op = ins[i][1].split()[0]
-        if op in ("s_setpc_b64", "s_swappc_b64", "s_call_b64") or op.startswith("s_cbranch_i_fork"):
-            raise RuntimeError("%s:%d: indirect control flow: %s" % (asm_path, ins[i][0], ins[i][1]))
-        if op == "s_endpgm":
-            return []
-        if op == "s_branch":
-            return [labels[ins[i][1].split()[1]]]
-        out = [i + 1] if i + 1 < len(ins) else []
-        if op.startswith("s_cbranch"):
-            out.append(labels[ins[i][1].split()[1]])
-        return out
+        return _successors(asm_path, ins, labels, i)
 
     def reach(start, stop=None):
         seen, todo = set(), [start]
@@ -148,6 +212,7 @@ def check_named_acc_registers(src) -> None:
     n_kernels = 0
     for name, body in _kernel_bodies(asm):
         _check_kernel(asm, name, body)
+        _check_result_distance(asm, name, body)
         n_kernels += 1
     if n_kernels == 0:
         raise RuntimeError("%s: no kernel found" % asm)

@@ -56,6 +56,45 @@ def test_missing_marker_is_rejected(tmp_path):
         check(tmp_path, bad)
 
 
+# a hand-written matrix instruction, `%s` behind it, then a loop around the code that uses its result
+RESULT = """\
+_Z6kernelv:
+.LBB0_1:
+\tv_add_f32_e32 v40, v3, v41
+\t;;#ASMSTART
+\tv_mfma_f32_32x32x16_bf16 v[0:15], a[32:35], a[0:3], 0
+\t;;#ASMEND
+%s
+\ts_cbranch_scc1 .LBB0_1
+\tv_mul_f32_e32 v50, v15, v51
+\ts_endpgm
+.Lfunc_end0:
+"""
+MORE = "\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 v[0:15], a[36:39], a[4:7], v[0:15]\n\t;;#ASMEND\n"
+OTHER = "\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 a[64:79], a[40:43], v[%d:%d], a[64:79]\n\t;;#ASMEND\n"
+
+
+def check_distance(tmp_path, text):
+    f = tmp_path / "r.s"
+    f.write_text(RESULT % text)
+    for name, body in B._kernel_bodies(str(f)):
+        B._check_result_distance(str(f), name, body)
+
+
+@pytest.mark.parametrize("between", ["\ts_nop 10", "\ts_nop 7\n\ts_nop 2", "\tv_mov_b32_e32 v60, 0\n" * 11, MORE + "\ts_nop 10",
+                                     OTHER % (20, 23) + "\ts_nop 2"])
+def test_matrix_results_used_late_enough(tmp_path, between):
+    check_distance(tmp_path, between)
+
+
+@pytest.mark.parametrize("between", ["", "\ts_nop 9", "\tv_mov_b32_e32 v60, 0\n" * 10, "\ts_nop 10\n" + MORE, "\tv_mov_b32_e32 v7, 0\n\ts_nop 15",
+                                     OTHER % (20, 23) + "\ts_nop 1", "\ts_nop 5\n" + OTHER % (12, 15) + "\ts_nop 15"])
+def test_matrix_results_used_too_early_are_rejected(tmp_path, between):
+    """By the next instruction, around the loop, by an overwriting move, or as another product's factor."""
+    with pytest.raises(RuntimeError, match="issue slots after it instead of 12"):
+        check_distance(tmp_path, between)
+
+
 SCRATCH = """\
 _Z9my_kernelv:
 \tscratch_store_dword off, v1, off
