@@ -325,6 +325,18 @@ def cpu_baseline(inp, T, d, L, H, target_rows):
                       "full causal key range per row, fp64" % (len(rows), B * H)}
 
 
+def fwd_kernel_name(B, Hq, Hk, T, d, L, dtype):
+    """The kernel that the forward of this shape runs, as the library reports it."""
+    import ctypes
+
+    from paper_2603_15619_amd import MODAShape, lib
+
+    name = ctypes.create_string_buffer(64)
+    shape = MODAShape(B, Hq, Hk, T, d, L, L, 1, 0.0, 1 if dtype == "bf16" else 0)
+    lib().moda_fwd_kernel_name(ctypes.byref(shape), None, name, len(name))
+    return name.value.decode()
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -410,8 +422,7 @@ def main():
               "traffic_source": ("stored: profiles/traffic.json (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this "
                                  "command), not measured by this run") if stored is not None
               else "no counter run stored for this workload",
-              "kernel": ("moda_fwd_bf16_kernel<%d>" % d)
-              if dtype == "bf16" else ("moda_fwd_f32_kernel<%d>" % d),
+              "kernel": fwd_kernel_name(B, Hq, Hk, T, d, L, dtype),
               "kernel_ms_mean": round(ms_kernel, 4), "kernel_ms_min": round(ms_min, 4),
               "flops_per_launch": flops, "bytes_per_launch": alg_bytes}
     if alg_bytes / 8.0e12 > flops / (PEAK_TFLOPS[dtype] * 1e12):

@@ -238,6 +238,15 @@ int moda_version(void);
  */
 int moda_kernels_per_call(const moda_shape* s, int which);
 
+/*
+ * The name, without its namespace, of the kernel that moda_attn_fwd_tuned (or,
+ * tuning NULL, moda_attn_fwd) enqueues for shape `s`, as a profiler prints it,
+ * e.g. "moda_fwd_bf16_kernel<128, 8, 2>" (head dimension, waves per workgroup,
+ * waves per SIMD).  Written to `name` as by snprintf: at most `size` bytes, the
+ * last one NUL.  Returns its length, 0 for an empty or rejected problem.
+ */
+int moda_fwd_kernel_name(const moda_shape* s, const moda_fwd_tuning* tuning, char* name, size_t size);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1,6 +1,7 @@
 // libmoda C ABI: argument validation and kernel dispatch (host code only).
 #include <algorithm>
 #include <math.h>
+#include <stdio.h>
 
 #include "../../include/moda.h"
 #include "moda_launch.h"
@@ -124,6 +125,43 @@ int heads_per_die_at_a_time(long long n_heads, int T, int d, bool four_per_simd 
   return hg;
 }
 
+// The forward kernel that a call takes.
+struct FwdRoute {
+  int heads_per_tile;
+  bool few_tiles;       // moda_fwd_short.hip; else, bf16, moda_fwd_bf16.hip with
+  int waves, per_simd;  // waves per workgroup, waves that share a SIMD
+};
+FwdRoute fwd_route(const moda_shape* s, const moda_fwd_tuning* tuning) {
+  FwdRoute r;
+  // grouped queries: as many heads of a group per tile (side by side in every wave) as divide the
+  // group, up to 32
+  const int G = s->Hq / s->Hk;
+  r.heads_per_tile = 1;
+  for (int gt = 32; gt > 1; gt /= 2)
+    if (G % gt == 0) {
+      r.heads_per_tile = gt;
+      break;
+    }
+  // (without depth slots two heads per wave only halve the positions a tile covers: measured 10 %
+  //  slower than one head per tile at G = 2, equal or faster from 4 heads on)
+  if (s->depth_count == 0 && r.heads_per_tile < 4) r.heads_per_tile = 1;
+  if (tuning && tuning->heads_per_tile > 0) r.heads_per_tile = tuning->heads_per_tile;
+  r.waves = tuning && s->dtype == MODA_BF16 && tuning->waves != 0 ? tuning->waves : fwd_waves_per_workgroup(s, r.heads_per_tile);
+  r.per_simd = fwd_waves_per_simd(s, r.heads_per_tile, r.waves);
+  r.few_tiles = s->dtype == MODA_BF16 && !tuning && fwd_few_tiles(s, r.heads_per_tile);
+  return r;
+}
+
+moda_status check_tuning(const moda_shape* s, const moda_fwd_tuning* tuning) {
+  if (!tuning || s->dtype != MODA_BF16) return MODA_OK;
+  if (tuning->waves != 0 && tuning->waves != 4 && tuning->waves != 8) return MODA_ERR_SHAPE;
+  const int gt = tuning->heads_per_tile;
+  if (gt < 0 || gt > 32 || (gt & (gt - 1)) != 0 || (gt > 0 && s->Hq / s->Hk % gt != 0)) return MODA_ERR_SHAPE;
+  if (tuning->head_group < 0) return MODA_ERR_SHAPE;
+  if (tuning->depth_path < 0 || tuning->depth_path > 2) return MODA_ERR_SHAPE;
+  return MODA_OK;
+}
+
 float resolve_scale(const moda_shape* s) {
   return s->scale > 0.f ? s->scale : 1.0f / sqrtf((float)s->d);
 }
@@ -162,19 +200,25 @@ int moda_kernels_per_call(const moda_shape* s, int which) {
   return moda::bwd_bf16_kernels(bwd_dims(s), s->d);
 }
 
+int moda_fwd_kernel_name(const moda_shape* s, const moda_fwd_tuning* tuning, char* name, size_t size) {
+  if (name && size > 0) name[0] = 0;
+  if (check_shape(s) != MODA_OK || check_tuning(s, tuning) != MODA_OK || s->B == 0 || s->T == 0) return 0;
+  const FwdRoute r = fwd_route(s, tuning);
+  moda::FwdParams p;
+  p.B = s->B; p.Hq = s->Hq; p.T = s->T;
+  if (s->dtype == MODA_F32) return snprintf(name, size, "moda_fwd_f32_%skernel<%d>", moda::fwd_f32_by_rows(p) ? "rows_" : "", s->d);
+  if (r.few_tiles) return snprintf(name, size, "moda_fwd_short_kernel<%d, %s>", s->d, r.heads_per_tile == 1 && s->depth_count > 0 ? "true" : "false");
+  return snprintf(name, size, "moda_fwd_bf16_kernel<%d, %d, %d>", s->d, r.waves, r.per_simd);
+}
+
 moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
                                 const void* Vdepth, void* O, float* LSE, const moda_shape* s,
                                 const moda_fwd_tuning* tuning, void* hip_stream) {
   moda_status st = check_shape(s);
   if (st != MODA_OK) return st;
   const int G = s->Hq / s->Hk;
-  if (tuning && s->dtype == MODA_BF16) {
-    if (tuning->waves != 0 && tuning->waves != 4 && tuning->waves != 8) return MODA_ERR_SHAPE;
-    const int gt = tuning->heads_per_tile;
-    if (gt < 0 || gt > 32 || (gt & (gt - 1)) != 0 || (gt > 0 && G % gt != 0)) return MODA_ERR_SHAPE;
-    if (tuning->head_group < 0) return MODA_ERR_SHAPE;
-    if (tuning->depth_path < 0 || tuning->depth_path > 2) return MODA_ERR_SHAPE;
-  }
+  st = check_tuning(s, tuning);
+  if (st != MODA_OK) return st;
   if (s->B == 0 || s->T == 0) return MODA_OK;
   if (!Q || !Kseq || !Vseq || !O || !LSE) return MODA_ERR_NULL;
   if (s->depth_count > 0 && (!Kdepth || !Vdepth)) return MODA_ERR_NULL;
@@ -190,18 +234,8 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   p.causal = s->causal;
   p.scale = resolve_scale(s);
   p.scale_log2 = p.scale * 1.4426950408889634f;
-  // grouped queries: as many heads of a group per tile (side by side in every wave) as divide the
-  // group, up to 32
-  p.heads_per_tile = 1;
-  for (int gt = 32; gt > 1; gt /= 2)
-    if (G % gt == 0) {
-      p.heads_per_tile = gt;
-      break;
-    }
-  // (without depth slots two heads per wave only halve the positions a tile covers: measured 10 %
-  //  slower than one head per tile at G = 2, equal or faster from 4 heads on)
-  if (s->depth_count == 0 && p.heads_per_tile < 4) p.heads_per_tile = 1;
-  if (tuning && tuning->heads_per_tile > 0) p.heads_per_tile = tuning->heads_per_tile;
+  const FwdRoute route = fwd_route(s, tuning);
+  p.heads_per_tile = route.heads_per_tile;
   // depth slots: on the matrix pipe when several heads share a position's slots (the block
   // products are then dense enough to beat the vector ALUs), else on the vector ALUs, where the
   // phase already runs at the rate a compute unit can fetch
@@ -209,8 +243,7 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   if (tuning && s->dtype == MODA_BF16 && tuning->depth_path != 0)
     p.depth_mfma = (tuning->depth_path == 2 && s->depth_count > 0) ? 1 : 0;
   p.depth_magic = s->depth_count > 1 ? (unsigned)((1ull << 32) / (unsigned)s->depth_count) + 1u : 0u;
-  const int waves = tuning && s->dtype == MODA_BF16 && tuning->waves != 0 ? tuning->waves : fwd_waves_per_workgroup(s, p.heads_per_tile);
-  const int per_simd = fwd_waves_per_simd(s, p.heads_per_tile, waves);
+  const int waves = route.waves, per_simd = route.per_simd;
   p.head_group = heads_per_die_at_a_time((long long)s->B * s->Hk * (G / p.heads_per_tile), s->T, s->d, per_simd == 4);
   if (tuning && tuning->head_group > 0) p.head_group = tuning->head_group;
   const int rows = moda::fwd_bf16_tile_rows(waves) / p.heads_per_tile;  // positions per tile
@@ -222,7 +255,7 @@ moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vse
   }
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (s->dtype == MODA_BF16 && !tuning && fwd_few_tiles(s, p.heads_per_tile)) {
+  if (route.few_tiles) {
     const int pos = moda::fwd_short_tile_pairs() / p.heads_per_tile;
     p.n_qtiles = (s->T + pos - 1) / pos;
     return launch_status(moda::launch_fwd_short(p, s->d, stream));

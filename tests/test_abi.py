@@ -188,3 +188,32 @@ def test_depth_gradients_of_8_heads_inside_dkdv_where_blocks_of_32_slots_are_fil
 
     s = MODAShape(8, 64, 8, 4096, 64, 64, L_slots, 1, 0.0, 1)
     assert L.moda_kernels_per_call(ctypes.byref(s), 1) == kernels
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,slots,causal,dtype,tuned,name", [
+    (1, 16, 16, 65536, 128, 15, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),
+    (8, 16, 16, 513, 128, 1, 1, 1, None, "moda_fwd_bf16_kernel<128, 4, 2>"),   # one and a half rounds, up to 1024 positions
+    (7, 12, 12, 1030, 128, 1, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),  # ... and more
+    (29, 4, 4, 1000, 128, 0, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),   # more than one and three quarters
+    (13, 12, 12, 1000, 64, 0, 1, 1, None, "moda_fwd_bf16_kernel<64, 4, 4>"),
+    (13, 12, 12, 1030, 64, 0, 1, 1, None, "moda_fwd_bf16_kernel<64, 8, 4>"),
+    (2, 16, 16, 1500, 64, 7, 1, 1, None, "moda_fwd_bf16_kernel<64, 4, 2>"),
+    (2, 16, 16, 1500, 64, 7, 1, 1, dict(waves=8), "moda_fwd_bf16_kernel<64, 8, 4>"),
+    (1, 12, 12, 2000, 64, 0, 0, 1, None, "moda_fwd_short_kernel<64, false>"),
+    (1, 13, 13, 2000, 64, 0, 0, 1, None, "moda_fwd_bf16_kernel<64, 4, 2>"),
+    (1, 2, 2, 100, 128, 3, 1, 1, None, "moda_fwd_short_kernel<128, true>"),
+    (1, 2, 2, 100, 128, 3, 1, 1, dict(), "moda_fwd_bf16_kernel<128, 4, 2>"),
+    (1, 2, 2, 256, 64, 4, 1, 0, None, "moda_fwd_f32_kernel<64>"),
+    (1, 2, 2, 5, 64, 4, 1, 0, None, "moda_fwd_f32_rows_kernel<64>"),
+    (0, 2, 2, 5, 64, 4, 1, 0, None, ""), (1, 2, 2, 5, 96, 4, 1, 1, None, ""), (1, 2, 2, 5, 64, 4, 1, 1, dict(waves=5), "")])
+def test_forward_kernel_names(L, B, Hq, Hk, T, d, slots, causal, dtype, tuned, name):
+    from paper_2603_15619_amd.binding import MODAFwdTuning, MODAShape
+
+    s = MODAShape(B, Hq, Hk, T, d, slots, slots, causal, 0.0, dtype)
+    tuning = None if tuned is None else ctypes.byref(MODAFwdTuning(**tuned))
+    out = ctypes.create_string_buffer(64)
+    assert L.moda_fwd_kernel_name(ctypes.byref(s), tuning, out, len(out)) == len(name)
+    assert out.value.decode() == name
+    cut = ctypes.create_string_buffer(8)
+    L.moda_fwd_kernel_name(ctypes.byref(s), tuning, cut, len(cut))
+    assert cut.value.decode() == name[:7]
