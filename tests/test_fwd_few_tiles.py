@@ -68,10 +68,13 @@ def test_depth_slots_of_weight_zero(T, d, L, dead):
 
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,causal", [(64, 16, 16, 100, 64, 3, True), (40, 8, 8, 384, 128, 0, False),
                                                   (40, 16, 4, 128, 64, 5, True), (12, 16, 16, 500, 64, 2, True),
-                                                  (6, 8, 8, 1800, 128, 0, False), (8, 16, 16, 513, 128, 1, True)])
+                                                  (6, 8, 8, 1800, 128, 0, False), (8, 16, 16, 513, 128, 1, True),
+                                                  (7, 12, 12, 1030, 128, 1, True), (29, 4, 4, 1000, 128, 0, True),
+                                                  (13, 12, 12, 1030, 64, 2, True)])
 def test_workgroups_of_four_waves(B, Hq, Hk, T, d, L, causal):
-    """Short sequences in large grids and one and a half rounds of workgroups take four waves (the last
-    case just does not): against eight on the same inputs, rows of whole heads against the oracle."""
+    """Short sequences in large grids and one and a half rounds of workgroups take four waves (the last three
+    cases just do not, see test_abi's kernel names): against eight on the same inputs, rows of whole heads
+    against the oracle."""
     inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1900 + T, device="cuda")
     O0, L0 = run_gpu(inp, L, causal)
     O1, L1 = run_gpu(inp, L, causal, tuning=dict(waves=8))
@@ -81,3 +84,17 @@ def test_workgroups_of_four_waves(B, Hq, Hk, T, d, L, causal):
     Oref, Lref = R.fwd(*(synth.to_f64(one[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), depth_count=L, causal=causal)
     assert np.abs(synth.to_f64(O0[B - 1:]) - Oref).max() <= 2e-2
     assert np.abs(synth.to_f64(L0[B - 1:]) - Lref).max() <= 1e-3
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,L,causal", [(3, 11, 11, 1300, 2, True), (5, 13, 13, 700, 0, True), (3, 10, 5, 1290, 3, True),
+                                                (2, 23, 23, 1100, 1, False)])
+def test_grids_of_one_round(B, Hq, Hk, T, L, causal):
+    """d = 128, more than 256 workgroups of four waves that are resident all at once (tiles of every other layer in
+    reverse where causal; 8 does not divide their number), slots first in the light tiles."""
+    inp = synth.make_inputs(B, Hq, Hk, T, 128, L, dtype="bf16", seed=1950 + T, device="cuda")
+    O, LSE = run_gpu(inp, L, causal)
+    for b in (0, B - 1):
+        one = {k: None if v is None else v[b:b + 1].contiguous() for k, v in inp.items()}
+        Oref, Lref = R.fwd(*(synth.to_f64(one[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), depth_count=L, causal=causal)
+        assert np.abs(synth.to_f64(O[b:b + 1]) - Oref).max() <= 2e-2
+        assert np.abs(synth.to_f64(LSE[b:b + 1]) - Lref).max() <= 1e-3
