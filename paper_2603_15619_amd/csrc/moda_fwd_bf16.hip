@@ -11,8 +11,8 @@
 // registers, into rings of 4 stages each, two iterations ahead of their use, and
 // consumed by v_mfma_f32_32x32x16_bf16:
 //   S^T = K Q^T   (keys on the MFMA M axis, queries on N): a lane then holds 16
-//                 scores of ONE query per 32x32 block, so the row max / row sum
-//                 are in-lane reductions plus one exchange with lane ^ 32;
+//                 scores of ONE query per 32x32 block, so a row's sum is an in-lane
+//                 reduction plus, once per call, one exchange with lane ^ 32;
 //   O^T += V^T P^T with P^T taken straight from the S^T accumulators (no layout
 //                 round trip); the V^T operand comes from ds_read_b64_tr_b16.
 // The key loop is software pipelined: while tile kt-1's P V and tile kt+1's K Q^T run
@@ -503,8 +503,9 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
   //               normalised and stored.
   // Work items (row step, chunk of kDepthChunk slots) are walked in order with the loads of
   // the next TWO items in flight while the current item is folded: the phase is bound by
-  // memory latency, i.e. by the bytes a compute unit keeps in flight, and the 128
-  // accumulation registers that the key loop does not need at that time hold most of them.
+  // memory latency, i.e. by the bytes a compute unit keeps in flight, and the
+  // accumulation registers (128; 64 with four waves per SIMD, hence the shorter chunk there) that the key loop
+  // does not need at that time hold most of them.
   constexpr std::integral_constant<int, 0> kDepthLast{};
   constexpr std::integral_constant<int, 1> kDepthFirst{};
   constexpr std::integral_constant<int, 2> kPlainStore{};

@@ -22,10 +22,10 @@
 // 900 at d = 128) and the matrix pipe, of different waves, on the sequence keys; HBM on the depth slots (4 bytes
 // per FLOP); every other workgroup takes its slots before its key tiles, the others after, so that both
 // are busy.
-//   B=1 H=16 T=2000 d=128, 15 slots: 0.190 ms, 88 TFLOP/s and 2.9 TB/s (fp32 matrix instructions: 0.226 ms; one
-//                                    wave per query on the vector ALUs: 2.69 ms); no slots 0.162 -> 0.119
-//   B=1 H=16 T=8000 d=128, no slots: 1.59 ms, 165 TFLOP/s (1.97; a library product of 8192^3 reaches 154)
-//   B=1 H=2 T=256 d=64, 4 slots:     9.8 us (10.8), most of it latency from one end to the other
+//   B=1 H=16 T=2000 d=128, 15 slots: 0.168 ms, 99 TFLOP/s and 3.3 TB/s (fp32 matrix instructions: 0.211 ms; one
+//                                    wave per query on the vector ALUs: 2.69 ms); no slots 0.162 -> 0.122
+//   B=1 H=16 T=8000 d=128, no slots: 1.60 ms, 164 TFLOP/s (1.97; a library product of 8192^3 reaches 154)
+//   B=1 H=2 T=256 d=64, 4 slots:     9.9 us (10.6), most of it latency from one end to the other
 // (Splitting the next operand between the matrix instructions of one wave: no change; subtracting the
 // parts with packed dot products, 7 instructions per two numbers instead of 11: 2 to 6 % slower.)
 //
