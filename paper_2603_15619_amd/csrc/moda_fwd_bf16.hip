@@ -49,13 +49,6 @@ constexpr int kUnroll = 4;               // the key loop is unrolled over 4 step
 // cache policy of loads whose data is used exactly once (depth K/V): non-temporal, so
 // that the stream does not push the re-used sequence K/V tiles out of the L2
 constexpr int kStreamOnce = 2;
-// A reference is raised to the largest score and this many powers of two beyond, so that scores that rise from
-// tile to tile raise it once in several tiles.  (None: a raise takes as long as half a tile and more, and where every
-// tile raised it, the call was 5 to 30 % slower than with a row maximum per tile.  0 / 8 / 16 / 24 / 32 against that
-// one, slope in nats per key: B=8 H=16 T=2048 d=64, 0.3: 1.34 1.10 1.05 0.97 0.96; H=16 T=16384 d=128, 0.1: 1.13 0.99
-// 0.91 0.87 0.86, 0.3: 1.11 1.10 1.10 0.93 0.90.  Weights that come out as zero are those below 2^-102 of the
-// largest, instead of 2^-126: next to 2^-9, the rounding of the largest, nothing.)
-constexpr float kHeadroom = 24.f;
 // Geometries, PS waves per SIMD (D = 64 for 4):
 //   W = 8: workgroups of 8 waves (256 queries), PS / 2 per compute unit, K and V rings of 4 stages
 //          (128 KB at d = 128, 64 KB at d = 64); copies run two tiles ahead of their use.
@@ -1050,10 +1043,16 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
   // and their sum, which the normaliser needs anyway, tells afterwards whether that was good enough.  As
   // long as a lane's weights sum to at most 2^8, none exceeds 2^8, which fp32 sums and bf16 P hold
   // without loss, and the final division is unchanged.  Otherwise (and for NaN) the rare path raises the
-  // reference to the row maximum and kHeadroom beyond, rescales the accumulators and forms the step's weights anew, before they
-  // are multiplied with anything.  (The maximum, its exchange between two lanes, comparison and branch stood
+  // reference to the row maximum, the next step's scores included, rescales the accumulators and forms the step's weights
+  // anew, before they are multiplied with anything.  (The maximum, its exchange between two lanes, comparison and branch stood
   // before the first exponential of every tile: 24 of 150 vector instructions, and nothing to overlap with.
   // B=1 H=16 T=65536 d=128: 14.2 -> 13.2 ms, 1.33 PFLOP/s; B=1 Hq=64 Hk=8 T=16384 d=64: 2.49 -> 2.09 ms, 1.05.)
+  // The next step's scores are there, so its maximum counts too: scores that rise from step to step raise the reference
+  // in every other one.  (A raise takes half a step's time and more.  Time against a row maximum per tile, raised by its own
+  // step's / by both, slope in nats per key: B=8 H=16 T=2048 d=64, 0.1: 1.17 / 1.01, 0.3: 1.30 / 1.03; H=16 T=16384 d=128, 0.05:
+  // 1.11 / 1.05, 0.1: 1.10 / 0.92, 0.3: 1.10 / 0.92; without slope 0.81, 0.92.  A reference 2^24 beyond the maximum is raised more
+  // rarely still, 0.85 to 0.98, but the largest weight, which carries a row of far apart scores, is no longer exactly 1 before it
+  // is rounded: error of O at softmax scale 1 1.8e-3 -> 2.1e-3.)
   // Once per tile: wait for the copies issued two tiles ago, barrier (kSyncAt); the copies of
   // K tile kt+4 and V tile kt+2 into the stages just vacated ride along with the instructions after it.
   // Every tile issues the same number of copies (tiles past the end of the tensor are
@@ -1072,13 +1071,18 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
   };
   // the step's sum is in; `k_next`: first key of the step after, whose scores were taken
   auto end_step = [&](const SBlock<C>& cur, SBlock<C>& nxt, PBlock<C>& pcur, int k_next) __attribute__((always_inline)) {
+    if (k_next / kBN == wave_last && needs_mask(wave_last)) {
+      MODA_PIN();
+      MODA_NOP(15);
+      mask_block(nxt, k_next);
+    }
     if (__builtin_amdgcn_ballot_w64(!(w.sum <= 256.f)) != 0) {
       // Rare path.  (The products of the steps before have retired.)
       MODA_PIN();
       MODA_NOP(15);
       MODA_NOP(15);
-      const float mx = block_max(cur);
-      const float m_new = mx > m_run ? fminf(mx + kHeadroom * __builtin_amdgcn_rcpf(c2), FLT_MAX) : m_run;
+      float m_new = fmaxf(m_run, block_max(cur));
+      if (k_next / kBN <= wave_last) m_new = fmaxf(m_new, block_max(nxt));
       const float alpha = m_new == m_run ? 1.0f : fast_exp2((m_run - m_new) * c2);
       m_run = m_new;
       l_run *= alpha;
@@ -1088,11 +1092,6 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
       weigh_block(cur, pcur, w, m_new * c2, c2);
     }
     l_run += w.sum;
-    if (k_next / kBN == wave_last && needs_mask(wave_last)) {
-      MODA_PIN();
-      MODA_NOP(15);
-      mask_block(nxt, k_next);
-    }
     MODA_ANCHOR(nxt.a[0]);  // (no reader is moved up)
     MODA_ANCHOR(nxt.a[C::kKB - 1]);
   };

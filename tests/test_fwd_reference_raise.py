@@ -126,3 +126,36 @@ def test_rows_that_one_key_carries(T, d):
     O, _ = run_gpu(inp, L, True, scale)
     Oref, _ = R.fwd(*(synth.to_f64(inp[k]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")), depth_count=L, scale=scale)
     assert (np.abs(synth.to_f64(O) - Oref) <= 2.0 ** -8 * (np.abs(Oref) + 7 * 2.0 ** -6) + 1e-5).all()
+
+
+@pytest.mark.parametrize("L", [0, 3])
+@pytest.mark.parametrize("B,H,T,d,waves", KERNELS)
+def test_raised_reference_is_the_largest_score(B, H, T, d, waves, L):
+    """Key 100 is 12 to 13.5 powers of two above the keys before it, key 250 another 28 to 31.5: it weighs exactly 1 and all
+    others, together below 300 * 2^-28, nothing, so that the rows behind it are its value, bit by bit."""
+    inp = synth.make_inputs(B, H, H, T, d, L, dtype="bf16", seed=1000 + d, device="cuda")
+    for k in ("Q", "Kseq", "Kdepth"):
+        if inp[k] is not None:
+            inp[k].zero_()
+    inp["Q"][..., 0] = (1.0 + 0.125 * torch.rand(B, H, T, device="cuda")).to(torch.bfloat16)
+    inp["Kseq"][:, :, 100, 0], inp["Kseq"][:, :, 250, 0] = 12.0, 40.0
+    inp["Vseq"] = inp["Vseq"].sign() * (inp["Vseq"].abs() + 2.0 ** -6)  # (no value so small that the others' share shows)
+    O, LSE = run_gpu(inp, L, True, float(np.log(2.0)), dict(waves=waves))
+    assert torch.equal(O[:, :, 250:], inp["Vseq"][:, :, 250:251].expand(-1, -1, T - 250, -1))
+    assert (LSE[:, :, 250:] / float(np.log(2.0)) - 40.0 * inp["Q"][:, :, 250:, 0].float()).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("B,H,T,d,waves", [(B, H, 250, d, waves) for B, H, _, d, waves in KERNELS])
+def test_references_leave_out_masked_keys(B, H, T, d, waves):
+    """Every key is 32 powers of two above the one before it: a row's last key carries it, and the keys that it does not
+    see, up to 8000 powers above, must not become its reference."""
+    inp = synth.make_inputs(B, H, H, T, d, 0, dtype="bf16", seed=1010 + d, device="cuda")
+    inp["Q"].zero_()
+    inp["Kseq"].zero_()
+    inp["Q"][..., 0] = 32.0
+    inp["Kseq"][..., 0] = torch.arange(T, device="cuda").to(torch.bfloat16)
+    inp["Vseq"] = inp["Vseq"].sign() * (inp["Vseq"].abs() + 2.0 ** -6)
+    O, LSE = run_gpu(inp, 0, True, float(np.log(2.0)), dict(waves=waves))
+    assert torch.equal(O, inp["Vseq"])
+    want = torch.arange(T, device="cuda").float() * float(32 * np.log(2.0))
+    assert ((LSE - want).abs() <= 4 * 2.0 ** -24 * want + 1e-6).all()
