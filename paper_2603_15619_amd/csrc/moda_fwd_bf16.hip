@@ -706,10 +706,16 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(PS, PS))
   // d=128, 15 slots 105.8 / 99.5; B=3 H=16 T=1000 d=64, 12 slots 46.9 / 43.2; B=1 H=5 T=6000 d=128, 31
   // slots 142 / 135; with two rounds and more of workgroups up to 11 % slower: B=4 H=16 T=2000 d=64, 24 slots
   // 165 / 183).
-  const bool depth_first = L > 0 && (one_round ? 2 * tile_idx >= p.n_qtiles : ((blockIdx.x >> 3) & 1) != 0);
+  // Heads of one or two tiles have no light half to speak of: on the vector ALUs they alternate there too, once the slots
+  // weigh enough (light half, of one tile none, first / alternating, us, d=128 where nothing else is said, 256 heads: T=128, 15 slots
+  // 55.9 / 51.8, 7: 31.9 / 31.3, 1: 17.5 / 19.0; d=64, 15 slots 28.1 / 26.5, 7: 17.5 / 17.8;  T=239, 15 slots 99.6 / 95.9, 7: 59.6 / 57.0,
+  // 1: 28.7 / 29.9; 208 heads, 15 slots 84.0 / 84.8; d=64 47.1 / 49.0).
   // Two implementations of the depth slots: on the vector ALUs in the row-major mapping
   // (depth_phase above), or on the matrix pipe as extra key blocks (depth_blocks below).
   const bool depth_on_mfma = p.depth_mfma != 0;
+  const bool even = p.n_qtiles == 1 ? (long long)L * p.T * D >= 89600 && gridDim.x > 192
+                                    : p.n_qtiles == 2 && D == 128 && L >= 7 && gridDim.x > 224 * kPerUnit;
+  const bool depth_first = L > 0 && (one_round && (depth_on_mfma || !even) ? 2 * tile_idx >= p.n_qtiles : ((blockIdx.x >> 3) & 1) != 0);
   if (depth_first && !depth_on_mfma) {
     depth_phase(kDepthFirst);
     __syncthreads();  // rows were written into the buffers of the waves that own them

@@ -91,7 +91,21 @@ def test_workgroups_of_four_waves(B, Hq, Hk, T, d, L, causal):
 def test_grids_of_one_round(B, Hq, Hk, T, L, causal):
     """d = 128, more than 256 workgroups of four waves that are resident all at once (tiles of every other layer in
     reverse where causal; 8 does not divide their number), slots first in the light tiles."""
-    inp = synth.make_inputs(B, Hq, Hk, T, 128, L, dtype="bf16", seed=1950 + T, device="cuda")
+    check_ends(B, Hq, Hk, T, 128, L, 1950 + T, causal)
+
+
+@pytest.mark.parametrize("d,B,H,T,L", [(128, 14, 14, 100, 7), (128, 14, 14, 100, 6), (64, 30, 14, 100, 14), (64, 30, 14, 128, 10),
+                                       (128, 14, 17, 129, 7), (128, 16, 16, 250, 8), (128, 16, 14, 250, 8), (128, 40, 13, 240, 12),
+                                       (128, 40, 13, 230, 12), (128, 40, 13, 500, 12), (128, 16, 16, 240, 13), (128, 16, 8, 490, 12)])
+def test_heads_of_one_or_two_tiles(d, B, H, T, L):
+    """Either side of the lines between slots first in the light half (in no tile, where a head has one) and in every
+    other workgroup, and between four and eight waves for many slots."""
+    check_ends(B, H, H, T, d, L, 1970 + T, True)
+
+
+def check_ends(B, Hq, Hk, T, d, L, seed, causal):
+    """The first and the last sequence (they differ in their data only)."""
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=seed, device="cuda")
     O, LSE = run_gpu(inp, L, causal)
     for b in (0, B - 1):
         one = {k: None if v is None else v[b:b + 1].contiguous() for k, v in inp.items()}
