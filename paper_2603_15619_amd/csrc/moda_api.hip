@@ -54,7 +54,10 @@ moda_status launch_status(hipError_t e) {
 // sequences in large grids take 8.  4 waves take
 //   - grids that would leave compute units without work;
 //   - sequences of up to 512 pairs, which 8 waves pad to 256, and whose ends weigh more than their copies
-//     (4 / 8 waves, us, one head per tile: 12 slots T=128, 768 tiles of 128: 127 / 171);
+//     (4 / 8 waves, us, one head per tile: 12 slots T=128, 768 tiles of 128: 127 / 171, but with many slots and
+//     little padding 8 take over where they fill the chip just once, or in two rounds and more (256 heads, 12 slots: T=256
+//     84.6 / 82.3, T=200 71.2 / 71.9; 128 heads T=512 96.2 / 90.8;  1024 heads, 15 slots: T=200 324 / 326, T=239 382 / 372, T=400
+//     745 / 738, T=512 892 / 863; 7 slots T=239 216 / 225; 256 heads, 31 slots T=512 376 / 366);
 //   - one and a half rounds of workgroups of 8 waves, whose last half round 4 waves spread over all units
 //     (768 tiles: 12 slots T=2000 not causal 168 / 187, causal T=1000 138 / 150; causal and longer 0.92 to 1.14:
 //     not there).
@@ -66,7 +69,8 @@ int fwd_waves_per_workgroup(const moda_shape* s, int heads_per_tile) {
   const long long heads = (long long)s->B * s->Hq / heads_per_tile, pairs = (long long)s->T * heads_per_tile;
   const long long n = heads * ((pairs + 255) / 256);
   if (s->d == 64) return n <= 768 || pairs <= 1024 ? 4 : 8;
-  if (n < 256 || pairs <= 512) return 4;
+  if (n < 256) return 4;
+  if (pairs <= 512) return heads_per_tile == 1 && s->depth_count >= 12 && (n == 256 || n >= 512) && 10 * heads * pairs > 9 * 256 * n ? 8 : 4;
   return n > 256 && n <= 448 && (!s->causal || s->T <= 1024) ? 4 : 8;
 }
 

@@ -195,6 +195,12 @@ def test_depth_gradients_of_8_heads_inside_dkdv_where_blocks_of_32_slots_are_fil
     (8, 16, 16, 513, 128, 1, 1, 1, None, "moda_fwd_bf16_kernel<128, 4, 2>"),   # one and a half rounds, up to 1024 positions
     (7, 12, 12, 1030, 128, 1, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),  # ... and more
     (29, 4, 4, 1000, 128, 0, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),   # more than one and three quarters
+    (40, 13, 13, 240, 128, 12, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),  # many slots, little padding, two rounds
+    (40, 13, 13, 230, 128, 12, 1, 1, None, "moda_fwd_bf16_kernel<128, 4, 2>"),
+    (40, 13, 13, 240, 128, 11, 1, 1, None, "moda_fwd_bf16_kernel<128, 4, 2>"),
+    (39, 13, 13, 240, 128, 12, 1, 1, None, "moda_fwd_bf16_kernel<128, 4, 2>"),
+    (16, 16, 16, 240, 128, 12, 1, 1, None, "moda_fwd_bf16_kernel<128, 8, 2>"),  # ... or just one round
+    (16, 17, 17, 240, 128, 12, 1, 1, None, "moda_fwd_bf16_kernel<128, 4, 2>"),
     (13, 12, 12, 1000, 64, 0, 1, 1, None, "moda_fwd_bf16_kernel<64, 4, 4>"),
     (13, 12, 12, 1030, 64, 0, 1, 1, None, "moda_fwd_bf16_kernel<64, 8, 4>"),
     (2, 16, 16, 1500, 64, 7, 1, 1, None, "moda_fwd_bf16_kernel<64, 4, 2>"),
