@@ -6,9 +6,11 @@
 //   p_c = exp(scale <q_t, k_c> - LSE_t),  delta_t = <dO_t, O_t>,
 //   dV_c += p_c dO_t,  e_c = p_c (<dO_t, v_c> - delta_t),
 //   dQ_t = scale sum_c e_c k_c,  dK_c += scale e_c q_t.
-// Three kernels (four where the depth slots of a group have one of their own, see the end), no
-// atomics, every output element written exactly once:
+// No atomics, every output element written exactly once:
 //   delta  : LSE_t log2(e) and -delta_t for every row (row-parallel, vector ALUs).
+//   grads  : dK, dV and dQ in ONE launch, whose workgroups each take a key tile or a query tile as the two
+//            kernels below do; the depth slots go with the query tiles.  Calls of more than 16 positions
+//            without depth slots, or with 1, 2 or 4 heads per group.  All others:
 //   dkdv   : one workgroup per 128 sequence keys; Q / dO tiles stream through LDS;
 //            S = Q K^T and dP = dO V^T are recomputed per 32x32 block on the MFMA
 //            pipe, P and dS = P (dP - delta) are packed to bf16 straight out of the
@@ -26,10 +28,12 @@
 // gradients of the shared keys and values sum over the group.  dkdv walks the query
 // tiles of all G heads; the depth-slot gradients hold the G heads of a position side by side, sum in
 // fp32 and round every depth gradient once:
-//   up to 4 heads  : inside dkdv (or dkdv_short), on the vector ALUs (depth_gqa_row);
+//   up to 4 heads  : inside grads (or dkdv, dkdv_short), on the vector ALUs (depth_gqa_row);
 //   5 to 8 heads   : at d = 64 with blocks of 32 slots well filled, inside dkdv on the matrix pipe
 //                    (depth_group_rows); otherwise a kernel of their own on the vector ALUs (depth_gqa);
 //   9 heads and up : a kernel of their own on the matrix pipe (depth_group).
+#include <algorithm>
+#include <math.h>
 #include <type_traits>
 
 #include "moda_launch.h"
@@ -86,6 +90,22 @@ __device__ __forceinline__ void buffer_store16_nt(const u32x4& v, const i32x4& r
   asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen nt\n\ts_nop 1" : : "v"(v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
+// Eight channels of a finished dQ row: the depth share `acc` plus the sum over the sequence keys in LDS, in PARTS
+// rows XPART bytes apart from `x` (the first channel of the first one) on; scaled and rounded once.
+template <int PARTS, int XPART>
+__device__ __forceinline__ void store_dq_row(const BwdParams& p, size_t row, int row_bytes, int l16, const float* acc, const unsigned char* x) {
+  f32x4 a = *(const f32x4*)(x + l16 * 32), b = *(const f32x4*)(x + l16 * 32 + 16);
+#pragma unroll
+  for (int w = 1; w < PARTS; ++w) {
+    a += *(const f32x4*)(x + w * XPART + l16 * 32);
+    b += *(const f32x4*)(x + w * XPART + l16 * 32 + 16);
+  }
+  const float f = p.scale;
+  *(u32x4*)((char*)p.dQ + row * row_bytes + l16 * 16) =
+      (u32x4){pack_bf16((acc[0] + a[0]) * f, (acc[1] + a[1]) * f), pack_bf16((acc[2] + a[2]) * f, (acc[3] + a[3]) * f),
+              pack_bf16((acc[4] + b[0]) * f, (acc[5] + b[1]) * f), pack_bf16((acc[6] + b[2]) * f, (acc[7] + b[3]) * f)};
+}
+
 // ---------------------------------------------------------------- depth-slot gradients (G = 1)
 // The depth slots of ROWS consecutive positions (row0 ...) of one head, handled by one wave in a
 // row-major mapping (d/8 lanes x 8 channels per row, 64 / (d/8) rows per wave step): dKdepth,
@@ -93,13 +113,18 @@ __device__ __forceinline__ void buffer_store16_nt(const u32x4& v, const i32x4& r
 // (fp32, not yet multiplied by the softmax scale) for the dQ kernel to start from.
 // Work items (row step, chunk of kChunk slots) are walked with the loads of the next two
 // items in flight (the phase is bound by memory latency).  Uses no LDS.
-template <int D, int ROWS>
-__device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int row0, int lane) {
+// With `xw` (dQ tiles that take their slots after their key tiles): the fp32 sums over the sequence keys in LDS, rows
+// XROW bytes apart (see store_dq_row), are added and dQ is finished and stored.
+template <int D, int ROWS, int CH = 5, int XROW = 0, int PARTS = 1, int XPART = 0>
+__device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int row0, int lane, const unsigned char* xw = nullptr) {
   using Tl = Tile<D>;
-  constexpr int LPR = Tl::kChunks, RPS = 64 / LPR, NIT = ROWS / RPS;
-  constexpr int kChunk = 5;
+  constexpr int LPR = Tl::kChunks, RPS = 64 / LPR;
+  static_assert(ROWS % RPS == 0, "whole row steps");
+  constexpr int kChunk = CH;
   const int T = p.T, L = p.depth_count, La = p.depth_alloc;
   const int bg = bh, qw0 = row0;
+  if (qw0 >= T) return;  // (wave-uniform)
+  const int NIT = min(ROWS / RPS, (T - qw0 + RPS - 1) / RPS);
   const float c2 = p.scale_log2;
   const char* Qb = (const char*)p.Q + (size_t)bh * T * Tl::kRowBytes;
   const char* dOb = (const char*)p.dO + (size_t)bh * T * Tl::kRowBytes;
@@ -111,7 +136,7 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
   // The depth tensors are addressed from the first of the wave's positions (a 64-bit base)
   // with 32-bit offsets from there, so they may be of any size; `slab` is what is left of the
   // (batch, head) slab from that position on, clamped to what 32 bits hold.
-  const int rbase = min(qw0, T - 1);
+  const int rbase = qw0;
   const size_t dbase = ((size_t)bg * T + rbase) * drow;
   const size_t left = (size_t)(T - rbase) * drow;
   const size_t slab = left < 0xffffffffull ? left : 0xffffffffull;
@@ -139,6 +164,10 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
   auto end_row = [&](int row) {
     const int t = qw0 + row;
     if (t < T) {
+      if constexpr (XROW > 0) {
+        store_dq_row<PARTS, XPART>(p, (size_t)bh * T + t, Tl::kRowBytes, l16, acc, xw + row * XROW);
+        return;
+      }
       float* dst = dQd + (size_t)t * D + l16 * 8;
       *(f32x4*)dst = (f32x4){acc[0], acc[1], acc[2], acc[3]};
       *(f32x4*)(dst + 4) = (f32x4){acc[4], acc[5], acc[6], acc[7]};
@@ -175,9 +204,8 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
       b.v[i] = __builtin_amdgcn_raw_buffer_load_b128(vd_buf, voff, min(c * kChunk + i, L - 1) * Tl::kRowBytes, 2);
   };
   auto fold = [&](int it, int c, const Item& b) {
-    const int t = qw0 + it * RPS + rg;
-    const bool live = t < T;  // rows past the end compute on row T-1 and store nothing
-    const int voff = (int)((unsigned)(min(t, T - 1) - rbase) * (unsigned)drow + (unsigned)l16 * 16u);
+    // (rows past the end compute on row T-1; their stores lie outside the buffers, i.e. are not made)
+    const int voff = (int)((unsigned)(it * RPS + rg) * (unsigned)drow + (unsigned)l16 * 16u);
     const int soff = c * kChunk * Tl::kRowBytes;
     float qx[8], gx[8];
 #pragma unroll
@@ -187,41 +215,10 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
       gx[2 * k] = bf16_lo(b.g[k]);
       gx[2 * k + 1] = bf16_hi(b.g[k]);
     }
-    // The common case, every slot of the chunk attended and every row of the wave inside the
-    // sequence, has no branch per slot: the slots' chains of dependent instructions (dot
-    // products, lane sums, exponential) then overlap.
-    if ((c + 1) * kChunk <= L && qw0 + ROWS <= T) {  // (uniform)
-      float pe[kChunk], e[kChunk];
-#pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        float sdot = 0.f, gdot = 0.f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          sdot = dot2_bf16(b.q[k], b.k[i][k], sdot);
-          gdot = dot2_bf16(b.g[k], b.v[i][k], gdot);
-        }
-        sdot = group_sum<LPR>(sdot);
-        gdot = group_sum<LPR>(gdot);
-        pe[i] = fast_exp2(sdot * c2 - b.l2);
-        e[i] = pe[i] * (gdot + b.md);
-      }
-#pragma unroll
-      for (int i = 0; i < kChunk; ++i) {
-        const float es = e[i] * p.scale;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          acc[2 * k] += e[i] * bf16_lo(b.k[i][k]);
-          acc[2 * k + 1] += e[i] * bf16_hi(b.k[i][k]);
-        }
-        const u32x4 o1 = {pack_bf16(pe[i] * gx[0], pe[i] * gx[1]), pack_bf16(pe[i] * gx[2], pe[i] * gx[3]),
-                          pack_bf16(pe[i] * gx[4], pe[i] * gx[5]), pack_bf16(pe[i] * gx[6], pe[i] * gx[7])};
-        const u32x4 o2 = {pack_bf16(es * qx[0], es * qx[1]), pack_bf16(es * qx[2], es * qx[3]),
-                          pack_bf16(es * qx[4], es * qx[5]), pack_bf16(es * qx[6], es * qx[7])};
-        buffer_store16_nt(o1, dvd_buf, voff + i * Tl::kRowBytes, soff);
-        buffer_store16_nt(o2, dkd_buf, voff + i * Tl::kRowBytes, soff);
-      }
-      return;
-    }
+    // No branch per slot before the stores: the slots' chains of dependent instructions (dot products, lane sums,
+    // exponential) overlap.  Slots past depth_count may hold anything (NaN included); here they repeat the last
+    // attended one, with weight zero, and those that are allocated get zero gradients.
+    float pe[kChunk], e[kChunk];
 #pragma unroll
     for (int i = 0; i < kChunk; ++i) {
       float sdot = 0.f, gdot = 0.f;
@@ -232,32 +229,36 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
       }
       sdot = group_sum<LPR>(sdot);
       gdot = group_sum<LPR>(gdot);
-      const int slot = c * kChunk + i;
-      if (slot >= L) {  // uniform
-        // slots past depth_count may hold anything (NaN included) and take no part; those
-        // that are allocated get zero gradients
-        if (slot < La && live) {
-          const u32x4 z = {0u, 0u, 0u, 0u};
-          buffer_store16_nt(z, dvd_buf, voff + i * Tl::kRowBytes, soff);
-          buffer_store16_nt(z, dkd_buf, voff + i * Tl::kRowBytes, soff);
-        }
-      } else {
-        const float pe = fast_exp2(sdot * c2 - b.l2);
-        const float e = pe * (gdot + b.md);
-        const float es = e * p.scale;
+      pe[i] = fast_exp2(sdot * c2 - b.l2);
+      e[i] = pe[i] * (gdot + b.md);
+    }
+    auto slot = [&](int i) {
+      const float es = e[i] * p.scale;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          acc[2 * k] += e * bf16_lo(b.k[i][k]);
-          acc[2 * k + 1] += e * bf16_hi(b.k[i][k]);
-        }
-        const u32x4 o1 = {pack_bf16(pe * gx[0], pe * gx[1]), pack_bf16(pe * gx[2], pe * gx[3]),
-                          pack_bf16(pe * gx[4], pe * gx[5]), pack_bf16(pe * gx[6], pe * gx[7])};
-        const u32x4 o2 = {pack_bf16(es * qx[0], es * qx[1]), pack_bf16(es * qx[2], es * qx[3]),
-                          pack_bf16(es * qx[4], es * qx[5]), pack_bf16(es * qx[6], es * qx[7])};
-        if (live) {
-          buffer_store16_nt(o1, dvd_buf, voff + i * Tl::kRowBytes, soff);
-          buffer_store16_nt(o2, dkd_buf, voff + i * Tl::kRowBytes, soff);
-        }
+      for (int k = 0; k < 4; ++k) {
+        acc[2 * k] += e[i] * bf16_lo(b.k[i][k]);
+        acc[2 * k + 1] += e[i] * bf16_hi(b.k[i][k]);
+      }
+      const u32x4 o1 = {pack_bf16(pe[i] * gx[0], pe[i] * gx[1]), pack_bf16(pe[i] * gx[2], pe[i] * gx[3]),
+                        pack_bf16(pe[i] * gx[4], pe[i] * gx[5]), pack_bf16(pe[i] * gx[6], pe[i] * gx[7])};
+      const u32x4 o2 = {pack_bf16(es * qx[0], es * qx[1]), pack_bf16(es * qx[2], es * qx[3]),
+                        pack_bf16(es * qx[4], es * qx[5]), pack_bf16(es * qx[6], es * qx[7])};
+      buffer_store16_nt(o1, dvd_buf, voff + i * Tl::kRowBytes, soff);
+      buffer_store16_nt(o2, dkd_buf, voff + i * Tl::kRowBytes, soff);
+    };
+    if ((c + 1) * kChunk <= L) {  // (uniform)
+#pragma unroll
+      for (int i = 0; i < kChunk; ++i) slot(i);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < kChunk; ++i) {
+      if (c * kChunk + i < L) {
+        slot(i);
+      } else if (c * kChunk + i < La) {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        buffer_store16_nt(z, dvd_buf, voff + i * Tl::kRowBytes, soff);
+        buffer_store16_nt(z, dkd_buf, voff + i * Tl::kRowBytes, soff);
       }
     }
   };
@@ -318,11 +319,12 @@ __device__ __forceinline__ void depth_grad_rows(const BwdParams& p, int bh, int 
 //   dVdepth_i = sum_h p_{h,i} dO_h,  dKdepth_i = scale sum_h e_{h,i} q_h  (summed in fp32, one
 //                                    rounding each),
 //   dQ_h     += e_{h,i} k_i          (left in the workspace, fp32, unscaled, for the dQ kernel).
-// Groups of up to 4 heads: runs inside the dK/dV kernel, for the 128 positions of a workgroup's
-// key tile, before or after its key-tile work: the phase is then bound by HBM (the slots read
-// once, their gradients written once), the key-tile work by the matrix pipe.
-template <int D, int GT>
-__device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row, bool live, int l16) {
+// Groups of up to 4 heads: runs inside the kernel of dQ's tiles, for the positions of a tile, before or after
+// its key tiles (3 heads: inside dK/dV): the phase is then bound by HBM (the slots read
+// once, their gradients written once), the key tiles by the matrix pipe.
+// XROW > 0: as for depth_grad_rows; `xw` is the row of the first head, the next head's XHEAD bytes further on.
+template <int D, int GT, int AHEAD = 4, int XROW = 0, int XHEAD = 0, int PARTS = 1, int XPART = 0>
+__device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row, bool live, int l16, const unsigned char* xw = nullptr) {
   constexpr int LPR = D / 8, RB = D * 2;
   const int T = p.T, L = p.depth_count, La = p.depth_alloc, G = p.Hq / p.Hk;
   const long long rc = row;
@@ -352,7 +354,7 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
   // of few heads waited out the memory latency at every slot.  (No load past the last slot, whose branch
   // is uniform.)  Backward call, one / four ahead: B=6 Hq=16 Hk=8 T=2048, 31 slots d=64 526 / 494 us, d=128
   // 1018 / 964; B=2 T=1000, 12 slots d=128 116 / 102.  At 8 heads the arithmetic is the longer part.
-  constexpr int kAhead = GT > 4 ? 1 : 4;
+  constexpr int kAhead = GT > 4 ? 1 : AHEAD;
   u32x4 kn[kAhead], vn[kAhead];
   auto request = [&](int u, int i) {
     if (i < L) {
@@ -423,6 +425,10 @@ __device__ __forceinline__ void depth_gqa_row(const BwdParams& p, long long row,
 #pragma unroll
     for (int j = 0; j < GT; ++j)
       if (j < G) {
+        if constexpr (XROW > 0) {
+          store_dq_row<PARTS, XPART>(p, (size_t)(bh0 + j) * T + t, RB, l16, dq[j], xw + j * XHEAD);
+          continue;
+        }
         float* dst = p.dq_depth + ((size_t)(bh0 + j) * T + t) * D + l16 * 8;
         *(f32x4*)dst = (f32x4){dq[j][0], dq[j][1], dq[j][2], dq[j][3]};
         *(f32x4*)(dst + 4) = (f32x4){dq[j][4], dq[j][5], dq[j][6], dq[j][7]};
@@ -706,24 +712,18 @@ __device__ __forceinline__ void depth_group_rows(const BwdParams& p, int bg, int
 // ---------------------------------------------------------------- dK, dV
 // Workgroup = 128 keys (4 waves x 32 keys).  Accumulators hold dK^T, dV^T
 // ([channel][key]: a lane owns one key and 64 of its channels).
-// GT: 2, 4, 8 = the depth-slot gradients of a group of up to GT heads are taken here as well (2, 4:
-// depth_gqa_row; 8, at d = 64: depth_group_rows); 0 = one query head per key/value head (depth_grad_rows), or
-// depth slots that have a kernel of their own, or none.
+// GT: 4, 8 = the depth-slot gradients of a group of up to GT heads are taken here as well (4:
+// depth_gqa_row; 8, at d = 64: depth_group_rows); 0 = none here.
 template <int D, int GT>
-__global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
+__device__ __forceinline__ void dkdv_tile(const BwdParams& p, unsigned char* smem, int bg, int jt) {
   using Tl = Tile<D>;
   using C = BwdCfg<D>;
-  constexpr int kSmem = GT == 8 && 4 * DepthWave<D>::kBytes > C::kLds ? 4 * DepthWave<D>::kBytes : C::kLds;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmem];
   float* aux = (float*)(smem + C::kLds - C::kAux);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
   const int T = p.T;
-  const int BHk = p.B * p.Hk;
-  int bg, jt;  // (batch, key/value head); key tiles in natural order: the first ones see the most queries
-  head_blocked_id(layered_id(p.causal, 2), BHk, (T + 127) / 128, bg, jt, p.head_group);
   const int j0 = jt * 128;
   const int kw0 = j0 + wave * 32;
   const int G = p.Hq / p.Hk;        // query heads per key/value head: their gradients add up here
@@ -732,16 +732,13 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
   const char* Kb = (const char*)p.Kseq + (size_t)bg * T * Tl::kRowBytes;
   const char* Vb = (const char*)p.Vseq + (size_t)bg * T * Tl::kRowBytes;
 
-  // ---- Depth-slot gradients (one query head per key/value head; groups: group_depth below, or a
-  // kernel of their own): row-local, bound by HBM (every depth slot read once, every gradient written
+  // ---- Depth-slot gradients: row-local, bound by HBM (every depth slot read once, every gradient written
   // once), and independent of everything else this kernel does, which is bound by the matrix
   // pipe and leaves HBM idle.  Each workgroup takes the 128 positions of its key tile, before
   // its key-tile work (every other workgroup) or after it, so that at any time some compute
   // units stream while others compute.
-  const bool own_depth = G == 1 && p.depth_alloc > 0;
   const bool depth_first = ((blockIdx.x >> 3) & 1) != 0;
-  if (own_depth && depth_first) depth_grad_rows<D, 32>(p, bg, kw0, lane);
-  // grouped queries: the workgroup's 128 positions, 256 / (d/8) at a time
+  // (the workgroup's 128 positions, 256 / (d/8) at a time)
   auto group_depth = [&]() {
     if constexpr (GT == 8) {
       __syncthreads();  // (the waves' parts of LDS are other waves' before and after)
@@ -751,6 +748,7 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
     } else if constexpr (GT > 0) {
       constexpr int LPR = D / 8, ROWS = 256 / LPR;
       for (int r0 = 0; r0 < 128; r0 += ROWS) {
+        if (j0 + r0 + wave * (64 / LPR) >= T) break;  // (whole waves)
         const int t = j0 + r0 + tid / LPR;
         depth_gqa_row<D, GT>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR);
       }
@@ -1024,8 +1022,17 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if (own_depth && !depth_first) depth_grad_rows<D, 32>(p, bg, kw0, lane);
   if (GT > 0 && !depth_first) group_depth();
+}
+
+template <int D, int GT>
+__global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
+  using C = BwdCfg<D>;
+  constexpr int kSmem = GT == 8 && 4 * DepthWave<D>::kBytes > C::kLds ? 4 * DepthWave<D>::kBytes : C::kLds;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmem];
+  int bg, jt;  // (batch, key/value head); key tiles in natural order: the first ones see the most queries
+  head_blocked_id(layered_id(p.causal, 2), p.B * p.Hk, (p.T + 127) / 128, bg, jt, p.head_group);
+  dkdv_tile<D, GT>(p, smem, bg, jt);
 }
 
 // ---------------------------------------------------------------- dK, dV, few key tiles
@@ -1044,43 +1051,47 @@ __global__ __launch_bounds__(256, 2) void moda_bwd_dkdv_kernel(BwdParams p) {
 // which see all queries of a large group, take half as long, where they are what the call waits for.  Backward
 // call, 4 / 8 waves, us: B=1 Hq=8 Hk=1 T=16384 1404 / 1035; Hq=64 Hk=8 T=1000 75.5 / 60.8; Hq=32 Hk=4 T=3000, 24
 // slots 260 / 220; but Hq=16 Hk=8 B=2 T=1000, 12 slots 46.1 / 50.9 (dkdv_waves draws the line).
-template <int D, int NW = 4>
+template <int D, int NW = 4, int ST = 2>
 struct BwdShortCfg {
+  static constexpr int kStages = ST;
   static constexpr int kTile = 32 * D * 2;               // 32 rows of Q or dO
   static constexpr int kStage = 2 * kTile + 64 * 8;      // Q, dO, LSE log2 e, -delta (of 64 rows, 32 of them used)
   static constexpr int kPieces = kTile / 1024;           // copy instructions per tile
   static constexpr int kXRow = D + 4;                    // floats per row of the exchange buffer
   static constexpr int kXWave = 32 * kXRow;
-  static constexpr int kRing = NW * 2 * kStage;
+  static constexpr int kRing = NW * ST * kStage;
   static constexpr int kLds = kRing > NW * kXWave * 4 ? kRing : NW * kXWave * 4;
 };
 
-template <int D, int GT, int NW>
-__global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kernel(BwdParams p) {
+// GT: 1, 2, 4 = the depth slots of the 32 positions are taken here as well, of groups of up to GT heads; 0 = not here.
+// ST: stages of a wave's Q and dO tiles.  With one (in the launch with dQ, four waves) Q's place is requested anew as soon as
+// dK is formed and dO's after dV: half the LDS, so that at d = 128 two workgroups share a unit and at d = 64
+// three.  (dK, dV and dQ in one launch, two stages / one, us: B=4 Hq=8 Hk=2 T=901 d=128 61 / 54; B=2 H=16 T=657 d=128 55 / 40;
+// B=4 Hq=32 Hk=8 T=719 d=64, 4 slots 71 / 62.)
+template <int D, int GT, int NW, int ST>
+__device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned char* smem, int bg, int jt) {
   using Tl = Tile<D>;
-  using C = BwdShortCfg<D, NW>;
+  using C = BwdShortCfg<D, NW, ST>;
   using Ld = TileLoader<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
   const int T = p.T, G = p.Hq / p.Hk;
-  int bg, jt;  // (batch, key/value head); key tiles in natural order: the first ones see the most queries
-  head_blocked_id((int)blockIdx.x, p.B * p.Hk, (T + 31) / 32, bg, jt, p.head_group);
   const int j0 = jt * 32;
   const int bh0 = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G;
   const float c2 = p.scale_log2;
 
   // depth slots of the 32 positions, before or after the key tile (alternating, as above)
   auto depth = [&]() {
-    if constexpr (GT > 0) {
+    if constexpr (GT > 1) {
       constexpr int LPR = D / 8, ROWS = NW * 64 / LPR;
       for (int r0 = 0; r0 < 32; r0 += ROWS) {
+        if (j0 + r0 + wave * (64 / LPR) >= T) break;  // (whole waves)
         const int t = j0 + r0 + tid / LPR;
         if (ROWS > 32 && t >= j0 + 32) break;  // (whole waves)
         depth_gqa_row<D, GT>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR);
       }
-    } else if (G == 1 && p.depth_alloc > 0) {
+    } else if constexpr (GT == 1) {
       if (wave < 4) depth_grad_rows<D, 8>(p, bg, j0 + wave * 8, lane);
     }
   };
@@ -1105,7 +1116,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
   const int qt0 = p.causal ? jt : 0;
   const int span = (T + 31) / 32 - qt0;
   const int n_items = G * span;
-  const unsigned ring = (unsigned)(size_t)(lds_ptr)smem + wave * 2 * C::kStage;
+  const unsigned ring = (unsigned)(size_t)(lds_ptr)smem + wave * ST * C::kStage;
   FragAddr<D> fa;
   fa.init(lane);
   const int goff = (lane / Tl::kChunks) * Tl::kRowBytes + (((lane % Tl::kChunks) ^ Tl::swz(lane / Tl::kChunks)) << 4);
@@ -1119,7 +1130,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
     l_buf = make_tile_buffer(p.lse2 + row, (unsigned)T * 4);
     d_buf = make_tile_buffer(p.minus_delta + row, (unsigned)T * 4);
   };
-  auto issue_next = [&](int stage) -> int {  // returns the first query of the item
+  int q_next = 0;  // first query of the next item
+  auto advance = [&]() {
     if (pos >= span) {
       do {
         pos -= span;
@@ -1127,32 +1139,44 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
       } while (pos >= span);
       at_head();
     }
-    const int qt = qt0 + pos;
-    const unsigned dst = ring + stage * C::kStage;
-#pragma unroll
-    for (int q = 0; q < C::kPieces; ++q) {
-      const int voff = xor_here(goff, Ld::piece_xor(q));
-      tile_copy16(q_buf, voff, qt * C::kTile + q * 1024, dst + q * 1024);
-      tile_copy16(do_buf, voff, qt * C::kTile + q * 1024, dst + C::kTile + q * 1024);
-    }
-    copy4(l_buf, lane * 4, qt * 128, dst + 2 * C::kTile);
-    copy4(d_buf, lane * 4, qt * 128, dst + 2 * C::kTile + 256);
+    q_next = (qt0 + pos) * 32;
     pos += NW;
-    return qt * 32;
   };
-  int q_next = 0;
+  auto issue_tile = [&](const i32x4& buf, unsigned dst) {
+#pragma unroll
+    for (int q = 0; q < C::kPieces; ++q)
+      tile_copy16(buf, xor_here(goff, Ld::piece_xor(q)), q_next / 32 * C::kTile + q * 1024, dst + q * 1024);
+  };
+  auto issue_q = [&](int stage) {
+    const unsigned dst = ring + stage * C::kStage;
+    issue_tile(q_buf, dst);
+    copy4(l_buf, lane * 4, q_next * 4, dst + 2 * C::kTile);
+    copy4(d_buf, lane * 4, q_next * 4, dst + 2 * C::kTile + 256);
+  };
+  auto issue_do = [&](int stage) { issue_tile(do_buf, ring + stage * C::kStage + C::kTile); };
   if (wave < n_items) {
     at_head();
-    q_next = issue_next(0);
+    advance();
+    issue_q(0);
+    issue_do(0);
   }
   int stage = 0;
-  for (int item = wave; item < n_items; item += NW, stage ^= 1) {
+  for (int item = wave; item < n_items; item += NW, stage ^= ST - 1) {
     // (the wave's own copies into its own LDS: its wait publishes them, and the stage that the next
     // copies overwrite may be refilled as soon as the wave's reads of it have returned)
-    wait_own_copies<0>();
-    wait_own_reads();
+    const bool more = item + NW < n_items;
     const int q0 = q_next;
-    if (item + NW < n_items) q_next = issue_next(stage ^ 1);
+    if constexpr (ST == 2) {
+      wait_own_copies<0>();
+      wait_own_reads();
+      if (more) {
+        advance();
+        issue_q(stage ^ 1);
+        issue_do(stage ^ 1);
+      }
+    } else {
+      wait_own_copies<C::kPieces>();  // (dO may still be on its way)
+    }
     const unsigned qtile = ring + stage * C::kStage;
     const unsigned b_row = fa.row + qtile, b_tr = fa.tr + qtile, b_tr8 = fa.tr8 + qtile;
     const float* lse_s = (const float*)(smem + (qtile - (unsigned)(size_t)(lds_ptr)smem) + 2 * C::kTile);
@@ -1166,11 +1190,21 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
         dp[4 * b4 + r] = x[r];
       }
     }
+    if constexpr (ST == 1) {
 #pragma unroll
-    for (int st = 0; st < Tl::kDSteps; ++st) {
-      const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
-      s = mfma_bf16(FragAddr<D>::row_frag(x, 0, 0), kf[st], s);
-      dp = mfma_bf16(FragAddr<D>::row_frag(x, 0, C::kTile), vf[st], dp);
+      for (int st = 0; st < Tl::kDSteps; ++st)
+        s = mfma_bf16(FragAddr<D>::row_frag((unsigned)xor_here((int)b_row, st << 5), 0, 0), kf[st], s);
+      wait_own_copies<0>();
+#pragma unroll
+      for (int st = 0; st < Tl::kDSteps; ++st)
+        dp = mfma_bf16(FragAddr<D>::row_frag((unsigned)xor_here((int)b_row, st << 5), 0, C::kTile), vf[st], dp);
+    } else {
+#pragma unroll
+      for (int st = 0; st < Tl::kDSteps; ++st) {
+        const unsigned x = (unsigned)xor_here((int)b_row, st << 5);
+        s = mfma_bf16(FragAddr<D>::row_frag(x, 0, 0), kf[st], s);
+        dp = mfma_bf16(FragAddr<D>::row_frag(x, 0, C::kTile), vf[st], dp);
+      }
     }
     if (q0 + 32 > T || (p.causal && q0 < j0 + 31)) {  // (uniform) the diagonal, rows past the end
       const int key = j0 + l32;
@@ -1180,8 +1214,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
         s[i] = q < T && (!p.causal || key <= q) ? s[i] : -INFINITY;
       }
     }
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
+    bf16x8 pb[2], dsb[2];
+    auto weights = [&](int hf) {
       float pv[8], dsv[8];
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) {
@@ -1195,12 +1229,37 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
           dsv[b2 * 4 + r] = pe * dp[i];
         }
       }
-      const bf16x8 pb = pack8(pv), dsb = pack8(dsv);
+      pb[hf] = pack8(pv);
+      dsb[hf] = pack8(dsv);
+    };
+    auto product = [&](int hf, int db, bool of_v) {
+      const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
+      if (of_v) dv[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, C::kTile), pb[hf], dv[db]);
+      else dk[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, 0), dsb[hf], dk[db]);
+    };
+    if constexpr (ST == 1) {  // Q's place is free, and requested anew, before dO's
+      weights(0);
+      weights(1);
 #pragma unroll
-      for (int db = 0; db < Tl::kDBlocks; ++db) {
-        const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
-        dv[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, C::kTile), pb, dv[db]);
-        dk[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, 0), dsb, dk[db]);
+      for (int n = 0; n < 2 * Tl::kDBlocks; ++n) product(n / Tl::kDBlocks, n % Tl::kDBlocks, false);
+      wait_own_reads();
+      if (more) {
+        advance();
+        issue_q(0);
+      }
+#pragma unroll
+      for (int n = 0; n < 2 * Tl::kDBlocks; ++n) product(n / Tl::kDBlocks, n % Tl::kDBlocks, true);
+      wait_own_reads();
+      if (more) issue_do(0);
+    } else {
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        weights(hf);
+#pragma unroll
+        for (int db = 0; db < Tl::kDBlocks; ++db) {
+          product(hf, db, true);
+          product(hf, db, false);
+        }
       }
     }
   }
@@ -1239,33 +1298,34 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_
   if (!depth_first) depth();
 }
 
+template <int D, int GT, int NW>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void moda_bwd_dkdv_short_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[BwdShortCfg<D, NW>::kLds];
+  int bg, jt;  // (batch, key/value head); key tiles in natural order: the first ones see the most queries
+  head_blocked_id((int)blockIdx.x, p.B * p.Hk, (p.T + 31) / 32, bg, jt, p.head_group);
+  dkdv_short_tile<D, GT, NW, 2>(p, smem, bg, jt);
+}
+
 // ---------------------------------------------------------------- dQ
 // Workgroup = NW waves x 32 queries.  Accumulators hold dQ^T ([channel][query]: a lane owns
 // one query).  Launched with NW = 4 (two workgroups per compute unit); NW = 8 (one workgroup
 // per unit, a K/V tile serving twice as many queries) measured 6 % slower at B=8 H=16 T=4096.
 // PS: workgroups per compute unit, i.e. waves per SIMD: 2, or at d = 64 3 (dq_per_unit draws the line).
-template <int D, int NW, int PS>
-__global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
+// A tile is kQT / heads positions (from q0 on) of `heads` query heads (from bh0 on) of a group.
+// GT: 1, 2, 4 = the depth slots of the tile's positions, which then has all heads of the group, are taken here,
+// before the key tiles or (depth_first false) after them; 0 = their share of dQ, if there are any, is in the workspace.
+template <int D, int NW, int PS, int GT>
+__device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem, int bg, int bh0, int heads, int q0, bool depth_first) {
   using Tl = Tile<D>;
   using C = BwdCfg<D, NW>;
   constexpr int kQT = NW * 32;  // queries per workgroup
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
   const int T = p.T;
-  const int n_qt = (T + kQT - 1) / kQT;
-  // Ids are dealt to the dies by key/value head (see head_blocked_id): the G query heads of a
-  // group stream the same K/V, so a die takes a group's heads one right after the other, query
-  // tile by query tile (heavy, i.e. late, tiles first).
-  const int G = p.Hq / p.Hk;
-  int bg, tile_idx;  // (batch, key/value head); position in the walk over (query tile, head of the group)
-  head_blocked_id(layered_id(p.causal, PS), p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
-  const int qt = n_qt - 1 - tile_idx / G;
-  const int bh = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G;
-  const int q0 = qt * kQT;
-  const int qw0 = q0 + wave * 32;
+  const int n_pos = kQT / heads;
+  const int bh = bh0 + wave % heads;
+  const int qw0 = q0 + wave / heads * 32;
 
   const char* Qb = (const char*)p.Q + (size_t)bh * T * Tl::kRowBytes;
   const char* Kb = (const char*)p.Kseq + (size_t)bg * T * Tl::kRowBytes;
@@ -1283,8 +1343,21 @@ __global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
   // The depth-slot gradients and the depth share of dQ were computed before this kernel (by
   // the dK/dV kernel, or by the depth_gqa kernels with grouped queries); the share is in the
   // workspace, in fp32, not yet multiplied by the softmax scale.
+  constexpr int kDepthRows = NW * 64 / LPR;  // rows of depth slots per pass
+  if constexpr (GT > 0) {
+    if (depth_first) {
+      if constexpr (GT == 1) depth_grad_rows<D, 32>(p, bh, qw0, lane);
+      else
+        for (int r0 = 0; r0 < kQT / GT; r0 += kDepthRows) {
+          if (q0 + r0 + wave * (64 / LPR) >= T) break;  // (whole waves)
+          const int t = q0 + r0 + tid / LPR;
+          depth_gqa_row<D, GT>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR);
+        }
+      __syncthreads();
+    }
+  }
   f32x16 dq[Tl::kDBlocks];
-  if (La > 0) {
+  if (GT > 0 ? depth_first : La > 0) {
     const float* src = p.dq_depth + ((size_t)bh * T + qrow) * D;
 #pragma unroll
     for (int db = 0; db < Tl::kDBlocks; ++db)
@@ -1320,7 +1393,7 @@ __global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
     return r;
   };
 
-  const int n_keys = p.causal ? min(T, q0 + kQT) : T;
+  const int n_keys = p.causal ? min(T, q0 + n_pos) : T;
   const int nt = (n_keys + 63) / 64;
   const int wave_last = p.causal ? min(nt - 1, (qw0 + 31) / 64) : nt - 1;
   const int lim = p.causal ? min(qi, T - 1) : T - 1;  // last visible key of this lane's query
@@ -1440,6 +1513,20 @@ __global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
       f32x4 v = {dq[db][4 * bq], dq[db][4 * bq + 1], dq[db][4 * bq + 2], dq[db][4 * bq + 3]};
       *(f32x4*)(xw + l32 * C::kXRow + (db * 32 + bq * 8 + hi * 4) * 4) = v;
     }
+  if constexpr (GT > 0) {
+    if (!depth_first) {
+      __syncthreads();
+      if constexpr (GT == 1) depth_grad_rows<D, 32, 5, C::kXRow>(p, bh, qw0, lane, xw);
+      else
+        for (int r0 = 0; r0 < kQT / GT; r0 += kDepthRows) {
+          if (q0 + r0 + wave * (64 / LPR) >= T) break;
+          const int r = r0 + tid / LPR, t = q0 + r;
+          depth_gqa_row<D, GT, 4, C::kXRow, C::kXWave>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR,
+                                                    smem + r / 32 * GT * C::kXWave + r % 32 * C::kXRow);
+        }
+      return;
+    }
+  }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1460,6 +1547,21 @@ __global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
   }
 }
 
+template <int D, int NW, int PS>
+__global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
+  using C = BwdCfg<D, NW>;
+  constexpr int kQT = NW * 32;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
+  const int n_qt = (p.T + kQT - 1) / kQT;
+  // Ids are dealt to the dies by key/value head (see head_blocked_id): the G query heads of a
+  // group stream the same K/V, so a die takes a group's heads one right after the other, query
+  // tile by query tile (heavy, i.e. late, tiles first).
+  const int G = p.Hq / p.Hk;
+  int bg, tile_idx;  // (batch, key/value head); position in the walk over (query tile, head of the group)
+  head_blocked_id(layered_id(p.causal, PS), p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
+  dq_tile<D, NW, PS, 0>(p, smem, bg, (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G, 1, (n_qt - 1 - tile_idx / G) * kQT, false);
+}
+
 // ---------------------------------------------------------------- dQ, few query tiles
 // The same change of split for dQ when the kernel above would have fewer workgroups than the chip
 // takes: a workgroup = 32 queries, its 4 waves deal out the key tiles (32 keys, private LDS stages),
@@ -1468,21 +1570,16 @@ __global__ __launch_bounds__(NW * 64, PS) void moda_bwd_dq_kernel(BwdParams p) {
 // T=16384: d=64 365 -> 320 us, d=128 712 -> 636 us.
 // One LDS tile of K and one of V per wave (V is requested anew as soon as the scores are formed, K after
 // the products): twice the workgroups fit a compute unit that did with two stages.
-template <int D>
-__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel(BwdParams p) {
+// A tile is 32 positions of `heads` (1, 2 or 4) query heads of a group: each has 4 / heads of the waves.  GT: as in dq_tile.
+template <int D, int GT, int CH, int AHEAD, int NW = 4>
+__device__ __forceinline__ void dq_short_tile(const BwdParams& p, unsigned char* smem, int bg, int bh0, int heads, int q0, bool depth_first) {
   using Tl = Tile<D>;
   using C = BwdShortCfg<D>;
-  constexpr int kTiles = 4 * 2 * C::kTile, kExchange = 4 * C::kXWave * 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kTiles > kExchange ? kTiles : kExchange];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
-  const int T = p.T, G = p.Hq / p.Hk;
-  const int n_qt = (T + 31) / 32;
-  int bg, tile_idx;  // (as above: a group's heads one right after the other, late query tiles first)
-  head_blocked_id((int)blockIdx.x, p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
-  const int q0 = (n_qt - 1 - tile_idx / G) * 32;
-  const int bh = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G;
+  const int T = p.T;
+  const int bh = bh0 + wave % heads, wave0 = wave / heads, per_head = NW / heads;
   const float c2 = p.scale_log2;
 
   const int nt = ((p.causal ? min(T, q0 + 32) : T) + 31) / 32;
@@ -1498,9 +1595,25 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
       tile_copy16(buf, xor_here(goff, TileLoader<D>::piece_xor(q)), (int)((unsigned)kt * (unsigned)C::kTile) + q * 1024,
                   dst + q * 1024);
   };
-  if (wave < nt) {
-    issue(k_buf, wave, ktile);
-    issue(v_buf, wave, vtile);
+  constexpr int LPR = Tl::kChunks, ROWS = NW * 64 / LPR;
+  constexpr int kRows = NW * 64 / LPR > 32 ? 64 / LPR : 32 / NW;  // rows of slots per wave
+  if constexpr (GT > 0) {
+    if (depth_first) {
+      if constexpr (GT == 1) {
+        if (wave * kRows < 32) depth_grad_rows<D, kRows, CH>(p, bh, q0 + wave * kRows, lane);
+      }
+      else
+        for (int r0 = 0; r0 < 32; r0 += ROWS) {
+          if (q0 + r0 + wave * (64 / LPR) >= T) break;  // (whole waves)
+          const int t = q0 + r0 + tid / LPR;
+          if (ROWS > 32 && r0 + tid / LPR >= 32) break;  // (whole waves)
+          depth_gqa_row<D, GT, AHEAD>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR);
+        }
+    }
+  }
+  if (wave0 < nt) {
+    issue(k_buf, wave0, ktile);
+    issue(v_buf, wave0, vtile);
   }
 
   const int qrow = min(q0 + l32, T - 1);
@@ -1525,7 +1638,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
     for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
 
   const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
-  for (int kt = wave; kt < nt; kt += 4) {
+  for (int kt = wave0; kt < nt; kt += per_head) {
     wait_own_copies<0>();
     f32x16 s, dp = minus_delta;
 #pragma unroll
@@ -1537,7 +1650,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
       dp = mfma_bf16(FragAddr<D>::row_frag(x, 0, C::kTile), dof[st], dp);
     }
     wait_own_reads();
-    if (kt + 4 < nt) issue(v_buf, kt + 4, vtile);
+    if (kt + per_head < nt) issue(v_buf, kt + per_head, vtile);
     const int k0 = kt * 32;
     if (k0 + 32 > T || (p.causal && k0 + 31 > q0)) {  // (uniform) the diagonal, keys past the end
 #pragma unroll
@@ -1559,7 +1672,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
                                                 hf, 0), dsb, dq[db]);
     }
     wait_own_reads();
-    if (kt + 4 < nt) issue(k_buf, kt + 4, ktile);
+    if (kt + per_head < nt) issue(k_buf, kt + per_head, ktile);
   }
 
   // ---- depth share + the four waves, row-major, 16-byte stores
@@ -1572,27 +1685,110 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
       *(f32x4*)(xb + wave * C::kXWave + l32 * C::kXRow + db * 32 + bq * 8 + hi * 4) =
           (f32x4){dq[db][4 * bq], dq[db][4 * bq + 1], dq[db][4 * bq + 2], dq[db][4 * bq + 3]};
   __syncthreads();
-  constexpr int LPR = Tl::kChunks;
-  for (int row = tid / LPR; row < 32; row += 256 / LPR) {
-    const int t = q0 + row, ch = (tid % LPR) * 8;
-    if (t >= T) break;
+  if constexpr (GT > 0) {
+    if (!depth_first) {
+      constexpr int XROW = C::kXRow * 4, XWAVE = C::kXWave * 4;
+      if constexpr (GT == 1) {
+        if (wave * kRows < 32) depth_grad_rows<D, kRows, CH, XROW, NW, XWAVE>(p, bh, q0 + wave * kRows, lane, smem + wave * kRows * XROW);
+      }
+      else
+        for (int r0 = 0; r0 < 32; r0 += ROWS) {
+          if (q0 + r0 + wave * (64 / LPR) >= T) break;
+          const int r = r0 + tid / LPR, t = q0 + r;
+          if (ROWS > 32 && r >= 32) break;
+          depth_gqa_row<D, GT, AHEAD, XROW, XWAVE, NW / GT, GT * XWAVE>(p, (long long)bg * T + min(t, T - 1), t < T, tid % LPR, smem + r * XROW);
+        }
+      return;
+    }
+  }
+  for (int r = tid / LPR; r < 32 * heads; r += ROWS) {
+    const int row = r % 32, h = r / 32, t = q0 + row, ch = (tid % LPR) * 8;
+    if (t >= T) continue;
+    const size_t at = (size_t)(bh0 + h) * T + t;
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
     if (p.depth_alloc > 0) {
-      const float* share = p.dq_depth + ((size_t)bh * T + t) * D + ch;
+      const float* share = p.dq_depth + at * D + ch;
       a = *(const f32x4*)share;
       b = *(const f32x4*)(share + 4);
     }
     const float* x = xb + row * C::kXRow + ch;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = h; w < NW; w += heads) {
       a += *(const f32x4*)(x + w * C::kXWave);
       b += *(const f32x4*)(x + w * C::kXWave + 4);
     }
     const float f = p.scale;
-    *(u32x4*)((char*)p.dQ + ((size_t)bh * T + t) * Tl::kRowBytes + ch * 2) =
+    *(u32x4*)((char*)p.dQ + at * Tl::kRowBytes + ch * 2) =
         (u32x4){pack_bf16(a[0] * f, a[1] * f), pack_bf16(a[2] * f, a[3] * f), pack_bf16(b[0] * f, b[1] * f),
                 pack_bf16(b[2] * f, b[3] * f)};
   }
+}
+
+template <int D, int NW = 4>
+struct DqShortCfg {
+  using C = BwdShortCfg<D>;
+  static constexpr int kTiles = NW * 2 * C::kTile, kExchange = NW * C::kXWave * 4;
+  static constexpr int kLds = kTiles > kExchange ? kTiles : kExchange;
+};
+template <int D>
+__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DqShortCfg<D>::kLds];
+  const int G = p.Hq / p.Hk, n_qt = (p.T + 31) / 32;
+  int bg, tile_idx;  // (as above: a group's heads one right after the other, late query tiles first)
+  head_blocked_id((int)blockIdx.x, p.B * p.Hk, n_qt * G, bg, tile_idx, p.head_group);
+  dq_short_tile<D, 0, 5, 4>(p, smem, bg, (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + tile_idx % G, 1, (n_qt - 1 - tile_idx / G) * 32, false);
+}
+
+// ---------------------------------------------------------------- dK, dV and dQ in one launch
+// One after the other, the two kernels each end with a last round that leaves units idle, and in grids of one
+// round with their longest workgroups alone; and the depth slots, bound by HBM, ran beside the products of dK and dV only.
+// Here a workgroup is a key tile (dK, dV; all of them first, the heaviest ones in front) or a query tile (dQ, late
+// ones first), and the depth slots of a query tile's positions are taken by its workgroup, so that nothing passes
+// between workgroups: a tile is 128 / G positions of all G heads of the group (few queries: 32 positions).  The first
+// quarter of the query tiles takes its slots first, while key tiles keep the matrix pipe busy, the others after their keys,
+// straight into the finished row.
+// Key tiles of 128 keys or (KS) 32 dealt out to the waves, query tiles of 128 rows or (QS) 32 positions dealt out; eight
+// waves instead of four (NW, d = 64 with KS) where few key tiles see many queries: grads_plan draws the lines.
+// Backward call, two launches / one: B=8 H=16 T=4096 d=128, 15 slots 2.80 / 2.65 ms; B=2 Hq=16 Hk=8 T=1000 d=64, 12
+// slots 58 / 45 us; B=2 H=16 T=1105 d=128, 1 slot 104 / 64; B=2 H=2 T=206 d=128, 12 slots 25 / 17; B=1 Hq=4 Hk=1 T=4026 d=128, 64
+// slots 290 / 220; B=3 Hq=8 Hk=2 T=71 d=128, 1 slot 23.3 / 14.8.  0.77 on average of 3200 random shapes.
+// All key tiles first / one every so often among the query tiles, largest share first: within 2 % of the best order;
+// the first quarter / half / eighth / none of the query tiles with slots first 1.018 / 1.024 / 1.020 / 1.029 of the best.
+constexpr int grads_waves_per_simd(int D, bool KS, bool QS, int NW) { return D == 64 && KS && QS && NW == 4 ? 3 : 2; }
+template <int D, bool KS, bool QS, int NW>
+struct GradsCfg {
+  static constexpr int kPerSimd = grads_waves_per_simd(D, KS, QS, NW);
+  static constexpr int kStages = NW == 8 ? 2 : 1;                          // of a wave's Q and dO tiles (KS)
+  static constexpr int kKeyLds = KS ? BwdShortCfg<D, NW, kStages>::kLds : BwdCfg<D>::kLds;
+  static constexpr int kQueryLds = QS ? DqShortCfg<D, NW>::kLds : BwdCfg<D, NW>::kLds;
+  static constexpr int kLds = kKeyLds > kQueryLds ? kKeyLds : kQueryLds;
+};
+template <int D, int GT, bool KS, bool QS, int NW>
+__global__ __launch_bounds__(NW * 64, (grads_waves_per_simd(D, KS, QS, NW))) void moda_bwd_grads_kernel(BwdParams p, int heads, int spread) {
+  using C = GradsCfg<D, KS, QS, NW>;
+  constexpr int kKeys = KS ? 32 : 128;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::kLds];
+  const int G = p.Hq / p.Hk, sub = G / heads, n_pos = QS ? 32 : NW * 32 / heads;
+  const int n_kt = (p.T + kKeys - 1) / kKeys, n_qt = (p.T + n_pos - 1) / n_pos;
+  int bg, w;
+  head_walk_id(QS ? (int)blockIdx.x : layered_id(p.causal, 2), p.B * p.Hk, n_kt + n_qt * sub, bg, w, p.head_group);
+  int kt = w, qi = w - n_kt;
+  if (spread) {  // key tiles evenly among the query tiles
+    const unsigned long long m = n_kt + (long long)n_qt * sub;
+    kt = (int)((unsigned long long)(unsigned)w * n_kt / m);
+    if ((int)((w + 1ull) * n_kt / m) == kt) {
+      qi = w - kt;
+      kt = n_kt;
+    }
+  }
+  if (kt < n_kt) {
+    if constexpr (KS) dkdv_short_tile<D, 0, NW, C::kStages>(p, smem, bg, kt);
+    else dkdv_tile<D, 0>(p, smem, bg, kt);
+    return;
+  }
+  const int bh0 = (bg / p.Hk) * p.Hq + (bg % p.Hk) * G + qi % sub * heads, q0 = (n_qt - 1 - qi / sub) * n_pos;
+  const bool depth_first = qi * 4 < n_qt;
+  if constexpr (QS) dq_short_tile<D, GT, C::kPerSimd == 3 ? 3 : 5, C::kPerSimd == 3 && GT == 4 ? 2 : 4, NW>(p, smem, bg, bh0, heads, q0, depth_first);
+  else dq_tile<D, NW, 2, GT>(p, smem, bg, bh0, heads, q0, depth_first);
 }
 
 // ---------------------------------------------------------------- depth-slot gradients of a large group, matrix pipe
@@ -1933,7 +2129,106 @@ static bool own_depth_kernel(const BwdParams& p, int d) {
   if (p.depth_alloc == 0 || G <= 4) return false;
   return G > 8 || d != 64 || dkdv_waves(p, d) != 0 || L * 16 < blocks * 32 * 11 || L == 0;
 }
-int bwd_bf16_kernels(const BwdParams& p, int d) { return 3 + (own_depth_kernel(p, d) ? 1 : 0); }
+// Calls that take one kernel for dK, dV and dQ (moda_bwd_grads_kernel).  With depth slots the heads of a group have to fill the
+// waves of a workgroup evenly, and up to 4 of them their gradients on the vector ALUs.  Up to 16 positions the launches
+// stay apart, as moda_kernels_per_call has them (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).
+static bool one_launch(const BwdParams& p) {
+  const int G = p.Hq / p.Hk;
+  return p.T > 16 && (p.depth_alloc == 0 || G == 1 || G == 2 || G == 4);
+}
+struct GradsPlan {
+  bool few_keys, few_queries;
+  int waves;
+  int heads(const BwdParams& p) const {
+    const int G = p.Hq / p.Hk;
+    return p.depth_alloc > 0 ? G : few_queries ? 1 : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+  }
+  long long key_tiles(const BwdParams& p) const { return ((long long)p.T + (few_keys ? 31 : 127)) / (few_keys ? 32 : 128); }
+  long long query_tiles(const BwdParams& p) const {
+    const int n = few_queries ? 32 : waves * 32 / heads(p);
+    return ((long long)p.T + n - 1) / n;
+  }
+};
+// Heads that a die walks together there (see head_walk_id): up to two rounds of workgroups all of them, so that the
+// longest workgroups of all heads start first and neighbouring units do not all get one kind of tile (with one head of
+// two key and two query tiles at a time every other unit had all the depth slots: B=72 H=1 T=37 d=128, 64 slots 101 -> 65 us);
+// beyond, as many as have K and V in 512 KB of the L2, which their tiles then find there (256 KB / 512 KB / 1 MB / 2 MB / 4 MB, 70
+// shapes: 0.894 / 0.890 / 0.892 / 0.894 / 0.899 of the time of two launches).
+static int grads_head_group(const BwdParams& p, int d, long long grid) {
+  if (p.B * p.Hk % 8 != 0) return 0;
+  const long long per_die = (long long)p.B * p.Hk / 8;
+  if (grid <= 1024) return (int)per_die;
+  return (int)std::max(1ll, std::min(per_die, (512ll << 10) / (4ll * p.T * d)));
+}
+// The kind of tiles whose estimated time is shortest.  As for dkdv_waves: the chains of the longest key tile and of the longest
+// query tile (a step: 64 queries x 128 keys, 128 x 64, or 32 x 32 per wave; chunks of slots one after the other), and what
+// all tiles ask of 256 units (steps, ends, slots).  Constants (us; per 256 units) fitted to the times of all kinds at 4200
+// shapes (T = 17 to 20000, 1 to 12000 heads, 1 to 16 per group, 0 to 64 slots): 1.2 % behind the best kind on average,
+// more than 10 % at 1 of 26.  Backward call, us, 128-row tiles / 32 keys and 32 positions / 32 keys, 128 rows / the last
+// two with eight waves (d = 64):
+//   d=64   G=1 T=216 32 heads, 64 slots  109 / 99 / 108 / 87 / -;   B=5 H=2 T=6284, 1 slot  207 / 282 / 262 / - / -
+//          G=4 B=3 Hk=2 T=381, no slots  36 / 16.7 / 16.5 / 14.6 / -;   G=16 Hk=1 T=16817, no slots  4810 / 3130 / 2667 / 2654 / 2345
+//   d=128  G=1 B=2 H=8 T=1351, 24 slots  153 / 161 / -;   B=2 H=4 T=564, 7 slots  41 / 22 / -
+//          G=4 Hk=2 T=1099, 12 slots  170 / 63 / 52;   Hk=4 T=8447, 31 slots  1440 / 1216 / -
+// Heads that cannot be dealt to the dies are walked tile by tile, all heads at a time: with several rounds of workgroups all key
+// tiles would come before all slots, which then only the products of dQ hide.  Where the slots are the longer part the key
+// tiles go evenly among the query tiles instead (behind them / among them, us: B=89 Hq=4 Hk=2 T=997 d=128, 15 slots 887 / 802;
+// B=41 H=1 T=7189 d=64, 15 slots 1280 / 1200; but B=99 H=1 T=5190 d=128, 7 slots 2810 / 2910, B=5 Hq=2 Hk=1 T=18303 d=64, 15
+// slots 2782 / 3176.  Heads that can be dealt: 1.07 of the time on average.)
+static int spread_key_tiles(const BwdParams& p, long long grid) {
+  return p.head_group == 0 && grid > 1024 && p.depth_count >= 4 && (long long)p.T * (p.Hq / p.Hk) <= 600ll * p.depth_count;
+}
+struct GradsCost {
+  GradsPlan plan;
+  double key_step, query_step, key_unit, query_unit, key_ends, query_ends, slot, slot_unit, undealt, once;
+};
+static GradsPlan grads_plan(const BwdParams& p, int d) {
+  static const GradsCost costs64[] = {{{false, false, 4}, 1.16, 0.427, 0.992, 0.625, 1.59, 3.46, 0.422, 0.364, 0.044, 7.54},
+                                      {{true, true, 4}, 0.795, 0.63, 0.94, 0.000594, 1.86, 0.979, 0.377, 0.383, 0.152, 6.83},
+                                      {{true, false, 4}, 0.787, 0.707, 0.914, 0.000805, 2.44, 2.41, 0.458, 0.375, 0.121, 7.2},
+                                      {{true, true, 8}, 0.967, 0.707, 2.2, 0.00308, 4.16, 2.65, 0.368, 0.383, 0.0105, 7.58},
+                                      {{true, false, 8}, 1, 1.22, 1.9, 0.000928, 5.9, 4.1, 0.502, 0.361, 0.156, 7.62}};
+  static const GradsCost costs128[] = {{{false, false, 4}, 2.48, 0.831, 2.63, 0.443, 0.635, 7.67, 0.39, 0.357, 0.00968, 8.8},
+                                       {{true, true, 4}, 1.29, 1.05, 1.88, 0.000767, 3.98, 2.02, 0.367, 0.368, 0.137, 8.63},
+                                       {{true, false, 4}, 1.28, 1.17, 1.7, 0.00045, 4.59, 3.21, 0.472, 0.371, 0.22, 8.96}};
+  const double n32 = (p.T + 31) / 32, n64 = (p.T + 63) / 64, heads = (double)p.B * p.Hk / 256;
+  const int G = p.Hq / p.Hk, per_step = 512 / d;  // (rows of slots that a wave takes at a time)
+  const double walk32 = p.causal ? (n32 + 1) / 2 : n32;  // tiles of 32 that a tile of 32 sees on average
+  GradsPlan best{};
+  double least = 0;
+  for (int i = 0; i < (d == 64 ? 5 : 3); ++i) {
+    const GradsCost& c = d == 64 ? costs64[i] : costs128[i];
+    const int nw = c.plan.waves, h = c.plan.heads(p), n_pos = c.plan.few_queries ? 32 : nw * 32 / h;
+    const double kt = (double)c.plan.key_tiles(p), qt = (double)c.plan.query_tiles(p) * (G / h);
+    double k_first, k_all, q_first, q_all;
+    if (c.plan.few_keys) {
+      k_first = G * n32 / nw;
+      k_all = kt * (G * walk32 / nw + 0.5 - 0.5 / nw);
+    } else {
+      k_first = G * n64;
+      k_all = kt * G * (p.causal ? n64 - kt + 1 : n64);
+    }
+    if (c.plan.few_queries) {
+      q_first = n32 * h / nw;
+      q_all = qt * (walk32 * h / nw + 0.5 - 0.5 * h / nw);
+    } else {
+      q_first = n64;
+      q_all = qt * (p.causal ? (n64 + std::max(1.0, n_pos / 64.0)) / 2 : n64);
+    }
+    int passes = 0;
+    if (p.depth_alloc > 0 && G == 1) passes = (std::min(p.T, c.plan.few_queries ? std::max(32 / nw, per_step) : 32) + per_step - 1) / per_step;
+    else if (p.depth_alloc > 0) passes = (std::min(p.T, n_pos) + nw * per_step - 1) / (nw * per_step);
+    const double load = heads * ((k_all * c.key_unit + q_all * c.query_unit) * (1 + c.undealt * undealt_share((long long)p.B * p.Hk)) +
+                                 kt * c.key_ends + qt * c.query_ends + (double)p.T * p.depth_count * d / 1000 * c.slot_unit);
+    const double time = c.once + sqrt(sqrt(fourth(k_first * c.key_step) + fourth(q_first * c.query_step + passes * p.depth_count * c.slot) + fourth(load)));
+    if (i == 0 || time < least) {
+      least = time;
+      best = c.plan;
+    }
+  }
+  return best;
+}
+int bwd_bf16_kernels(const BwdParams& p, int d) { return one_launch(p) ? 2 : 3 + (own_depth_kernel(p, d) ? 1 : 0); }
 
 template <int D>
 static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
@@ -1953,6 +2248,13 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   if (G > bwd_bf16_max_group()) return hipErrorInvalidValue;
   // the group kernel gathers the G heads' rows of a position with 32-bit offsets from the first head
   if (G > 8 && p.depth_alloc > 0 && (unsigned long long)G * p.T * (D * 2) >= 0xffffff00ull) return kGridTooLarge;
+  GradsPlan plan{};
+  long long g_grads = 0;
+  if (one_launch(p)) {
+    plan = grads_plan(p, D);
+    g_grads = (long long)p.B * p.Hk * (plan.key_tiles(p) + plan.query_tiles(p) * (G / plan.heads(p)));
+    if (!grid_ok(g_grads)) return kGridTooLarge;
+  }
   p.minus_delta = p.lse2 + rows;
   p.dq_depth = (float*)((char*)p.lse2 + row_scalar_bytes(p));
   hipError_t e = launch_kernel(moda_bwd_delta_kernel<D>, dim3((unsigned)g_delta), dim3(256), stream, p.dO, p.O, p.LSE,
@@ -1969,15 +2271,30 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     }
     if (e != hipSuccess) return e;
   }
+  if (g_grads > 0) {
+    const int heads = plan.heads(p);
+    p.head_group = grads_head_group(p, D, g_grads);
+    const int spread = spread_key_tiles(p, g_grads);
+    auto launch = [&](auto gt) {
+      constexpr int GT = decltype(gt)::value, kEight = D == 64 ? 8 : 4;
+      const auto kernel = plan.waves == 8 ? (plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, kEight> : moda_bwd_grads_kernel<D, GT, true, false, kEight>)
+                          : !plan.few_keys ? moda_bwd_grads_kernel<D, GT, false, false, 4>
+                          : plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 4> : moda_bwd_grads_kernel<D, GT, true, false, 4>;
+      return launch_kernel(kernel, dim3((unsigned)g_grads), dim3(plan.waves * 64), stream, p, heads, spread);
+    };
+    if (p.depth_alloc == 0) return launch(std::integral_constant<int, 0>());
+    return G == 1 ? launch(std::integral_constant<int, 1>()) : G == 2 ? launch(std::integral_constant<int, 2>()) : launch(std::integral_constant<int, 4>());
+  }
   {
-    const int few = dkdv_waves(p, D);  // (see moda_bwd_dkdv_short_kernel)
+    const int few = G <= 2 ? 4 : dkdv_waves(p, D);  // (see moda_bwd_dkdv_short_kernel)
     constexpr int kEight = D == 64 ? 8 : 4;
     const dim3 gk((unsigned)(few ? (long long)p.B * p.Hk * ((p.T + 31) / 32) : g_dkdv)), blk(few ? few * 64 : 256);
     const bool grouped = G > 1 && p.depth_alloc > 0 && !own_depth_kernel(p, D);  // the group's depth-slot gradients run inside dK/dV
     auto pick = [few](auto other, auto four, auto eight) { return few == 0 ? other : few == 4 ? four : eight; };
     const auto kernel =
-        !grouped ? pick(moda_bwd_dkdv_kernel<D, 0>, moda_bwd_dkdv_short_kernel<D, 0, 4>, moda_bwd_dkdv_short_kernel<D, 0, kEight>)
-        : G <= 2 ? pick(moda_bwd_dkdv_kernel<D, 2>, moda_bwd_dkdv_short_kernel<D, 2, 4>, moda_bwd_dkdv_short_kernel<D, 2, kEight>)
+        few == 4 && G == 1 && p.depth_alloc > 0 ? moda_bwd_dkdv_short_kernel<D, 1, 4>  // (up to 16 positions: always 32 keys, four waves)
+        : !grouped ? pick(moda_bwd_dkdv_kernel<D, 0>, moda_bwd_dkdv_short_kernel<D, 0, 4>, moda_bwd_dkdv_short_kernel<D, 0, kEight>)
+        : G == 2 ? moda_bwd_dkdv_short_kernel<D, 2, 4>                                 // (the same)
         : G <= 4 ? pick(moda_bwd_dkdv_kernel<D, 4>, moda_bwd_dkdv_short_kernel<D, 4, 4>, moda_bwd_dkdv_short_kernel<D, 4, kEight>)
                  : moda_bwd_dkdv_kernel<D, D == 64 ? 8 : 4>;  // (d = 128: never more than 4 here)
     e = launch_kernel(kernel, gk, blk, stream, p);

@@ -97,6 +97,21 @@ __device__ __forceinline__ void head_blocked_id(int id, int n_heads, int n_tiles
   }
 }
 
+// The same for a `group` that need not divide the heads of a die: the last heads make a smaller one.
+__device__ __forceinline__ void head_walk_id(int id, int n_heads, int n_tiles, int& head, int& tile, int group) {
+  if (group > 0) {
+    const int die = id & 7, r = id >> 3;
+    const int per_group = group * n_tiles;
+    const int grp = r / per_group, w = r % per_group;
+    const int here = min(group, n_heads / 8 - grp * group);
+    tile = w / here;
+    head = (grp * group + w % here) * 8 + die;
+  } else {
+    head = id % n_heads;
+    tile = id / n_heads;
+  }
+}
+
 // Value held by lane (l ^ 32) of the same wave.
 __device__ __forceinline__ float partner32(float x) {
   int xi = __builtin_bit_cast(int, x);
