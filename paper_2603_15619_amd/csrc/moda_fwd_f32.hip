@@ -9,7 +9,7 @@
 // softmax scale 1 8.6e-7 -> 5.0e-7.  Factors that have no such parts take the fp32 instructions (see
 // fold_tile).  The depth slots run on the vector ALUs at the memory rate.
 //
-// A workgroup = 32 queries of one head; its 4 waves share the queries and DEAL OUT THE KEYS: key
+// A workgroup = 32 queries of one head; its 4 (few tiles: 8) waves share the queries and DEAL OUT THE KEYS: key
 // tile kt (32 keys) belongs to wave kt % 4, every wave keeps a running (max, normaliser, output) of
 // its own, and the four are folded into one softmax at the end, together with the partial result
 // of the depth slots.  Dealing out keys instead of queries makes the unit of work 32 queries per
@@ -44,7 +44,6 @@ namespace moda {
 
 constexpr int kF32Rows = 32;   // queries per workgroup
 constexpr int kF32Keys = 32;   // keys per tile (of one wave)
-constexpr int kF32Waves = 4;
 constexpr float kTiny = -100.f;       // (2^kTiny: weights below have not all of their bits in three parts either)
 constexpr float kLargest = 0x1p120f;  // (the sums of first parts, rounded up, could overflow where those of the values do not)
 // A minute value (below 2^-110) loses its last bits, 2^-134 of a number: nothing next to a value above kLeast whose
@@ -52,7 +51,7 @@ constexpr float kLargest = 0x1p120f;  // (the sums of first parts, rounded up, c
 constexpr float kWide = -50.f, kLeast = 0x1p-52f;
 constexpr unsigned kLeastSplit = (127 - 100) << 23;  // numbers below 2^-100 are not split where they count by themselves
 
-template <int D>
+template <int D, int NW>
 struct F32Cfg {
   static constexpr int kRow = D + 4;                 // floats per LDS row (16 consecutive rows hit 16 bank groups)
   static constexpr int kBlocks = D / 32;             // output blocks of 32 channels
@@ -63,7 +62,7 @@ struct F32Cfg {
   static constexpr int kXWave = kF32Rows * kXRow;    // floats of one wave's share in a round
   static constexpr int kQRow = D + 8;                // bf16 numbers per LDS row of a part of the queries
   static constexpr int kQPart = kF32Rows * kQRow;
-  static constexpr int kShared = kF32Waves * kXWave; // floats: the queries (three parts), later the outputs
+  static constexpr int kShared = NW * kXWave; // floats: the queries (three parts), later the outputs
   static_assert(3 * kQPart * 2 <= kShared * 4, "the queries fit");
 };
 
@@ -107,20 +106,20 @@ __device__ __forceinline__ float weight(float a, float b, float c2) {
   return exp2f((a - (b == -INFINITY ? 0.f : b)) * c2);
 }
 
-template <int D>
-__global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_kernel(FwdParams p) {
-  using C = F32Cfg<D>;
+template <int D, int NW>
+__device__ __forceinline__ void fwd_f32_tile(const FwdParams& p) {
+  using C = F32Cfg<D, NW>;
   // the queries, later the waves' outputs; the depth slots' partial outputs; (max, normaliser) of
   // each wave and of the depth slots; scratch for the rare path below
   __shared__ __attribute__((aligned(16))) float shared[C::kShared];
   __shared__ __attribute__((aligned(16))) float depth_o[kF32Rows * C::kRow];
-  __shared__ float stat_m[kF32Waves + 1][kF32Rows], stat_l[kF32Waves + 1][kF32Rows];
+  __shared__ float stat_m[NW + 1][kF32Rows], stat_l[NW + 1][kF32Rows];
   __shared__ float p_tile[kF32Keys][kF32Rows];
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int bh, tile;
-  head_blocked_id(layered_id(p.causal, D == 64 ? 3 : 2), p.B * p.Hq, p.n_qtiles, bh, tile, p.head_group);
+  head_blocked_id(layered_id(p.causal, NW == 8 ? 1 : D == 64 ? 3 : 2), p.B * p.Hq, p.n_qtiles, bh, tile, p.head_group);
   const int q0 = (p.n_qtiles - 1 - tile) * kF32Rows;  // heavy (late) tiles first
   const int b = bh / p.Hq, g = (bh - b * p.Hq) / (p.Hq / p.Hk);
   const size_t bg = (size_t)b * p.Hk + g;
@@ -137,7 +136,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
   unsigned least_q = 0xffffffffu;
   float largest_q = 0.f;
   unsigned short *q_parts = (unsigned short*)shared, *dst;
-  for (int i = tid; i < kF32Rows * (D / 4); i += kF32Waves * 64) {
+  for (int i = tid; i < kF32Rows * (D / 4); i += NW * 64) {
     const int r = i / (D / 4), c = i % (D / 4);
     const f32x4 q = *(const f32x4*)((const float*)p.Q + ((size_t)bh * T + min(q0 + r, T - 1)) * D + c * 4);
     float x[4] = {q[0], q[1], q[2], q[3]};
@@ -160,7 +159,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
   if (least_q < 2 * kLeastSplit - 1 || largest_q > (c2 <= 0x1p30f ? 0x1p64f : 0.f)) *dst = 0x7fc0;
   __syncthreads();
 
-  // ---- depth slots: 16 lanes per row, 4 (d = 64) or 8 (d = 128) channels each; a wave takes 8 of
+  // ---- depth slots: 16 lanes per row, 4 (d = 64) or 8 (d = 128) channels each; a wave takes 8 (of eight waves 4) of
   // the tile's rows, 4 at a time, kC slots at a time with the next kC in flight
   auto depth_rows = [&]() {
     constexpr int NV = D / 64, kC = D == 128 ? 3 : 6;
@@ -170,7 +169,8 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
       f32x4 k[kC][NV], v[kC][NV];
     };
     const size_t drow = (size_t)p.depth_alloc * D;
-    auto row_of = [&](int it) { return wave * 8 + it * 4 + rg; };
+    constexpr int kRowSteps = kF32Rows / 4 / NW;
+    auto row_of = [&](int it) { return (wave * kRowSteps + it) * 4 + rg; };
     auto issue = [&](int it, int c, Chunk& x) {
       const size_t base = (bg * T + min(q0 + row_of(it), T - 1)) * drow + l16 * 4;
 #pragma unroll
@@ -233,8 +233,8 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
       }
     };
     auto issue_next = [&](Chunk& x) {  // (past the end: the last chunk again, ignored)
-      issue(min(iti, 1), iti < 2 ? ci : nch - 1, x);
-      if (iti < 2) advance(iti, ci);
+      issue(min(iti, kRowSteps - 1), iti < kRowSteps ? ci : nch - 1, x);
+      if (iti < kRowSteps) advance(iti, ci);
       __builtin_amdgcn_sched_barrier(0);
     };
     auto one = [&](const Chunk& cur, Chunk& refill) -> bool {
@@ -254,12 +254,12 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
         for (int n = 0; n < NV; ++n) *(f32x4*)(depth_o + r * C::kRow + l16 * 4 + n * 64) = o[n];
         if (l16 == 0) {
-          stat_m[kF32Waves][r] = m;
-          stat_l[kF32Waves][r] = l;
+          stat_m[NW][r] = m;
+          stat_l[NW][r] = l;
         }
       }
       advance(it, c);
-      return it < 2;
+      return it < kRowSteps;
     };
     Chunk xa, xb;
     issue_next(xa);
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
     // loads in flight: half of the tile's V during the scores; then its other half; half of the next
     // tile's K from the output products on, the rest from their middle (all of K and V at once do
     // not fit 256 registers)
-    const int k_next = kt + kF32Waves;  // (past the last tile: rows that exist or zeros, not used)
+    const int k_next = kt + NW;  // (past the last tile: rows that exist or zeros, not used)
     load_v(kt, 0);
     __builtin_amdgcn_sched_barrier(0);
     // S^T = K Q^T: the products of the first parts in one chain, the five others down to 2^-16 of them in
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
     if (by_parts) products(1);
   };
   int kt = wave;
-  for (; kt < n_full; kt += kF32Waves) fold_tile(kt, std::false_type{});
+  for (; kt < n_full; kt += NW) fold_tile(kt, std::false_type{});
   if (kt < nt) fold_tile(kt, std::true_type{});
   if (L > 0 && !depth_first) depth_rows();
 
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
     stat_l[wave][l32] = l;
   }
   __syncthreads();  // (also: every wave is done with the queries in LDS)
-  const int n_part = kF32Waves + (L > 0 ? 1 : 0);
+  const int n_part = NW + (L > 0 ? 1 : 0);
   {
     float mt = stat_m[0][l32];
     for (int w = 1; w < n_part; ++w) mt = fmaxf(mt, stat_m[w][l32]);
@@ -525,13 +525,14 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[cb][i] *= f;
   }
-  // thread: row tid / 8, 8 of the round's 64 channels
-  const int row = tid >> 3, ch = (tid & 7) * 8, t = q0 + row;
+  // thread: a row, 8 (with eight waves 4) of the round's 64 channels
+  constexpr int TPR = NW * 64 / kF32Rows, CPT = 64 / TPR;
+  const int row = tid / TPR, ch = tid % TPR * CPT, t = q0 + row;
   float mt = stat_m[0][row];
   for (int w = 1; w < n_part; ++w) mt = fmaxf(mt, stat_m[w][row]);
   float lt = 0.f;
   for (int w = 0; w < n_part; ++w) lt += stat_l[w][row] * weight(stat_m[w][row], mt, c2);
-  const float fd = L > 0 ? weight(stat_m[kF32Waves][row], mt, c2) : 0.f;
+  const float fd = L > 0 ? weight(stat_m[NW][row], mt, c2) : 0.f;
   const float inv = 1.0f / lt;
 #pragma unroll
   for (int rd = 0; rd < C::kRounds; ++rd) {
@@ -545,35 +546,49 @@ __global__ __launch_bounds__(kF32Waves * 64, D == 64 ? 3 : 2) void moda_fwd_f32_
       else *(f32x2*)(xw + c0) = (f32x2){o[0][i], o[1][i]};
     }
     __syncthreads();
-    f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+    f32x4 x[CPT / 4];
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) {
-      x0 += *(const f32x4*)(shared + w * C::kXWave + row * C::kXRow + ch);
-      x1 += *(const f32x4*)(shared + w * C::kXWave + row * C::kXRow + ch + 4);
-    }
-    if (L > 0) {
-      x0 += *(const f32x4*)(depth_o + row * C::kRow + rd * 64 + ch) * fd;
-      x1 += *(const f32x4*)(depth_o + row * C::kRow + rd * 64 + ch + 4) * fd;
-    }
-    if (t < T) {
-      float* dst = (float*)p.O + ((size_t)bh * T + t) * D + rd * 64 + ch;
-      *(f32x4*)dst = x0 * inv;
-      *(f32x4*)(dst + 4) = x1 * inv;
+    for (int k = 0; k < CPT / 4; ++k) {
+      x[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) x[k] += *(const f32x4*)(shared + w * C::kXWave + row * C::kXRow + ch + 4 * k);
+      if (L > 0) x[k] += *(const f32x4*)(depth_o + row * C::kRow + rd * 64 + ch + 4 * k) * fd;
+      if (t < T) *(f32x4*)((float*)p.O + ((size_t)bh * T + t) * D + rd * 64 + ch + 4 * k) = x[k] * inv;
     }
   }
-  if ((tid & 7) == 0 && t < T) p.LSE[(size_t)bh * T + t] = mt * p.scale + logf(lt);
+  if (tid % TPR == 0 && t < T) p.LSE[(size_t)bh * T + t] = mt * p.scale + logf(lt);
+}
+
+// Few tiles are bound by the chains of a wave's key tiles and slots, which eight waves to a workgroup halve.
+template <int D>
+__global__ __launch_bounds__(512, 2) void moda_fwd_f32_kernel(FwdParams p) {
+  fwd_f32_tile<D, 8>(p);
+}
+template <int D>
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void moda_fwd_f32_four_kernel(FwdParams p) {
+  fwd_f32_tile<D, 4>(p);
 }
 
 int fwd_f32_tile_rows() { return kF32Rows; }
+// Eight waves while every workgroup has a unit of its own, unless there is no chain to halve (four / eight, us, tiles of
+// 32 queries; d = 64: H=2 T=20, 31 slots 17.3 / 11.8;  B=2 H=16 T=112, 15 slots 14.9 / 12.0;  H=4 T=1669, 15 slots, 212 tiles 38.3 / 32.2;
+// H=2 T=256, 4 slots 10.0 / 9.9;  288 tiles, T=548 21.3 / 21.0;  384 tiles 48.2 / 52.3;  no slots: H=8 T=56 6.2 / 6.8.
+// d = 128: H=2 T=25, 31 slots 26.8 / 18.5;  160 tiles, T=141, 7 slots 19.3 / 17.1;  208 tiles, T=403, 24 slots 40.4 / 41.1;  256
+// tiles, T=31, 4 slots 16.9 / 15.6;  416 tiles, T=404, 31 slots 94 / 106;  no slots: H=8 T=344 15.9 / 15.4, T=204 12.9 / 13.4.
+// Three chunks of slots in flight instead of two: 1.03 of the time.)
+bool fwd_f32_eight_waves(const FwdParams& p) {
+  return (long long)p.B * p.Hq * ((p.T + kF32Rows - 1) / kF32Rows) <= 256 && (p.depth_count > 0 || p.T > 256);
+}
 
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream) {
   if (fwd_f32_by_rows(p)) return launch_fwd_f32_rows(p, d, stream);
   if (p.n_qtiles != (p.T + kF32Rows - 1) / kF32Rows) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * p.Hq * p.n_qtiles;
   if (!grid_ok(blocks)) return kGridTooLarge;
-  dim3 grid((unsigned)blocks), block(kF32Waves * 64);
-  if (d == 128) return launch_kernel(moda_fwd_f32_kernel<128>, grid, block, stream, p);
-  if (d == 64) return launch_kernel(moda_fwd_f32_kernel<64>, grid, block, stream, p);
+  const bool eight = fwd_f32_eight_waves(p);
+  dim3 grid((unsigned)blocks), block(eight ? 512 : 256);
+  if (d == 128) return launch_kernel(eight ? moda_fwd_f32_kernel<128> : moda_fwd_f32_four_kernel<128>, grid, block, stream, p);
+  if (d == 64) return launch_kernel(eight ? moda_fwd_f32_kernel<64> : moda_fwd_f32_four_kernel<64>, grid, block, stream, p);
   return hipErrorInvalidValue;
 }
 

@@ -1,14 +1,17 @@
 """GPU parity of the fp32 forward at the edges of its tiles (32 queries x 32 keys, key tiles dealt
-to 4 waves, depth slots in chunks of 3 or 6): against the fp64 oracle, through the C ABI.
+to 4 or 8 waves, depth slots in chunks of 3 or 6): against the fp64 oracle, through the C ABI.
 
 Tolerance 1e-5 (max abs): |O| <= 5 here and a weight or an output is a sum of at most a few hundred
 terms rounded at 2^-24 relative, an error of some 1e-6 at most."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 from oracle import moda_ref as R
 from paper_2603_15619_amd import moda_attn_fwd, synth
+from paper_2603_15619_amd.binding import MODAShape, lib
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-5
@@ -35,6 +38,21 @@ def run(B, Hq, Hk, T, d, L, seed, causal=True, depth_alloc=None, spoil=None):
                                               (1, 8, 8, 129, 64, 1, 3), (3, 8, 2, 161, 128, 13, None), (1, 2, 1, 517, 128, 2, None)])
 def test_f32_tile_edges(B, Hq, Hk, T, d, L, La, causal):
     O, LSE, (Oref, Lref) = run(B, Hq, Hk, T, d, L, 40 + T + L, causal, La)
+    assert np.abs(O - Oref).max() <= TOL and np.abs(LSE - Lref).max() <= TOL
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,four", [(32, 8, 4, 9, 64, 5, 6, False), (43, 6, 3, 32, 128, 4, None, True), (33, 4, 2, 33, 64, 7, 8, True),
+                                                   (22, 3, 1, 97, 128, 6, None, True), (8, 8, 2, 100, 64, 13, None, False), (13, 4, 4, 129, 128, 1, 2, True),
+                                                   (2, 2, 2, 257, 128, 0, None, False), (2, 2, 2, 256, 64, 0, None, True)])
+def test_f32_four_and_eight_waves(B, Hq, Hk, T, d, L, La, four, causal):
+    """Both sides of the line between four waves per workgroup and eight, which takes up to 256 tiles with slots or more
+    than 256 positions."""
+    s = MODAShape(B, Hq, Hk, T, d, L if La is None else La, L, int(causal), 0.0, 0)
+    name = ctypes.create_string_buffer(64)
+    lib().moda_fwd_kernel_name(ctypes.byref(s), None, name, len(name))
+    assert name.value.decode() == "moda_fwd_f32_%skernel<%d>" % ("four_" if four else "", d)
+    O, LSE, (Oref, Lref) = run(B, Hq, Hk, T, d, L, 140 + T + L, causal, La)
     assert np.abs(O - Oref).max() <= TOL and np.abs(LSE - Lref).max() <= TOL
 
 
