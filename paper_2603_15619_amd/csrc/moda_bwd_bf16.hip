@@ -1064,7 +1064,7 @@ struct BwdShortCfg {
 };
 
 // GT: 1, 2, 4 = the depth slots of the 32 positions are taken here as well, of groups of up to GT heads; 0 = not here.
-// ST: stages of a wave's Q and dO tiles.  With one (in the launch with dQ, four waves) Q's place is requested anew as soon as
+// ST: stages of a wave's Q and dO tiles.  With one (in the launch with dQ, four waves, and eight at d = 128) Q's place is requested anew as soon as
 // dK is formed and dO's after dV: half the LDS, so that at d = 128 two workgroups share a unit and at d = 64
 // three.  (dK, dV and dQ in one launch, two stages / one, us: B=4 Hq=8 Hk=2 T=901 d=128 61 / 54; B=2 H=16 T=657 d=128 55 / 40;
 // B=4 Hq=32 Hk=8 T=719 d=64, 4 slots 71 / 62.)
@@ -1747,7 +1747,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
 // quarter of the query tiles takes its slots first, while key tiles keep the matrix pipe busy, the others after their keys,
 // straight into the finished row.
 // Key tiles of 128 keys or (KS) 32 dealt out to the waves, query tiles of 128 rows or (QS) 32 positions dealt out; eight
-// waves instead of four (NW, d = 64 with KS) where few key tiles see many queries: grads_plan draws the lines.
+// waves instead of four (NW, with KS) where few tiles have long walks: grads_plan draws the lines.
 // Backward call, two launches / one: B=8 H=16 T=4096 d=128, 15 slots 2.80 / 2.65 ms; B=2 Hq=16 Hk=8 T=1000 d=64, 12
 // slots 58 / 45 us; B=2 H=16 T=1105 d=128, 1 slot 104 / 64; B=2 H=2 T=206 d=128, 12 slots 25 / 17; B=1 Hq=4 Hk=1 T=4026 d=128, 64
 // slots 290 / 220; B=3 Hq=8 Hk=2 T=71 d=128, 1 slot 23.3 / 14.8.  0.77 on average of 3200 random shapes.
@@ -1757,7 +1757,7 @@ constexpr int grads_waves_per_simd(int D, bool KS, bool QS, int NW) { return D =
 template <int D, bool KS, bool QS, int NW>
 struct GradsCfg {
   static constexpr int kPerSimd = grads_waves_per_simd(D, KS, QS, NW);
-  static constexpr int kStages = NW == 8 ? 2 : 1;                          // of a wave's Q and dO tiles (KS)
+  static constexpr int kStages = NW == 8 && D == 64 ? 2 : 1;               // of a wave's Q and dO tiles (KS)
   static constexpr int kKeyLds = KS ? BwdShortCfg<D, NW, kStages>::kLds : BwdCfg<D>::kLds;
   static constexpr int kQueryLds = QS ? DqShortCfg<D, NW>::kLds : BwdCfg<D, NW>::kLds;
   static constexpr int kLds = kKeyLds > kQueryLds ? kKeyLds : kQueryLds;
@@ -2162,14 +2162,15 @@ static int grads_head_group(const BwdParams& p, int d, long long grid) {
 }
 // The kind of tiles whose estimated time is shortest.  As for dkdv_waves: the chains of the longest key tile and of the longest
 // query tile (a step: 64 queries x 128 keys, 128 x 64, or 32 x 32 per wave; chunks of slots one after the other), and what
-// all tiles ask of 256 units (steps, ends, slots).  Constants (us; per 256 units) fitted to the times of all kinds at 4200
-// shapes (T = 17 to 20000, 1 to 12000 heads, 1 to 16 per group, 0 to 64 slots): 1.2 % behind the best kind on average,
-// more than 10 % at 1 of 26.  Backward call, us, 128-row tiles / 32 keys and 32 positions / 32 keys, 128 rows / the last
-// two with eight waves (d = 64):
+// all tiles ask of 256 units (steps, ends, slots).  Constants (us; per 256 units) fitted to the times of all kinds at 2100 and
+// 4800 shapes (T = 17 to 20000, 1 to 12000 heads, 1 to 16 per group, 0 to 64 slots): 1.3 and 1.7 % behind the best kind on
+// average, more than 10 % at 1 of 25 and of 16.  Backward call, us, 128-row tiles / 32 keys and 32 positions / 32 keys, 128
+// rows / the last two with eight waves:
 //   d=64   G=1 T=216 32 heads, 64 slots  109 / 99 / 108 / 87 / -;   B=5 H=2 T=6284, 1 slot  207 / 282 / 262 / - / -
 //          G=4 B=3 Hk=2 T=381, no slots  36 / 16.7 / 16.5 / 14.6 / -;   G=16 Hk=1 T=16817, no slots  4810 / 3130 / 2667 / 2654 / 2345
-//   d=128  G=1 B=2 H=8 T=1351, 24 slots  153 / 161 / -;   B=2 H=4 T=564, 7 slots  41 / 22 / -
-//          G=4 Hk=2 T=1099, 12 slots  170 / 63 / 52;   Hk=4 T=8447, 31 slots  1440 / 1216 / -
+//   d=128  G=1 B=2 H=8 T=1351, 24 slots  153 / 161 / - / - / -;   B=2 H=4 T=564, 7 slots  41 / 22 / - / - / -
+//          G=4 Hk=2 T=1099, 12 slots  170 / 63 / 52 / - / -;   Hk=4 T=8447, 31 slots  1440 / 1216 / - / - / -
+//          G=1 H=1 T=5592, 15 slots not causal  205 / 93 / 159 / 107 / 247;   G=2 Hk=1 T=8526, 15 slots  623 / 449 / 320 / 393 / 450
 // Heads that cannot be dealt to the dies are walked tile by tile, all heads at a time: with several rounds of workgroups all key
 // tiles would come before all slots, which then only the products of dQ hide.  Where the slots are the longer part the key
 // tiles go evenly among the query tiles instead (behind them / among them, us: B=89 Hq=4 Hk=2 T=997 d=128, 15 slots 887 / 802;
@@ -2188,15 +2189,17 @@ static GradsPlan grads_plan(const BwdParams& p, int d) {
                                       {{true, false, 4}, 0.787, 0.707, 0.914, 0.000805, 2.44, 2.41, 0.458, 0.375, 0.121, 7.2},
                                       {{true, true, 8}, 0.967, 0.707, 2.2, 0.00308, 4.16, 2.65, 0.368, 0.383, 0.0105, 7.58},
                                       {{true, false, 8}, 1, 1.22, 1.9, 0.000928, 5.9, 4.1, 0.502, 0.361, 0.156, 7.62}};
-  static const GradsCost costs128[] = {{{false, false, 4}, 2.48, 0.831, 2.63, 0.443, 0.635, 7.67, 0.39, 0.357, 0.00968, 8.8},
-                                       {{true, true, 4}, 1.29, 1.05, 1.88, 0.000767, 3.98, 2.02, 0.367, 0.368, 0.137, 8.63},
-                                       {{true, false, 4}, 1.28, 1.17, 1.7, 0.00045, 4.59, 3.21, 0.472, 0.371, 0.22, 8.96}};
+  static const GradsCost costs128[] = {{{false, false, 4}, 2.48, 0.7, 2.73, 0.393, 0.993, 7.07, 0.421, 0.355, 0.000535, 8.97},
+                                       {{true, true, 4}, 1.29, 1.08, 1.91, 0.000348, 4.08, 2.04, 0.367, 0.365, 0.143, 8.59},
+                                       {{true, false, 4}, 1.27, 1.13, 1.73, 0.000227, 4.37, 3.44, 0.494, 0.37, 0.23, 9.1},
+                                       {{true, true, 8}, 1.63, 1.44, 4.04, 0.00248, 7.33, 3.53, 0.657, 0.37, 0.0338, 9.42},
+                                       {{true, false, 8}, 1.61, 1.76, 3.58, 0.000687, 8.49, 6.65, 0.704, 0.362, 0.226, 10.3}};
   const double n32 = (p.T + 31) / 32, n64 = (p.T + 63) / 64, heads = (double)p.B * p.Hk / 256;
   const int G = p.Hq / p.Hk, per_step = 512 / d;  // (rows of slots that a wave takes at a time)
   const double walk32 = p.causal ? (n32 + 1) / 2 : n32;  // tiles of 32 that a tile of 32 sees on average
   GradsPlan best{};
   double least = 0;
-  for (int i = 0; i < (d == 64 ? 5 : 3); ++i) {
+  for (int i = 0; i < 5; ++i) {
     const GradsCost& c = d == 64 ? costs64[i] : costs128[i];
     const int nw = c.plan.waves, h = c.plan.heads(p), n_pos = c.plan.few_queries ? 32 : nw * 32 / h;
     const double kt = (double)c.plan.key_tiles(p), qt = (double)c.plan.query_tiles(p) * (G / h);
@@ -2276,8 +2279,8 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     p.head_group = grads_head_group(p, D, g_grads);
     const int spread = spread_key_tiles(p, g_grads);
     auto launch = [&](auto gt) {
-      constexpr int GT = decltype(gt)::value, kEight = D == 64 ? 8 : 4;
-      const auto kernel = plan.waves == 8 ? (plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, kEight> : moda_bwd_grads_kernel<D, GT, true, false, kEight>)
+      constexpr int GT = decltype(gt)::value;
+      const auto kernel = plan.waves == 8 ? (plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 8> : moda_bwd_grads_kernel<D, GT, true, false, 8>)
                           : !plan.few_keys ? moda_bwd_grads_kernel<D, GT, false, false, 4>
                           : plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 4> : moda_bwd_grads_kernel<D, GT, true, false, 4>;
       return launch_kernel(kernel, dim3((unsigned)g_grads), dim3(plan.waves * 64), stream, p, heads, spread);

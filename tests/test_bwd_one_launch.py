@@ -40,13 +40,19 @@ def check(B, Hq, Hk, T, d, L, La, causal):
         assert torch.count_nonzero(grads[3][:, :, :, L:].float()) == 0 and torch.count_nonzero(grads[4][:, :, :, L:].float()) == 0
 
 
+EIGHT_128 = [(2, 1, 1, 127, 12, 13, True), (1, 1, 1, 17, 12, None, False), (2, 2, 1, 97, 12, None, True), (1, 2, 1, 500, 3, 4, False), (4, 4, 1, 200, 1, None, True),
+             (1, 4, 1, 33, 1, 2, False), (3, 1, 1, 257, 0, None, True), (2, 3, 1, 161, 0, None, False), (8, 8, 1, 33, 0, None, True),
+             (16, 8, 1, 127, 0, None, True), (8, 8, 1, 257, 0, None, False), (2, 32, 4, 300, 0, None, True)]
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,Hq,Hk,T,L,La", [(1, 1, 1, 17, 3, 4), (2, 3, 3, 33, 6, None), (1, 2, 2, 127, 5, 9), (1, 4, 2, 31, 4, None),
                                             (3, 2, 1, 65, 12, 13), (1, 4, 1, 32, 7, 8), (2, 8, 2, 97, 2, None), (1, 6, 6, 129, 0, 3),
-                                            (1, 1, 1, 161, 0, None), (2, 3, 1, 63, 0, None), (1, 5, 1, 17, 0, None)])
+                                            (1, 1, 1, 161, 0, None), (2, 3, 1, 63, 0, None), (1, 5, 1, 17, 0, None),
+                                            (16, 2, 1, 33, 3, 4), (40, 4, 1, 33, 5, None)])
 def test_few_tiles(B, Hq, Hk, T, d, L, La, causal):
-    """32 keys and 32 positions to a workgroup."""
+    """32 keys and 32 positions to a workgroup (d = 128: of four waves, or eight where groups or slots are longest)."""
     check(B, Hq, Hk, T, d, L, La, causal)
 
 
@@ -60,9 +66,9 @@ def test_many_tiles(B, Hq, Hk, T, d, L, La, causal):
     check(B, Hq, Hk, T, d, L, La, causal)
 
 
-@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(3, 4, 1, 200, 128, 5, 6, True), (1, 16, 4, 161, 128, 5, None, False), (1, 4, 1, 33, 128, 1, None, False),
-                                                     (24, 2, 1, 300, 128, 1, 2, True), (16, 4, 1, 97, 64, 3, None, False), (8, 4, 1, 1000, 64, 5, None, True),
-                                                     (40, 1, 1, 257, 128, 0, None, True), (9, 3, 1, 300, 128, 0, None, False), (8, 8, 1, 257, 128, 0, None, True),
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(16, 4, 1, 500, 128, 5, 6, True), (16, 4, 1, 97, 128, 1, None, False), (4, 2, 1, 1100, 128, 1, None, False),
+                                                     (24, 2, 1, 300, 128, 1, 2, False), (16, 4, 1, 97, 64, 3, None, False), (8, 4, 1, 1000, 64, 5, None, True),
+                                                     (40, 1, 1, 257, 128, 0, None, True), (9, 3, 1, 300, 128, 0, None, False), (24, 8, 1, 129, 128, 0, None, True),
                                                      (33, 8, 1, 127, 64, 0, None, False), (16, 3, 1, 500, 64, 0, None, True)])
 def test_few_key_tiles_of_many_rows(B, Hq, Hk, T, d, L, La, causal):
     """32 keys and 128 rows to a workgroup."""
@@ -75,6 +81,12 @@ def test_few_key_tiles_of_many_rows(B, Hq, Hk, T, d, L, La, causal):
 def test_eight_waves(B, Hq, Hk, T, L, La, causal):
     """d = 64: eight waves to a workgroup, 32 positions or (the last ones) 256 rows of dQ."""
     check(B, Hq, Hk, T, 64, L, La, causal)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,L,La,causal", EIGHT_128)
+def test_eight_waves_d_128(B, Hq, Hk, T, L, La, causal):
+    """... and at d = 128."""
+    check(B, Hq, Hk, T, 128, L, La, causal)
 
 
 @pytest.mark.parametrize("Hq,T", [(2, 97), (4, 97), (8, 97)])
