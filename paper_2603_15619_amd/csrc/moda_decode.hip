@@ -15,6 +15,7 @@
 // query row: no matrix shape to speak of); a lane owns 8 channels, d/8 lanes a key row,
 // 64 / (d/8) key rows per wave instruction.  Grouped queries: the G heads of a group are the
 // columns of small matrix products (keys x heads), see moda_decode_partial_mfma_kernel.
+#include <algorithm>
 #include <atomic>
 
 #include "moda_launch.h"
@@ -425,9 +426,10 @@ void moda_decode_partial_mfma_kernel(DecodeParams p) {
 // One workgroup of NG x D threads per (batch, query head): thread = channel, group g of D threads folds
 // the slices g, g + NG, ... eight at a time (their loads issued together), with a running reference
 // like any other online softmax; the groups' states are folded through LDS.  The fold of a head is
-// a chain of memory latencies, one per eight slices, hence NG = 4 where there are more than 16 (B=8
-// Hq=64, 49 slices of d=64: 7.6 -> 4.8 us; B=8 Hq=16, 17 slices of d=128: 5.1 -> 5.0 us).
-constexpr int kMergeOne = 16;
+// a chain of memory latencies, one per eight slices, hence NG = 4 where there are more than 8 (B=8
+// Hq=64, 49 slices of d=64: 7.6 -> 4.8 us; whole call, 9 slices, T=1003 H=16 d=128 6.8 -> 6.5; 16 slices, Hq=8 Hk=2 B=6 T=1000
+// d=64 6.9 -> 6.6; with 8 slices or fewer 0 to 5 % longer).
+constexpr int kMergeOne = 8;
 
 template <int D, int NG>
 __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams p) {
@@ -502,6 +504,14 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
 // compute units would be left over: 288 workgroups instead of 256 (B=4 Hq=16 Hk=8 T=1662 d=128) took 12.0 us
 // instead of 9.3, 512 instead of 384 (B=64 Hk=2 T=281) 0.88 of the time.  Over 900 random calls, caches just read
 // and from memory, this is 0.3 % behind the better cut on average; always the finer one 1.6 %.
+// Calls that leave units without work take finer slices still (finest_slices): a slice of 128 keys is a chain of four blocks
+// (d = 128: one in flight) or of two batches of rows that such a call only waits for.  Slices of 128 (vector ALUs, above 1792
+// keys 256) / 64 / 32 keys, us, whole call, (batch, key/value head)s on the left:
+//   G=8 d=128   2 T=122 10.6 / 7.9 / 7.1;   4 T=549 12.2 / 9.8 / 7.8;   32 T=371 12.2 / 9.3 / 8.6;   36 T=1604 15.9 / 12.8 / 14.9;   104 T=125 11.7 / 9.2 / 8.5;
+//               2 T=4909 13.6 / 11.4 / 12.3;   20 T=5693 18.7 / 19.9 / 20;   48 T=3421 23 / 28
+//   G=8 d=64    12 T=343 8.7 / 7.3 / 7.2;   48 T=1271 10.6 / 9.7 / 11.6;   2 T=9867 11.4 / 11.6;   104 T=2618 19 / 22
+//   vector ALUs, d=128   G=1 8 T=1977 7.7 / 6.2, with 128 keys 6.6;   16 T=189 6.1 / 5.5;   30 T=1080 8.6 / 8.2;   G=4 32 T=233 8.1 / 7.2;   G=2 120 T=197 8.5 / 8.4
+//   slices of 256 / 128 keys: d=128 8 T=3880 8.5 / 7.3;   8 T=7343 9.4 / 10.5;   d=64 8 T=2094 7.1 / 6.3;   4 T=3706 7.4 / 6.4;   32 T=1717 7.2 / 8.4;   2 T=4786 6.6 / 7.0
 struct DecodePlan {
   bool mfma;
   int n_split;
@@ -509,6 +519,7 @@ struct DecodePlan {
 };
 struct DecodeRule {
   bool mfma;
+  int d;
   int want;      // slices that fill the chip, whatever the length
   int step;      // keys_per_split is a multiple of this
   int most_fine;    // most slices of the finer cut
@@ -528,6 +539,7 @@ static DecodeRule decode_rule(int B, int Hq, int Hk, int d) {
   const int G = Hq / Hk;
   // up to 4 heads per group the vector-ALU kernel is at the memory rate and ahead (measured)
   r.mfma = G > 4;
+  r.d = d;
   if (r.mfma) {
     const int n_gc = (G + 31) / 32;
     // 12 wave-slices per compute unit: all resident at once at d = 64, one and a half rounds
@@ -557,6 +569,19 @@ static int fine_slices(bool mfma, int T) {
   const int fine = (T + 127) / 128, coarse = coarse_slices(T);
   return mfma || fine <= 8 ? fine : coarse > 8 ? coarse : 8;
 }
+// Slices of the finest cut of a call with few workgroups, 0: it has none.
+static int finest_slices(const DecodeRule& r, int T, int depth) {
+  const int n32 = (T + 31) / 32, n64 = (T + 63) / 64, n128 = (T + 127) / 128;
+  if (r.mfma) return n32 <= 16 && r.groups * n32 <= 768 ? n32 : n64 <= 96 && r.groups * n64 <= 1024 ? n64 : 0;
+  if (r.d == 128 && (n64 <= 8 || (coarse_slices(T) >= 8 && n64 <= 32)) && r.groups * (n64 + depth) <= 256) return n64;
+  return coarse_slices(T) >= 8 && n128 <= 32 && r.groups * (n128 + depth) <= 256 ? n128 : 0;
+}
+// No length up to T has more of them.
+static int most_finest_slices(const DecodeRule& r, int T) {
+  const long long n32 = (T + 31) / 32, n64 = (T + 63) / 64, n128 = (T + 127) / 128;
+  if (r.mfma) return (int)std::max(std::min({n32, 16ll, 768 / r.groups}), std::min({n64, 96ll, 1024 / r.groups}));
+  return (int)std::min({r.d == 128 ? n64 : n128, 32ll, 256 / r.groups});
+}
 static DecodePlan cut(const DecodeRule& r, int T, int most) {
   int s = r.want < most ? r.want : most;
   if (s < 1) s = 1;
@@ -569,6 +594,8 @@ static DecodePlan cut(const DecodeRule& r, int T, int most) {
 // The cut of a call whose partial results (of n_split slices and the depth slots) have `room` bytes: the finer
 // slices if they fit and make no more rounds, else the coarser ones.  `depth`: 1 if there are depth slots.
 static DecodePlan decode_plan(const DecodeRule& r, int T, int depth, size_t room) {
+  const int finest = finest_slices(r, T, depth);
+  if (finest > 0 && finest <= r.most_fine && (size_t)(finest + 1) * r.slice_bytes <= room) return cut(r, T, finest);
   const DecodePlan coarse = cut(r, T, coarse_slices(T));
   const int most = fine_slices(r.mfma, T);
   if (most > r.most_fine || (!r.mfma && T > 1024 && coarse_slices(T) > r.most_for_8)) return coarse;
@@ -582,7 +609,7 @@ static DecodePlan decode_plan(const DecodeRule& r, int T, int depth, size_t room
 // T the finer ones take every number of slices up to min(fine, most_fine).)
 size_t decode_workspace_bytes(int B, int Hq, int Hk, int T, int d) {
   const DecodeRule r = decode_rule(B, Hq, Hk, d);
-  int most = fine_slices(r.mfma, T);
+  int most = std::max(fine_slices(r.mfma, T), most_finest_slices(r, T));
   if (most > r.most_fine) most = r.most_fine > coarse_slices(T) ? r.most_fine : coarse_slices(T);
   return (size_t)((r.want < most ? r.want : most) + 1) * r.slice_bytes;
 }

@@ -200,3 +200,26 @@ def test_finer_slices_only_where_they_make_no_more_rounds(B, Hq, Hk, T, d, L, sl
     torch.cuda.synchronize()
     written = int((~torch.isnan(ws)).sum().item())
     assert written == B * Hq * (slices + (L > 0)) * (d + 2)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,slices", [(1, 8, 1, 512, 64, 0, 16), (1, 8, 1, 513, 64, 3, 9), (1, 16, 2, 33, 128, 1, 2), (6, 64, 8, 512, 128, 0, 16),
+                                                  (7, 64, 8, 500, 128, 2, 8), (1, 8, 1, 6144, 64, 0, 96), (1, 8, 1, 6145, 64, 0, 49),
+                                                  (1, 4, 4, 512, 128, 1, 8), (1, 4, 4, 513, 128, 1, 5), (28, 8, 8, 64, 128, 0, 1), (1, 4, 4, 1793, 128, 0, 29),
+                                                  (1, 4, 4, 2048, 128, 5, 32), (1, 4, 4, 2049, 128, 5, 17), (1, 4, 4, 1792, 64, 2, 7), (1, 4, 2, 1793, 64, 2, 15),
+                                                  (1, 2, 2, 4096, 64, 1, 32), (1, 2, 2, 4097, 64, 1, 17), (3, 16, 4, 3000, 128, 4, 12)])
+def test_finest_slices_of_calls_with_few_workgroups(B, Hq, Hk, T, d, L, slices):
+    """Slices of 32 and 64 keys (groups of more than 4 heads), of 64 and 128 (others), where their workgroups leave
+    units over, and the next coarser ones beyond."""
+    from paper_2603_15619_amd import moda_attn_decode
+    from paper_2603_15619_amd.binding import MODAShape, lib
+    import ctypes
+
+    one = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2400, device="cuda")
+    seq = synth.make_inputs(B, Hq, Hk, T, d, 0, dtype="bf16", seed=2401, device="cuda")
+    kd, vd = (None if L == 0 else one[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))
+    size = lib().moda_attn_decode_workspace_bytes(ctypes.byref(MODAShape(B, Hq, Hk, T, d, L, L, 1, 0.0, 1)))
+    ws = torch.full((size // 4 + 1000,), float("nan"), device="cuda")
+    moda_attn_decode(one["Q"][:, :, 0].contiguous(), seq["Kseq"], seq["Vseq"], kd, vd, workspace=ws[:size // 4])
+    torch.cuda.synchronize()
+    assert int((~torch.isnan(ws)).sum().item()) == B * Hq * (slices + (L > 0)) * (d + 2)
+    check(B, Hq, Hk, T, d, L, 2402)
