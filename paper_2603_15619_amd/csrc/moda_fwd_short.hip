@@ -13,7 +13,7 @@
 // before the key tiles in every other workgroup and after them in the others, as a fifth partial
 // state that stays in registers meanwhile.  Several heads per tile: the slots of the tile's
 // positions are 32-key blocks on the matrix pipe (key kk belongs to position kk / L), dealt out to
-// the waves after the key tiles.
+// the waves after the key tiles, or in every other workgroup before them (alternate_blocks).
 //
 // Bound by a wave's chain copy -> products -> exponentials -> products on the key tiles and by HBM on
 // the depth slots.  B=1 H=8 T=2048, 4 slots: d=64 33 -> 17 us, d=128 43 -> 29 us;
@@ -145,7 +145,10 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
   const int n_keys = p.causal ? min(T, q0 + PW) : T;
   const int nt = (n_keys + 31) / 32;
   const int nd = L > 0 && GT > 1 ? PW * L : 0;  // depth slots of the tile's positions
-  const int n_tiles = nt + (nd + 31) / 32;
+  const int n_blocks = (nd + 31) / 32, n_tiles = nt + n_blocks;
+  // the order in which they are dealt out: every other workgroup its blocks of slots first, where that pays
+  const bool blocks_first = !ROWS && p.depth_mfma == 2 && ((blockIdx.x >> 3) & 1) != 0;
+  auto tile_of = [&](int n) { return !blocks_first || n >= n_tiles ? n : n < n_blocks ? nt + n : n - n_blocks; };
   const unsigned k_tile = (unsigned)(size_t)(lds_ptr)smem + wave * 2 * C::kTile, v_tile = k_tile + C::kTile;
   FragAddr<D> fa;
   fa.init(lane);
@@ -160,7 +163,8 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
   const int goff = jr * Tl::kRowBytes + ((pc ^ Tl::swz(jr)) << 4);
   // one K or V tile, global -> LDS; always kPieces operations (a tile past the last: none of its lanes
   // is in range, zeros arrive)
-  auto copy = [&](const i32x4& seq, const i32x4& depth, unsigned dst, int i) {
+  auto copy = [&](const i32x4& seq, const i32x4& depth, unsigned dst, int n) {
+    const int i = tile_of(n);
     if (i < nt) {
 #pragma unroll
       for (int q = 0; q < C::kPieces; ++q)
@@ -201,7 +205,8 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
     copy(k_buf, kd_buf, k_tile, wave);
     copy(v_buf, vd_buf, v_tile, wave);
   }
-  for (int i = wave; i < n_tiles; i += kShortWaves) {
+  for (int n = wave; n < n_tiles; n += kShortWaves) {
+    const int i = tile_of(n);
     wait_own_copies<C::kPieces>();  // this tile's K (its V was requested after it)
     const unsigned b_row = fa.row + k_tile, b_tr = fa.tr + v_tile, b_tr8 = fa.tr8 + v_tile;
     // two accumulation chains
@@ -214,7 +219,7 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
       s1 = mfma_bf16(FragAddr<D>::row_frag((unsigned)xor_here((int)b_row, (st + 1) << 5), 0, 0), qf[st + 1], s1);
     }
     wait_own_reads();  // the K tile has been read: it may be overwritten
-    copy(k_buf, kd_buf, k_tile, i + kShortWaves);
+    copy(k_buf, kd_buf, k_tile, n + kShortWaves);
 #pragma unroll
     for (int k = 0; k < 16; ++k) s[k] += s1[k];
     if (i >= nt) {  // (uniform) slot r of the block is attended by the columns of its position
@@ -263,7 +268,7 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
         o[db] = mfma_bf16(FragAddr<D>::tr_frag((unsigned)xor_here((int)b_tr, db << 6), (unsigned)xor_here((int)b_tr8, db << 6),
                                                hf, 0), pb[hf], o[db]);
     wait_own_reads();
-    copy(v_buf, vd_buf, v_tile, i + kShortWaves);
+    copy(v_buf, vd_buf, v_tile, n + kShortWaves);
   }
   if (rows_on_valu && !depth_first) depth_rows();
 
@@ -334,12 +339,23 @@ __global__ __launch_bounds__(kShortWaves * 64, D == 128 ? 2 : ROWS ? 3 : 4) void
 
 int fwd_short_tile_pairs() { return kShortCols; }
 
-hipError_t launch_fwd_short(const FwdParams& p, int d, hipStream_t stream) {
+// Blocks of slots that all workgroups take last come all at once, and HBM idles before.  Every other workgroup takes them
+// first where units hold several workgroups and the slots are a good part of the call (last / alternating, us, d = 64:
+// B=2 Hq=16 Hk=8 T=1000, 12 slots 18.7 / 17.5;  1024 tiles, G=2 T=511, 15 slots 18.2 / 16.1;  760 tiles, G=4 T=593, 64 slots 23.9 / 21.0;
+// 832, G=8 T=829, 64 slots 17.3 / 15.7;  but 720, G=8 T=1416, 4 slots 13.2 / 13.7;  528, G=4 T=2093, 4 slots 16.0 / 16.5;  744,
+// G=2 T=2969, 7 slots 23.7 / 23.9;  336, G=4 T=238, 64 slots 8.8 / 9.5).
+static bool alternate_blocks(const FwdParams& p, long long blocks) {
+  return blocks > 512 && p.depth_count >= 12 && p.T <= 50ll * p.depth_count * (p.Hq / p.Hk);
+}
+
+hipError_t launch_fwd_short(const FwdParams& params, int d, hipStream_t stream) {
+  FwdParams p = params;
   const int gt = p.heads_per_tile, pos = kShortCols / gt;
   if (gt < 1 || gt > kShortCols || (gt & (gt - 1)) != 0 || (p.Hq / p.Hk) % gt != 0) return hipErrorInvalidValue;
   if (p.n_qtiles != (p.T + pos - 1) / pos) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * (p.Hq / gt) * p.n_qtiles;
   if (!grid_ok(blocks)) return kGridTooLarge;
+  if (p.depth_mfma && alternate_blocks(p, blocks)) p.depth_mfma = 2;
   dim3 grid((unsigned)blocks), block(kShortWaves * 64);
   if (d != 64 && d != 128) return hipErrorInvalidValue;
   const bool rows = p.depth_count > 0 && gt == 1;

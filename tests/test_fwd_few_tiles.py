@@ -25,6 +25,27 @@ def test_fwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
     check_full(B, Hq, Hk, T, d, L, "bf16", 0, causal=causal, depth_alloc=La, inp=inp)
 
 
+@pytest.mark.parametrize("B,Hq,Hk,T,L,La,causal", [(2, 16, 8, 1000, 12, 13, True), (5, 8, 4, 485, 24, None, False), (3, 32, 8, 226, 31, 32, True),
+                                                   (1, 64, 8, 300, 12, None, True)])
+def test_blocks_of_slots_first_in_every_other_workgroup(B, Hq, Hk, T, L, La, causal):
+    """Two, four and eight heads per tile, more workgroups than two per unit; the slots of the first position score -inf
+    (its query is positive), so that a workgroup's first block holds columns that have seen no key yet."""
+    inp = synth.make_inputs(B, Hq, Hk, T, 64, L, dtype="bf16", seed=1550 + T + L, device="cuda", depth_alloc=La)
+    inp["Q"][:, :, 0] = inp["Q"][:, :, 0].abs() + 0.1
+    inp["Kdepth"][:, :, 0] = -float("inf")
+    inp["Vdepth"][:, :, 0] = 0.0  # (weight zero either way)
+    if La is not None:
+        inp["Kdepth"][:, :, :, L:] = float("nan")
+        inp["Vdepth"][:, :, :, L:] = float("nan")
+    O, LSE = run_gpu(inp, L, causal)
+    finite = dict(inp, Kdepth=inp["Kdepth"].clone())
+    finite["Kdepth"][:, :, 0] = torch.where(torch.isneginf(finite["Kdepth"][:, :, 0]), -1e4, finite["Kdepth"][:, :, 0])  # (scores below -1e3: weight zero)
+    args = [synth.to_f64(finite[k][:1]) for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")]
+    Oref, Lref = R.fwd(*(np.nan_to_num(a) for a in args), depth_count=L, causal=causal)
+    assert np.abs(synth.to_f64(O[:1]) - Oref).max() <= 2e-2 and np.abs(synth.to_f64(LSE[:1]) - Lref).max() <= 1e-3
+    assert torch.isfinite(O.float()).all() and torch.isfinite(LSE).all()
+
+
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,causal", [(1, 8, 8, 700, 64, 4, True), (1, 8, 2, 513, 128, 6, True),
                                                   (1, 16, 2, 300, 64, 0, False), (1, 2, 2, 4100, 128, 1, True),
                                                   (1, 12, 12, 4096, 64, 0, True), (1, 3, 3, 9000, 128, 2, True), (1, 12, 12, 2000, 64, 0, False),
