@@ -11,6 +11,7 @@
 //            more slice (the last one), read from the depth cache instead of the sequence cache;
 //   merge  : per (batch, query head): folds the slices into one softmax, normalises, stores
 //            O and LSE.
+// (A few hundred keys take one kernel: moda_decode_one_kernel.)
 // Two forms of the partial kernel.  One query head per key/value head: vector ALUs only (one
 // query row: no matrix shape to speak of); a lane owns 8 channels, d/8 lanes a key row,
 // 64 / (d/8) key rows per wave instruction.  Grouped queries: the G heads of a group are the
@@ -71,10 +72,56 @@ struct DecodeParams {
   float scale, scale_log2;
 };
 
+// Two registers of which one's lanes 32.. and the other's lanes ..31 change places, added; the same with odd and even
+// rows of 16 lanes.
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b), false, false);
+  return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b), false, false);
+  return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+}
+// Sum and maximum over a wave's groups of LPR lanes: every lane gets that of the lanes at its place.
+template <int LPR>
+__device__ __forceinline__ float groups_sum(float x) {
+  if (LPR == 8) x += dpp_mov<0x128>(x);  // row_ror:8
+  return pair_sum(swap_add16(x, x));
+}
+template <int LPR>
+__device__ __forceinline__ float groups_max(float x) {
+  if (LPR == 8) x = fmaxf(x, dpp_mov<0x128>(x));
+  const int i = __builtin_bit_cast(int, x);
+  auto r = __builtin_amdgcn_permlane16_swap(i, i, false, false);
+  return pair_max(fmaxf(__builtin_bit_cast(float, (int)r[0]), __builtin_bit_cast(float, (int)r[1])));
+}
+
+// A wave's state of one head, of its groups of LPR lanes (their references, normalisers, eight channels each), folded and
+// written to red[0 .. D) (channels), red[D] (reference), red[D + 1] (normaliser).  Every exchange halves the channels that a
+// lane holds.
+template <int D>
+__device__ __forceinline__ void fold_groups(float m, float l, const float (&o)[8], float c2, int lane, float* red) {
+  constexpr int LPR = D / 8;
+  const float mm = groups_max<LPR>(m);
+  const float f = m == -INFINITY ? 0.f : fast_exp2((m - mm) * c2);
+  const float ll = groups_sum<LPR>(l * f);
+  float half[4], quarter[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) half[k] = swap_add32(o[k] * f, o[k + 4] * f);  // lanes < 32: channel k, others k + 4
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {  // even rows of 16 lanes: channel k, odd ones k + 2 of those
+    quarter[k] = swap_add16(half[k], half[k + 2]);
+    if (LPR == 8) quarter[k] += dpp_mov<0x128>(quarter[k]);
+  }
+  if ((lane & 15) < LPR)
+    *(f32x2*)&red[lane % LPR * 8 + (lane >> 5) * 4 + ((lane >> 4) & 1) * 2] = (f32x2){quarter[0], quarter[1]};
+  if (lane == 0) *(f32x2*)&red[D] = (f32x2){mm, ll};
+}
+
 template <int D, int GT>
 __global__ __launch_bounds__(kDecWaves * 64) void moda_decode_partial_kernel(DecodeParams p) {
   constexpr int LPR = D / 8, RPS = 64 / LPR, RB = D * 2;
-  __shared__ float red[kDecWaves][RPS][GT][D + 2];
+  __shared__ __attribute__((aligned(16))) float red[kDecWaves][GT][D + 2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rg = lane / LPR, l16 = lane % LPR;
   const int G = p.Hq / p.Hk;
@@ -168,38 +215,141 @@ __global__ __launch_bounds__(kDecWaves * 64) void moda_decode_partial_kernel(Dec
     }
   }
 
-  // ---- combine the (kDecWaves * RPS) row groups of the workgroup, per head
+  // ---- the row groups of a wave, then the waves
 #pragma unroll
-  for (int j = 0; j < GT; ++j) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) red[wave][rg][j][l16 * 8 + k] = o[j][k];
-    if (l16 == 0) {
-      red[wave][rg][j][D] = m[j];
-      red[wave][rg][j][D + 1] = l[j];
-    }
-  }
+  for (int j = 0; j < GT; ++j) fold_groups<D>(m[j], l[j], o[j], c2, lane, red[wave][j]);
   __syncthreads();
   // thread t < GT * D: head j = t / D, channel t % D
   for (int t = tid; t < GT * D; t += kDecWaves * 64) {
     const int j = t / D, ch = t % D;
     if (h0 + j >= g * G + G) continue;
-    float mm = -INFINITY;
-    for (int w = 0; w < kDecWaves; ++w)
-      for (int r = 0; r < RPS; ++r) mm = fmaxf(mm, red[w][r][j][D]);
-    float ll = 0.f, oo = 0.f;
-    for (int w = 0; w < kDecWaves; ++w)
-      for (int r = 0; r < RPS; ++r) {
-        const float mi = red[w][r][j][D];
-        const float f = mi == -INFINITY ? 0.f : fast_exp2((mi - mm) * c2);
-        ll += f * red[w][r][j][D + 1];
-        oo += f * red[w][r][j][ch];
-      }
+    float mm = -INFINITY, ll = 0.f, oo = 0.f;
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) mm = fmaxf(mm, red[w][j][D]);
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) {
+      const float mi = red[w][j][D];
+      const float f = mi == -INFINITY ? 0.f : fast_exp2((mi - mm) * c2);
+      ll += f * red[w][j][D + 1];
+      oo += f * red[w][j][ch];
+    }
     float* dst = p.ws + (((size_t)b * p.Hq + h0 + j) * p.n_slices + split) * (D + 2);
     dst[ch] = oo;
     if (ch == 0) {
       dst[D] = mm;
       dst[D + 1] = ll;
     }
+  }
+}
+
+// ---------------------------------------------------------------- short contexts: one kernel
+// With a few hundred rows (keys, then slots) per key/value head the second kernel takes as long as the first.  Here a
+// workgroup of eight waves walks all rows of its (batch, key/value head, chunk of heads) as above and normalises.
+constexpr int kDecOneWaves = 8;
+
+template <int D, int GT>
+__global__ __launch_bounds__(kDecOneWaves * 64, 2) void moda_decode_one_kernel(DecodeParams p) {
+  constexpr int LPR = D / 8, RPS = 64 / LPR, RB = D * 2;
+  __shared__ __attribute__((aligned(16))) float red[kDecOneWaves][GT][D + 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rg = lane / LPR, l16 = lane % LPR;
+  const int G = p.Hq / p.Hk;
+  const int n_gc = (G + GT - 1) / GT;
+  const int gc = blockIdx.x % n_gc, bg = blockIdx.x / n_gc;
+  const int b = bg / p.Hk, g = bg - b * p.Hk;
+  const int h0 = g * G + gc * GT;
+  const float c2 = p.scale_log2;
+  const int T = p.T, n = T + p.depth_count;
+
+  // row r: key r of the sequence cache, or slot r - T
+  const size_t seq = (size_t)bg * p.T_alloc * RB + l16 * 16, dep = (size_t)bg * p.depth_alloc * RB + l16 * 16;
+  auto load = [&](const void* cache, const void* slots, int r) {
+    r = min(r, n - 1);
+    const char* at = r < T ? (const char*)cache + seq + (size_t)r * RB : (const char*)slots + dep + (size_t)(r - T) * RB;
+    return __builtin_nontemporal_load((const u32x4*)at);
+  };
+  constexpr int STEP = kDecOneWaves * RPS, kU = 4;
+  const int row0 = wave * RPS + rg;
+  u32x4 kn[kU], vn[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    kn[u] = load(p.Kseq, p.Kdepth, row0 + u * STEP);
+    vn[u] = load(p.Vseq, p.Vdepth, row0 + u * STEP);
+  }
+  u32x4 q[GT];
+  float m[GT], l[GT], o[GT][8];
+#pragma unroll
+  for (int j = 0; j < GT; ++j) {
+    const int h = min(h0 + j, g * G + G - 1);  // heads past the group repeat the last one; never stored
+    q[j] = *(const u32x4*)((const char*)p.Q + ((size_t)b * p.Hq + h) * RB + l16 * 16);
+    m[j] = -INFINITY;
+    l[j] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) o[j][k] = 0.f;
+  }
+  auto factor = [&](float x, float ref) { return x == -INFINITY ? 0.f : fast_exp2((x - ref) * c2); };
+  for (int base = 0; base < n; base += kU * STEP) {  // (uniform)
+    u32x4 kv[kU], vv[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      kv[u] = kn[u];
+      vv[u] = vn[u];
+    }
+    if (base + kU * STEP < n) {  // (uniform)
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        kn[u] = load(p.Kseq, p.Kdepth, row0 + base + (kU + u) * STEP);
+        vn[u] = load(p.Vseq, p.Vdepth, row0 + base + (kU + u) * STEP);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < GT; ++j) {
+      float sc[kU], mn = m[j];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        float a = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a = dot2_bf16(q[j][k], kv[u][k], a);
+        a = group_sum<LPR>(a);
+        sc[u] = row0 + base + u * STEP < n ? a : -INFINITY;
+        mn = fmaxf(mn, sc[u]);
+      }
+      const float al = factor(m[j], mn);
+      m[j] = mn;
+      l[j] *= al;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) o[j][k] *= al;
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const float pw = factor(sc[u], mn);
+        l[j] += pw;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          o[j][2 * k] += pw * bf16_lo(vv[u][k]);
+          o[j][2 * k + 1] += pw * bf16_hi(vv[u][k]);
+        }
+      }
+    }
+  }
+  // ---- the row groups of a wave, then the waves
+#pragma unroll
+  for (int j = 0; j < GT; ++j) fold_groups<D>(m[j], l[j], o[j], c2, lane, red[wave][j]);
+  __syncthreads();
+  for (int t = tid; t < GT * D; t += kDecOneWaves * 64) {
+    const int j = t / D, ch = t % D;
+    if (h0 + j >= g * G + G) continue;
+    float mm = -INFINITY, ll = 0.f, oo = 0.f;
+#pragma unroll
+    for (int w = 0; w < kDecOneWaves; ++w) mm = fmaxf(mm, red[w][j][D]);
+#pragma unroll
+    for (int w = 0; w < kDecOneWaves; ++w) {
+      const float f = factor(red[w][j][D], mm);
+      ll += f * red[w][j][D + 1];
+      oo += f * red[w][j][ch];
+    }
+    const size_t row = (size_t)b * p.Hq + h0 + j;
+    ((__bf16*)p.O)[row * D + ch] = (__bf16)(oo / ll);
+    if (ch == 0) p.LSE[row] = mm * p.scale + __logf(ll);
   }
 }
 
@@ -619,10 +769,35 @@ size_t decode_least_bytes(int B, int Hq, int Hk, int T, int d) {
   return (size_t)(cut(r, T, coarse_slices(T)).n_split + 1) * r.slice_bytes;
 }
 
+// Calls that take one kernel: few batches of rows (256 at d = 64, 128 at d = 128), more of them where the workgroups fill the
+// chip anyway; groups of more than 4 heads, in chunks of 4, one batch and no more workgroups than units.  Two kernels / one,
+// us, whole call, (batch, key/value head)s, rows:
+//   1 head   d=64 48, 35 5.4 / 3.7;   180, 150 5.9 / 3.6;   24, 308 5.4 / 4.4;   12, 745 5.5 / 5.1;   48, 1217 6.2 / 7.4;   720, 1015 34.6 / 28.4
+//            d=128 16, 93 5.4 / 3.5;   80, 151 6.1 / 4.5;   368, 293 13.5 / 11.6;   16, 510 6.0 / 6.0;   8, 843 5.9 / 8.7
+//   2 heads  d=64 40, 220 5.8 / 4.4;   8, 341 5.8 / 5.4;   64, 593 6.5 / 6.8;   d=128 816, 79 17.0 / 10.6;   50, 351 6.5 / 6.8
+//   4 heads  d=64 128, 80 6.5 / 5.6;   32, 527 6.7 / 9.7;   d=128 148, 121 10.3 / 5.7;   8, 129 6.9 / 7.4
+//   8 heads  d=64 4, 236 6.9 / 5.4;   164, 210 8.1 / 10.0;   d=128 112, 118 9.2 / 6.0;   32 heads: 29, 108 9.0 / 5.6, 56, 34 8.5 / 9.6
+static bool decode_in_one(const DecodeParams& p, int d, int gt) {
+  const int batch = kDecOneWaves * (64 / (d / 8)) * 4, G = p.Hq / p.Hk;
+  const long long batches = ((long long)p.T + p.depth_count + batch - 1) / batch, blocks = (long long)p.B * p.Hk * ((G + gt - 1) / gt);
+  if (G > 4) return batches <= 1 && blocks <= 256;
+  if (gt == 4) return batches <= 1;
+  return batches <= (blocks >= 256 ? 4 : gt == 1 && d == 64 ? 3 : 2);
+}
+
+template <int D>
+static hipError_t launch_in_one(const DecodeParams& p, int gt, hipStream_t stream) {
+  const long long blocks = (long long)p.B * p.Hk * ((p.Hq / p.Hk + gt - 1) / gt);
+  if (!grid_ok(blocks)) return kGridTooLarge;
+  return launch_kernel(gt == 4 ? moda_decode_one_kernel<D, 4> : gt == 2 ? moda_decode_one_kernel<D, 2> : moda_decode_one_kernel<D, 1>,
+                       dim3((unsigned)blocks), dim3(kDecOneWaves * 64), stream, p);
+}
+
 template <int D>
 static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream) {
   const int G = p.Hq / p.Hk;
   if (!grid_ok((long long)p.B * p.Hq)) return kGridTooLarge;
+  if (decode_in_one(p, D, decode_heads_per_chunk(G))) return launch_in_one<D>(p, decode_heads_per_chunk(G), stream);
   hipError_t e;
   if (mfma) {
     const long long blocks = (long long)p.B * p.Hk * ((G + 31) / 32) * ((p.n_slices + kDecMWaves - 1) / kDecMWaves);

@@ -202,9 +202,9 @@ def test_finer_slices_only_where_they_make_no_more_rounds(B, Hq, Hk, T, d, L, sl
     assert written == B * Hq * (slices + (L > 0)) * (d + 2)
 
 
-@pytest.mark.parametrize("B,Hq,Hk,T,d,L,slices", [(1, 8, 1, 512, 64, 0, 16), (1, 8, 1, 513, 64, 3, 9), (1, 16, 2, 33, 128, 1, 2), (6, 64, 8, 512, 128, 0, 16),
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,slices", [(1, 8, 1, 512, 64, 0, 16), (1, 8, 1, 513, 64, 3, 9), (1, 16, 2, 129, 128, 1, 5), (6, 64, 8, 512, 128, 0, 16),
                                                   (7, 64, 8, 500, 128, 2, 8), (1, 8, 1, 6144, 64, 0, 96), (1, 8, 1, 6145, 64, 0, 49),
-                                                  (1, 4, 4, 512, 128, 1, 8), (1, 4, 4, 513, 128, 1, 5), (28, 8, 8, 64, 128, 0, 1), (1, 4, 4, 1793, 128, 0, 29),
+                                                  (1, 4, 4, 512, 128, 1, 8), (1, 4, 4, 513, 128, 1, 5), (9, 3, 3, 300, 128, 0, 5), (1, 4, 4, 1793, 128, 0, 29),
                                                   (1, 4, 4, 2048, 128, 5, 32), (1, 4, 4, 2049, 128, 5, 17), (1, 4, 4, 1792, 64, 2, 7), (1, 4, 2, 1793, 64, 2, 15),
                                                   (1, 2, 2, 4096, 64, 1, 32), (1, 2, 2, 4097, 64, 1, 17), (3, 16, 4, 3000, 128, 4, 12)])
 def test_finest_slices_of_calls_with_few_workgroups(B, Hq, Hk, T, d, L, slices):
@@ -223,3 +223,33 @@ def test_finest_slices_of_calls_with_few_workgroups(B, Hq, Hk, T, d, L, slices):
     torch.cuda.synchronize()
     assert int((~torch.isnan(ws)).sum().item()) == B * Hq * (slices + (L > 0)) * (d + 2)
     check(B, Hq, Hk, T, d, L, 2402)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La", [(1, 1, 1, 1, 64, 0, 0), (1, 2, 2, 1, 128, 3, 4), (2, 4, 4, 255, 64, 1, None), (3, 4, 4, 257, 64, 0, 2), (1, 3, 3, 700, 64, 67, 70),
+                                              (5, 4, 4, 127, 128, 1, None), (2, 2, 2, 129, 128, 0, None), (3, 2, 2, 200, 128, 56, 60), (40, 16, 8, 100, 64, 7, None), (2, 4, 2, 480, 64, 31, 33),
+                                              (3, 4, 2, 250, 128, 5, None), (4, 8, 2, 250, 64, 6, 7), (2, 6, 2, 96, 128, 32, None), (7, 4, 1, 31, 128, 0, None), (33, 16, 16, 400, 128, 15, 16),
+                                              (3, 8, 1, 200, 64, 56, None), (2, 10, 2, 100, 128, 15, 17), (1, 64, 1, 128, 128, 0, None), (1, 13, 1, 17, 64, 0, 1)])
+def test_short_contexts_take_one_kernel(B, Hq, Hk, T, d, L, La):
+    """Keys and slots of few batches: nothing is written to the workspace; rows past T in the cache and slots past L hold NaN."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    La = L if La is None else La
+    one = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2500 + T, device="cuda", depth_alloc=La)
+    seq = synth.make_inputs(B, Hq, Hk, T + 3, d, 0, dtype="bf16", seed=2501 + T, device="cuda")
+    K, V = seq["Kseq"], seq["Vseq"]
+    K[:, :, T:] = float("nan")
+    V[:, :, T:] = float("nan")
+    kd, vd = (None if La == 0 else one[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))
+    if La > L:
+        kd[:, :, L:] = float("nan")
+        vd[:, :, L:] = float("nan")
+    Q = one["Q"][:, :, 0].contiguous()
+    ws = torch.full((1 << 22,), float("nan"), device="cuda")
+    O, LSE = moda_attn_decode(Q, K, V, kd, vd, T=T, depth_count=L, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(ws).all()
+    f = lambda t: synth.to_f64(t)  # noqa: E731
+    Oref, Lref = R.fwd_rows(f(Q)[:, :, None], f(K[:, :, :T].contiguous()), f(V[:, :, :T].contiguous()),
+                            None if L == 0 else f(kd[:, :, :L].contiguous())[:, :, None], None if L == 0 else f(vd[:, :, :L].contiguous())[:, :, None],
+                            np.array([T - 1], dtype=np.int32), depth_count=L)
+    assert np.abs(f(O) - Oref[:, :, 0]).max() <= 2e-2 and np.abs(f(LSE) - Lref[:, :, 0]).max() <= 1e-3
