@@ -1142,23 +1142,39 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
     q_next = (qt0 + pos) * 32;
     pos += NW;
   };
+  auto issue_rows = [&](unsigned dst) {
+    copy4(l_buf, lane * 4, q_next * 4, dst + 2 * C::kTile);
+    copy4(d_buf, lane * 4, q_next * 4, dst + 2 * C::kTile + 256);
+  };
   auto issue_tile = [&](const i32x4& buf, unsigned dst) {
 #pragma unroll
     for (int q = 0; q < C::kPieces; ++q)
       tile_copy16(buf, xor_here(goff, Ld::piece_xor(q)), q_next / 32 * C::kTile + q * 1024, dst + q * 1024);
   };
-  auto issue_q = [&](int stage) {
-    const unsigned dst = ring + stage * C::kStage;
-    issue_tile(q_buf, dst);
-    copy4(l_buf, lane * 4, q_next * 4, dst + 2 * C::kTile);
-    copy4(d_buf, lane * 4, q_next * 4, dst + 2 * C::kTile + 256);
+  auto issue_q = [&]() {  // (one stage)
+    issue_tile(q_buf, ring);
+    issue_rows(ring);
   };
-  auto issue_do = [&](int stage) { issue_tile(do_buf, ring + stage * C::kStage + C::kTile); };
+  auto issue_do = [&]() { issue_tile(do_buf, ring + C::kTile); };
+  auto issue = [&](int stage) {
+    if constexpr (ST == 1) {
+      issue_q();
+      issue_do();
+    } else {  // (an offset serves both tiles)
+      const unsigned dst = ring + stage * C::kStage;
+#pragma unroll
+      for (int q = 0; q < C::kPieces; ++q) {
+        const int voff = xor_here(goff, Ld::piece_xor(q));
+        tile_copy16(q_buf, voff, q_next / 32 * C::kTile + q * 1024, dst + q * 1024);
+        tile_copy16(do_buf, voff, q_next / 32 * C::kTile + q * 1024, dst + C::kTile + q * 1024);
+      }
+      issue_rows(dst);
+    }
+  };
   if (wave < n_items) {
     at_head();
     advance();
-    issue_q(0);
-    issue_do(0);
+    issue(0);
   }
   int stage = 0;
   for (int item = wave; item < n_items; item += NW, stage ^= ST - 1) {
@@ -1171,8 +1187,7 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
       wait_own_reads();
       if (more) {
         advance();
-        issue_q(stage ^ 1);
-        issue_do(stage ^ 1);
+        issue(stage ^ 1);
       }
     } else {
       wait_own_copies<C::kPieces>();  // (dO may still be on its way)
@@ -1232,34 +1247,31 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
       pb[hf] = pack8(pv);
       dsb[hf] = pack8(dsv);
     };
-    auto product = [&](int hf, int db, bool of_v) {
+    auto product = [&](int hf, int db, bool of_v, bool of_k) {
       const unsigned x0 = (unsigned)xor_here((int)b_tr, db << 6), x8 = (unsigned)xor_here((int)b_tr8, db << 6);
       if (of_v) dv[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, C::kTile), pb[hf], dv[db]);
-      else dk[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, 0), dsb[hf], dk[db]);
+      if (of_k) dk[db] = mfma_bf16(FragAddr<D>::tr_frag(x0, x8, hf, 0), dsb[hf], dk[db]);
     };
     if constexpr (ST == 1) {  // Q's place is free, and requested anew, before dO's
       weights(0);
       weights(1);
 #pragma unroll
-      for (int n = 0; n < 2 * Tl::kDBlocks; ++n) product(n / Tl::kDBlocks, n % Tl::kDBlocks, false);
+      for (int n = 0; n < 2 * Tl::kDBlocks; ++n) product(n / Tl::kDBlocks, n % Tl::kDBlocks, false, true);
       wait_own_reads();
       if (more) {
         advance();
-        issue_q(0);
+        issue_q();
       }
 #pragma unroll
-      for (int n = 0; n < 2 * Tl::kDBlocks; ++n) product(n / Tl::kDBlocks, n % Tl::kDBlocks, true);
+      for (int n = 0; n < 2 * Tl::kDBlocks; ++n) product(n / Tl::kDBlocks, n % Tl::kDBlocks, true, false);
       wait_own_reads();
-      if (more) issue_do(0);
+      if (more) issue_do();
     } else {
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         weights(hf);
 #pragma unroll
-        for (int db = 0; db < Tl::kDBlocks; ++db) {
-          product(hf, db, true);
-          product(hf, db, false);
-        }
+        for (int db = 0; db < Tl::kDBlocks; ++db) product(hf, db, true, true);
       }
     }
   }
