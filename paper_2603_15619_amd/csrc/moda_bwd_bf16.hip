@@ -2165,11 +2165,17 @@ struct GradsPlan {
 // longest workgroups of all heads start first and neighbouring units do not all get one kind of tile (with one head of
 // two key and two query tiles at a time every other unit had all the depth slots: B=72 H=1 T=37 d=128, 64 slots 101 -> 65 us);
 // beyond, as many as have K and V in 512 KB of the L2, which their tiles then find there (256 KB / 512 KB / 1 MB / 2 MB / 4 MB, 70
-// shapes: 0.894 / 0.890 / 0.892 / 0.894 / 0.899 of the time of two launches).
-static int grads_head_group(const BwdParams& p, int d, long long grid) {
+// shapes: 0.894 / 0.890 / 0.892 / 0.894 / 0.899 of the time of two launches).  But all of them also where up to 1024 key tiles are
+// most of the work: head by head the longest key tiles of a die's last heads start last, and the call ends with them alone.  One
+// head at a time / all, us: d=64 B=2 Hq=16 Hk=8 T=3253, no slots 196 / 167; B=4 Hq=48 Hk=16 T=316, no slots, not causal 38.2 / 31.1;
+// d=128 B=3 Hq=16 Hk=8 T=3816, 1 slot 702 / 587.  Slots as long as the key tiles keep the order head by head, which reads them
+// between the key tiles: B=4 H=16 T=3979 d=64, 15 slots 684 / 708, B=1 H=16 T=4389 213 / 240.  90 shapes, up to 512 / 1024 / 2048 /
+// any number of key tiles: 0.988 / 0.978 / 0.979 / 0.980 of the time head by head; with the line at 200 / 400 / 800 / 2000 positions
+// of the group to a slot 0.981 / 0.978 / 0.981 / 0.985, and 0.981 without it.
+static int grads_head_group(const BwdParams& p, int d, long long grid, long long key_tiles) {
   if (p.B * p.Hk % 8 != 0) return 0;
   const long long per_die = (long long)p.B * p.Hk / 8;
-  if (grid <= 1024) return (int)per_die;
+  if (grid <= 1024 || (key_tiles <= 1024 && (long long)p.T * (p.Hq / p.Hk) > 400ll * p.depth_count)) return (int)per_die;
   return (int)std::max(1ll, std::min(per_die, (512ll << 10) / (4ll * p.T * d)));
 }
 // The kind of tiles whose estimated time is shortest.  As for dkdv_waves: the chains of the longest key tile and of the longest
@@ -2288,7 +2294,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   }
   if (g_grads > 0) {
     const int heads = plan.heads(p);
-    p.head_group = grads_head_group(p, D, g_grads);
+    p.head_group = grads_head_group(p, D, g_grads, (long long)p.B * p.Hk * plan.key_tiles(p));
     const int spread = spread_key_tiles(p, g_grads);
     auto launch = [&](auto gt) {
       constexpr int GT = decltype(gt)::value;

@@ -66,6 +66,12 @@ def test_many_tiles(B, Hq, Hk, T, d, L, La, causal):
     check(B, Hq, Hk, T, d, L, La, causal)
 
 
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(16, 16, 4, 500, 64, 0, None, True), (16, 8, 4, 900, 128, 1, 2, False), (24, 4, 1, 1500, 64, 3, None, True)])
+def test_heads_of_a_die_together(B, Hq, Hk, T, d, L, La, causal):
+    """More than 1024 workgroups with up to 1024 key tiles that are most of the work: a die walks all its heads at once."""
+    check(B, Hq, Hk, T, d, L, La, causal)
+
+
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(16, 4, 1, 500, 128, 5, 6, True), (16, 4, 1, 97, 128, 1, None, False), (4, 2, 1, 1100, 128, 1, None, False),
                                                      (24, 2, 1, 300, 128, 1, 2, False), (16, 4, 1, 97, 64, 3, None, False), (8, 4, 1, 1000, 64, 5, None, True),
                                                      (40, 1, 1, 257, 128, 0, None, True), (9, 3, 1, 300, 128, 0, None, False), (24, 8, 1, 129, 128, 0, None, True),
