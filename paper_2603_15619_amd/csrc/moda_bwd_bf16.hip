@@ -1130,7 +1130,7 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
     l_buf = make_tile_buffer(p.lse2 + row, (unsigned)T * 4);
     d_buf = make_tile_buffer(p.minus_delta + row, (unsigned)T * 4);
   };
-  int q_next = 0;  // first query of the next item
+  int next = 0;  // query tile of the next item
   auto advance = [&]() {
     if (pos >= span) {
       do {
@@ -1139,17 +1139,17 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
       } while (pos >= span);
       at_head();
     }
-    q_next = (qt0 + pos) * 32;
+    next = qt0 + pos;
     pos += NW;
   };
   auto issue_rows = [&](unsigned dst) {
-    copy4(l_buf, lane * 4, q_next * 4, dst + 2 * C::kTile);
-    copy4(d_buf, lane * 4, q_next * 4, dst + 2 * C::kTile + 256);
+    copy4(l_buf, lane * 4, next * 128, dst + 2 * C::kTile);
+    copy4(d_buf, lane * 4, next * 128, dst + 2 * C::kTile + 256);
   };
   auto issue_tile = [&](const i32x4& buf, unsigned dst) {
 #pragma unroll
     for (int q = 0; q < C::kPieces; ++q)
-      tile_copy16(buf, xor_here(goff, Ld::piece_xor(q)), q_next / 32 * C::kTile + q * 1024, dst + q * 1024);
+      tile_copy16(buf, xor_here(goff, Ld::piece_xor(q)), next * C::kTile + q * 1024, dst + q * 1024);
   };
   auto issue_q = [&]() {  // (one stage)
     issue_tile(q_buf, ring);
@@ -1165,8 +1165,8 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
 #pragma unroll
       for (int q = 0; q < C::kPieces; ++q) {
         const int voff = xor_here(goff, Ld::piece_xor(q));
-        tile_copy16(q_buf, voff, q_next / 32 * C::kTile + q * 1024, dst + q * 1024);
-        tile_copy16(do_buf, voff, q_next / 32 * C::kTile + q * 1024, dst + C::kTile + q * 1024);
+        tile_copy16(q_buf, voff, next * C::kTile + q * 1024, dst + q * 1024);
+        tile_copy16(do_buf, voff, next * C::kTile + q * 1024, dst + C::kTile + q * 1024);
       }
       issue_rows(dst);
     }
@@ -1181,7 +1181,7 @@ __device__ __forceinline__ void dkdv_short_tile(const BwdParams& p, unsigned cha
     // (the wave's own copies into its own LDS: its wait publishes them, and the stage that the next
     // copies overwrite may be refilled as soon as the wave's reads of it have returned)
     const bool more = item + NW < n_items;
-    const int q0 = q_next;
+    const int q0 = next * 32;
     if constexpr (ST == 2) {
       wait_own_copies<0>();
       wait_own_reads();
@@ -1409,6 +1409,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
   const int nt = (n_keys + 63) / 64;
   const int wave_last = p.causal ? min(nt - 1, (qw0 + 31) / 64) : nt - 1;
   const int lim = p.causal ? min(qi, T - 1) : T - 1;  // last visible key of this lane's query
+  const int n_visible = p.causal ? min(T, qw0 + 1) : T;  // keys that exist and that every query of the wave sees
   const unsigned smem_addr = (unsigned)(size_t)(lds_ptr)smem;
   TileLoader<D, NW> ld;
   ld.init(wave, lane);
@@ -1430,8 +1431,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
     f32x16 s[2], dp[2];  // S^T, dP^T - delta: [key block]; a lane holds 16 keys of its query
     u32x4 ds[2][2];      // dS^T packed to bf16: [key block][16-key half]
     const int k0 = kt * 64;
-    // every key of the tile exists and is visible to every query of the wave
-    const bool all_visible = k0 + 64 <= T && (!p.causal || k0 + 63 <= qw0);
+    const bool all_visible = k0 + 64 <= n_visible;
     auto mask = [&](int kb) {
       if (!all_visible) {  // (uniform) diagonal tile, keys past the end: invisible pairs get weight zero
 #pragma unroll
