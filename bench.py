@@ -273,7 +273,7 @@ def run_backward(args, B, Hq, Hk, T, d, L, dtype):
         "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_step, 4), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": dtype, "data": "synthetic",
-        "config": {"workload": "%s: B=%d H=%d T=%d d=%d depth_count=%d causal bwd (3 kernels per call)" %
+        "config": {"workload": "%s: B=%d H=%d T=%d d=%d depth_count=%d causal bwd (2 kernels per call)" %
                                (args.workload, B, Hq, T, d, L)},
         "roofline": {"bound": "hbm", "achieved": round(alg_bytes / (ms_kernel * 1e-3) / 1e9, 1), "peak": 8000.0,
                      "unit": "GB/s", "frac": round(alg_bytes / (ms_kernel * 1e-3) / 1e9 / 8000.0, 4),
