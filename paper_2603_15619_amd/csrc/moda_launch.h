@@ -36,8 +36,8 @@ hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream);
 bool fwd_f32_by_rows(const FwdParams& p);
 hipError_t launch_fwd_f32_rows(const FwdParams& p, int d, hipStream_t stream);
 
-// Backward (bf16, Hq / Hk <= bwd_bf16_max_group()): delta, [depth slots of grouped queries,]
-// dK/dV and dQ(/depth) kernels on `stream`.
+// Backward (bf16, Hq / Hk <= bwd_bf16_max_group()): delta, then one kernel for dK, dV, dQ and the depth slots, or
+// [depth slots of grouped queries,] dK/dV and dQ kernels, on `stream`.
 int bwd_bf16_max_group();
 int bwd_bf16_kernels(const BwdParams& p, int d);  // kernels one call enqueues
 size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d);
