@@ -82,7 +82,8 @@ typedef struct {
 /*
  * Size limits of this build (MODA_ERR_UNSUPPORTED beyond them): d is 64 or 128; one
  * (batch, head) slab of a SEQUENCE tensor, T * d elements, stays below 4 GiB (32-bit byte
- * offsets inside a slab); depth_alloc <= 8192.  The depth tensors themselves are addressed
+ * offsets inside a slab); depth_alloc <= 8192; no kernel of the call has 2^32 threads or more
+ * (tens of millions of heads).  The depth tensors themselves are addressed
  * with 64-bit tile bases and may be of any size.
  */
 

@@ -2143,11 +2143,8 @@ static bool own_depth_kernel(const BwdParams& p, int d) {
 }
 // Calls that take one kernel for dK, dV and dQ (moda_bwd_grads_kernel).  With depth slots the heads of a group have to fill the
 // waves of a workgroup evenly, and up to 4 of them their gradients on the vector ALUs.  Up to 16 positions the launches
-// stay apart, as moda_kernels_per_call has them (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).
-static bool one_launch(const BwdParams& p) {
-  const int G = p.Hq / p.Hk;
-  return p.T > 16 && (p.depth_alloc == 0 || G == 1 || G == 2 || G == 4);
-}
+// stay apart, as moda_kernels_per_call has them (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).  So they do where the
+// workgroups of both kinds, at 17 positions 2^24 of four waves, are too many for one grid.
 struct GradsPlan {
   bool few_keys, few_queries;
   int waves;
@@ -2159,6 +2156,9 @@ struct GradsPlan {
   long long query_tiles(const BwdParams& p) const {
     const int n = few_queries ? 32 : waves * 32 / heads(p);
     return ((long long)p.T + n - 1) / n;
+  }
+  long long workgroups(const BwdParams& p) const {
+    return (long long)p.B * p.Hk * (key_tiles(p) + query_tiles(p) * (p.Hq / p.Hk / heads(p)));
   }
 };
 // Heads that a die walks together there (see head_walk_id): up to two rounds of workgroups all of them, so that the
@@ -2249,7 +2249,17 @@ static GradsPlan grads_plan(const BwdParams& p, int d) {
   }
   return best;
 }
-int bwd_bf16_kernels(const BwdParams& p, int d) { return one_launch(p) ? 2 : 3 + (own_depth_kernel(p, d) ? 1 : 0); }
+// Whether a call takes one launch, and the plan of it.
+static bool one_launch(const BwdParams& p, int d, GradsPlan& plan) {
+  const int G = p.Hq / p.Hk;
+  if (p.T <= 16 || (p.depth_alloc > 0 && G != 1 && G != 2 && G != 4)) return false;
+  plan = grads_plan(p, d);
+  return grid_ok(plan.workgroups(p), plan.waves * 64);
+}
+int bwd_bf16_kernels(const BwdParams& p, int d) {
+  GradsPlan plan;
+  return one_launch(p, d, plan) ? 2 : 3 + (own_depth_kernel(p, d) ? 1 : 0);
+}
 
 template <int D>
 static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
@@ -2257,42 +2267,38 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   const int G = p.Hq / p.Hk;
   const long long g_delta = (rows * (D / 8) + 255) / 256;
   const long long n_kt = (p.T + 127) / 128;
-  const long long g_dkdv = (long long)p.B * p.Hk * n_kt;
-  constexpr int kDqWaves = 4;
-  const long long g_dq = (long long)p.B * p.Hq * ((p.T + kDqWaves * 32 - 1) / (kDqWaves * 32));
   const long long kv_rows = (long long)p.B * p.Hk * p.T;
-  const long long g_depth = (kv_rows * (D / 8) + 255) / 256;  // 5 <= G <= 8: 256 / (d/8) positions per workgroup
-  const long long g_wide = kv_rows;                            // G > 8: one workgroup (of one wave) per position
+  const long long g_depth = G <= 8 ? (kv_rows * (D / 8) + 255) / 256 : kv_rows;
   // every grid is checked before the first kernel is enqueued
-  if (!grid_ok(g_delta) || !grid_ok(g_dkdv) || !grid_ok(g_dq) || !grid_ok(g_depth) || !grid_ok(g_wide))
-    return kGridTooLarge;
+  GradsPlan plan{};
+  const bool one = one_launch(p, D, plan), own_depth = own_depth_kernel(p, D), short_dq = few_queries(p, D);
+  const int few = G <= 2 ? 4 : dkdv_waves(p, D);  // (see moda_bwd_dkdv_short_kernel)
+  const long long g_grads = one ? plan.workgroups(p) : 0;
+  const long long n32 = ((long long)p.T + 31) / 32;
+  const long long g_dkdv = (long long)p.B * p.Hk * (few ? n32 : n_kt), g_dq = (long long)p.B * p.Hq * (short_dq ? n32 : n_kt);
+  if (!grid_ok(g_delta, 256) || (!one && (!grid_ok(g_dkdv, few ? few * 64 : 256) || !grid_ok(g_dq, 256))) ||
+      (own_depth && !grid_ok(g_depth, G <= 8 ? 256 : 64)))
+    return kGridTooLarge;  // (own_depth: up to 8 heads 256 / (d/8) positions to a workgroup, above one, of one wave)
   if (G > bwd_bf16_max_group()) return hipErrorInvalidValue;
   // the group kernel gathers the G heads' rows of a position with 32-bit offsets from the first head
   if (G > 8 && p.depth_alloc > 0 && (unsigned long long)G * p.T * (D * 2) >= 0xffffff00ull) return kGridTooLarge;
-  GradsPlan plan{};
-  long long g_grads = 0;
-  if (one_launch(p)) {
-    plan = grads_plan(p, D);
-    g_grads = (long long)p.B * p.Hk * (plan.key_tiles(p) + plan.query_tiles(p) * (G / plan.heads(p)));
-    if (!grid_ok(g_grads)) return kGridTooLarge;
-  }
   p.minus_delta = p.lse2 + rows;
   p.dq_depth = (float*)((char*)p.lse2 + row_scalar_bytes(p));
   hipError_t e = launch_kernel(moda_bwd_delta_kernel<D>, dim3((unsigned)g_delta), dim3(256), stream, p.dO, p.O, p.LSE,
                                p.lse2, p.minus_delta, rows);
   if (e != hipSuccess) return e;
-  if (own_depth_kernel(p, D)) {
+  if (own_depth) {
     if (G <= 8) {
       e = launch_kernel(moda_bwd_depth_gqa_kernel<D, 8>, dim3((unsigned)g_depth), dim3(256), stream, p);
     } else {
       // large groups: one wave per position, the group's products on the matrix pipe
-      const dim3 gw((unsigned)g_wide);
+      const dim3 gw((unsigned)g_depth);
       if (G <= 32) e = launch_kernel(moda_bwd_depth_group_kernel<D, 1>, gw, dim3(64), stream, p);
       else e = launch_kernel(moda_bwd_depth_group_kernel<D, 2>, gw, dim3(64), stream, p);
     }
     if (e != hipSuccess) return e;
   }
-  if (g_grads > 0) {
+  if (one) {
     const int heads = plan.heads(p);
     p.head_group = grads_head_group(p, D, g_grads, (long long)p.B * p.Hk * plan.key_tiles(p));
     const int spread = spread_key_tiles(p, g_grads);
@@ -2307,13 +2313,12 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     return G == 1 ? launch(std::integral_constant<int, 1>()) : G == 2 ? launch(std::integral_constant<int, 2>()) : launch(std::integral_constant<int, 4>());
   }
   {
-    const int few = G <= 2 ? 4 : dkdv_waves(p, D);  // (see moda_bwd_dkdv_short_kernel)
     constexpr int kEight = D == 64 ? 8 : 4;
-    const dim3 gk((unsigned)(few ? (long long)p.B * p.Hk * ((p.T + 31) / 32) : g_dkdv)), blk(few ? few * 64 : 256);
-    const bool grouped = G > 1 && p.depth_alloc > 0 && !own_depth_kernel(p, D);  // the group's depth-slot gradients run inside dK/dV
+    const dim3 gk((unsigned)g_dkdv), blk(few ? few * 64 : 256);
+    const bool grouped = G > 1 && p.depth_alloc > 0 && !own_depth;  // the group's depth-slot gradients run inside dK/dV
     auto pick = [few](auto other, auto four, auto eight) { return few == 0 ? other : few == 4 ? four : eight; };
     const auto kernel =
-        few == 4 && G == 1 && p.depth_alloc > 0 ? moda_bwd_dkdv_short_kernel<D, 1, 4>  // (up to 16 positions: always 32 keys, four waves)
+        few == 4 && G == 1 && p.depth_alloc > 0 ? moda_bwd_dkdv_short_kernel<D, 1, 4>  // (up to 16 positions, or very many heads: 32 keys, four waves)
         : !grouped ? pick(moda_bwd_dkdv_kernel<D, 0>, moda_bwd_dkdv_short_kernel<D, 0, 4>, moda_bwd_dkdv_short_kernel<D, 0, kEight>)
         : G == 2 ? moda_bwd_dkdv_short_kernel<D, 2, 4>                                 // (the same)
         : G <= 4 ? pick(moda_bwd_dkdv_kernel<D, 4>, moda_bwd_dkdv_short_kernel<D, 4, 4>, moda_bwd_dkdv_short_kernel<D, 4, kEight>)
@@ -2321,11 +2326,9 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;
-  if (few_queries(p, D))
-    return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)((long long)p.B * p.Hq * ((p.T + 31) / 32))), dim3(256),
-                         stream, p);
-  return launch_kernel(dq_per_unit(p, D, g_dq) == 3 ? moda_bwd_dq_kernel<D, kDqWaves, D == 64 ? 3 : 2> : moda_bwd_dq_kernel<D, kDqWaves, 2>,
-                       dim3((unsigned)g_dq), dim3(kDqWaves * 64), stream, p);
+  if (short_dq) return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)g_dq), dim3(256), stream, p);
+  return launch_kernel(dq_per_unit(p, D, g_dq) == 3 ? moda_bwd_dq_kernel<D, 4, D == 64 ? 3 : 2> : moda_bwd_dq_kernel<D, 4, 2>,
+                       dim3((unsigned)g_dq), dim3(256), stream, p);
 }
 
 hipError_t launch_bwd_bf16(const BwdParams& p, int d, hipStream_t stream) {

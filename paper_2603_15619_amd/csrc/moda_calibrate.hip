@@ -38,7 +38,7 @@ double calibrate_flops(int workgroups, int iters) {
 }
 
 hipError_t launch_calibrate_mfma(const void* operands, float* sink, int workgroups, int iters, hipStream_t stream) {
-  if (!grid_ok(workgroups) || iters < 0) return kGridTooLarge;
+  if (!grid_ok(workgroups, kCalibThreads) || iters < 0) return kGridTooLarge;
   return launch_kernel(moda_calibrate_mfma_kernel, dim3((unsigned)workgroups), dim3(kCalibThreads), stream,
                        (const bf16x8*)operands, sink, iters);
 }

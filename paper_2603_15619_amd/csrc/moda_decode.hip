@@ -780,6 +780,7 @@ size_t decode_least_bytes(int B, int Hq, int Hk, int T, int d) {
 static bool decode_in_one(const DecodeParams& p, int d, int gt) {
   const int batch = kDecOneWaves * (64 / (d / 8)) * 4, G = p.Hq / p.Hk;
   const long long batches = ((long long)p.T + p.depth_count + batch - 1) / batch, blocks = (long long)p.B * p.Hk * ((G + gt - 1) / gt);
+  if (!grid_ok(blocks, kDecOneWaves * 64)) return false;
   if (G > 4) return batches <= 1 && blocks <= 256;
   if (gt == 4) return batches <= 1;
   return batches <= (blocks >= 256 ? 4 : gt == 1 && d == 64 ? 3 : 2);
@@ -788,7 +789,6 @@ static bool decode_in_one(const DecodeParams& p, int d, int gt) {
 template <int D>
 static hipError_t launch_in_one(const DecodeParams& p, int gt, hipStream_t stream) {
   const long long blocks = (long long)p.B * p.Hk * ((p.Hq / p.Hk + gt - 1) / gt);
-  if (!grid_ok(blocks)) return kGridTooLarge;
   return launch_kernel(gt == 4 ? moda_decode_one_kernel<D, 4> : gt == 2 ? moda_decode_one_kernel<D, 2> : moda_decode_one_kernel<D, 1>,
                        dim3((unsigned)blocks), dim3(kDecOneWaves * 64), stream, p);
 }
@@ -796,24 +796,25 @@ static hipError_t launch_in_one(const DecodeParams& p, int gt, hipStream_t strea
 template <int D>
 static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream) {
   const int G = p.Hq / p.Hk;
-  if (!grid_ok((long long)p.B * p.Hq)) return kGridTooLarge;
   if (decode_in_one(p, D, decode_heads_per_chunk(G))) return launch_in_one<D>(p, decode_heads_per_chunk(G), stream);
+  const int merge_groups = p.n_slices <= kMergeOne ? 1 : 4;
+  if (!grid_ok((long long)p.B * p.Hq, merge_groups * D)) return kGridTooLarge;
   hipError_t e;
   if (mfma) {
     const long long blocks = (long long)p.B * p.Hk * ((G + 31) / 32) * ((p.n_slices + kDecMWaves - 1) / kDecMWaves);
-    if (!grid_ok(blocks)) return kGridTooLarge;
+    if (!grid_ok(blocks, kDecMWaves * 64)) return kGridTooLarge;
     e = launch_kernel(moda_decode_partial_mfma_kernel<D>, dim3((unsigned)blocks), dim3(kDecMWaves * 64), stream, p);
   } else {
     const int gt = decode_heads_per_chunk(G);
     const long long blocks = (long long)p.B * p.Hk * ((G + gt - 1) / gt) * p.n_slices;
-    if (!grid_ok(blocks)) return kGridTooLarge;
+    if (!grid_ok(blocks, kDecWaves * 64)) return kGridTooLarge;
     dim3 grid((unsigned)blocks), block(kDecWaves * 64);
     if (gt == 4) e = launch_kernel(moda_decode_partial_kernel<D, 4>, grid, block, stream, p);
     else if (gt == 2) e = launch_kernel(moda_decode_partial_kernel<D, 2>, grid, block, stream, p);
     else e = launch_kernel(moda_decode_partial_kernel<D, 1>, grid, block, stream, p);
   }
   if (e != hipSuccess) return e;
-  if (p.n_slices <= kMergeOne)
+  if (merge_groups == 1)
     return launch_kernel(moda_decode_merge_kernel<D, 1>, dim3((unsigned)(p.B * p.Hq)), dim3(D), stream, p);
   return launch_kernel(moda_decode_merge_kernel<D, 4>, dim3((unsigned)(p.B * p.Hq)), dim3(4 * D), stream, p);
 }

@@ -1248,7 +1248,7 @@ hipError_t launch_fwd_bf16(const FwdParams& p, int d, int waves, int per_simd, h
   const int tile_pos = waves * kQPerWave / gt;
   if (p.n_qtiles != (p.T + tile_pos - 1) / tile_pos) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * (p.Hq / gt) * p.n_qtiles;
-  if (!grid_ok(blocks)) return kGridTooLarge;
+  if (!grid_ok(blocks, waves * 64)) return kGridTooLarge;
   dim3 grid((unsigned)blocks), block(waves * 64);
   if (d == 128 && per_simd == 2 && waves == 8) return launch_kernel(moda_fwd_bf16_kernel<128, 8, 2>, grid, block, stream, p);
   if (d == 128 && per_simd == 2) return launch_kernel(moda_fwd_bf16_kernel<128, 4, 2>, grid, block, stream, p);

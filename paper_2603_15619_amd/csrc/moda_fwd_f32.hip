@@ -584,8 +584,8 @@ hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream) {
   if (fwd_f32_by_rows(p)) return launch_fwd_f32_rows(p, d, stream);
   if (p.n_qtiles != (p.T + kF32Rows - 1) / kF32Rows) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * p.Hq * p.n_qtiles;
-  if (!grid_ok(blocks)) return kGridTooLarge;
   const bool eight = fwd_f32_eight_waves(p);
+  if (!grid_ok(blocks, eight ? 512 : 256)) return kGridTooLarge;
   dim3 grid((unsigned)blocks), block(eight ? 512 : 256);
   if (d == 128) return launch_kernel(eight ? moda_fwd_f32_kernel<128> : moda_fwd_f32_four_kernel<128>, grid, block, stream, p);
   if (d == 64) return launch_kernel(eight ? moda_fwd_f32_kernel<64> : moda_fwd_f32_four_kernel<64>, grid, block, stream, p);

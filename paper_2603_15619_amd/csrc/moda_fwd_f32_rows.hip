@@ -125,7 +125,7 @@ bool fwd_f32_by_rows(const FwdParams& p) { return p.T <= ((long long)p.B * p.Hq 
 
 hipError_t launch_fwd_f32_rows(const FwdParams& p, int d, hipStream_t stream) {
   const long long blocks = ((long long)p.B * p.Hq * p.T + 3) / 4;
-  if (!grid_ok(blocks)) return kGridTooLarge;
+  if (!grid_ok(blocks, 256)) return kGridTooLarge;
   dim3 grid((unsigned)blocks), block(256);
   if (d == 128) return launch_kernel(moda_fwd_f32_rows_kernel<128>, grid, block, stream, p);
   if (d == 64) return launch_kernel(moda_fwd_f32_rows_kernel<64>, grid, block, stream, p);

@@ -354,7 +354,7 @@ hipError_t launch_fwd_short(const FwdParams& params, int d, hipStream_t stream) 
   if (gt < 1 || gt > kShortCols || (gt & (gt - 1)) != 0 || (p.Hq / p.Hk) % gt != 0) return hipErrorInvalidValue;
   if (p.n_qtiles != (p.T + pos - 1) / pos) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * (p.Hq / gt) * p.n_qtiles;
-  if (!grid_ok(blocks)) return kGridTooLarge;
+  if (!grid_ok(blocks, kShortWaves * 64)) return kGridTooLarge;
   if (p.depth_mfma && alternate_blocks(p, blocks)) p.depth_mfma = 2;
   dim3 grid((unsigned)blocks), block(kShortWaves * 64);
   if (d != 64 && d != 128) return hipErrorInvalidValue;

@@ -17,7 +17,9 @@ inline hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block
 // A grid that does not fit a launch: reported before anything is enqueued (the C ABI turns it
 // into MODA_ERR_UNSUPPORTED).
 constexpr hipError_t kGridTooLarge = hipErrorInvalidConfiguration;
-inline bool grid_ok(long long blocks) { return blocks > 0 && blocks <= 0x7fffffffLL; }
+// A launch has less than 2^32 threads.  The runtime does not refuse all larger ones: 2^24 + 1 workgroups of 256 threads
+// were accepted and ran as one workgroup.
+inline bool grid_ok(long long blocks, int threads) { return blocks > 0 && blocks <= 0xffffffffLL / threads; }
 
 // bf16 forward kernel: `waves` (8 or 4) waves per workgroup, 32 queries each, per_simd (2, or at d = 64 4; 8 waves at
 // d = 64 go with 4) of them resident on a SIMD; p.n_qtiles

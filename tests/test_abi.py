@@ -148,6 +148,24 @@ def test_size_limits_without_gpu(L):
     assert tuned(waves=5) == 2 and tuned(heads_per_tile=4) == 2 and tuned(head_group=-2) == 2
 
 
+def test_grids_of_2_to_the_32_threads_are_refused(L):
+    """Before anything is launched (the runtime itself takes some of them and runs a part of the workgroups).  A backward
+    call whose key and query tiles are too many for one launch keeps them apart."""
+    from paper_2603_15619_amd.binding import MODAShape
+
+    p = ctypes.c_void_p(0x1000)
+
+    def shape(B, H, T, dtype=1):
+        return ctypes.byref(MODAShape(B, H, H, T, 64, 0, 0, 1, 0.0, dtype))
+
+    for T, B, dtype in ((1, 1 << 21, 1), (9, 1 << 21, 0), (128, 1 << 21, 1)):
+        assert L.moda_attn_fwd(p, p, p, None, None, p, p, shape(B, 8, T, dtype), None) == 3
+    assert L.moda_attn_decode(p, p, p, None, None, p, p, 1, p, 1 << 50, shape(1 << 21, 8, 1), None) == 3
+    assert L.moda_attn_bwd(*([p] * 14), 1 << 50, shape(1 << 21, 8, 1), None) == 3
+    for heads, kernels in ((1 << 22, 2), (1 << 23, 3)):
+        assert L.moda_kernels_per_call(shape(heads // 8, 8, 17), 1) == kernels
+
+
 @pytest.mark.parametrize("d,kernels", [(64, 3), (128, 4)])
 def test_depth_gradients_of_5_to_8_heads_take_their_own_kernel_at_d_128(d, kernels):
     """Many key tiles, full blocks of slots: inside dK/dV at d = 64 only (at d = 128 the registers do not

@@ -253,3 +253,14 @@ def test_short_contexts_take_one_kernel(B, Hq, Hk, T, d, L, La):
                             None if L == 0 else f(kd[:, :, :L].contiguous())[:, :, None], None if L == 0 else f(vd[:, :, :L].contiguous())[:, :, None],
                             np.array([T - 1], dtype=np.int32), depth_count=L)
     assert np.abs(f(O) - Oref[:, :, 0]).max() <= 2e-2 and np.abs(f(LSE) - Lref[:, :, 0]).max() <= 1e-3
+
+
+def test_more_heads_than_one_kernel_has_workgroups():
+    """2^23 + 8 heads: too many workgroups of eight waves for one launch, so two kernels take the call.  One key has
+    weight 1: O is V."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    Q = torch.zeros(((1 << 20) + 1, 8, 64), dtype=torch.bfloat16, device="cuda")
+    V = torch.randn(Q.shape, dtype=torch.bfloat16, device="cuda")[:, :, None]
+    O, LSE = moda_attn_decode(Q, Q[:, :, None], V)
+    assert torch.equal(O, V[:, :, 0]) and torch.count_nonzero(LSE) == 0
