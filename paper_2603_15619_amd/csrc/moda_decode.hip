@@ -301,6 +301,10 @@ __global__ __launch_bounds__(kDecOneWaves * 64, 2) void moda_decode_one_kernel(D
         kn[u] = load(p.Kseq, p.Kdepth, row0 + base + (kU + u) * STEP);
         vn[u] = load(p.Vseq, p.Vdepth, row0 + base + (kU + u) * STEP);
       }
+    } else {  // rows past the end repeat the last one with weight zero, which an infinite value would turn into NaN
+#pragma unroll
+      for (int u = 0; u < kU; ++u)
+        if (row0 + base + u * STEP >= n) vv[u] = (u32x4){0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int j = 0; j < GT; ++j) {

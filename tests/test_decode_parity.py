@@ -264,3 +264,24 @@ def test_more_heads_than_one_kernel_has_workgroups():
     V = torch.randn(Q.shape, dtype=torch.bfloat16, device="cuda")[:, :, None]
     O, LSE = moda_attn_decode(Q, Q[:, :, None], V)
     assert torch.equal(O, V[:, :, 0]) and torch.count_nonzero(LSE) == 0
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L", [(1, 2, 2, 128, 64, 0), (2, 2, 1, 256, 64, 0), (1, 4, 1, 128, 128, 0), (1, 8, 1, 100, 64, 0), (1, 1, 1, 33, 128, 0),
+                                           (3, 2, 2, 200, 64, 5), (1, 3, 1, 1, 64, 1)])
+def test_infinite_value_of_the_last_row(B, Hq, Hk, T, d, L):
+    """Short contexts: the last key (or slot) has an infinite value in two channels; its weight is positive, so the
+    output is infinite there, with its sign, and what it was everywhere else."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    one = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2600, device="cuda")
+    seq = synth.make_inputs(B, Hq, Hk, T, d, 0, dtype="bf16", seed=2601, device="cuda")
+    kd, vd = (None if L == 0 else one[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))
+    args = [one["Q"][:, :, 0].contiguous(), seq["Kseq"], seq["Vseq"], kd, vd]
+    O, LSE = moda_attn_decode(*args)
+    last = seq["Vseq"] if L == 0 else vd
+    last[:, :, -1, 3] = float("inf")
+    last[:, :, -1, d - 1] = -float("inf")
+    Oinf, LSEinf = moda_attn_decode(*args)
+    assert (Oinf[..., 3] == float("inf")).all() and (Oinf[..., d - 1] == -float("inf")).all()
+    keep = [c for c in range(d) if c not in (3, d - 1)]
+    assert torch.equal(Oinf[..., keep], O[..., keep]) and torch.equal(LSEinf, LSE)
