@@ -582,8 +582,12 @@ void moda_decode_partial_mfma_kernel(DecodeParams p) {
 // like any other online softmax; the groups' states are folded through LDS.  The fold of a head is
 // a chain of memory latencies, one per eight slices, hence NG = 4 where there are more than 8 (B=8
 // Hq=64, 49 slices of d=64: 7.6 -> 4.8 us; whole call, 9 slices, T=1003 H=16 d=128 6.8 -> 6.5; 16 slices, Hq=8 Hk=2 B=6 T=1000
-// d=64 6.9 -> 6.6; with 8 slices or fewer 0 to 5 % longer).
-constexpr int kMergeOne = 8;
+// d=64 6.9 -> 6.6; with 8 slices or fewer 0 to 5 % longer).  From 2^17 outputs on the workgroups are several to a unit and
+// hide each other's latency: up to 16 slices one group then (four / one, whole call, 9 to 12 slices: 2048 to 10496 heads
+// of d=128 1.02 to 1.05, B=41 Hq=256 Hk=8 T=2419 115 / 106 us; 17 to 24: 0.99 to 1.01).
+static int merge_groups(int n_slices, long long heads, int d) {
+  return n_slices <= (heads * d > 1 << 17 ? 16 : 8) ? 1 : 4;
+}
 
 template <int D, int NG>
 __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams p) {
@@ -801,8 +805,8 @@ template <int D>
 static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream) {
   const int G = p.Hq / p.Hk;
   if (decode_in_one(p, D, decode_heads_per_chunk(G))) return launch_in_one<D>(p, decode_heads_per_chunk(G), stream);
-  const int merge_groups = p.n_slices <= kMergeOne ? 1 : 4;
-  if (!grid_ok((long long)p.B * p.Hq, merge_groups * D)) return kGridTooLarge;
+  const int groups = merge_groups(p.n_slices, (long long)p.B * p.Hq, D);
+  if (!grid_ok((long long)p.B * p.Hq, groups * D)) return kGridTooLarge;
   hipError_t e;
   if (mfma) {
     const long long blocks = (long long)p.B * p.Hk * ((G + 31) / 32) * ((p.n_slices + kDecMWaves - 1) / kDecMWaves);
@@ -818,7 +822,7 @@ static hipError_t launch_decode_d(DecodeParams p, bool mfma, hipStream_t stream)
     else e = launch_kernel(moda_decode_partial_kernel<D, 1>, grid, block, stream, p);
   }
   if (e != hipSuccess) return e;
-  if (merge_groups == 1)
+  if (groups == 1)
     return launch_kernel(moda_decode_merge_kernel<D, 1>, dim3((unsigned)(p.B * p.Hq)), dim3(D), stream, p);
   return launch_kernel(moda_decode_merge_kernel<D, 4>, dim3((unsigned)(p.B * p.Hq)), dim3(4 * D), stream, p);
 }

@@ -285,3 +285,8 @@ def test_infinite_value_of_the_last_row(B, Hq, Hk, T, d, L):
     assert (Oinf[..., 3] == float("inf")).all() and (Oinf[..., d - 1] == -float("inf")).all()
     keep = [c for c in range(d) if c not in (3, d - 1)]
     assert torch.equal(Oinf[..., keep], O[..., keep]) and torch.equal(LSEinf, LSE)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L", [(33, 64, 2, 1100, 64, 3), (17, 64, 2, 1300, 128, 0), (32, 64, 2, 1100, 64, 3), (257, 8, 2, 2304, 64, 0)])
+def test_merge_of_9_to_16_slices_on_both_sides_of_2_to_the_17_outputs(B, Hq, Hk, T, d, L):
+    check(B, Hq, Hk, T, d, L, 2700)
