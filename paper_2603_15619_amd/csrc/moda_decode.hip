@@ -778,20 +778,24 @@ size_t decode_least_bytes(int B, int Hq, int Hk, int T, int d) {
 }
 
 // Calls that take one kernel: few batches of rows (256 at d = 64, 128 at d = 128), more of them where the workgroups fill the
-// chip anyway; groups of more than 4 heads, in chunks of 4, one batch and no more workgroups than units.  Two kernels / one,
+// chip anyway (a little more than one round of them does not); groups of more than 4 heads, in chunks of 4, one batch and no more
+// workgroups than units; 3 or 4 heads one batch, and above 256 workgroups, of which a unit holds one at a time, only up to two
+// rounds and where the other kernels have a second slice to fold.  Two kernels / one,
 // us, whole call, (batch, key/value head)s, rows:
 //   1 head   d=64 48, 35 5.4 / 3.7;   180, 150 5.9 / 3.6;   24, 308 5.4 / 4.4;   12, 745 5.5 / 5.1;   48, 1217 6.2 / 7.4;   720, 1015 34.6 / 28.4
 //            d=128 16, 93 5.4 / 3.5;   80, 151 6.1 / 4.5;   368, 293 13.5 / 11.6;   16, 510 6.0 / 6.0;   8, 843 5.9 / 8.7
 //   2 heads  d=64 40, 220 5.8 / 4.4;   8, 341 5.8 / 5.4;   64, 593 6.5 / 6.8;   d=128 816, 79 17.0 / 10.6;   50, 351 6.5 / 6.8
-//   4 heads  d=64 128, 80 6.5 / 5.6;   32, 527 6.7 / 9.7;   d=128 148, 121 10.3 / 5.7;   8, 129 6.9 / 7.4
+//            d=64 264, 986 16.1 / 18.2;   400 to 640, 800 to 1000 0.93
+//   4 heads  d=64 128, 80 6.5 / 5.6;   32, 527 6.7 / 9.7;   d=128 148, 121 10.3 / 5.7;   8, 129 6.9 / 7.4;   3 or 4 heads, no slots:
+//            d=64 536, 12 9.8 / 13.3;   666, 55 10.0 / 13.6;   d=128 648, 49 10.3 / 13.9;   with slots: 257 to 512 0.68 to 1.03, 552, 61 1.07
 //   8 heads  d=64 4, 236 6.9 / 5.4;   164, 210 8.1 / 10.0;   d=128 112, 118 9.2 / 6.0;   32 heads: 29, 108 9.0 / 5.6, 56, 34 8.5 / 9.6
 static bool decode_in_one(const DecodeParams& p, int d, int gt) {
   const int batch = kDecOneWaves * (64 / (d / 8)) * 4, G = p.Hq / p.Hk;
   const long long batches = ((long long)p.T + p.depth_count + batch - 1) / batch, blocks = (long long)p.B * p.Hk * ((G + gt - 1) / gt);
   if (!grid_ok(blocks, kDecOneWaves * 64)) return false;
   if (G > 4) return batches <= 1 && blocks <= 256;
-  if (gt == 4) return batches <= 1;
-  return batches <= (blocks >= 256 ? 4 : gt == 1 && d == 64 ? 3 : 2);
+  if (gt == 4) return batches <= 1 && (blocks <= 256 || (blocks <= 512 && p.n_slices > 1));
+  return batches <= (blocks >= 384 ? 4 : blocks >= 256 ? 3 : gt == 1 && d == 64 ? 3 : 2);
 }
 
 template <int D>

@@ -290,3 +290,21 @@ def test_infinite_value_of_the_last_row(B, Hq, Hk, T, d, L):
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L", [(33, 64, 2, 1100, 64, 3), (17, 64, 2, 1300, 128, 0), (32, 64, 2, 1100, 64, 3), (257, 8, 2, 2304, 64, 0)])
 def test_merge_of_9_to_16_slices_on_both_sides_of_2_to_the_17_outputs(B, Hq, Hk, T, d, L):
     check(B, Hq, Hk, T, d, L, 2700)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,one", [(256, 3, 1, 12, 64, 0, True), (257, 3, 1, 12, 64, 0, False), (257, 4, 1, 12, 64, 3, True), (64, 32, 8, 49, 128, 7, True),
+                                               (513, 4, 1, 12, 64, 3, False), (65, 24, 8, 49, 128, 7, False), (33, 16, 8, 979, 64, 7, False), (48, 16, 8, 979, 64, 7, True),
+                                               (33, 8, 8, 760, 64, 0, True)])
+def test_one_kernel_above_256_workgroups(B, Hq, Hk, T, d, L, one):
+    """Groups of 3 and 4 heads: only up to 512 workgroups and with a second slice; others: up to three batches of rows,
+    and four from 384 workgroups on.  The kernel writes nothing to the workspace."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    tok = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2800, device="cuda")
+    seq = synth.make_inputs(B, Hq, Hk, T, d, 0, dtype="bf16", seed=2801, device="cuda")
+    kd, vd = (None if L == 0 else tok[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))
+    ws = torch.full((1 << 23,), float("nan"), device="cuda")
+    moda_attn_decode(tok["Q"][:, :, 0].contiguous(), seq["Kseq"], seq["Vseq"], kd, vd, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(ws).all()) == one
+    check(B, Hq, Hk, T, d, L, 2802)
