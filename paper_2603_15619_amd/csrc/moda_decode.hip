@@ -668,6 +668,9 @@ __global__ __launch_bounds__(NG * D) void moda_decode_merge_kernel(DecodeParams 
 //   G=8 d=128   2 T=122 10.6 / 7.9 / 7.1;   4 T=549 12.2 / 9.8 / 7.8;   32 T=371 12.2 / 9.3 / 8.6;   36 T=1604 15.9 / 12.8 / 14.9;   104 T=125 11.7 / 9.2 / 8.5;
 //               2 T=4909 13.6 / 11.4 / 12.3;   20 T=5693 18.7 / 19.9 / 20;   48 T=3421 23 / 28
 //   G=8 d=64    12 T=343 8.7 / 7.3 / 7.2;   48 T=1271 10.6 / 9.7 / 11.6;   2 T=9867 11.4 / 11.6;   104 T=2618 19 / 22
+// Large groups write, and the merge reads, more per slice: fewer workgroups per slice then (32 heads a group, slices of 128 /
+// these, us: d=64 64 T=378 12.5 / 14.8, 36 T=35 9.7 / 10.8, 104 T=482 11.2 / 13.6;  d=128 135 T=46 1.06).  And not two slices of 32 keys
+// beside more than 32 slots, which last as long as both (d=128 G=8 192 T=39, 64 slots 1.07).
 //   vector ALUs, d=128   G=1 8 T=1977 7.7 / 6.2, with 128 keys 6.6;   16 T=189 6.1 / 5.5;   30 T=1080 8.6 / 8.2;   G=4 32 T=233 8.1 / 7.2;   G=2 120 T=197 8.5 / 8.4
 //   slices of 256 / 128 keys: d=128 8 T=3880 8.5 / 7.3;   8 T=7343 9.4 / 10.5;   d=64 8 T=2094 7.1 / 6.3;   4 T=3706 7.4 / 6.4;   32 T=1717 7.2 / 8.4;   2 T=4786 6.6 / 7.0
 struct DecodePlan {
@@ -678,6 +681,7 @@ struct DecodePlan {
 struct DecodeRule {
   bool mfma;
   int d;
+  int heads;     // query heads of a workgroup (matrix pipe)
   int want;      // slices that fill the chip, whatever the length
   int step;      // keys_per_split is a multiple of this
   int most_fine;    // most slices of the finer cut
@@ -698,6 +702,7 @@ static DecodeRule decode_rule(int B, int Hq, int Hk, int d) {
   // up to 4 heads per group the vector-ALU kernel is at the memory rate and ahead (measured)
   r.mfma = G > 4;
   r.d = d;
+  r.heads = std::min(G, 32);
   if (r.mfma) {
     const int n_gc = (G + 31) / 32;
     // 12 wave-slices per compute unit: all resident at once at d = 64, one and a half rounds
@@ -727,17 +732,24 @@ static int fine_slices(bool mfma, int T) {
   const int fine = (T + 127) / 128, coarse = coarse_slices(T);
   return mfma || fine <= 8 ? fine : coarse > 8 ? coarse : 8;
 }
-// Slices of the finest cut of a call with few workgroups, 0: it has none.
+// Most workgroups of the matrix-pipe kernel (one per slice) with slices of 32 and of 64 keys.
+static int most_of_32(const DecodeRule& r) { return std::min(768, (r.d == 64 ? 3072 : 8192) / r.heads); }
+static int most_of_64(const DecodeRule& r) { return std::min(1024, 16384 / r.heads); }
+// Slices of the finest cut of a call with few workgroups, 0: it has none.  `depth`: its slots.
 static int finest_slices(const DecodeRule& r, int T, int depth) {
   const int n32 = (T + 31) / 32, n64 = (T + 63) / 64, n128 = (T + 127) / 128;
-  if (r.mfma) return n32 <= 16 && r.groups * n32 <= 768 ? n32 : n64 <= 96 && r.groups * n64 <= 1024 ? n64 : 0;
+  if (r.mfma) {
+    if (n32 <= 16 && r.groups * n32 <= most_of_32(r) && !(n32 == 2 && depth > 32)) return n32;
+    return n64 <= 96 && r.groups * n64 <= most_of_64(r) ? n64 : 0;
+  }
+  depth = depth > 0;
   if (r.d == 128 && (n64 <= 8 || (coarse_slices(T) >= 8 && n64 <= 32)) && r.groups * (n64 + depth) <= 256) return n64;
   return coarse_slices(T) >= 8 && n128 <= 32 && r.groups * (n128 + depth) <= 256 ? n128 : 0;
 }
 // No length up to T has more of them.
 static int most_finest_slices(const DecodeRule& r, int T) {
   const long long n32 = (T + 31) / 32, n64 = (T + 63) / 64, n128 = (T + 127) / 128;
-  if (r.mfma) return (int)std::max(std::min({n32, 16ll, 768 / r.groups}), std::min({n64, 96ll, 1024 / r.groups}));
+  if (r.mfma) return (int)std::max(std::min({n32, 16ll, most_of_32(r) / r.groups}), std::min({n64, 96ll, most_of_64(r) / r.groups}));
   return (int)std::min({r.d == 128 ? n64 : n128, 32ll, 256 / r.groups});
 }
 static DecodePlan cut(const DecodeRule& r, int T, int most) {
@@ -750,9 +762,10 @@ static DecodePlan cut(const DecodeRule& r, int T, int most) {
   return pl;
 }
 // The cut of a call whose partial results (of n_split slices and the depth slots) have `room` bytes: the finer
-// slices if they fit and make no more rounds, else the coarser ones.  `depth`: 1 if there are depth slots.
-static DecodePlan decode_plan(const DecodeRule& r, int T, int depth, size_t room) {
-  const int finest = finest_slices(r, T, depth);
+// slices if they fit and make no more rounds, else the coarser ones.
+static DecodePlan decode_plan(const DecodeRule& r, int T, int depth_count, size_t room) {
+  const int depth = depth_count > 0 ? 1 : 0;
+  const int finest = finest_slices(r, T, depth_count);
   if (finest > 0 && finest <= r.most_fine && (size_t)(finest + 1) * r.slice_bytes <= room) return cut(r, T, finest);
   const DecodePlan coarse = cut(r, T, coarse_slices(T));
   const int most = fine_slices(r.mfma, T);
@@ -840,7 +853,7 @@ hipError_t launch_decode_bf16(const void* Q, const void* Kseq, const void* Vseq,
   p.O = O; p.LSE = LSE; p.ws = ws;
   p.B = B; p.Hq = Hq; p.Hk = Hk; p.T = T; p.T_alloc = T_alloc;
   p.depth_alloc = depth_alloc; p.depth_count = depth_count;
-  const DecodePlan pl = decode_plan(decode_rule(B, Hq, Hk, d), T, depth_count > 0, ws_bytes);
+  const DecodePlan pl = decode_plan(decode_rule(B, Hq, Hk, d), T, depth_count, ws_bytes);
   p.n_split = pl.n_split;
   p.keys_per_split = pl.keys_per_split;
   p.n_slices = pl.n_split + (depth_count > 0 ? 1 : 0);

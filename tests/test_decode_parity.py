@@ -206,7 +206,11 @@ def test_finer_slices_only_where_they_make_no_more_rounds(B, Hq, Hk, T, d, L, sl
                                                   (7, 64, 8, 500, 128, 2, 8), (1, 8, 1, 6144, 64, 0, 96), (1, 8, 1, 6145, 64, 0, 49),
                                                   (1, 4, 4, 512, 128, 1, 8), (1, 4, 4, 513, 128, 1, 5), (9, 3, 3, 300, 128, 0, 5), (1, 4, 4, 1793, 128, 0, 29),
                                                   (1, 4, 4, 2048, 128, 5, 32), (1, 4, 4, 2049, 128, 5, 17), (1, 4, 4, 1792, 64, 2, 7), (1, 4, 2, 1793, 64, 2, 15),
-                                                  (1, 2, 2, 4096, 64, 1, 32), (1, 2, 2, 4097, 64, 1, 17), (3, 16, 4, 3000, 128, 4, 12)])
+                                                  (1, 2, 2, 4096, 64, 1, 32), (1, 2, 2, 4097, 64, 1, 17), (3, 16, 4, 3000, 128, 4, 12),
+                                                  # 32 heads per workgroup; two slices of 32 keys beside 32 and 33 slots
+                                                  (4, 64, 2, 300, 64, 0, 10), (5, 64, 2, 300, 64, 0, 5), (4, 64, 2, 1000, 64, 3, 16), (16, 128, 4, 512, 64, 1, 8), (17, 128, 4, 378, 64, 7, 6),
+                                                  (16, 64, 4, 256, 128, 0, 8), (17, 64, 4, 256, 128, 0, 4), (3, 64, 1, 512, 128, 2, 16),
+                                                  (130, 8, 1, 43, 64, 32, 2), (130, 8, 1, 43, 64, 33, 1), (130, 8, 1, 43, 128, 64, 1)])
 def test_finest_slices_of_calls_with_few_workgroups(B, Hq, Hk, T, d, L, slices):
     """Slices of 32 and 64 keys (groups of more than 4 heads), of 64 and 128 (others), where their workgroups leave
     units over, and the next coarser ones beyond."""
