@@ -211,7 +211,7 @@ int moda_fwd_kernel_name(const moda_shape* s, const moda_fwd_tuning* tuning, cha
   moda::FwdParams p;
   p.B = s->B; p.Hq = s->Hq; p.T = s->T; p.depth_count = s->depth_count;
   if (s->dtype == MODA_F32)
-    return snprintf(name, size, "moda_fwd_f32_%skernel<%d>", moda::fwd_f32_by_rows(p) ? "rows_" : moda::fwd_f32_eight_waves(p) ? "" : "four_", s->d);
+    return snprintf(name, size, "moda_fwd_f32_%skernel<%d>", moda::fwd_f32_by_rows(p) ? "rows_" : moda::fwd_f32_eight_waves(p, s->d) ? "" : "four_", s->d);
   if (r.few_tiles) return snprintf(name, size, "moda_fwd_short_kernel<%d, %s>", s->d, r.heads_per_tile == 1 && s->depth_count > 0 ? "true" : "false");
   return snprintf(name, size, "moda_fwd_bf16_kernel<%d, %d, %d>", s->d, r.waves, r.per_simd);
 }

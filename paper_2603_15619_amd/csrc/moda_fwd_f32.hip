@@ -10,8 +10,8 @@
 // fold_tile).  The depth slots run on the vector ALUs at the memory rate.
 //
 // A workgroup = 32 queries of one head; its 4 (few tiles: 8) waves share the queries and DEAL OUT THE KEYS: key
-// tile kt (32 keys) belongs to wave kt % 4, every wave keeps a running (max, normaliser, output) of
-// its own, and the four are folded into one softmax at the end, together with the partial result
+// tile kt (32 keys) belongs to wave kt % NW, every wave keeps a running (max, normaliser, output) of
+// its own, and all of them are folded into one softmax at the end, together with the partial result
 // of the depth slots.  Dealing out keys instead of queries makes the unit of work 32 queries per
 // 4 SIMDs: a few thousand rows of causal attention then fill 256 compute units evenly (32 queries
 // per wave left the last query tiles of a T = 2000 call alone on the chip for twice the mean), and
@@ -271,7 +271,7 @@ __device__ __forceinline__ void fwd_f32_tile(const FwdParams& p) {
   const bool depth_first = L > 0 && ((blockIdx.x >> 3) & 1) != 0;
   if (depth_first) depth_rows();
 
-  // ---- this wave's key tiles: wave, wave + 4, ...
+  // ---- this wave's key tiles: wave, wave + NW, ...
   f32x16 o[C::kBlocks];
 #pragma unroll
   for (int cb = 0; cb < C::kBlocks; ++cb)
@@ -575,16 +575,17 @@ int fwd_f32_tile_rows() { return kF32Rows; }
 // H=2 T=256, 4 slots 10.0 / 9.9;  288 tiles, T=548 21.3 / 21.0;  384 tiles 48.2 / 52.3;  no slots: H=8 T=56 6.2 / 6.8.
 // d = 128: H=2 T=25, 31 slots 26.8 / 18.5;  160 tiles, T=141, 7 slots 19.3 / 17.1;  208 tiles, T=403, 24 slots 40.4 / 41.1;  256
 // tiles, T=31, 4 slots 16.9 / 15.6;  416 tiles, T=404, 31 slots 94 / 106;  no slots: H=8 T=344 15.9 / 15.4, T=204 12.9 / 13.4.
-// Three chunks of slots in flight instead of two: 1.03 of the time.)
-bool fwd_f32_eight_waves(const FwdParams& p) {
-  return (long long)p.B * p.Hq * ((p.T + kF32Rows - 1) / kF32Rows) <= 256 && (p.depth_count > 0 || p.T > 256);
+// Three chunks of slots in flight instead of two: 1.03 of the time.)  One slot is no chain either at d = 128, where the fold
+// is longer (T=107 11.9 / 12.4, T=246 15.2 / 15.9, 128 to 192 positions 0.98; d = 64: 0.96 to 0.99).
+bool fwd_f32_eight_waves(const FwdParams& p, int d) {
+  return (long long)p.B * p.Hq * ((p.T + kF32Rows - 1) / kF32Rows) <= 256 && (p.depth_count > (d == 128 ? 1 : 0) || p.T > 256);
 }
 
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream) {
   if (fwd_f32_by_rows(p)) return launch_fwd_f32_rows(p, d, stream);
   if (p.n_qtiles != (p.T + kF32Rows - 1) / kF32Rows) return hipErrorInvalidValue;
   const long long blocks = (long long)p.B * p.Hq * p.n_qtiles;
-  const bool eight = fwd_f32_eight_waves(p);
+  const bool eight = fwd_f32_eight_waves(p, d);
   if (!grid_ok(blocks, eight ? 512 : 256)) return kGridTooLarge;
   dim3 grid((unsigned)blocks), block(eight ? 512 : 256);
   if (d == 128) return launch_kernel(eight ? moda_fwd_f32_kernel<128> : moda_fwd_f32_four_kernel<128>, grid, block, stream, p);

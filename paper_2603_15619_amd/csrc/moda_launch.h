@@ -32,7 +32,7 @@ int fwd_short_tile_pairs();
 hipError_t launch_fwd_short(const FwdParams& p, int d, hipStream_t stream);
 // fp32 forward kernel: tiles of fwd_f32_tile_rows() queries of one head; p.n_qtiles must be their number.
 int fwd_f32_tile_rows();
-bool fwd_f32_eight_waves(const FwdParams& p);  // moda_fwd_f32_kernel, else moda_fwd_f32_four_kernel
+bool fwd_f32_eight_waves(const FwdParams& p, int d);  // moda_fwd_f32_kernel, else moda_fwd_f32_four_kernel
 hipError_t launch_fwd_f32(const FwdParams& p, int d, hipStream_t stream);
 // The same for short sequences, one wave per query (launch_fwd_f32 hands over what fwd_f32_by_rows says).
 bool fwd_f32_by_rows(const FwdParams& p);

@@ -44,10 +44,12 @@ def test_f32_tile_edges(B, Hq, Hk, T, d, L, La, causal):
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,four", [(32, 8, 4, 9, 64, 5, 6, False), (43, 6, 3, 32, 128, 4, None, True), (33, 4, 2, 33, 64, 7, 8, True),
                                                    (22, 3, 1, 97, 128, 6, None, True), (8, 8, 2, 100, 64, 13, None, False), (13, 4, 4, 129, 128, 1, 2, True),
-                                                   (2, 2, 2, 257, 128, 0, None, False), (2, 2, 2, 256, 64, 0, None, True)])
+                                                   (2, 2, 2, 257, 128, 0, None, False), (2, 2, 2, 256, 64, 0, None, True),
+                                                   (2, 4, 2, 256, 128, 1, 2, True), (2, 4, 2, 256, 128, 2, None, False), (2, 4, 4, 257, 128, 1, None, False),
+                                                   (2, 4, 4, 100, 64, 1, None, False)])
 def test_f32_four_and_eight_waves(B, Hq, Hk, T, d, L, La, four, causal):
-    """Both sides of the line between four waves per workgroup and eight, which takes up to 256 tiles with slots or more
-    than 256 positions."""
+    """Both sides of the line between four waves per workgroup and eight, which takes up to 256 tiles with slots (d = 128:
+    two or more of them) or more than 256 positions."""
     s = MODAShape(B, Hq, Hk, T, d, L if La is None else La, L, int(causal), 0.0, 0)
     name = ctypes.create_string_buffer(64)
     lib().moda_fwd_kernel_name(ctypes.byref(s), None, name, len(name))
