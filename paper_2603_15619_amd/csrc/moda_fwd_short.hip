@@ -343,9 +343,15 @@ int fwd_short_tile_pairs() { return kShortCols; }
 // first where units hold several workgroups and the slots are a good part of the call (last / alternating, us, d = 64:
 // B=2 Hq=16 Hk=8 T=1000, 12 slots 18.7 / 17.5;  1024 tiles, G=2 T=511, 15 slots 18.2 / 16.1;  760 tiles, G=4 T=593, 64 slots 23.9 / 21.0;
 // 832, G=8 T=829, 64 slots 17.3 / 15.7;  but 720, G=8 T=1416, 4 slots 13.2 / 13.7;  528, G=4 T=2093, 4 slots 16.0 / 16.5;  744,
-// G=2 T=2969, 7 slots 23.7 / 23.9;  336, G=4 T=238, 64 slots 8.8 / 9.5).
+// G=2 T=2969, 7 slots 23.7 / 23.9;  336, G=4 T=238, 64 slots 8.8 / 9.5).  The lines, from 12700 calls (alternating, of the time of last):
+// more than 512 workgroups (up to 512 1.00 to 1.05) and no second round of them (1024 at d = 64: 1.01 to 1.03); five slots to a head
+// of the group, whose queries share what is read (d = 64: 0.97 from there on; two heads 8 / 9 / 10 / 11 / 12 slots 1.005 / 1.002 / 0.998 /
+// 0.992 / 0.989, eight heads 15 to 31 1.01); up to 100 positions to a slot; heads in fours, as with an odd number of them neighbouring
+// workgroups do not alternate (0.97 / 0.97 / 0.98 / 0.995 of multiples of 8, 4, 2 and odd numbers, B=15 Hq=2 T=1018, 64 slots 53 / 61).
+// d = 128 the same: 0.96.
 static bool alternate_blocks(const FwdParams& p, long long blocks) {
-  return blocks > 512 && p.depth_count >= 12 && p.T <= 50ll * p.depth_count * (p.Hq / p.Hk);
+  const int G = p.Hq / p.Hk;
+  return blocks > 512 && blocks <= 1024 && p.depth_count >= 5 * G && p.T <= 100ll * p.depth_count && (long long)p.B * p.Hk % 4 == 0;
 }
 
 hipError_t launch_fwd_short(const FwdParams& params, int d, hipStream_t stream) {

@@ -25,12 +25,13 @@ def test_fwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
     check_full(B, Hq, Hk, T, d, L, "bf16", 0, causal=causal, depth_alloc=La, inp=inp)
 
 
-@pytest.mark.parametrize("B,Hq,Hk,T,L,La,causal", [(2, 16, 8, 1000, 12, 13, True), (5, 8, 4, 485, 24, None, False), (3, 32, 8, 226, 31, 32, True),
-                                                   (1, 64, 8, 300, 12, None, True)])
-def test_blocks_of_slots_first_in_every_other_workgroup(B, Hq, Hk, T, L, La, causal):
-    """Two, four and eight heads per tile, more workgroups than two per unit; the slots of the first position score -inf
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,La,causal", [(2, 16, 8, 1000, 64, 12, 13, True), (5, 8, 4, 485, 64, 24, None, False), (3, 32, 8, 226, 64, 31, 32, True),
+                                                     (1, 64, 8, 300, 64, 64, None, True), (1, 16, 8, 1100, 128, 12, None, True), (1, 16, 4, 1069, 128, 24, 25, True)])
+def test_blocks_of_slots_first_in_every_other_workgroup(B, Hq, Hk, T, d, L, La, causal):
+    """Two, four and eight heads per tile, more workgroups than two per unit, five slots and more to a head of the
+    group; the slots of the first position score -inf
     (its query is positive), so that a workgroup's first block holds columns that have seen no key yet."""
-    inp = synth.make_inputs(B, Hq, Hk, T, 64, L, dtype="bf16", seed=1550 + T + L, device="cuda", depth_alloc=La)
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=1550 + T + L, device="cuda", depth_alloc=La)
     inp["Q"][:, :, 0] = inp["Q"][:, :, 0].abs() + 0.1
     inp["Kdepth"][:, :, 0] = -float("inf")
     inp["Vdepth"][:, :, 0] = 0.0  # (weight zero either way)
