@@ -1782,7 +1782,8 @@ __global__ __launch_bounds__(NW * 64, (grads_waves_per_simd(D, KS, QS, NW))) voi
   const int G = p.Hq / p.Hk, sub = G / heads, n_pos = QS ? 32 : NW * 32 / heads;
   const int n_kt = (p.T + kKeys - 1) / kKeys, n_qt = (p.T + n_pos - 1) / n_pos;
   int bg, w;
-  head_walk_id(QS ? (int)blockIdx.x : layered_id(p.causal, 2), p.B * p.Hk, n_kt + n_qt * sub, bg, w, p.head_group);
+  // (a unit holds one workgroup of eight waves: LDS)
+  head_walk_id(QS ? (int)blockIdx.x : layered_id(p.causal, NW == 8 ? 1 : 2), p.B * p.Hk, n_kt + n_qt * sub, bg, w, p.head_group);
   int kt = w, qi = w - n_kt;
   if (spread) {  // key tiles evenly among the query tiles
     const unsigned long long m = n_kt + (long long)n_qt * sub;

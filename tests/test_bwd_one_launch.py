@@ -95,6 +95,12 @@ def test_eight_waves_d_128(B, Hq, Hk, T, L, La, causal):
     check(B, Hq, Hk, T, 128, L, La, causal)
 
 
+@pytest.mark.parametrize("B,Hq,Hk,T,d", [(11, 8, 1, 430, 64), (1, 64, 8, 399, 64), (9, 16, 1, 498, 128), (1, 32, 4, 1311, 128)])
+def test_eight_waves_and_128_rows_in_one_to_two_rounds(B, Hq, Hk, T, d):
+    """257 to 512 causal workgroups, of which a unit holds one at a time: the walk is not folded over two layers."""
+    check(B, Hq, Hk, T, d, 0, None, True)
+
+
 @pytest.mark.parametrize("Hq,T", [(2, 97), (4, 97), (8, 97)])
 def test_slots_that_are_not_finite_reach_their_own_position_only(Hq, T):
     """(O and LSE are those of finite slots: the forward of several heads per tile makes no such promise.)"""
