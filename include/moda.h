@@ -248,6 +248,15 @@ int moda_kernels_per_call(const moda_shape* s, int which);
  */
 int moda_fwd_kernel_name(const moda_shape* s, const moda_fwd_tuning* tuning, char* name, size_t size);
 
+/*
+ * The same for moda_attn_bwd: the kernel that computes dK and dV (which = 0) or
+ * dQ (which = 1), one and the same where a call takes one launch for all three,
+ * e.g. "moda_bwd_grads_kernel<64, 2, true, true, 4>" (head dimension, query heads
+ * per group whose depth slots it takes or 0, key tiles of 32 keys, query tiles of
+ * 32 positions, waves per workgroup).
+ */
+int moda_bwd_kernel_name(const moda_shape* s, int which, char* name, size_t size);
+
 #ifdef __cplusplus
 }
 #endif

@@ -25,7 +25,8 @@ EXPORTS = ("moda_attn_fwd", "moda_attn_fwd_tuned", "moda_attn_bwd_workspace_byte
            "moda_attn_decode", "moda_attn_decode_workspace_bytes", "moda_attn_decode_noalloc",
            "moda_attn_decode_noalloc_max_bytes",
            "moda_calibrate_mfma", "moda_calibrate_mfma_operand_bytes", "moda_calibrate_mfma_sink_bytes",
-           "moda_status_string", "moda_version", "moda_kernels_per_call", "moda_fwd_kernel_name")
+           "moda_status_string", "moda_version", "moda_kernels_per_call", "moda_fwd_kernel_name",
+           "moda_bwd_kernel_name")
 
 
 class MODAShape(ctypes.Structure):
@@ -90,6 +91,8 @@ def lib():
         L.moda_kernels_per_call.restype = ctypes.c_int
         L.moda_fwd_kernel_name.argtypes = [sp, ctypes.POINTER(MODAFwdTuning), ctypes.c_char_p, ctypes.c_size_t]
         L.moda_fwd_kernel_name.restype = ctypes.c_int
+        L.moda_bwd_kernel_name.argtypes = [sp, ctypes.c_int, ctypes.c_char_p, ctypes.c_size_t]
+        L.moda_bwd_kernel_name.restype = ctypes.c_int
         _lib = L
     return _lib
 

@@ -216,6 +216,13 @@ int moda_fwd_kernel_name(const moda_shape* s, const moda_fwd_tuning* tuning, cha
   return snprintf(name, size, "moda_fwd_bf16_kernel<%d, %d, %d>", s->d, r.waves, r.per_simd);
 }
 
+int moda_bwd_kernel_name(const moda_shape* s, int which, char* name, size_t size) {
+  if (name && size > 0) name[0] = 0;
+  if (check_shape(s) != MODA_OK || s->B == 0 || s->T == 0 || which < 0 || which > 1) return 0;
+  if (s->dtype != MODA_BF16 || s->Hq / s->Hk > moda::bwd_bf16_max_group()) return 0;
+  return moda::bwd_bf16_kernel_name(bwd_dims(s), s->d, which, name, size);
+}
+
 moda_status moda_attn_fwd_tuned(const void* Q, const void* Kseq, const void* Vseq, const void* Kdepth,
                                 const void* Vdepth, void* O, float* LSE, const moda_shape* s,
                                 const moda_fwd_tuning* tuning, void* hip_stream) {

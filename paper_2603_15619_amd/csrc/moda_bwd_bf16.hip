@@ -34,6 +34,7 @@
 //   9 heads and up : a kernel of their own on the matrix pipe (depth_group).
 #include <algorithm>
 #include <math.h>
+#include <stdio.h>
 #include <type_traits>
 
 #include "moda_launch.h"
@@ -2181,9 +2182,12 @@ static int grads_head_group(const BwdParams& p, int d, long long grid, long long
 }
 // The kind of tiles whose estimated time is shortest.  As for dkdv_waves: the chains of the longest key tile and of the longest
 // query tile (a step: 64 queries x 128 keys, 128 x 64, or 32 x 32 per wave; chunks of slots one after the other), and what
-// all tiles ask of 256 units (steps, ends, slots).  Constants (us; per 256 units) fitted to the times of all kinds at 2100 and
-// 4800 shapes (T = 17 to 20000, 1 to 12000 heads, 1 to 16 per group, 0 to 64 slots): 1.3 and 1.7 % behind the best kind on
-// average, more than 10 % at 1 of 25 and of 16.  Backward call, us, 128-row tiles / 32 keys and 32 positions / 32 keys, 128
+// all tiles ask of 256 units (steps, ends, slots), in part rounded up to whole rounds of workgroups.  Constants (us; per 256
+// units) fitted to the times of all kinds at 34500 shapes (T = 17 to 66000, 1 to 12000 heads, 1 to 16 per group, 0 to 64
+// slots) so that the choice is right more than the time: the kind taken is 1.0 % (d = 64) and 1.1 % (d = 128) behind the best one on
+// average, more than 10 % at 1 of 33; slower than two launches by more than 2 % at 16 and 4 of 1000.  (Without the rounds, and fitted
+// to the times alone, 1.7 and 2.0 %, more than 10 % at 1 of 15; 24 and 11 of 1000; with two launches as a sixth kind, where they are
+// ahead of the kind taken, 14 and 4: not worth it.)  Backward call, us, 128-row tiles / 32 keys and 32 positions / 32 keys, 128
 // rows / the last two with eight waves:
 //   d=64   G=1 T=216 32 heads, 64 slots  109 / 99 / 108 / 87 / -;   B=5 H=2 T=6284, 1 slot  207 / 282 / 262 / - / -
 //          G=4 B=3 Hk=2 T=381, no slots  36 / 16.7 / 16.5 / 14.6 / -;   G=16 Hk=1 T=16817, no slots  4810 / 3130 / 2667 / 2654 / 2345
@@ -2201,18 +2205,19 @@ static int spread_key_tiles(const BwdParams& p, long long grid) {
 struct GradsCost {
   GradsPlan plan;
   double key_step, query_step, key_unit, query_unit, key_ends, query_ends, slot, slot_unit, undealt, once;
+  double group, last_round, key_step_all;  // (the last one: of calls that are not causal, of key_step)
 };
 static GradsPlan grads_plan(const BwdParams& p, int d) {
-  static const GradsCost costs64[] = {{{false, false, 4}, 1.16, 0.427, 0.992, 0.625, 1.59, 3.46, 0.422, 0.364, 0.044, 7.54},
-                                      {{true, true, 4}, 0.795, 0.63, 0.94, 0.000594, 1.86, 0.979, 0.377, 0.383, 0.152, 6.83},
-                                      {{true, false, 4}, 0.787, 0.707, 0.914, 0.000805, 2.44, 2.41, 0.458, 0.375, 0.121, 7.2},
-                                      {{true, true, 8}, 0.967, 0.707, 2.2, 0.00308, 4.16, 2.65, 0.368, 0.383, 0.0105, 7.58},
-                                      {{true, false, 8}, 1, 1.22, 1.9, 0.000928, 5.9, 4.1, 0.502, 0.361, 0.156, 7.62}};
-  static const GradsCost costs128[] = {{{false, false, 4}, 2.48, 0.7, 2.73, 0.393, 0.993, 7.07, 0.421, 0.355, 0.000535, 8.97},
-                                       {{true, true, 4}, 1.29, 1.08, 1.91, 0.000348, 4.08, 2.04, 0.367, 0.365, 0.143, 8.59},
-                                       {{true, false, 4}, 1.27, 1.13, 1.73, 0.000227, 4.37, 3.44, 0.494, 0.37, 0.23, 9.1},
-                                       {{true, true, 8}, 1.63, 1.44, 4.04, 0.00248, 7.33, 3.53, 0.657, 0.37, 0.0338, 9.42},
-                                       {{true, false, 8}, 1.61, 1.76, 3.58, 0.000687, 8.49, 6.65, 0.704, 0.362, 0.226, 10.3}};
+  static const GradsCost costs64[] = {{{false, false, 4}, 1.26, 0.0026, 0.861, 0.0562, 1.16, 4.19, 0.52, 0.359, 0.00497, 6.8, -0.0455, 0.293, 0.947},
+                                      {{true, true, 4}, 1.13, 1, 0.545, 0.29, 1.83, 1.06, 0.512, 0.359, 0.223, 4.46, 0.0628, 0.214, 0.854},
+                                      {{true, false, 4}, 0.998, 1.11, 0.812, 0.000684, 3.57, 2.59, 0.485, 0.416, 0.155, 5.11, -0.0733, 0.133, 0.759},
+                                      {{true, true, 8}, 0.907, 0.518, 2.16, 0.00272, 5.1, 3.82, 0.409, 0.397, 0.000167, 7.26, -0.00562, 0.348, 0.866},
+                                      {{true, false, 8}, 0.762, 2.35, 1.96, 0.000176, 4.97, 9.84, 0.645, 0.479, 0.000755, 5.21, -0.122, 0.422, 0.386}};
+  static const GradsCost costs128[] = {{{false, false, 4}, 2.52, 0.000545, 1.63, 0.0982, 2.18, 6.48, 0.482, 0.355, 0.0209, 8.9, -0.0273, 0.187, 1.03},
+                                       {{true, true, 4}, 1.62, 1.44, 1.77, 0.000563, 2.4, 3.67, 0.465, 0.325, 0.188, 6.45, 0.0939, 0.0721, 0.883},
+                                       {{true, false, 4}, 1.53, 1.7, 1.39, 7.96e-05, 4.97, 4.66, 0.568, 0.427, 0.439, 7.29, -0.0669, 0.0125, 0.859},
+                                       {{true, true, 8}, 1.69, 1.06, 2.79, 1.04, 11.7, 4.09, 0.549, 0.396, 0.000252, 8.6, -0.0337, 0.143, 1.03},
+                                       {{true, false, 8}, 1.3, 3.42, 3.52, 9.13e-05, 7.73, 12.1, 0.779, 0.44, 0.00589, 7.5, -0.0691, 0.35, 0.93}};
   const double n32 = (p.T + 31) / 32, n64 = (p.T + 63) / 64, heads = (double)p.B * p.Hk / 256;
   const int G = p.Hq / p.Hk, per_step = 512 / d;  // (rows of slots that a wave takes at a time)
   const double walk32 = p.causal ? (n32 + 1) / 2 : n32;  // tiles of 32 that a tile of 32 sees on average
@@ -2240,8 +2245,13 @@ static GradsPlan grads_plan(const BwdParams& p, int d) {
     int passes = 0;
     if (p.depth_alloc > 0 && G == 1) passes = (std::min(p.T, c.plan.few_queries ? std::max(32 / nw, per_step) : 32) + per_step - 1) / per_step;
     else if (p.depth_alloc > 0) passes = (std::min(p.T, n_pos) + nw * per_step - 1) / (nw * per_step);
-    const double load = heads * ((k_all * c.key_unit + q_all * c.query_unit) * (1 + c.undealt * undealt_share((long long)p.B * p.Hk)) +
-                                 kt * c.key_ends + qt * c.query_ends + (double)p.T * p.depth_count * d / 1000 * c.slot_unit);
+    double load = heads * ((k_all * c.key_unit + q_all * c.query_unit) * (1 + c.undealt * undealt_share((long long)p.B * p.Hk)) +
+                           kt * c.key_ends + qt * c.query_ends + (double)p.T * p.depth_count * d / 1000 * c.slot_unit);
+    // (rounds of workgroups that the chip holds at once: the last one lasts as long as a full one)
+    const double rounds = heads * (kt + qt) / (nw == 8 ? 1 : d == 64 && c.plan.few_keys && c.plan.few_queries ? 3 : 2);
+    if (rounds > 1) load *= 1 + c.last_round * (ceil(rounds) / rounds - 1);
+    load *= pow(G, c.group);
+    if (!p.causal) k_first *= c.key_step_all;
     const double time = c.once + sqrt(sqrt(fourth(k_first * c.key_step) + fourth(q_first * c.query_step + passes * p.depth_count * c.slot) + fourth(load)));
     if (i == 0 || time < least) {
       least = time;
@@ -2257,9 +2267,39 @@ static bool one_launch(const BwdParams& p, int d, GradsPlan& plan) {
   plan = grads_plan(p, d);
   return grid_ok(plan.workgroups(p), plan.waves * 64);
 }
-int bwd_bf16_kernels(const BwdParams& p, int d) {
+// The kernels of a call.
+struct BwdRoute {
+  bool one;        // moda_bwd_grads_kernel, as `plan` says; else
   GradsPlan plan;
-  return one_launch(p, d, plan) ? 2 : 3 + (own_depth_kernel(p, d) ? 1 : 0);
+  bool own_depth;  // a kernel for the depth-slot gradients,
+  int waves;       // dK/dV (0: 128 keys to a workgroup) and
+  bool few_queries;  // dQ
+  int gt;          // heads per group whose depth slots the kernel of dQ (one launch) or of dK, dV takes, rounded up; 0: none
+};
+static BwdRoute bwd_route(const BwdParams& p, int d) {
+  BwdRoute r{};
+  const int G = p.Hq / p.Hk;
+  r.one = one_launch(p, d, r.plan);
+  r.own_depth = own_depth_kernel(p, d);
+  // (up to 2 heads: up to 16 positions, where the estimate takes them too, or very many heads)
+  r.waves = G <= 2 ? 4 : dkdv_waves(p, d);
+  r.few_queries = few_queries(p, d);
+  r.gt = p.depth_alloc == 0 || r.own_depth ? 0 : G <= 2 ? G : G <= 4 ? 4 : 8;
+  return r;
+}
+int bwd_bf16_kernels(const BwdParams& p, int d) {
+  const BwdRoute r = bwd_route(p, d);
+  return r.one ? 2 : 3 + (r.own_depth ? 1 : 0);
+}
+int bwd_bf16_kernel_name(const BwdParams& p, int d, int which, char* name, size_t size) {
+  const BwdRoute r = bwd_route(p, d);
+  if (r.one)
+    return snprintf(name, size, "moda_bwd_grads_kernel<%d, %d, %s, %s, %d>", d, r.gt, r.plan.few_keys ? "true" : "false",
+                    r.plan.few_queries ? "true" : "false", r.plan.waves);
+  if (which == 0 && r.waves == 0) return snprintf(name, size, "moda_bwd_dkdv_kernel<%d, %d>", d, r.gt);
+  if (which == 0) return snprintf(name, size, "moda_bwd_dkdv_short_kernel<%d, %d, %d>", d, r.gt, r.waves);
+  if (r.few_queries) return snprintf(name, size, "moda_bwd_dq_short_kernel<%d>", d);
+  return snprintf(name, size, "moda_bwd_dq_kernel<%d, 4, %d>", d, dq_per_unit(p, d, (long long)p.B * p.Hq * (((long long)p.T + 127) / 128)));
 }
 
 template <int D>
@@ -2271,14 +2311,14 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   const long long kv_rows = (long long)p.B * p.Hk * p.T;
   const long long g_depth = G <= 8 ? (kv_rows * (D / 8) + 255) / 256 : kv_rows;
   // every grid is checked before the first kernel is enqueued
-  GradsPlan plan{};
-  const bool one = one_launch(p, D, plan), own_depth = own_depth_kernel(p, D), short_dq = few_queries(p, D);
-  const int few = G <= 2 ? 4 : dkdv_waves(p, D);  // (see moda_bwd_dkdv_short_kernel)
-  const long long g_grads = one ? plan.workgroups(p) : 0;
+  const BwdRoute r = bwd_route(p, D);
+  const GradsPlan& plan = r.plan;
+  const int few = r.waves;
+  const long long g_grads = r.one ? plan.workgroups(p) : 0;
   const long long n32 = ((long long)p.T + 31) / 32;
-  const long long g_dkdv = (long long)p.B * p.Hk * (few ? n32 : n_kt), g_dq = (long long)p.B * p.Hq * (short_dq ? n32 : n_kt);
-  if (!grid_ok(g_delta, 256) || (!one && (!grid_ok(g_dkdv, few ? few * 64 : 256) || !grid_ok(g_dq, 256))) ||
-      (own_depth && !grid_ok(g_depth, G <= 8 ? 256 : 64)))
+  const long long g_dkdv = (long long)p.B * p.Hk * (few ? n32 : n_kt), g_dq = (long long)p.B * p.Hq * (r.few_queries ? n32 : n_kt);
+  if (!grid_ok(g_delta, 256) || (!r.one && (!grid_ok(g_dkdv, few ? few * 64 : 256) || !grid_ok(g_dq, 256))) ||
+      (r.own_depth && !grid_ok(g_depth, G <= 8 ? 256 : 64)))
     return kGridTooLarge;  // (own_depth: up to 8 heads 256 / (d/8) positions to a workgroup, above one, of one wave)
   if (G > bwd_bf16_max_group()) return hipErrorInvalidValue;
   // the group kernel gathers the G heads' rows of a position with 32-bit offsets from the first head
@@ -2288,7 +2328,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
   hipError_t e = launch_kernel(moda_bwd_delta_kernel<D>, dim3((unsigned)g_delta), dim3(256), stream, p.dO, p.O, p.LSE,
                                p.lse2, p.minus_delta, rows);
   if (e != hipSuccess) return e;
-  if (own_depth) {
+  if (r.own_depth) {
     if (G <= 8) {
       e = launch_kernel(moda_bwd_depth_gqa_kernel<D, 8>, dim3((unsigned)g_depth), dim3(256), stream, p);
     } else {
@@ -2299,7 +2339,7 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     }
     if (e != hipSuccess) return e;
   }
-  if (one) {
+  if (r.one) {
     const int heads = plan.heads(p);
     p.head_group = grads_head_group(p, D, g_grads, (long long)p.B * p.Hk * plan.key_tiles(p));
     const int spread = spread_key_tiles(p, g_grads);
@@ -2310,24 +2350,25 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
                           : plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 4> : moda_bwd_grads_kernel<D, GT, true, false, 4>;
       return launch_kernel(kernel, dim3((unsigned)g_grads), dim3(plan.waves * 64), stream, p, heads, spread);
     };
-    if (p.depth_alloc == 0) return launch(std::integral_constant<int, 0>());
-    return G == 1 ? launch(std::integral_constant<int, 1>()) : G == 2 ? launch(std::integral_constant<int, 2>()) : launch(std::integral_constant<int, 4>());
+    return r.gt == 0   ? launch(std::integral_constant<int, 0>())
+           : r.gt == 1 ? launch(std::integral_constant<int, 1>())
+           : r.gt == 2 ? launch(std::integral_constant<int, 2>())
+                       : launch(std::integral_constant<int, 4>());
   }
   {
     constexpr int kEight = D == 64 ? 8 : 4;
     const dim3 gk((unsigned)g_dkdv), blk(few ? few * 64 : 256);
-    const bool grouped = G > 1 && p.depth_alloc > 0 && !own_depth;  // the group's depth-slot gradients run inside dK/dV
     auto pick = [few](auto other, auto four, auto eight) { return few == 0 ? other : few == 4 ? four : eight; };
     const auto kernel =
-        few == 4 && G == 1 && p.depth_alloc > 0 ? moda_bwd_dkdv_short_kernel<D, 1, 4>  // (up to 16 positions, or very many heads: 32 keys, four waves)
-        : !grouped ? pick(moda_bwd_dkdv_kernel<D, 0>, moda_bwd_dkdv_short_kernel<D, 0, 4>, moda_bwd_dkdv_short_kernel<D, 0, kEight>)
-        : G == 2 ? moda_bwd_dkdv_short_kernel<D, 2, 4>                                 // (the same)
-        : G <= 4 ? pick(moda_bwd_dkdv_kernel<D, 4>, moda_bwd_dkdv_short_kernel<D, 4, 4>, moda_bwd_dkdv_short_kernel<D, 4, kEight>)
-                 : moda_bwd_dkdv_kernel<D, D == 64 ? 8 : 4>;  // (d = 128: never more than 4 here)
+        r.gt == 1   ? moda_bwd_dkdv_short_kernel<D, 1, 4>
+        : r.gt == 2 ? moda_bwd_dkdv_short_kernel<D, 2, 4>
+        : r.gt == 0 ? pick(moda_bwd_dkdv_kernel<D, 0>, moda_bwd_dkdv_short_kernel<D, 0, 4>, moda_bwd_dkdv_short_kernel<D, 0, kEight>)
+        : r.gt == 4 ? pick(moda_bwd_dkdv_kernel<D, 4>, moda_bwd_dkdv_short_kernel<D, 4, 4>, moda_bwd_dkdv_short_kernel<D, 4, kEight>)
+                    : moda_bwd_dkdv_kernel<D, D == 64 ? 8 : 4>;  // (d = 128: never more than 4 here)
     e = launch_kernel(kernel, gk, blk, stream, p);
   }
   if (e != hipSuccess) return e;
-  if (short_dq) return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)g_dq), dim3(256), stream, p);
+  if (r.few_queries) return launch_kernel(moda_bwd_dq_short_kernel<D>, dim3((unsigned)g_dq), dim3(256), stream, p);
   return launch_kernel(dq_per_unit(p, D, g_dq) == 3 ? moda_bwd_dq_kernel<D, 4, D == 64 ? 3 : 2> : moda_bwd_dq_kernel<D, 4, 2>,
                        dim3((unsigned)g_dq), dim3(256), stream, p);
 }

@@ -42,6 +42,8 @@ hipError_t launch_fwd_f32_rows(const FwdParams& p, int d, hipStream_t stream);
 // [depth slots of grouped queries,] dK/dV and dQ kernels, on `stream`.
 int bwd_bf16_max_group();
 int bwd_bf16_kernels(const BwdParams& p, int d);  // kernels one call enqueues
+// The kernel of dK and dV (which = 0) or of dQ (1), as a profiler prints it; as snprintf.
+int bwd_bf16_kernel_name(const BwdParams& p, int d, int which, char* name, size_t size);
 size_t bwd_bf16_workspace_bytes(const BwdParams& p, int d);
 hipError_t launch_bwd_bf16(const BwdParams& p, int d, hipStream_t stream);
 

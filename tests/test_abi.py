@@ -241,3 +241,29 @@ def test_forward_kernel_names(L, B, Hq, Hk, T, d, slots, causal, dtype, tuned, n
     cut = ctypes.create_string_buffer(8)
     L.moda_fwd_kernel_name(ctypes.byref(s), tuning, cut, len(cut))
     assert cut.value.decode() == name[:7]
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,slots,causal,names", [
+    (8, 16, 16, 4096, 128, 15, 1, ["moda_bwd_grads_kernel<128, 1, false, false, 4>"]),
+    (2, 16, 8, 1000, 64, 12, 1, ["moda_bwd_grads_kernel<64, 2, true, true, 4>"]),
+    # calls that a chain or a second round of 128-row tiles made slower than two launches, or than another kind
+    (17, 8, 8, 192, 128, 64, 1, ["moda_bwd_grads_kernel<128, 1, true, true, 4>"]),
+    (7, 8, 8, 537, 64, 64, 1, ["moda_bwd_grads_kernel<64, 1, true, true, 4>"]),
+    (17, 8, 8, 264, 128, 31, 1, ["moda_bwd_grads_kernel<128, 1, true, true, 4>"]),
+    (1, 8, 2, 5166, 64, 0, 1, ["moda_bwd_grads_kernel<64, 0, true, true, 8>"]),
+    (3, 8, 1, 10305, 128, 0, 1, ["moda_bwd_grads_kernel<128, 0, true, false, 8>"]),
+    (3, 4, 1, 13537, 128, 7, 1, ["moda_bwd_grads_kernel<128, 4, true, false, 8>"]),
+    (1, 64, 8, 16384, 64, 64, 1, ["moda_bwd_dkdv_kernel<64, 8>", "moda_bwd_dq_kernel<64, 4, 2>"]),
+    (1, 9, 1, 97, 128, 2, 1, ["moda_bwd_dkdv_short_kernel<128, 0, 4>", "moda_bwd_dq_short_kernel<128>"]),
+    (1, 2, 2, 16, 64, 2, 1, ["moda_bwd_dkdv_short_kernel<64, 1, 4>", "moda_bwd_dq_short_kernel<64>"]),
+    (0, 2, 2, 16, 64, 2, 1, [""]), (1, 65, 1, 16, 64, 2, 1, [""])])
+def test_backward_kernel_names(L, B, Hq, Hk, T, d, slots, causal, names):
+    from paper_2603_15619_amd.binding import MODAShape
+
+    s = MODAShape(B, Hq, Hk, T, d, slots, slots, causal, 0.0, 1)
+    for which in (0, 1):
+        name = names[which % len(names)]
+        out = ctypes.create_string_buffer(64)
+        assert L.moda_bwd_kernel_name(ctypes.byref(s), which, out, len(out)) == len(name)
+        assert out.value.decode() == name
+    assert L.moda_bwd_kernel_name(ctypes.byref(s), 2, out, len(out)) == 0 and out.value == b""
