@@ -2147,6 +2147,8 @@ static bool own_depth_kernel(const BwdParams& p, int d) {
 // waves of a workgroup evenly, and up to 4 of them their gradients on the vector ALUs.  Up to 16 positions the launches
 // stay apart, as moda_kernels_per_call has them (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).  So they do where the
 // workgroups of both kinds, at 17 positions 2^24 of four waves, are too many for one grid.
+// Key tiles of 32 keys with query tiles of 128 rows: kinds that no call with slots is estimated to be fastest with are not built.
+constexpr bool grads_mixed(int d, int gt, int waves) { return gt == 0 || gt == 4 || (gt == 2 ? waves == 4 || d == 128 : waves == 4 && d == 128); }
 struct GradsPlan {
   bool few_keys, few_queries;
   int waves;
@@ -2225,6 +2227,7 @@ static GradsPlan grads_plan(const BwdParams& p, int d) {
   double least = 0;
   for (int i = 0; i < 5; ++i) {
     const GradsCost& c = d == 64 ? costs64[i] : costs128[i];
+    if (p.depth_alloc > 0 && c.plan.few_keys && !c.plan.few_queries && !grads_mixed(d, G, c.plan.waves)) continue;
     const int nw = c.plan.waves, h = c.plan.heads(p), n_pos = c.plan.few_queries ? 32 : nw * 32 / h;
     const double kt = (double)c.plan.key_tiles(p), qt = (double)c.plan.query_tiles(p) * (G / h);
     double k_first, k_all, q_first, q_all;
@@ -2345,9 +2348,9 @@ static hipError_t launch_bwd_bf16_d(BwdParams p, hipStream_t stream) {
     const int spread = spread_key_tiles(p, g_grads);
     auto launch = [&](auto gt) {
       constexpr int GT = decltype(gt)::value;
-      const auto kernel = plan.waves == 8 ? (plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 8> : moda_bwd_grads_kernel<D, GT, true, false, 8>)
+      const auto kernel = plan.waves == 8 ? (plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 8> : moda_bwd_grads_kernel<D, GT, true, !grads_mixed(D, GT, 8), 8>)
                           : !plan.few_keys ? moda_bwd_grads_kernel<D, GT, false, false, 4>
-                          : plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 4> : moda_bwd_grads_kernel<D, GT, true, false, 4>;
+                          : plan.few_queries ? moda_bwd_grads_kernel<D, GT, true, true, 4> : moda_bwd_grads_kernel<D, GT, true, !grads_mixed(D, GT, 4), 4>;
       return launch_kernel(kernel, dim3((unsigned)g_grads), dim3(plan.waves * 64), stream, p, heads, spread);
     };
     return r.gt == 0   ? launch(std::integral_constant<int, 0>())
