@@ -2147,8 +2147,9 @@ static bool own_depth_kernel(const BwdParams& p, int d) {
 // waves of a workgroup evenly, and up to 4 of them their gradients on the vector ALUs.  Up to 16 positions the launches
 // stay apart, as moda_kernels_per_call has them (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).  So they do where the
 // workgroups of both kinds, at 17 positions 2^24 of four waves, are too many for one grid.
-// Key tiles of 32 keys with query tiles of 128 rows: kinds that no call with slots is estimated to be fastest with are not built.
-constexpr bool grads_mixed(int d, int gt, int waves) { return gt == 0 || gt == 4 || (gt == 2 ? waves == 4 || d == 128 : waves == 4 && d == 128); }
+// Key tiles of 32 keys with query tiles of 128 rows: not built for calls with slots that hardly ever are estimated to be fastest
+// with them (9 of 25000 calls, whose next best kind takes 1.01 of the time).
+constexpr bool grads_mixed(int d, int gt, int waves) { return gt == 0 || (waves == 8 ? gt == 4 && d == 128 : gt > 1 || d == 128); }
 struct GradsPlan {
   bool few_keys, few_queries;
   int waves;

@@ -1,6 +1,7 @@
-"""GPU parity of the backward on both sides of the rules that pick its dK/dV and dQ kernels by the
+"""GPU parity of the backward on both sides of the rules that pick its kernels by the
 number of tiles: few tiles (32 keys or queries per workgroup, dealt out to its waves) and many (128 per
-workgroup).  Bound and oracle as in test_bwd_parity."""
+workgroup), in the dK/dV and dQ kernels (groups of 3, 5 and more heads with slots, or up to 16 positions) and in
+the kernel of all three gradients.  Bound and oracle as in test_bwd_parity."""
 import ctypes
 
 import numpy as np
@@ -23,11 +24,20 @@ def test_bwd_few_tiles(B, Hq, Hk, T, d, L, La, causal):
     check_full(B, Hq, T, d, L, 1300 + T + L, causal=causal, depth_alloc=La, Hk=Hk)
 
 
+def kernel(B, Hq, Hk, T, d, L, causal, which, La=None):
+    """The kernel of dK and dV (which = 0) or of dQ (1)."""
+    s = MODAShape(B, Hq, Hk, T, d, L if La is None else La, L, int(causal), 0.0, 1)
+    name = ctypes.create_string_buffer(64)
+    lib().moda_bwd_kernel_name(ctypes.byref(s), which, name, len(name))
+    return name.value.decode()
+
+
 @pytest.mark.parametrize("B,Hq,Hk,T,L,La,causal", [(1, 8, 1, 777, 0, None, True), (1, 6, 2, 1500, 4, 5, True),
                                                    (1, 4, 2, 1100, 7, None, True), (1, 3, 3, 2050, 5, 6, True), (2, 10, 1, 333, 2, None, False),
                                                    (1, 8, 2, 1001, 24, None, False), (1, 8, 1, 97, 0, None, True), (3, 8, 1, 33, 9, 10, True)])
 def test_bwd_few_tiles_of_many_queries(B, Hq, Hk, T, L, La, causal):
-    """d = 64, few key tiles that see many queries: eight waves per key tile in the dK/dV kernel."""
+    """d = 64, few key tiles that see many queries: eight waves per key tile, in the dK/dV kernel or in one launch."""
+    assert kernel(B, Hq, Hk, T, 64, L, causal, 0, La).endswith(", 8>")
     check_full(B, Hq, T, 64, L, 1350 + T + L, causal=causal, depth_alloc=La, Hk=Hk)
 
 
@@ -45,18 +55,29 @@ def check_ends(B, Hq, Hk, T, d, L, seed, causal):
         assert g is None or torch.isfinite(g.float()).all()
 
 
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L", [(5, 39, 13, 610, 128, 2), (51, 9, 3, 300, 64, 2), (1, 15, 5, 3300, 64, 2), (1, 21, 7, 2100, 128, 1)])
+def test_bwd_grids_of_one_round(B, Hq, Hk, T, d, L):
+    """Between one and two workgroups per compute unit in the dK/dV kernel of 128 keys (the first two) or in the dQ kernel of 128
+    queries, a number that 8 does not divide: tiles of every other layer in reverse."""
+    names = [kernel(B, Hq, Hk, T, d, L, True, which) for which in (0, 1)]
+    grids = [B * H * -(-T // 128) for n, H in zip(names, (Hk, Hq)) if n.startswith(("moda_bwd_dkdv_kernel", "moda_bwd_dq_kernel"))]
+    assert any(256 < g <= 512 and g % 8 != 0 for g in grids)
+    check_ends(B, Hq, Hk, T, d, L, 1380 + T, True)
+
+
 @pytest.mark.parametrize("B,Hq,T,d,L", [(3, 11, 1600, 128, 0), (1, 23, 2500, 64, 2), (5, 13, 610, 128, 3)])
-def test_bwd_grids_of_one_round(B, Hq, T, d, L):
-    """Between one and two workgroups per compute unit, a number that 8 does not divide: tiles of every other
-    layer in reverse."""
+def test_bwd_heads_that_8_does_not_divide(B, Hq, T, d, L):
+    """One launch for all three gradients, heads walked tile by tile over all dies."""
+    assert "grads" in kernel(B, Hq, Hq, T, d, L, True, 0)
     check_ends(B, Hq, Hq, T, d, L, 1380 + T, True)
 
 
-@pytest.mark.parametrize("B,Hq,Hk,T,L,causal", [(65, 8, 8, 33, 2, True), (75, 16, 2, 127, 0, False), (37, 6, 6, 321, 3, True), (17, 8, 4, 640, 0, True),
-                                                (8, 8, 8, 1100, 1, False), (19, 4, 2, 1100, 0, False), (70, 8, 8, 400, 0, True)])
+@pytest.mark.parametrize("B,Hq,Hk,T,L,causal", [(65, 24, 8, 33, 2, True), (75, 10, 2, 127, 1, False), (37, 30, 6, 321, 1, True), (23, 6, 2, 400, 2, True),
+                                                (8, 40, 8, 1100, 1, False), (13, 15, 5, 300, 2, True), (70, 24, 8, 400, 1, True)])
 def test_bwd_three_workgroups_per_unit(B, Hq, Hk, T, L, causal):
     """d = 64, the dQ kernel's grids that take three workgroups per compute unit: short sequences, one
     round of three (in layers where causal; 8 does not divide it), many workgroups."""
+    assert kernel(B, Hq, Hk, T, 64, L, causal, 1) == "moda_bwd_dq_kernel<64, 4, 3>"
     check_ends(B, Hq, Hk, T, 64, L, 1390 + T, causal)
 
 
