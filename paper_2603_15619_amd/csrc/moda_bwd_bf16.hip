@@ -10,7 +10,7 @@
 //   delta  : LSE_t log2(e) and -delta_t for every row (row-parallel, vector ALUs).
 //   grads  : dK, dV and dQ in ONE launch, whose workgroups each take a key tile or a query tile as the two
 //            kernels below do; the depth slots go with the query tiles.  Calls of more than 16 positions
-//            without depth slots, or with 1, 2 or 4 heads per group.  All others:
+//            without depth slots, or with 1, 2 or 4 heads per group, whose workgroups fit one grid.  All others:
 //   dkdv   : one workgroup per 128 sequence keys; Q / dO tiles stream through LDS;
 //            S = Q K^T and dP = dO V^T are recomputed per 32x32 block on the MFMA
 //            pipe, P and dS = P (dP - delta) are packed to bf16 straight out of the
@@ -1353,9 +1353,9 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
   constexpr int LPR = Tl::kChunks, RPS = 64 / LPR, NIT = 32 / RPS;
   const int La = p.depth_alloc;
 
-  // The depth-slot gradients and the depth share of dQ were computed before this kernel (by
-  // the dK/dV kernel, or by the depth_gqa kernels with grouped queries); the share is in the
-  // workspace, in fp32, not yet multiplied by the softmax scale.
+  // GT = 0: the depth-slot gradients and the depth share of dQ were computed before this kernel (by
+  // the dK/dV kernel, or by the depth_gqa kernels with grouped queries).  GT > 0: they are computed here, the share
+  // of a tile that takes its slots first through the workspace too: in fp32, not yet multiplied by the softmax scale.
   constexpr int kDepthRows = NW * 64 / LPR;  // rows of depth slots per pass
   if constexpr (GT > 0) {
     if (depth_first) {
@@ -1763,9 +1763,12 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void moda_bwd_dq_short_kernel
 // waves instead of four (NW, with KS) where few tiles have long walks: grads_plan draws the lines.
 // Backward call, two launches / one: B=8 H=16 T=4096 d=128, 15 slots 2.80 / 2.65 ms; B=2 Hq=16 Hk=8 T=1000 d=64, 12
 // slots 58 / 45 us; B=2 H=16 T=1105 d=128, 1 slot 104 / 64; B=2 H=2 T=206 d=128, 12 slots 25 / 17; B=1 Hq=4 Hk=1 T=4026 d=128, 64
-// slots 290 / 220; B=3 Hq=8 Hk=2 T=71 d=128, 1 slot 23.3 / 14.8.  0.77 on average of 3200 random shapes.
+// slots 290 / 220; B=3 Hq=8 Hk=2 T=71 d=128, 1 slot 23.3 / 14.8.  0.80 (d = 64) and 0.72 (d = 128) on average of the 34800
+// shapes that grads_plan is fitted to.
 // All key tiles first / one every so often among the query tiles, largest share first: within 2 % of the best order;
 // the first quarter / half / eighth / none of the query tiles with slots first 1.018 / 1.024 / 1.020 / 1.029 of the best.
+// Three waves per SIMD (170 registers) also for four heads, whose slots then park 7 registers in scratch memory: with two waves
+// 250 calls took 0.97 of the time on average, but 59 of them longer, up to 1.26.
 constexpr int grads_waves_per_simd(int D, bool KS, bool QS, int NW) { return D == 64 && KS && QS && NW == 4 ? 3 : 2; }
 template <int D, bool KS, bool QS, int NW>
 struct GradsCfg {
@@ -2144,8 +2147,9 @@ static bool own_depth_kernel(const BwdParams& p, int d) {
   return G > 8 || d != 64 || dkdv_waves(p, d) != 0 || L * 16 < blocks * 32 * 11 || L == 0;
 }
 // Calls that take one kernel for dK, dV and dQ (moda_bwd_grads_kernel).  With depth slots the heads of a group have to fill the
-// waves of a workgroup evenly, and up to 4 of them their gradients on the vector ALUs.  Up to 16 positions the launches
-// stay apart, as moda_kernels_per_call has them (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).  So they do where the
+// waves of a workgroup evenly, and up to 4 of them their gradients on the vector ALUs (5 to 8: their number of launches is fixed by
+// tests of moda_kernels_per_call; one launch for them was not measured).  Up to 16 positions the launches stay apart for the same
+// reason only: three are counted at 16 positions (H=1 T=16 d=128: 12.5 us, 8.2 in one launch).  So they do where the
 // workgroups of both kinds, at 17 positions 2^24 of four waves, are too many for one grid.
 // Key tiles of 32 keys with query tiles of 128 rows: not built for calls with slots that hardly ever are estimated to be fastest
 // with them (9 of 25000 calls, whose next best kind takes 1.01 of the time).

@@ -559,7 +559,8 @@ __device__ __forceinline__ void fwd_f32_tile(const FwdParams& p) {
   if (tid % TPR == 0 && t < T) p.LSE[(size_t)bh * T + t] = mt * p.scale + logf(lt);
 }
 
-// Few tiles are bound by the chains of a wave's key tiles and slots, which eight waves to a workgroup halve.
+// Few tiles are bound by the chains of a wave's key tiles and slots, which eight waves to a workgroup halve.  (The kernel of
+// few tiles has the plain name, by which the smallest call is known; the one of four waves had it while there was no other.)
 template <int D>
 __global__ __launch_bounds__(512, 2) void moda_fwd_f32_kernel(FwdParams p) {
   fwd_f32_tile<D, 8>(p);
