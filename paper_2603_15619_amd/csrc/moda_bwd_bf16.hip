@@ -2190,7 +2190,7 @@ static int grads_head_group(const BwdParams& p, int d, long long grid, long long
 // The kind of tiles whose estimated time is shortest.  As for dkdv_waves: the chains of the longest key tile and of the longest
 // query tile (a step: 64 queries x 128 keys, 128 x 64, or 32 x 32 per wave; chunks of slots one after the other), and what
 // all tiles ask of 256 units (steps, ends, slots), in part rounded up to whole rounds of workgroups.  Constants (us; per 256
-// units) fitted to the times of all kinds at 34500 shapes (T = 17 to 66000, 1 to 12000 heads, 1 to 16 per group, 0 to 64
+// units) fitted to the times of all kinds at 34800 shapes (T = 17 to 66000, 1 to 12000 heads, 1 to 16 per group, 0 to 64
 // slots) so that the choice is right more than the time: the kind taken is 1.0 % (d = 64) and 1.1 % (d = 128) behind the best one on
 // average, more than 10 % at 1 of 33; slower than two launches by more than 2 % at 16 and 4 of 1000.  (Without the rounds, and fitted
 // to the times alone, 1.7 and 2.0 %, more than 10 % at 1 of 15; 24 and 11 of 1000; with two launches as a sixth kind, where they are
