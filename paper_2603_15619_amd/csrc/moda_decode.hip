@@ -195,16 +195,16 @@ __global__ __launch_bounds__(kDecWaves * 64) void moda_decode_partial_kernel(Dec
         sc[u] = key + u * STEP < k_end ? a : -INFINITY;
         mn = fmaxf(mn, sc[u]);
       }
-      // (mn is -inf only while every key so far was past the slice: then nothing is added)
-      const bool none = mn == -INFINITY;
-      const float al = none ? 0.f : fast_exp2((m[j] - mn) * c2);
+      // (mn is -inf only while every score so far was, or was NaN, which stays NaN; with reference 0 the others weigh nothing)
+      const float ref = mn == -INFINITY ? 0.f : mn;
+      const float al = fast_exp2((m[j] - ref) * c2);
       m[j] = mn;
       l[j] *= al;
 #pragma unroll
       for (int k = 0; k < 8; ++k) o[j][k] *= al;
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const float pw = none ? 0.f : fast_exp2((sc[u] - mn) * c2);
+        const float pw = fast_exp2((sc[u] - ref) * c2);
         l[j] += pw;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {

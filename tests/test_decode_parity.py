@@ -312,3 +312,22 @@ def test_one_kernel_above_256_workgroups(B, Hq, Hk, T, d, L, one):
     torch.cuda.synchronize()
     assert bool(torch.isnan(ws).all()) == one
     check(B, Hq, Hk, T, d, L, 2802)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L,row", [(2, 4, 4, 1000, 128, 1, None), (3, 4, 2, 700, 64, 2, None), (1, 4, 1, 600, 64, 1, None), (2, 3, 3, 513, 128, 0, 512),
+                                               (2, 16, 2, 1000, 64, 1, None), (2, 4, 2, 100, 64, 1, None), (1, 2, 2, 65, 128, 0, 64), (1, 4, 4, 1, 64, 0, 0)])
+def test_nan_key_is_not_lost(B, Hq, Hk, T, d, L, row):
+    """A key (or, row None, the last slot) of the last sequence's last head is NaN, alone in its lanes' share of the rows:
+    the outputs of its query heads are NaN, the others what they were."""
+    from paper_2603_15619_amd import moda_attn_decode
+
+    one = synth.make_inputs(B, Hq, Hk, 1, d, L, dtype="bf16", seed=2900, device="cuda")
+    seq = synth.make_inputs(B, Hq, Hk, T, d, 0, dtype="bf16", seed=2901, device="cuda")
+    kd, vd = (None if L == 0 else one[k][:, :, 0].contiguous() for k in ("Kdepth", "Vdepth"))
+    args = [one["Q"][:, :, 0].contiguous(), seq["Kseq"], seq["Vseq"], kd, vd]
+    O, LSE = (x.view(B, Hk, Hq // Hk, -1).clone() for x in moda_attn_decode(*args))
+    (kd if row is None else seq["Kseq"])[-1, -1, -1 if row is None else row, 5] = float("nan")
+    On, LSEn = (x.view(B, Hk, Hq // Hk, -1) for x in moda_attn_decode(*args))
+    assert torch.isnan(On[-1, -1]).all() and torch.isnan(LSEn[-1, -1]).all()
+    On[-1, -1], LSEn[-1, -1] = O[-1, -1], LSE[-1, -1]
+    assert torch.equal(On, O) and torch.equal(LSEn, LSE)
