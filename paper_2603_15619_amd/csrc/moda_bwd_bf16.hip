@@ -1423,8 +1423,9 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
     ld.issue(v_buf, kt * 64, smem_addr + stage * C::kStageBytes + Tl::kBytes);
   };
 
-  // One key tile: S^T, dP^T, dS^T and dQ^T += K^T dS^T for this wave's 32 queries.
-  auto tile = [&](int kt, int stage) {
+  // One key tile, or (BLOCKS = 1) its first 32 keys: S^T, dP^T, dS^T and dQ^T += K^T dS^T for this wave's 32 queries.
+  auto tile = [&](int kt, int stage, auto blocks) {
+    constexpr int BLOCKS = decltype(blocks)::value;
     // per-lane fragment bases inside this stage (K tile; the V tile sits Tl::kBytes after it)
     const unsigned ktile = smem_addr + stage * C::kStageBytes;
     const unsigned b_row = fa.row + ktile, b_tr = fa.tr + ktile, b_tr8 = fa.tr8 + ktile;
@@ -1459,15 +1460,15 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
     // steps ahead; the order is pinned step by step.  (Against scores, exponentials, products one
     // after the other: B=8 H=16 T=4096 d=128 0.88 -> 0.83 ms; B=1 Hq=64 Hk=8 T=16384 d=64 3.01 ->
     // 2.97 ms, where 1.11 PFLOP/s of matrix work hold the clock at 1.7 GHz.)
-    constexpr int NS = Tl::kDSteps, NP = 2 * Tl::kDBlocks, kAhead = 2, kBuf = kAhead + 1;
+    constexpr int NS = Tl::kDSteps, NP = 2 * Tl::kDBlocks, kAhead = 2, kBuf = kAhead + 1, kScores = BLOCKS * NS, kSteps = kScores + BLOCKS * NP;
     bf16x8 fk[kBuf], fv[kBuf];
     auto read_frags = [&](int n) {
-      if (n < 2 * NS) {
+      if (n < kScores) {
         const unsigned x = (unsigned)xor_here((int)b_row, (n % NS) << 5);
         fk[n % kBuf] = fa.row_frag(x, n / NS, 0);
         fv[n % kBuf] = fa.row_frag(x, n / NS, Tl::kBytes);
-      } else if (n < 2 * NS + 2 * NP) {
-        const int m = n - 2 * NS, db = m % Tl::kDBlocks;
+      } else if (n < kSteps) {
+        const int m = n - kScores, db = m % Tl::kDBlocks;
         fk[n % kBuf] = fa.tr_frag((unsigned)xor_here((int)b_tr, db << 6), (unsigned)xor_here((int)b_tr8, db << 6),
                                   m / Tl::kDBlocks, 0);
       }
@@ -1475,11 +1476,11 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
 #pragma unroll
     for (int n = 0; n < kAhead; ++n) read_frags(n);
 #pragma unroll
-    for (int n = 0; n < 2 * NS + 2 * NP; ++n) {
-      if (n == NS) __builtin_amdgcn_s_setprio(1);  // (as in the dK/dV kernel)
-      if (n == 2 * NS + NP) __builtin_amdgcn_s_setprio(0);
+    for (int n = 0; n < kSteps; ++n) {
+      if (BLOCKS == 2 && n == NS) __builtin_amdgcn_s_setprio(1);  // (as in the dK/dV kernel)
+      if (BLOCKS == 2 && n == 2 * NS + NP) __builtin_amdgcn_s_setprio(0);
       read_frags(n + kAhead);
-      if (n < 2 * NS) {
+      if (n < kScores) {
         const int kb = n / NS, st = n % NS;
         if (st == 0)
 #pragma unroll
@@ -1488,13 +1489,17 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
         dp[kb] = mfma_bf16(fv[n % kBuf], dof[st], st == 0 ? minus_delta() : dp[kb]);
         if (kb == 1 && st % (NS / 4) == 0) weights(0, st / (NS / 4));
       } else {
-        const int m = n - 2 * NS, ks = m / Tl::kDBlocks, db = m % Tl::kDBlocks;
+        const int m = n - kScores, ks = m / Tl::kDBlocks, db = m % Tl::kDBlocks;
         dq[db] = mfma_bf16(fk[n % kBuf], __builtin_bit_cast(bf16x8, ds[ks >> 1][ks & 1]), dq[db]);
-        if (m < NP && m % (NP / 4) == 0) weights(1, m / (NP / 4));
+        if (BLOCKS == 2 && m < NP && m % (NP / 4) == 0) weights(1, m / (NP / 4));
       }
       __builtin_amdgcn_sched_barrier(0);
       if (n == NS - 1) mask(0);
-      if (n == 2 * NS - 1) mask(1);
+      if (BLOCKS == 1 && n == NS - 1) {
+#pragma unroll
+        for (int b4 = 0; b4 < 4; ++b4) weights(0, b4);
+      }
+      if (BLOCKS == 2 && n == 2 * NS - 1) mask(1);
     }
   };
 
@@ -1502,14 +1507,24 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, unsigned char* smem,
   // tiles its queries see: first those (no branch around the products inside the loop, which
   // made the compiler copy the accumulators from one register block to another every tile),
   // then the rest.
+  // Of the tile of its own positions a wave whose 32 queries are the first ones sees the first 32 keys only: the others stay out of
+  // its products, where weights of zero would turn values that are not finite into NaN.
+  const bool half = p.causal && (qw0 & 32) == 0;
   issue(0, 0);
   int kt = 0;
-  for (; kt <= wave_last; ++kt) {
-    const int stage = kt & 1;
+  auto next = [&]() {
     wait_copies();
     __syncthreads();
-    if (kt + 1 < nt) issue(kt + 1, stage ^ 1);
-    tile(kt, stage);
+    if (kt + 1 < nt) issue(kt + 1, (kt & 1) ^ 1);
+  };
+  for (; kt <= wave_last - (half ? 1 : 0); ++kt) {
+    next();
+    tile(kt, kt & 1, std::integral_constant<int, 2>());
+  }
+  if (half && kt <= wave_last) {
+    next();
+    tile(kt, kt & 1, std::integral_constant<int, 1>());
+    ++kt;
   }
   for (; kt < nt; ++kt) {
     wait_copies();

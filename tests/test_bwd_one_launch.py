@@ -154,3 +154,24 @@ def test_slots_that_are_not_finite_reach_their_own_position_only(Hq, T):
     for i in (0, 3, 4):
         assert torch.equal(got[i][:, :, keep], clean[i][:, :, keep])
     assert torch.equal(got[0][:, :G], clean[0][:, :G]) and not torch.isfinite(got[0][0, G, 50].float()).all()
+
+
+@pytest.mark.parametrize("B,Hq,Hk,T,d,L", [(16, 16, 2, 225, 64, 0), (24, 8, 1, 129, 128, 0), (40, 3, 3, 257, 128, 0), (30, 4, 4, 129, 128, 3), (200, 4, 1, 97, 128, 3),
+                                           (24, 24, 8, 200, 64, 2), (24, 40, 8, 130, 128, 1), (1, 2, 2, 161, 64, 5)])
+def test_key_that_is_not_finite_leaves_the_query_blocks_before_it_alone(B, Hq, Hk, T, d, L):
+    """Causal: an infinite value, or a NaN key, at position j reaches dQ of the queries that see it and, as a product with weight
+    zero, at most of those from the last multiple of 32 on (all kinds of query tiles, in one launch or of their own)."""
+    inp = synth.make_inputs(B, Hq, Hk, T, d, L, dtype="bf16", seed=79, device="cuda", with_dO=True)
+    args = [inp[k] for k in ("Q", "Kseq", "Vseq", "Kdepth", "Vdepth")]
+    O, LSE = moda_attn_fwd(*args)
+    clean = moda_attn_bwd(*args, O, LSE, inp["dO"])[0].clone()
+    j = T // 2 // 32 * 32 + 5
+    for k, v in (("Vseq", float("inf")), ("Kseq", float("nan"))):
+        old = inp[k][-1, -1, j, 7].clone()
+        inp[k][-1, -1, j, 7] = v
+        got = moda_attn_bwd(*args, O, LSE, inp["dO"])[0]
+        inp[k][-1, -1, j, 7] = old
+        G = Hq // Hk
+        assert not torch.isfinite(got[-1, -G:, j:].float()).all(-1).any()
+        got[-1, -G:, j - 5:] = clean[-1, -G:, j - 5:]
+        assert torch.equal(got, clean)
